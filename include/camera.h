@@ -173,9 +173,9 @@ int camera_select_prune(camera_ctx* ctx, void* stream,
 /*
  * camera_select_prune for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, order, counts and outputs as
- * camera_select_prune without the `rank` output, but the kernels' scratch (class bytes, select histograms,
- * per-workgroup counts) lies in a static device array of the library instead of the context workspace: the
- * call makes no hipMalloc / hipFree and no other allocating call.  The array (1.5 MiB) exists once per GPU
+ * camera_select_prune without the `rank` output, but the kernels' scratch (the select histograms) lies in a
+ * static device array of the library instead of a buffer of the context: the
+ * call makes no hipMalloc / hipFree and no other allocating call.  The array (2.25 MiB) exists once per GPU
  * for the life of the process and serves n_micro <= CAMERA_NOALLOC_MAX_MICRO; larger inputs are refused with
  * CAMERA_EUNSUPPORTED before anything is launched.  All calls on one GPU share that array, whatever their
  * context or stream: calls that overlap in time on one GPU race (order them on one stream or with events).

@@ -31,7 +31,7 @@ struct camera_ctx {
 // Scratch of camera_select_prune_noalloc: one copy per GPU, held until the process ends.  In host code this
 // name is only a handle for hipGetSymbolAddress; the device address it yields (one per device) is what the
 // kernels and every other HIP call are given.
-constexpr size_t kScratchBytes = 1536 * 1024;
+constexpr size_t kScratchBytes = 2304 * 1024;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -876,38 +876,29 @@ void plan_cuts(const RankRequest& r, int64_t n_micro, camera::RankCuts* cuts, ca
   seg_out->perm = r.perm;
 }
 
-// state: the persistent select state; ws: class bytes + per-call words (+ the sort buffers when rank is asked for)
+// state: the persistent select state; ws: the sort buffers when the full rank is asked for
 int launch_rank(camera_ctx* ctx, hipStream_t stream, const float* energy, int64_t n_micro, const camera::SegTable& seg,
                 const RankRequest& r, void* state, bool* state_dirty, char* ws) {
   camera::RankCuts cuts;
   camera::SegOutputs seg_out;
   plan_cuts(r, n_micro, &cuts, &seg_out);
-  Carver cv;
-  const size_t o_class = cv.take((size_t)n_micro + 64);
-  const size_t o_words = cv.take(sizeof(int32_t) * camera::rank_workspace_words(n_micro, r.rank ? 1 : 0));
-  uint8_t* class_buf = reinterpret_cast<uint8_t*>(ws + o_class);
-  int32_t* words = reinterpret_cast<int32_t*>(ws + o_words);
   if (*state_dirty) {  // an earlier call failed between its passes: start from a clean state again
     CAMERA_HIP(hipMemsetAsync(state, 0, camera::rank_state_bytes(), stream), "hipMemsetAsync(select state)");
     *state_dirty = false;
   }
   uint8_t* first = r.n_ratios > 0 ? r.keep_out : r.bit_of;
   uint8_t* second = r.n_ratios > 0 && r.n_levels > 0 ? r.bit_of : nullptr;
-  hipError_t e = camera::launch_classify(stream, energy, n_micro, cuts, class_buf, first, second, r.kept_idx, state, words);
+  hipError_t e = camera::launch_rank_decisions(stream, energy, n_micro, cuts, seg, seg_out, first, second, r.kept_idx, state);
   if (e != hipSuccess) {
     *state_dirty = true;
-    return fail_hip(ctx, e, "classify launch");
+    return fail_hip(ctx, e, "rank launch");
   }
-  CAMERA_HIP(camera::launch_segment_outputs(stream, class_buf, seg, seg_out), "segment launch");
-  if (r.rank) CAMERA_HIP(camera::launch_full_rank(stream, energy, n_micro, r.rank, words), "rank launch");
+  if (r.rank) CAMERA_HIP(camera::launch_full_rank(stream, energy, n_micro, r.rank, reinterpret_cast<int32_t*>(ws)), "full rank launch");
   return CAMERA_OK;
 }
 
 size_t rank_ws_bytes(int64_t n_micro, bool want_rank) {
-  Carver cv;
-  cv.take((size_t)n_micro + 64);
-  cv.take(sizeof(int32_t) * camera::rank_workspace_words(n_micro, want_rank ? 1 : 0));
-  return cv.used;
+  return sizeof(int32_t) * camera::rank_workspace_words(n_micro, want_rank ? 1 : 0);
 }
 
 // Checks shared by the ranking entry points, then the launches on the context's workspace and select state.
@@ -968,11 +959,9 @@ int camera_select_prune_noalloc(camera_ctx* ctx, void* stream_, const float* ene
   r.kept = kept_per_expert;
   r.kept_idx = kept_idx;
   if (int rc = check_ratios(ctx, r)) return rc;
-  // the scratch: the select state first, the per-call buffers behind it
-  const size_t state_bytes = (camera::rank_state_bytes() + 255) & ~size_t(255);
-  const size_t need = state_bytes + rank_ws_bytes(n_micro, false);
-  if (need > kScratchBytes)
-    return fail(ctx, CAMERA_EUNSUPPORTED, "n_micro: needs %zu bytes of scratch, the static buffer has %zu", need, kScratchBytes);
+  if (camera::rank_state_bytes() > kScratchBytes)
+    return fail(ctx, CAMERA_EUNSUPPORTED, "select state: needs %zu bytes of scratch, the static buffer has %zu",
+                camera::rank_state_bytes(), kScratchBytes);
   DeviceGuard guard;
   CAMERA_HIP(guard.enter(ctx->device), "hipSetDevice");
   char* base = nullptr;
@@ -987,11 +976,9 @@ int camera_select_prune_noalloc(camera_ctx* ctx, void* stream_, const float* ene
     }
     base = static_cast<char*>(g_scratch_ptr[ctx->device]);
   }
-  // The array starts as zeros and keeps the previous call's contents: the select state at its start cleans itself
-  // (every pass leaves its histograms and ticket at zero), class bytes and per-workgroup counts are written before
-  // they are read.
+  // The array starts as zeros and keeps the previous call's contents: the select state in it cleans itself.
   hipStream_t stream = static_cast<hipStream_t>(stream_);
-  return launch_rank(ctx, stream, energy, n_micro, seg, r, base, &g_scratch_dirty[ctx->device], base + state_bytes);
+  return launch_rank(ctx, stream, energy, n_micro, seg, r, base, &g_scratch_dirty[ctx->device], nullptr);
 }
 
 int camera_select_prune_multi(camera_ctx* ctx, void* stream_, const float* energy, int64_t n_micro,

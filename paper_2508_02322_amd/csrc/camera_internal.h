@@ -100,7 +100,7 @@ struct SegTable {
   int n_seg;
   int32_t off[CAMERA_MAX_SEGMENTS + 1];
 };
-// What the per-segment kernel derives from the class bytes (class = number of cuts an element is below; an
+// What the segment kernel derives from an element's class (class = number of cuts it is below; an
 // element below k cuts is below the k cuts of highest rank, so the class fixes which cuts those are).
 struct SegOutputs {
   int n_classes;                 // n_cuts + 1, <= CAMERA_MAX_LEVELS
@@ -113,16 +113,15 @@ struct SegOutputs {
   int32_t* perm;                 // optional: inside every segment level 0 first, then level 1, ..., ascending index inside a level
 };
 // Bytes of the persistent select state (zero when made, self-cleaning afterwards) and the int32 words of
-// per-call workspace the rank kernels need for n_micro keys.
+// per-call workspace that a call for the full rank needs for n_micro keys.
 size_t rank_state_bytes();
 int64_t rank_workspace_words(int64_t n_micro, int want_rank);
-// class_out[i] = number of cuts element i is below; byte_out[i] = out_of_below[class_out[i]], byte_out2
-// (optional) likewise from out2_of_below.  kept_idx (optional): ascending indices of the elements below no cut.
-hipError_t launch_classify(hipStream_t stream, const float* energy, int64_t n_micro, const RankCuts& cuts,
-                           uint8_t* class_out, uint8_t* byte_out, uint8_t* byte_out2, int32_t* kept_idx, void* state,
-                           int32_t* ws);
-hipError_t launch_segment_outputs(hipStream_t stream, const uint8_t* class_out, const SegTable& seg,
-                                  const SegOutputs& out);
+// byte_out[i] = out_of_below[k] for an element i below k cuts, byte_out2 (optional) likewise from out2_of_below; the
+// per-segment outputs of `out`.  kept_idx (optional, with one pruning ratio): ascending indices of the elements below
+// no cut.
+hipError_t launch_rank_decisions(hipStream_t stream, const float* energy, int64_t n_micro, const RankCuts& cuts,
+                                 const SegTable& seg, const SegOutputs& out, uint8_t* byte_out, uint8_t* byte_out2,
+                                 int32_t* kept_idx, void* state);
 // Full stable ascending rank by LSD radix sort.
 hipError_t launch_full_rank(hipStream_t stream, const float* energy, int64_t n_micro, uint32_t* rank,
                             int32_t* ws);

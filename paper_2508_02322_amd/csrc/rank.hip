@@ -4,21 +4,16 @@
 // The order is the stable ascending order of (energy, index).  A cut at rank t
 // separates the t lowest-ranked micro-experts from the rest; CAMERA-P needs one
 // cut (t = n_prune), CAMERA-Q one per class boundary.  No sort is needed for
-// that: a radix select (11 + 11 + 10 bits) finds, for every cut, the key K of the
+// that: a radix select (16 + 16 bits) finds, for every cut, the key K of the
 // element of rank t and how many elements equal to K lie below the cut (r);
 // element i is below the cut iff key_i < K, or key_i == K and fewer than r equal
 // keys precede it.  The "equal keys that precede" count comes from an ordered
 // walk: every wave owns a contiguous index range, ballots + popcounts give the
-// order inside 256-element steps.
+// order inside 64-element steps.
 //
-// rank_* kernels: the select passes and the walk for all cuts at once (the
-// CAMERA-P cuts of several ratios and the CAMERA-Q class boundaries of a layer
-// are cuts on the same order, so one set of passes serves both decisions), one
-// workgroup per 4096 keys (<= 184 320 keys per layer in the paper's models:
-// latency- and launch-bound, not bandwidth-bound).
-// segment_kernel: one workgroup per expert: class sizes, from them the kept
-// counts per ratio and the level sizes, and the stable partition of its
-// micro-experts by precision level.
+// rank_top / rank_low / rank_segment: all cuts of a call at once (the CAMERA-P
+// cuts of several ratios and the CAMERA-Q class boundaries of a layer are cuts
+// on the same order, so one set of passes serves both decisions).
 // full rank: LSD radix sort (4 x 8 bits) of (key, index) built from a stable
 // counting sort whose in-wave order again comes from ballots.
 #include "camera_internal.h"
@@ -34,478 +29,349 @@ __device__ __forceinline__ uint32_t key_of(float v) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// 4 consecutive keys starting at i (i is a multiple of 4); keys past n are 0xffffffff with valid = false
-struct Keys4 {
-  uint32_t k[4];
-  bool valid[4];
-};
-__device__ __forceinline__ Keys4 load_keys4(const float* __restrict__ E, int64_t i, int64_t n) {
-  Keys4 out;
-  if (i + 3 < n) {
-    const float4 v = *reinterpret_cast<const float4*>(E + i);
-    out.k[0] = key_of(v.x);
-    out.k[1] = key_of(v.y);
-    out.k[2] = key_of(v.z);
-    out.k[3] = key_of(v.w);
-    out.valid[0] = out.valid[1] = out.valid[2] = out.valid[3] = true;
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      out.valid[j] = i + j < n;
-      out.k[j] = out.valid[j] ? key_of(E[i + j]) : 0xffffffffu;
-    }
-  }
-  return out;
-}
-
 // ---------------------------------------------------------------------------
-// classify: radix select for every cut, then the ordered classification walk.
+// The decisions: two histogram passes over the keys, then the walk over the segments (experts).
 //
-// A layer has at most a few hundred thousand keys, so every pass is latency- and launch-bound:
-// the work is spread over one workgroup per 4096 keys (each thread has its 16 keys in flight at
-// once) and chained as short kernels on the stream.  After each histogram pass the workgroup
-// that finishes last (a ticket from an atomic counter after a __threadfence; nobody waits for
-// anybody) picks, for every cut, the bin that holds the cut element and publishes prefix / rest.
-//   hist<P>   P = 0, 1, 2: 11 + 11 + 10 key bits; keys that share the cut's prefix so far
-//   label     ordered walk: class byte, up to two output bytes, kept counts per workgroup
-//   compact   (optional) ascending list of the kept indices
-// The select state is self-cleaning: it starts as zeros (the library clears it when it makes it), pass 0
-// seeds the per-cut fields from the call's cuts, and the last workgroup of every pass clears the histograms
-// and the ticket it has just used.  A call therefore needs no clearing launch and leaves the state as it
-// found it.  Equal keys that a cut runs through (rare: energies of experts without tokens) are ordered by
-// index inside the label kernel, each workgroup counting the equal keys that precede it.
+// A layer has at most a few hundred thousand keys (<= 0.74 MB), so a call is bound by launches and by the latency of
+// what each of them does in sequence, not by bandwidth.  Hence few passes and nothing serial between them:
+//   top      one histogram of the upper 16 key bits, counted per workgroup in LDS (2^16 counters of 16 bits, 128 KiB)
+//            and added to global memory where it is not zero: 8192 keys fall on one to two thousand values, so few
+//            atomics leave a workgroup
+//   low      the lower 16 bits of the keys that share a cut's upper 16; few keys do (a value of the upper 16 bits spans
+//            1/128 of an octave), so they go to global memory one by one
+//   segment  one workgroup per segment: class of every element, output bytes, counts and the stable partition by level
+//   compact  (optional) ascending list of the kept indices
+// No workgroup picks for the others: `low` and `segment` begin with every workgroup reading the histogram of the pass
+// before for itself -- a wave per cut, 256 coarse counters (8 bits) and then the 256 fine ones under the bin it found,
+// two dependent loads -- so nothing needs a fence, a ticket or a last workgroup, and a kernel boundary is the only
+// synchronisation.  Measured for 98 304 keys and five cuts: 28 us in 3 launches (7 + 12 + 9); with three passes of
+// 11 + 11 + 10 bits over all keys and all cuts, each closed by a last workgroup that picked, 82 us in 5 launches, 53 of
+// them in two passes' atomics and picks.  A call on 4096 keys: 18 us against 61.
+// The select state cleans itself: it starts as zeros (the library clears it when it makes it), `top` clears what `low`
+// will count in, `segment` clears what `top` counted in.  A call needs no clearing launch and leaves the state as it
+// found it.  Equal keys that a cut runs through (energies of experts without tokens) are ordered by index inside the
+// segment kernel, each workgroup counting the equal keys that precede it.
 // ---------------------------------------------------------------------------
-constexpr int kRankThreads = 256;
+constexpr int kRankThreads = 1024;
 constexpr int kRankWaves = kRankThreads / kWave;
-constexpr int kKeysPerBlock = kRankThreads * 16;  // 4096
-constexpr int kKeysPerWave = kKeysPerBlock / kRankWaves;  // 1024 consecutive keys
-constexpr int kBins = 2048;
+constexpr int kKeysPerBlock = kRankThreads * 8;  // a counter of the LDS histogram cannot overflow its 16 bits
+constexpr int kFine = 1 << 16, kCoarse = 1 << 8;
+constexpr int kMinTopBlocks = 64;                // workgroups that clear for `low` (0.25 MB per cut) when the keys are few
+static_assert(kMaxCuts <= kRankWaves, "a wave per cut in the pick");
 
 struct RankState {  // persistent, see above
-  uint32_t hist[3][kMaxCuts][kBins];
-  uint32_t ticket[4];
-  uint32_t prefix[kMaxCuts];  // key bits fixed so far (right-aligned); after pass 2 the key K of the cut element
-  uint32_t rest[kMaxCuts];    // rank of the cut among keys sharing the prefix; after pass 2: equal keys below the cut
-  int32_t mode[kMaxCuts];     // 0 select, 1 nothing below, 2 everything below
-  uint32_t ties_split;        // some cut runs through a group of equal keys
+  uint32_t top_coarse[kCoarse];           // counts by key bits 31..24
+  uint32_t top_fine[kFine];               // counts by key bits 31..16
+  struct Low {
+    uint32_t coarse[kCoarse];             // of the keys that share the cut's bits 31..16: counts by bits 15..8
+    uint32_t fine[kFine];                 // and by bits 15..0
+  } low[kMaxCuts];
+  uint32_t prefix[kMaxCuts];              // bits 31..16 of the cut element
+  uint32_t rest[kMaxCuts];                // its rank among the keys that share them
 };
 
-__device__ __forceinline__ Keys4 keys_of(float4 v) {
-  Keys4 k;
-  k.k[0] = key_of(v.x);
-  k.k[1] = key_of(v.y);
-  k.k[2] = key_of(v.z);
-  k.k[3] = key_of(v.w);
-  k.valid[0] = k.valid[1] = k.valid[2] = k.valid[3] = true;
-  return k;
-}
-
-// The 16 keys of this thread: wave w of the block owns 1024 consecutive keys, step u of the wave
-// 256 of them, lane l keys 4 l .. 4 l + 3 of the step.  All four loads are issued together.
-struct Keys16 {
-  Keys4 g[4];
-  int64_t first[4];
+// The 8 keys of this thread: two float4 of consecutive keys, kKeysPerBlock / 2 apart.  Both loads are issued together.
+struct Keys8 {
+  uint32_t k[8];
+  int n_valid[2];  // of each four, the valid ones come first
 };
-__device__ __forceinline__ Keys16 load_keys16(const float* __restrict__ E, int64_t n) {
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int64_t base = (int64_t)blockIdx.x * kKeysPerBlock + (int64_t)wave * kKeysPerWave + lane * 4;
-  Keys16 out;
-  if ((int64_t)blockIdx.x * kKeysPerBlock + kKeysPerBlock <= n) {  // block-uniform: whole block inside
-    float4 v[4];
+__device__ __forceinline__ Keys8 load_keys8(const float* __restrict__ E, int64_t n) {
+  Keys8 out;
+  float4 v[2];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4*>(E + base + u * 256);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) out.g[u] = keys_of(v[u]);
-  } else {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) out.g[u] = load_keys4(E, base + u * 256, n);
+  for (int u = 0; u < 2; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kKeysPerBlock + u * (kKeysPerBlock / 2) + threadIdx.x * 4;
+    out.n_valid[u] = i >= n ? 0 : (int)min((int64_t)4, n - i);
+    if (out.n_valid[u] == 4) {
+      v[u] = *reinterpret_cast<const float4*>(E + i);
+    } else {
+      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (out.n_valid[u] > 0) v[u].x = E[i];
+      if (out.n_valid[u] > 1) v[u].y = E[i + 1];
+      if (out.n_valid[u] > 2) v[u].z = E[i + 2];
+    }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) out.first[u] = base + u * 256;
+  for (int u = 0; u < 2; ++u) {
+    out.k[4 * u] = key_of(v[u].x);
+    out.k[4 * u + 1] = key_of(v[u].y);
+    out.k[4 * u + 2] = key_of(v[u].z);
+    out.k[4 * u + 3] = key_of(v[u].w);
+  }
   return out;
 }
 
-// What another workgroup wrote before it took its ticket: read past this CU's vector cache.
-__device__ __forceinline__ uint32_t load_agent(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// A cut needs a select unless nothing or everything lies below it.
+enum { kCutSelect = 0, kCutNone = 1, kCutAll = 2 };
+__host__ __device__ inline int cut_mode(const RankCuts& cuts, int q, int64_t n) {
+  if (q >= cuts.n_cuts || cuts.cut_rank[q] <= 0) return kCutNone;
+  return cuts.cut_rank[q] >= n ? kCutAll : kCutSelect;
 }
 
-__device__ __forceinline__ int cut_mode(const RankCuts& cuts, int q, int64_t n) {
-  if (q >= cuts.n_cuts) return 1;
-  const int64_t t = cuts.cut_rank[q];
-  return t <= 0 ? 1 : (t >= n ? 2 : 0);
-}
-
-// Histogram pass P over the keys that share each cut's prefix, then (last workgroup) the pick.
-template <int P>
-__global__ __launch_bounds__(kRankThreads) void rank_hist_kernel(const float* __restrict__ E, int64_t n, RankCuts cuts,
-                                                                RankState* __restrict__ st) {
-  constexpr int kShift = P == 0 ? 21 : (P == 1 ? 10 : 0);
-  constexpr int kBits = P == 2 ? 10 : 11;
-  constexpr int kPrevShift = kShift + kBits;
-  constexpr uint32_t kMask = (1u << kBits) - 1u;
-  constexpr int kHists = P == 0 ? 1 : kMaxCuts;  // pass 0 has no prefix yet: one histogram serves every cut
-  __shared__ uint32_t hist[kHists][kBins];
-  __shared__ uint32_t s_last;
-  const int tid = threadIdx.x;
-  const int n_cuts = cuts.n_cuts;
-
-  uint32_t want[kMaxCuts];
-  bool any = false;
+// By one whole wave: which of 256 counters holds the element of rank `rank`, and its rank inside that counter.
+struct Pick {
+  uint32_t bin, rest;
+};
+__device__ __forceinline__ Pick pick256(const uint32_t* __restrict__ counters, uint32_t rank) {
+  const int lane = threadIdx.x % kWave;
+  const uint4 c = *reinterpret_cast<const uint4*>(counters + lane * 4);
+  const uint32_t sum = c.x + c.y + c.z + c.w;
+  uint32_t before = sum;
 #pragma unroll
-  for (int q = 0; q < kMaxCuts; ++q) {
-    const bool on = P == 0 ? cut_mode(cuts, q, n) == 0 : (q < n_cuts && st->mode[q] == 0);
-    want[q] = on ? (P == 0 ? 0u : st->prefix[q]) : 0xffffffffu;  // a real prefix has at most 22 bits
-    any |= on;
+  for (int d = 1; d < kWave; d <<= 1) {
+    const uint32_t o = __shfl_up(before, d);
+    if (lane >= d) before += o;
   }
-  if (P == 0 && blockIdx.x == 0 && tid < kMaxCuts) {
-    // The per-cut fields of this call.  Nobody else reads them during pass 0 (the pick below takes the cut
-    // ranks from the kernel argument) and only the pick of this pass writes prefix / rest after them.
-    st->mode[tid] = cut_mode(cuts, tid, n);
-    if (cut_mode(cuts, tid, n) != 0) {
-      st->prefix[tid] = 0u;
-      st->rest[tid] = 0u;
+  before -= sum;
+  uint32_t bin = lane * 4, rest = rank - before;
+  const bool mine = rank >= before && rest < sum;
+  if (rest >= c.x) {
+    rest -= c.x;
+    ++bin;
+    if (rest >= c.y) {
+      rest -= c.y;
+      ++bin;
+      if (rest >= c.z) {
+        rest -= c.z;
+        ++bin;
+      }
     }
-    if (tid == 0) st->ties_split = 0u;
   }
-  if (!any) return;  // block-uniform: no cut needs a select
-  const int n_hists = P == 0 ? 1 : n_cuts;
-  for (int i = tid; i < n_hists * kBins; i += kRankThreads) (&hist[0][0])[i] = 0u;
-  __syncthreads();
-  const Keys16 keys = load_keys16(E, n);
+  const uint64_t who = __ballot(mine);
+  const int src = who ? __ffsll((unsigned long long)who) - 1 : 0;  // exactly one lane: the counters add up to more than `rank`
+  return {__shfl(bin, src), __shfl(rest, src)};
+}
+__device__ __forceinline__ Pick pick_2level(const uint32_t* coarse, const uint32_t* fine, uint32_t rank) {
+  const Pick c = pick256(coarse, rank);
+  const Pick f = pick256(fine + c.bin * kCoarse, c.rest);
+  return {c.bin * kCoarse + f.bin, f.rest};
+}
+
+constexpr int kTopLds = kFine * 2 + kCoarse * 4;
+
+__global__ __launch_bounds__(kRankThreads) void rank_top_kernel(const float* __restrict__ E, int64_t n, int key_blocks,
+                                                                int n_cuts, RankState* __restrict__ st) {
+  extern __shared__ __align__(16) uint32_t hist[];  // [kFine / 2] pairs of 16-bit counters, then [kCoarse]
+  uint32_t* coarse = hist + kFine / 2;
+  const int tid = threadIdx.x;
+  const bool has_keys = (int)blockIdx.x < key_blocks;
+  Keys8 keys;
+  if (has_keys) keys = load_keys8(E, n);
+  {  // this workgroup's share of the counters that `low` adds to: consecutive cuts are consecutive in memory
+    uint4* low = reinterpret_cast<uint4*>(&st->low[0]);
+    const int total = n_cuts * (int)(sizeof(RankState::Low) / 16);
+    for (int i = blockIdx.x * kRankThreads + tid; i < total; i += gridDim.x * kRankThreads) low[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  if (!has_keys) return;  // block-uniform
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int i = 0; i < kFine / 8 / kRankThreads; ++i) reinterpret_cast<uint4*>(hist)[tid + i * kRankThreads] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid < kCoarse) coarse[tid] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j < keys.n_valid[u]) {
+        const uint32_t top = keys.k[4 * u + j] >> 16;
+        atomicAdd(&hist[top >> 1], 1u << (16 * (top & 1)));
+      }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kFine / 8 / kRankThreads; ++i) {
+    const int at = tid + i * kRankThreads;  // eight counters, all under one coarse one
+    const uint4 c = reinterpret_cast<const uint4*>(hist)[at];
+    if ((c.x | c.y | c.z | c.w) == 0u) continue;
+    const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+    uint32_t sum = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (!keys.g[u].valid[j]) continue;
-      const uint32_t k = keys.g[u].k[j];
-      if constexpr (P == 0) {
-        atomicAdd(&hist[0][k >> kShift], 1u);
-      } else {
-        const uint32_t top = k >> kPrevShift;
-#pragma unroll
-        for (int q = 0; q < kMaxCuts; ++q)
-          if (top == want[q]) atomicAdd(&hist[q][(k >> kShift) & kMask], 1u);
-      }
+      const uint32_t lo = w[j] & 0xffffu, hi = w[j] >> 16;
+      if (lo) atomicAdd(&st->top_fine[at * 8 + 2 * j], lo);
+      if (hi) atomicAdd(&st->top_fine[at * 8 + 2 * j + 1], hi);
+      sum += lo + hi;
     }
-  __syncthreads();
-  for (int i = tid; i < n_hists * kBins; i += kRankThreads) {
-    const uint32_t c = (&hist[0][0])[i];
-    if (c) atomicAdd(&st->hist[P][0][0] + i, c);
-  }
-  // last workgroup to get here sees every other workgroup's additions
-  __threadfence();
-  __syncthreads();
-  if (tid == 0) s_last = atomicAdd(&st->ticket[P], 1u) == gridDim.x - 1 ? 1u : 0u;
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
-  // The pick, for all cuts together (one round of loads, one scan): thread t owns bins kPer t .. kPer t + kPer - 1
-  // of every cut's histogram (pass 0: the one histogram all cuts share).
-  constexpr int kPer = kBins / kRankThreads;
-  uint32_t c[kHists][kPer], before[kHists];
-#pragma unroll
-  for (int q = 0; q < kHists; ++q) {
-    before[q] = 0u;
-    const bool on = P == 0 || want[q] != 0xffffffffu;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      c[q][i] = on ? load_agent(&st->hist[P][q][tid * kPer + i]) : 0u;
-      before[q] += c[q][i];
-    }
-  }
-  {  // exclusive prefix over the threads, every histogram at once
-    const int lane = tid % kWave, wave = tid / kWave;
-    __shared__ uint32_t s_tot[kRankWaves][kHists];
-    uint32_t inc[kHists];
-#pragma unroll
-    for (int q = 0; q < kHists; ++q) {
-      inc[q] = before[q];
-#pragma unroll
-      for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t o = __shfl_up(inc[q], d);
-        if (lane >= d) inc[q] += o;
-      }
-      if (lane == kWave - 1) s_tot[wave][q] = inc[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kHists; ++q) {
-      uint32_t base = 0;
-      for (int w = 0; w < wave; ++w) base += s_tot[w][q];
-      before[q] = base + inc[q] - before[q];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < kMaxCuts; ++q) {
-    if (q >= n_cuts || want[q] == 0xffffffffu) continue;  // block-uniform
-    constexpr int kShared = P == 0 ? 1 : kMaxCuts;
-    const int hq = q % kShared;  // pass 0: histogram 0 serves every cut
-    const uint32_t rest = P == 0 ? (uint32_t)cuts.cut_rank[q] : st->rest[q];
-    uint32_t run = before[hq];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      if (rest >= run && rest < run + c[hq][i]) {
-        st->prefix[q] = (want[q] << kBits) | (uint32_t)(tid * kPer + i);
-        st->rest[q] = rest - run;
-        if (P == 2 && rest - run > 0) st->ties_split = 1u;
-      }
-      run += c[hq][i];
-    }
+    atomicAdd(&coarse[at / (kCoarse / 8)], sum);
   }
   __syncthreads();
-  // leave the state as the next call needs it: this pass's histograms and ticket back to zero
-  for (int i = tid; i < n_hists * kBins; i += kRankThreads) (&st->hist[P][0][0])[i] = 0u;
-  if (tid == 0) st->ticket[P] = 0u;
+  if (tid < kCoarse && coarse[tid]) atomicAdd(&st->top_coarse[tid], coarse[tid]);
 }
 
-// Ordered walk: an element is below cut q iff key < K_q, or key == K_q and fewer than rest_q equal
-// keys precede it (by index).  Writes the class (number of cuts it is below) and the output bytes.
-__global__ __launch_bounds__(kRankThreads) void rank_label_kernel(const float* __restrict__ E, int64_t n,
-                                                                 RankCuts cuts, const RankState* __restrict__ st,
-                                                                 uint8_t* __restrict__ class_out,
-                                                                 uint8_t* __restrict__ byte_out,
-                                                                 uint8_t* __restrict__ byte_out2 /*or NULL*/,
-                                                                 uint32_t* __restrict__ kept_cnt /*[grid] or NULL*/) {
-  __shared__ uint32_t s_tie[kMaxCuts][kRankWaves];
-  __shared__ uint32_t s_before[kMaxCuts][kRankWaves];
-  __shared__ uint32_t s_kept[kRankWaves];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const uint64_t lower = (1ull << lane) - 1ull;
-  const bool ties_split = st->ties_split != 0;
-  uint32_t K[kMaxCuts], R[kMaxCuts];
-  int mode[kMaxCuts];
+__global__ __launch_bounds__(kRankThreads) void rank_low_kernel(const float* __restrict__ E, int64_t n, RankCuts cuts,
+                                                                RankState* __restrict__ st) {
+  __shared__ uint32_t s_prefix[kMaxCuts];
+  __shared__ uint32_t s_coarse[kMaxCuts][kCoarse];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const Keys8 keys = load_keys8(E, n);
+  for (int i = tid; i < kMaxCuts * kCoarse; i += kRankThreads) (&s_coarse[0][0])[i] = 0u;
+  if (wave < kMaxCuts) {
+    Pick p = {0xffffffffu, 0u};  // not a value of 16 bits: no key matches
+    if (cut_mode(cuts, wave, n) == kCutSelect) p = pick_2level(st->top_coarse, st->top_fine, (uint32_t)cuts.cut_rank[wave]);
+    if (lane == 0) {
+      s_prefix[wave] = p.bin;
+      if (blockIdx.x == 0) {
+        st->prefix[wave] = p.bin;
+        st->rest[wave] = p.rest;
+      }
+    }
+  }
+  __syncthreads();
+  uint32_t want[kMaxCuts];
+#pragma unroll
+  for (int q = 0; q < kMaxCuts; ++q) want[q] = s_prefix[q];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool valid = j < keys.n_valid[u];
+      const uint32_t k = keys.k[4 * u + j], low = k & 0xffffu;
+#pragma unroll
+      for (int q = 0; q < kMaxCuts; ++q) {
+        bool match = valid && (k >> 16) == want[q];
+        uint64_t m = __ballot(match);
+        if (m == 0) continue;  // wave-uniform
+        if (match) atomicAdd(&s_coarse[q][low >> 8], 1u);
+        // Many matches in one wave are mostly equal keys (experts without tokens): one addition for all that equal the
+        // first, a few times; the rest, and the usual one or two, each for itself.
+        for (int round = 0; round < 3 && __popcll(m) > 4; ++round) {
+          const int leader = __ffsll((unsigned long long)m) - 1;
+          const uint64_t same = __ballot(match && low == __shfl(low, leader));
+          if (lane == leader) atomicAdd(&st->low[q].fine[low], (uint32_t)__popcll(same));
+          m &= ~same;
+          match = match && ((same >> lane) & 1) == 0;
+        }
+        if (match) atomicAdd(&st->low[q].fine[low], 1u);
+      }
+    }
+  __syncthreads();
+  for (int i = tid; i < kMaxCuts * kCoarse; i += kRankThreads) {
+    const uint32_t c = (&s_coarse[0][0])[i];
+    if (c) atomicAdd(&st->low[i / kCoarse].coarse[i % kCoarse], c);
+  }
+}
+
+__device__ __forceinline__ int nibble(uint32_t packed, int c) { return (int)((packed >> (4 * c)) & 15u); }
+
+// The cuts as the walk sees them.
+struct CutKeys {
+  uint32_t key[kMaxCuts];   // key of the cut element; 0 where nothing, 0xffffffff where everything lies below (with all set)
+  uint32_t ties[kMaxCuts];  // how many keys equal to it lie below the cut
+  uint32_t all;             // bit q: everything lies below cut q
+};
+
+// Number of cuts that the element with key k is below.  tie_run[q]: keys equal to the cut's at lower indices than this
+// wave's step; moved on by the step.  ANY_TIES: some cut runs through a group of equal keys.
+template <bool ANY_TIES>
+__device__ __forceinline__ int class_of(const CutKeys& c, uint32_t k, bool valid, uint64_t lower, uint32_t* tie_run) {
+  int below = __popc(c.all);
 #pragma unroll
   for (int q = 0; q < kMaxCuts; ++q) {
-    mode[q] = q < cuts.n_cuts ? st->mode[q] : 1;
-    K[q] = st->prefix[q];
-    R[q] = mode[q] == 0 ? st->rest[q] : 0u;
+    below += k < c.key[q] ? 1 : 0;
+    if (ANY_TIES && c.ties[q] != 0) {  // block-uniform
+      const bool eq = valid && k == c.key[q];
+      const uint64_t b = __ballot(eq);
+      if (eq && tie_run[q] + __popcll(b & lower) < c.ties[q]) below += 1;
+      tie_run[q] += __popcll(b);
+    }
   }
-  const Keys16 keys = load_keys16(E, n);
+  return below;
+}
+
+template <bool ANY_TIES>
+__device__ __forceinline__ void segment_walk(const float* __restrict__ E, const CutKeys& cut, int begin, int end,
+                                             uint64_t out_table, uint64_t out2_table, const SegOutputs& out, int n_seg,
+                                             uint8_t* __restrict__ byte_out, uint8_t* __restrict__ byte_out2,
+                                             uint32_t (*s_cnt)[CAMERA_MAX_LEVELS], uint32_t (*s_lvl)[CAMERA_MAX_LEVELS],
+                                             uint32_t (*s_tie)[kRankWaves]) {
+  const int s = blockIdx.x;
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const uint64_t lower = (1ull << lane) - 1ull;
+  const int span = ((end - begin + kRankWaves * kWave - 1) / (kRankWaves * kWave)) * kWave;
+  const int w_begin = min(end, begin + wave * span);
+  const int w_end = min(end, w_begin + span);
+  constexpr int U = 4;  // steps whose loads are in flight together
 
   uint32_t tie_base[kMaxCuts];
 #pragma unroll
   for (int q = 0; q < kMaxCuts; ++q) tie_base[q] = 0u;
-  if (ties_split) {  // block-uniform
-    // equal keys before this wave: in the workgroups before this one (counted here, by all threads, over
-    // keys [0, first key of this workgroup)) and in the earlier waves of this one
-    uint32_t mine[kMaxCuts], before[kMaxCuts];
+  if constexpr (ANY_TIES) {
+    // equal keys before this wave: in the segments before this one (counted here by all threads) and in the earlier
+    // waves of this one
+    uint32_t before[kMaxCuts], mine[kMaxCuts];
 #pragma unroll
-    for (int q = 0; q < kMaxCuts; ++q) {
-      mine[q] = 0u;
-      before[q] = 0u;
-      if (mode[q] == 0 && R[q] > 0) {
+    for (int q = 0; q < kMaxCuts; ++q) before[q] = mine[q] = 0u;
+    for (int i0 = 0; i0 < begin; i0 += U * kRankThreads) {
+      uint32_t k[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            mine[q] += __popcll(__ballot(keys.g[u].valid[j] && keys.g[u].k[j] == K[q]));
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * kRankThreads + (int)threadIdx.x;
+        k[u] = i < begin ? key_of(E[i]) : 0u;
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int q = 0; q < kMaxCuts; ++q)
+          before[q] += (i0 + u * kRankThreads + (int)threadIdx.x < begin && k[u] == cut.key[q]) ? 1u : 0u;
     }
-    const int64_t n_before = (int64_t)blockIdx.x * kKeysPerBlock;  // a multiple of 4, all inside [0, n)
-    for (int64_t i = (int64_t)threadIdx.x * 4; i < n_before; i += kRankThreads * 4) {
-      const Keys4 k = keys_of(*reinterpret_cast<const float4*>(E + i));
+    for (int i0 = w_begin; i0 < w_end; i0 += kWave) {
+      const bool valid = i0 + lane < w_end;
+      const uint32_t k = valid ? key_of(E[i0 + lane]) : 0u;
 #pragma unroll
-      for (int q = 0; q < kMaxCuts; ++q)
-        if (mode[q] == 0 && R[q] > 0) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) before[q] += k.k[j] == K[q] ? 1u : 0u;
-        }
+      for (int q = 0; q < kMaxCuts; ++q) mine[q] += __popcll(__ballot(valid && k == cut.key[q]));
     }
 #pragma unroll
     for (int q = 0; q < kMaxCuts; ++q) {
 #pragma unroll
       for (int m = 32; m >= 1; m >>= 1) before[q] += __shfl_xor(before[q], m);
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int q = 0; q < kMaxCuts; ++q) {
+      if (lane == 0) {
         s_tie[q][wave] = mine[q];
-        s_before[q][wave] = before[q];
+        s_tie[kMaxCuts + q][wave] = before[q];
       }
     }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kMaxCuts; ++q) {
-      if (mode[q] == 0 && R[q] > 0) {
-        uint32_t run = 0;
-        for (int w = 0; w < kRankWaves; ++w) run += s_before[q][w];
-        for (int w = 0; w < wave; ++w) run += s_tie[q][w];
-        tie_base[q] = run;
-      }
+      uint32_t run = 0;
+      for (int w = 0; w < kRankWaves; ++w) run += s_tie[kMaxCuts + q][w] + (w < wave ? s_tie[q][w] : 0u);
+      tie_base[q] = run;
     }
   }
 
-  uint32_t kept = 0;
+  // first walk: output bytes and class sizes
+  uint32_t cnt[CAMERA_MAX_LEVELS], tie_run[kMaxCuts];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const Keys4& k = keys.g[u];
-    const int64_t i = keys.first[u];
-    int below[4] = {0, 0, 0, 0};
+  for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) cnt[m] = 0u;
 #pragma unroll
-    for (int q = 0; q < kMaxCuts; ++q) {
-      if (mode[q] == 1) continue;
-      if (mode[q] == 2) {
+  for (int q = 0; q < kMaxCuts; ++q) tie_run[q] = tie_base[q];
+  for (int i0 = w_begin; i0 < w_end; i0 += U * kWave) {
+    float v[U];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) below[j] += 1;
-        continue;
-      }
-      if (R[q] == 0) {  // no key equal to K is below this cut
-#pragma unroll
-        for (int j = 0; j < 4; ++j) below[j] += k.k[j] < K[q] ? 1 : 0;
-        continue;
-      }
-      bool eq[4];
-      uint32_t lanes_before = 0, total = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        eq[j] = k.valid[j] && k.k[j] == K[q];
-        const uint64_t b = __ballot(eq[j]);
-        lanes_before += __popcll(b & lower);
-        total += __popcll(b);
-      }
-      uint32_t tie_rank = tie_base[q] + lanes_before;  // equal keys at lower indices
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (k.k[j] < K[q] || (eq[j] && tie_rank < R[q])) below[j] += 1;
-        tie_rank += eq[j] ? 1u : 0u;
-      }
-      tie_base[q] += total;
-    }
-    if (k.valid[3]) {  // whole group inside: one 4-byte store per output
-      const uint32_t cls4 = (uint32_t)below[0] | ((uint32_t)below[1] << 8) | ((uint32_t)below[2] << 16) |
-                            ((uint32_t)below[3] << 24);
-      const uint32_t out4 = (uint32_t)cuts.out_of_below[below[0]] | ((uint32_t)cuts.out_of_below[below[1]] << 8) |
-                            ((uint32_t)cuts.out_of_below[below[2]] << 16) |
-                            ((uint32_t)cuts.out_of_below[below[3]] << 24);
-      *reinterpret_cast<uint32_t*>(class_out + i) = cls4;
-      *reinterpret_cast<uint32_t*>(byte_out + i) = out4;
-      if (byte_out2) {
-        const uint32_t second4 = (uint32_t)cuts.out2_of_below[below[0]] | ((uint32_t)cuts.out2_of_below[below[1]] << 8) |
-                                 ((uint32_t)cuts.out2_of_below[below[2]] << 16) |
-                                 ((uint32_t)cuts.out2_of_below[below[3]] << 24);
-        *reinterpret_cast<uint32_t*>(byte_out2 + i) = second4;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (k.valid[j]) {
-          class_out[i + j] = (uint8_t)below[j];
-          byte_out[i + j] = cuts.out_of_below[below[j]];
-          if (byte_out2) byte_out2[i + j] = cuts.out2_of_below[below[j]];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) kept += __popcll(__ballot(k.valid[j] && below[j] == 0));
-  }
-  if (kept_cnt == nullptr) return;  // block-uniform
-  if (lane == 0) s_kept[wave] = kept;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t total = 0;
-    for (int w = 0; w < kRankWaves; ++w) total += s_kept[w];
-    kept_cnt[blockIdx.x] = total;
-  }
-}
-
-// Ascending list of the indices of class 0 (below no cut).
-__global__ __launch_bounds__(kRankThreads) void rank_compact_kernel(const uint8_t* __restrict__ class_in, int64_t n,
-                                                                   const uint32_t* __restrict__ kept_cnt,
-                                                                   int32_t* __restrict__ kept_idx) {
-  __shared__ uint32_t s_kept[kRankWaves];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const uint64_t lower = (1ull << lane) - 1ull;
-  const int64_t base = (int64_t)blockIdx.x * kKeysPerBlock + (int64_t)wave * kKeysPerWave + lane * 4;
-  bool is_kept[4][4];
-  uint32_t mine = 0;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int64_t i = base + u * 256;
-    uint32_t c4 = 0x01010101u;
-    if (i + 3 < n) {
-      c4 = *reinterpret_cast<const uint32_t*>(class_in + i);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (i + j < n) c4 = (c4 & ~(0xffu << (8 * j))) | ((uint32_t)class_in[i + j] << (8 * j));
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      is_kept[u][j] = ((c4 >> (8 * j)) & 0xffu) == 0u;
-      mine += __popcll(__ballot(is_kept[u][j]));
-    }
-  }
-  if (lane == 0) s_kept[wave] = mine;
-  __syncthreads();
-  uint32_t pos = 0;
-  for (int b = lane; b < (int)blockIdx.x; b += kWave) pos += kept_cnt[b];
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) pos += __shfl_xor(pos, m);
-  for (int w = 0; w < wave; ++w) pos += s_kept[w];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    uint32_t lanes_before = 0, total = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint64_t b = __ballot(is_kept[u][j]);
-      lanes_before += __popcll(b & lower);
-      total += __popcll(b);
-    }
-    uint32_t p = pos + lanes_before;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (is_kept[u][j]) kept_idx[p++] = (int32_t)(base + u * 256 + j);
-    pos += total;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// per segment (expert): class sizes, from them the kept counts of every pruning ratio and the sizes of
-// the precision levels, and the stable partition of the segment by level
-// ---------------------------------------------------------------------------
-constexpr int kSegThreads = 1024;  // a shared expert can be a 20 480-element segment: 16 waves walk it
-constexpr int kSegWaves = kSegThreads / kWave;
-
-__device__ __forceinline__ int nibble(uint32_t packed, int c) { return (int)((packed >> (4 * c)) & 15u); }
-
-__global__ __launch_bounds__(kSegThreads) void segment_kernel(const uint8_t* __restrict__ class_in, SegTable seg,
-                                                              SegOutputs out) {
-  __shared__ uint32_t s_cnt[kSegWaves][CAMERA_MAX_LEVELS];   // per wave and class
-  __shared__ uint32_t s_lvl[kSegWaves][CAMERA_MAX_LEVELS];   // per wave and level
-  const int s = blockIdx.x;
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int begin = seg.off[s], end = seg.off[s + 1];
-  const int span = ((end - begin + kSegWaves * kWave - 1) / (kSegWaves * kWave)) * kWave;
-  const int w_begin = min(end, begin + wave * span);
-  const int w_end = min(end, w_begin + span);
-  const uint64_t lower = (1ull << lane) - 1ull;
-  const int n_classes = out.n_classes;
-
-  uint32_t cnt[CAMERA_MAX_LEVELS];
-#pragma unroll
-  for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) cnt[m] = 0;
-  for (int i0 = w_begin; i0 < w_end; i0 += 4 * kWave) {  // four independent byte loads in flight
-    int c[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int i = i0 + u * kWave + lane;
-      c[u] = i < w_end ? (int)class_in[i] : -1;
+      v[u] = i < w_end ? E[i] : 0.0f;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * kWave + lane;
+      const bool valid = i < w_end;
+      const int c = class_of<ANY_TIES>(cut, key_of(v[u]), valid, lower, tie_run);
+      if (valid) {
+        byte_out[i] = (uint8_t)(out_table >> (8 * c));
+        if (byte_out2) byte_out2[i] = (uint8_t)(out2_table >> (8 * c));
+      }
 #pragma unroll
       for (int m = 0; m < CAMERA_MAX_LEVELS; ++m)
-        if (m < n_classes) cnt[m] += __popcll(__ballot(c[u] == m));
+        if (m < out.n_classes) cnt[m] += __popcll(__ballot(valid && c == m));
+    }
   }
   if (lane == 0) {
 #pragma unroll
     for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) s_cnt[wave][m] = cnt[m];
   }
   __syncthreads();
-  if (threadIdx.x < kSegWaves * CAMERA_MAX_LEVELS) {  // (wave w, level m): members of level m in wave w's range
+  if (threadIdx.x < kRankWaves * CAMERA_MAX_LEVELS) {  // (wave w, level m): members of level m in wave w's range
     const int w = threadIdx.x / CAMERA_MAX_LEVELS, m = threadIdx.x % CAMERA_MAX_LEVELS;
     uint32_t total = 0;
-    for (int c = 0; c < n_classes; ++c)
+    for (int c = 0; c < out.n_classes; ++c)
       if (nibble(out.level_of_class, c) == m) total += s_cnt[w][c];
     s_lvl[w][m] = total;
   }
@@ -513,52 +379,152 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(const uint8_t* __r
     // kept at ratio k: the members of the classes that lie below at most n_ratios - 1 - k of the pruning cuts
     const int k = threadIdx.x - 512;
     uint32_t total = 0;
-    for (int c = 0; c < n_classes; ++c)
+    for (int c = 0; c < out.n_classes; ++c)
       if (nibble(out.prune_cuts_of_class, c) <= out.n_ratios - 1 - k)
-        for (int w = 0; w < kSegWaves; ++w) total += s_cnt[w][c];
-    out.kept[k * seg.n_seg + s] = (int32_t)total;
+        for (int w = 0; w < kRankWaves; ++w) total += s_cnt[w][c];
+    out.kept[k * n_seg + s] = (int32_t)total;
   }
   __syncthreads();
   if (threadIdx.x < out.n_levels) {
     uint32_t total = 0;
-    for (int w = 0; w < kSegWaves; ++w) total += s_lvl[w][threadIdx.x];
+    for (int w = 0; w < kRankWaves; ++w) total += s_lvl[w][threadIdx.x];
     out.level_count[s * out.n_levels + threadIdx.x] = (int32_t)total;
   }
   if (out.perm == nullptr) return;  // block-uniform
 
-  // first slot of level m for this wave: segment start + all earlier levels + earlier waves
+  // second walk: first slot of level m for this wave = segment start + all earlier levels + earlier waves
   uint32_t slot[CAMERA_MAX_LEVELS];
   uint32_t run = (uint32_t)begin;
 #pragma unroll
   for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) {
     slot[m] = 0;
     if (m < out.n_levels) {
-      for (int w = 0; w < kSegWaves; ++w) {
+      for (int w = 0; w < kRankWaves; ++w) {
         if (w == wave) slot[m] = run;
         run += s_lvl[w][m];
       }
     }
   }
-  for (int i0 = w_begin; i0 < w_end; i0 += 4 * kWave) {
-    int lv[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+  for (int q = 0; q < kMaxCuts; ++q) tie_run[q] = tie_base[q];
+  for (int i0 = w_begin; i0 < w_end; i0 += U * kWave) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
       const int i = i0 + u * kWave + lane;
-      lv[u] = i < w_end ? nibble(out.level_of_class, (int)class_in[i] & 7) : -1;
+      v[u] = i < w_end ? E[i] : 0.0f;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int i = i0 + u * kWave + lane;
+      const bool valid = i < w_end;
+      const int lv = nibble(out.level_of_class, class_of<ANY_TIES>(cut, key_of(v[u]), valid, lower, tie_run));
 #pragma unroll
       for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) {
         if (m < out.n_levels) {
-          const uint64_t b = __ballot(lv[u] == m);
-          if (lv[u] == m) out.perm[slot[m] + __popcll(b & lower)] = i;
+          const uint64_t b = __ballot(valid && lv == m);
+          if (valid && lv == m) out.perm[slot[m] + __popcll(b & lower)] = i;
           slot[m] += __popcll(b);
         }
       }
     }
   }
+}
+
+// One workgroup per segment (a shared expert can be a 20 480-element segment: 16 waves walk it).
+// low_counted: the select passes ran (some cut has keys on both sides).
+__global__ __launch_bounds__(kRankThreads) void rank_segment_kernel(const float* __restrict__ E, int64_t n, RankCuts cuts,
+                                                                   SegTable seg, SegOutputs out, int low_counted,
+                                                                   RankState* __restrict__ st, uint8_t* __restrict__ byte_out,
+                                                                   uint8_t* __restrict__ byte_out2 /*or NULL*/) {
+  __shared__ uint32_t s_key[kMaxCuts], s_ties[kMaxCuts];
+  __shared__ uint32_t s_cnt[kRankWaves][CAMERA_MAX_LEVELS];   // per wave and class
+  __shared__ uint32_t s_lvl[kRankWaves][CAMERA_MAX_LEVELS];   // per wave and level
+  __shared__ uint32_t s_tie[2 * kMaxCuts][kRankWaves];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  if (wave < kMaxCuts) {
+    Pick p = {0u, 0u};
+    if (cut_mode(cuts, wave, n) == kCutSelect) {
+      p = pick_2level(st->low[wave].coarse, st->low[wave].fine, st->rest[wave]);
+      p.bin |= st->prefix[wave] << 16;
+    }
+    if (lane == 0) {
+      s_key[wave] = p.bin;
+      s_ties[wave] = p.rest;
+    }
+  }
+  if (low_counted) {  // leave the state as the next call needs it: nobody reads these counters any more
+    uint4* top = reinterpret_cast<uint4*>(st->top_coarse);
+    static_assert(offsetof(RankState, top_fine) == kCoarse * 4, "coarse and fine counters lie side by side");
+    for (int i = blockIdx.x * kRankThreads + tid; i < (kCoarse + kFine) / 4; i += gridDim.x * kRankThreads)
+      top[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  __syncthreads();
+  CutKeys cut;
+  cut.all = 0u;
+  bool any_ties = false;
+  uint64_t out_table = 0, out2_table = 0;
+#pragma unroll
+  for (int q = 0; q < kMaxCuts; ++q) {
+    cut.key[q] = __builtin_amdgcn_readfirstlane(s_key[q]);
+    cut.ties[q] = __builtin_amdgcn_readfirstlane(s_ties[q]);
+    any_ties |= cut.ties[q] != 0;
+    if (cut_mode(cuts, q, n) == kCutAll) cut.all |= 1u << q;
+  }
+#pragma unroll
+  for (int c = 0; c <= kMaxCuts; ++c) {
+    out_table |= (uint64_t)cuts.out_of_below[c] << (8 * c);
+    out2_table |= (uint64_t)cuts.out2_of_below[c] << (8 * c);
+  }
+  const int begin = seg.off[blockIdx.x], end = seg.off[blockIdx.x + 1];
+  if (any_ties)  // block-uniform
+    segment_walk<true>(E, cut, begin, end, out_table, out2_table, out, seg.n_seg, byte_out, byte_out2, s_cnt, s_lvl, s_tie);
+  else
+    segment_walk<false>(E, cut, begin, end, out_table, out2_table, out, seg.n_seg, byte_out, byte_out2, s_cnt, s_lvl, s_tie);
+}
+
+// Ascending list of the kept indices (keep byte 1), one workgroup per segment; kept [n_seg]: how many each segment keeps.
+__global__ __launch_bounds__(kRankThreads) void rank_compact_kernel(const uint8_t* __restrict__ keep, SegTable seg,
+                                                                   const int32_t* __restrict__ kept,
+                                                                   int32_t* __restrict__ kept_idx) {
+  __shared__ uint32_t s_first, s_mine[kRankWaves];
+  const int s = blockIdx.x, lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const uint64_t lower = (1ull << lane) - 1ull;
+  const int begin = seg.off[s], end = seg.off[s + 1];
+  const int span = ((end - begin + kRankWaves * kWave - 1) / (kRankWaves * kWave)) * kWave;
+  const int w_begin = min(end, begin + wave * span);
+  const int w_end = min(end, w_begin + span);
+  constexpr int U = 4;
+  if (wave == 0) {
+    uint32_t first = 0;
+    for (int b = lane; b < s; b += kWave) first += (uint32_t)kept[b];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) first += __shfl_xor(first, m);
+    if (lane == 0) s_first = first;
+  }
+  auto walk = [&](auto&& step) {  // step(index, kept) in index order, all lanes together
+    for (int i0 = w_begin; i0 < w_end; i0 += U * kWave) {
+      uint8_t b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * kWave + lane;
+        b[u] = i < w_end ? keep[i] : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) step(i0 + u * kWave + lane, b[u] != 0);
+    }
+  };
+  uint32_t mine = 0;
+  walk([&](int, bool k) { mine += __popcll(__ballot(k)); });
+  if (lane == 0) s_mine[wave] = mine;
+  __syncthreads();
+  uint32_t pos = s_first;
+  for (int w = 0; w < wave; ++w) pos += s_mine[w];
+  walk([&](int i, bool k) {
+    const uint64_t b = __ballot(k);
+    if (k) kept_idx[pos + __popcll(b & lower)] = i;
+    pos += __popcll(b);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -681,42 +647,39 @@ static_assert(kSortThreads == kDigits, "one thread per digit in the scatter prol
 
 }  // namespace
 
-int64_t rank_blocks(int64_t n_micro) { return (n_micro + kKeysPerBlock - 1) / kKeysPerBlock; }
-
 size_t rank_state_bytes() { return sizeof(RankState); }
 
 int64_t rank_workspace_words(int64_t n_micro, int want_rank) {
-  const int64_t g = rank_blocks(n_micro);
-  int64_t words = g + 64;  // kept counts per workgroup
-  if (want_rank) {
-    const int64_t n_blocks = (n_micro + kSortChunk - 1) / kSortChunk;
-    words += 4 * (n_micro + 64) + n_blocks * kDigits;
-  }
-  return words;
+  if (!want_rank) return 0;
+  const int64_t n_blocks = (n_micro + kSortChunk - 1) / kSortChunk;
+  return 4 * (n_micro + 64) + n_blocks * kDigits;
 }
 
-hipError_t launch_classify(hipStream_t stream, const float* energy, int64_t n_micro, const RankCuts& cuts,
-                           uint8_t* class_out, uint8_t* byte_out, uint8_t* byte_out2, int32_t* kept_idx, void* state,
-                           int32_t* ws) {
-  if (n_micro <= 0) return hipSuccess;
-  const unsigned g = (unsigned)rank_blocks(n_micro);
+hipError_t launch_rank_decisions(hipStream_t stream, const float* energy, int64_t n_micro, const RankCuts& cuts,
+                                 const SegTable& seg, const SegOutputs& out, uint8_t* byte_out, uint8_t* byte_out2,
+                                 int32_t* kept_idx, void* state) {
   RankState* st = static_cast<RankState*>(state);
-  uint32_t* kept_cnt = reinterpret_cast<uint32_t*>(ws);
-  hipLaunchKernelGGL(rank_hist_kernel<0>, dim3(g), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, st);
-  hipLaunchKernelGGL(rank_hist_kernel<1>, dim3(g), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, st);
-  hipLaunchKernelGGL(rank_hist_kernel<2>, dim3(g), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, st);
-  hipLaunchKernelGGL(rank_label_kernel, dim3(g), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, st, class_out,
-                     byte_out, byte_out2, kept_idx ? kept_cnt : nullptr);
-  if (kept_idx)
-    hipLaunchKernelGGL(rank_compact_kernel, dim3(g), dim3(kRankThreads), 0, stream, class_out, n_micro, kept_cnt,
+  bool select = false;
+  for (int q = 0; q < cuts.n_cuts; ++q) select |= cut_mode(cuts, q, n_micro) == kCutSelect;
+  if (select) {
+    static bool attr_set = false;
+    if (!attr_set) {
+      const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_top_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kTopLds);
+      if (err != hipSuccess) return err;
+      attr_set = true;
+    }
+    const int blocks = (int)((n_micro + kKeysPerBlock - 1) / kKeysPerBlock);
+    hipLaunchKernelGGL(rank_top_kernel, dim3((unsigned)(blocks > kMinTopBlocks ? blocks : kMinTopBlocks)), dim3(kRankThreads),
+                       kTopLds, stream, energy, n_micro, blocks, cuts.n_cuts, st);
+    hipLaunchKernelGGL(rank_low_kernel, dim3((unsigned)blocks), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, st);
+  }
+  if (seg.n_seg > 0)
+    hipLaunchKernelGGL(rank_segment_kernel, dim3((unsigned)seg.n_seg), dim3(kRankThreads), 0, stream, energy, n_micro, cuts,
+                       seg, out, select ? 1 : 0, st, byte_out, byte_out2);
+  if (kept_idx && n_micro > 0)
+    hipLaunchKernelGGL(rank_compact_kernel, dim3((unsigned)seg.n_seg), dim3(kRankThreads), 0, stream, byte_out, seg, out.kept,
                        kept_idx);
-  return hipGetLastError();
-}
-
-hipError_t launch_segment_outputs(hipStream_t stream, const uint8_t* class_out, const SegTable& seg,
-                                  const SegOutputs& out) {
-  if (seg.n_seg <= 0) return hipSuccess;
-  hipLaunchKernelGGL(segment_kernel, dim3((unsigned)seg.n_seg), dim3(kSegThreads), 0, stream, class_out, seg, out);
   return hipGetLastError();
 }
 
@@ -724,7 +687,6 @@ hipError_t launch_full_rank(hipStream_t stream, const float* energy, int64_t n_m
                             int32_t* ws) {
   if (n_micro <= 0) return hipSuccess;
   const int64_t padded = n_micro + 64;
-  ws += rank_workspace_words(n_micro, 0);  // behind the kept counts
   uint32_t* keys_a = reinterpret_cast<uint32_t*>(ws);
   uint32_t* keys_b = keys_a + padded;
   uint32_t* idx_a = keys_b + padded;

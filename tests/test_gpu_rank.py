@@ -157,3 +157,17 @@ def test_ranking_state_survives_interleaved_calls(cam):
         check_multi(cam, E, seg, [0.1, 0.5, 0.9])
         check_select(cam, E, seg, 0.4, want_rank=False)
         check_decisions_one_pass(cam, E, seg, [0.2, 0.6], [4, 3, 2], [0.25, 0.5, 0.25])
+
+
+@pytest.mark.parametrize("n,n_seg", [(8191, 3), (8192, 8), (8193, 512), (65537, 1), (300007, 48)])
+def test_keys_that_share_their_upper_bits(cam, n, n_seg):
+    """Block edges of the select passes (8192 keys), and keys as the second pass sees them at its busiest: all with the
+    same upper 16 bits; two groups of equal keys under one value of them; negative keys between positive ones."""
+    g = torch.Generator().manual_seed(n)
+    seg = even_segments(n, n_seg)
+    one_prefix = 1.0 + torch.rand(n, generator=g) * 2.0 ** -8
+    two_groups = torch.where(torch.rand(n, generator=g) < 0.5, torch.tensor(1.0), torch.tensor(1.0 + 2.0 ** -20))
+    signed = torch.randn(n, generator=g)
+    for E in (one_prefix, two_groups, signed):
+        check_decisions_one_pass(cam, E, seg, [0.1, 0.45, 0.55], [4, 3, 2, 1], [0.25, 0.25, 0.25, 0.25])
+        check_select(cam, E, seg, 0.3, want_rank=False)
