@@ -18,7 +18,7 @@
 // ((row >> 1) & 7): the LDS has 64 four-byte banks, so two 128-byte tile rows
 // fill one bank row and 16 consecutive rows reading the same K chunk (one
 // quarter of a fragment read) then hit 16 different 16-byte bank groups.
-// fp32: plain FMA tiles (used by the float32 configuration only).
+// fp32: v_mfma_f32_32x32x2_f32 tiles (float32 layers only).
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
@@ -1016,130 +1016,158 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
 }
 
 // ---------------------------------------------------------------------------
-// fp32 FMA kernel: 64 tokens x 64 channels per block of 256 threads, K step 16,
-// each thread 4 rows x 4 channels of gate and of up.
+// fp32 kernel: 64 tokens x 32 channels x {gate, up} per workgroup of four waves on v_mfma_f32_16x16x4_f32, each wave
+// 32 tokens x 16 channels of either product.  The instruction multiplies and accumulates in float32 and runs at twice
+// the rate of the vector FMA; a float32 contraction is bound by it.  K advances 32 elements per tile; the tile after
+// the one being multiplied is in flight in registers.  An instruction takes four K elements, one from each quarter of
+// the lanes, and a sum over K does not care which: quarter q holds elements [4q, 4q + 4) of every sixteen, so a
+// fragment is one 16-byte LDS read for four instructions and the tiles stay K-contiguous (rows padded by 16 bytes:
+// at most two-way conflicts).  The tiles are small because float32 layers are: 64 x 64 ones leave five per CU at the
+// shape below and the last of them run alone (195 us).  1499 tokens x top 3 of 12 experts, d_model 772, d_ff 1033:
+// 311 us with vector FMA, 172 us now (83 TFLOP/s); the matrix pipe is busy 64 % of that.
 // ---------------------------------------------------------------------------
-constexpr int F32_BM = 64, F32_BN = 64, F32_KT = 16;
+constexpr int F32_BM = 64, F32_BN = 32, F32_KT = 32;
+constexpr int kF32Row = F32_KT + 4;  // floats per padded tile row
 
 template <int EPI>
-__global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(
+__global__ __launch_bounds__(256, 6) void grouped_gemm_f32_kernel(
     const float* __restrict__ X, int64_t ldx, int d_model, int d_ff, const float* __restrict__ Wg,
     const float* __restrict__ Wu, int64_t stride_gu, const int32_t* __restrict__ offsets,
     const int32_t* __restrict__ tile_offset, const int32_t* __restrict__ tile_expert,
     const int32_t* __restrict__ perm, const float* __restrict__ w_perm, int n_experts, EpiArgs ep) {
-  const int slot = blockIdx.y;
-  if (slot >= tile_offset[n_experts]) return;
-  const int e = tile_expert[slot];
-  const int tile_in_expert = slot - tile_offset[e];
+  // Workgroup -> tile: every XCD runs a contiguous run of logical ids (see grouped_gemm_bf16_kernel), ordered expert,
+  // N-tile, M-tile, so that the M-tiles that read the same weight rows run side by side on one L2.
+  const int n_tiles_n = (d_ff + F32_BN - 1) / F32_BN;
+  const int total = tile_offset[n_experts] * n_tiles_n;
+  const int per_xcd = (total + kXcds - 1) / kXcds;
+  const int seq = blockIdx.x / kXcds;
+  const int logical = (blockIdx.x % kXcds) * per_xcd + seq;
+  if (seq >= per_xcd || logical >= total) return;
+  const int e = tile_expert[logical / n_tiles_n];
+  const int m_e = tile_offset[e + 1] - tile_offset[e];
+  const int local = logical - tile_offset[e] * n_tiles_n;
+  const int tile_in_expert = local % m_e;
+  const int slot = tile_offset[e] + tile_in_expert;
   const int row_first = offsets[e] + tile_in_expert * F32_BM;
-  const int m_len = min(F32_BM, offsets[e + 1] - row_first);
-  const int n0 = blockIdx.x * F32_BN;
+  const int m_len = min(F32_BM, offsets[e + 1] - row_first);  // >= 1
+  const int n0 = local / m_e * F32_BN;
 
-  __shared__ float sX[F32_KT][F32_BM + 4];
-  __shared__ float sG[F32_KT][F32_BN + 4];
-  __shared__ float sU[F32_KT][F32_BN + 4];
-  __shared__ int32_t s_tok[F32_BM];
-  __shared__ float s_a[F32_BM];
-  __shared__ float s_red[2][16][F32_BN];
+  __shared__ __align__(16) float s_x[F32_BM * kF32Row];
+  __shared__ __align__(16) float s_w[2][F32_BN * kF32Row];  // gate rows, up rows
+  __shared__ float s_a[F32_BM];                             // routing weights
+  __shared__ float s_red[2][2][F32_BN];
+  static_assert(F32_BM == 64 && F32_BN == 32 && F32_KT == 32, "256 threads bring in 32 rows at a time");
 
   const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  for (int r = tid; r < F32_BM; r += 256) {
-    int tok = -1;
-    float a = 0.0f;
-    if (r < m_len) {
-      if constexpr (EPI == kEpiProduct) tok = row_first + r;  // the left operand is indexed by bucket slot
-      else tok = perm ? perm[row_first + r] : tile_in_expert * F32_BM + r;
-      a = w_perm ? w_perm[row_first + r] : 1.0f;
-    }
-    s_tok[r] = tok;
-    s_a[r] = a;
+  const int lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int wave_m = wave & 1, wave_n = wave >> 1;
+  const int col = lane & 15, quarter = lane >> 4;
+
+  // loader: thread -> row tid / 8 (and tid / 8 + 32 of the tokens), 4 consecutive K at 4 (tid % 8).  Rows past the end
+  // of the expert's tokens or channels read its first token / last channel again; what comes of them is dropped.
+  const int lrow = tid / 8, lk = (tid % 8) * 4;
+  const float* x_src[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const int row = lrow + 32 * p;
+    const int rr = row_first + (row < m_len ? row : 0);
+    int64_t tok;
+    if constexpr (EPI == kEpiProduct) tok = rr;  // the left operand is indexed by bucket slot
+    else tok = perm ? perm[rr] : rr - offsets[e];
+    x_src[p] = X + tok * ldx + lk;
   }
-  __syncthreads();
+  const int64_t w_off = (int64_t)e * stride_gu + (int64_t)min(n0 + lrow, d_ff - 1) * d_model + lk;
+  const float* g_src = Wg + w_off;
+  const float* u_src = Wu + w_off;
+  if (tid < F32_BM) s_a[tid] = tid < m_len && w_perm ? w_perm[row_first + tid] : 1.0f;  // published by the K loop's barriers
+  f32x4 xv[2], gv, uv;
+  // Past d_model (a multiple of 4) a thread reads the first elements of its row again and stores zeros.
+  auto fetch = [&](int k0) {
+    const int k = k0 + lk < d_model ? k0 : -lk;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) xv[p] = *reinterpret_cast<const f32x4*>(x_src[p] + k);
+    gv = *reinterpret_cast<const f32x4*>(g_src + k);
+    uv = *reinterpret_cast<const f32x4*>(u_src + k);
+  };
 
-  // loader: thread -> (row = tid / 4, 4 consecutive K at (tid % 4) * 4)
-  const int lrow = tid / 4, lk = (tid % 4) * 4;
-  const int ltok = s_tok[lrow];
-  const float* x_src = ltok >= 0 ? X + (int64_t)ltok * ldx + lk : nullptr;
-  const int lc = n0 + lrow;
-  const int64_t w_off = (int64_t)e * stride_gu + (int64_t)lc * d_model + lk;
-  const float* g_src = lc < d_ff ? Wg + w_off : nullptr;
-  const float* u_src = lc < d_ff ? Wu + w_off : nullptr;
-
-  float acc_g[4][4] = {}, acc_u[4][4] = {};
+  f32x4 acc_g[2] = {}, acc_u[2] = {};
+  const float* fx = &s_x[(wave_m * 32 + col) * kF32Row + quarter * 4];
+  const float* fg = &s_w[0][(wave_n * 16 + col) * kF32Row + quarter * 4];
+  const float* fu = &s_w[1][(wave_n * 16 + col) * kF32Row + quarter * 4];
+  const bool active = wave_m * 32 < m_len;  // wave-uniform: a wave without tokens only brings in its share of the tiles
+  fetch(0);
   for (int k0 = 0; k0 < d_model; k0 += F32_KT) {
-    const bool k_ok = k0 + lk < d_model;  // d_model is a multiple of 4
-    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 xv = (x_src && k_ok) ? *reinterpret_cast<const float4*>(x_src + k0) : z;
-    const float4 gv = (g_src && k_ok) ? *reinterpret_cast<const float4*>(g_src + k0) : z;
-    const float4 uv = (u_src && k_ok) ? *reinterpret_cast<const float4*>(u_src + k0) : z;
-    __syncthreads();
-    sX[lk + 0][lrow] = xv.x; sX[lk + 1][lrow] = xv.y; sX[lk + 2][lrow] = xv.z; sX[lk + 3][lrow] = xv.w;
-    sG[lk + 0][lrow] = gv.x; sG[lk + 1][lrow] = gv.y; sG[lk + 2][lrow] = gv.z; sG[lk + 3][lrow] = gv.w;
-    sU[lk + 0][lrow] = uv.x; sU[lk + 1][lrow] = uv.y; sU[lk + 2][lrow] = uv.z; sU[lk + 3][lrow] = uv.w;
-    __syncthreads();
+    __syncthreads();  // the previous tile has been read
+    const bool k_ok = k0 + lk < d_model;
+    const f32x4 zero = {};
 #pragma unroll
-    for (int k = 0; k < F32_KT; ++k) {
-      float xr[4], gr[4], ur[4];
+    for (int p = 0; p < 2; ++p) *reinterpret_cast<f32x4*>(&s_x[(lrow + 32 * p) * kF32Row + lk]) = k_ok ? xv[p] : zero;
+    *reinterpret_cast<f32x4*>(&s_w[0][lrow * kF32Row + lk]) = k_ok ? gv : zero;
+    *reinterpret_cast<f32x4*>(&s_w[1][lrow * kF32Row + lk]) = k_ok ? uv : zero;
+    __syncthreads();
+    fetch(k0 + F32_KT);
+    if (active) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        xr[i] = sX[k][ty * 4 + i];
-        gr[i] = sG[k][tx * 4 + i];
-        ur[i] = sU[k][tx * 4 + i];
+      for (int k = 0; k < F32_KT; k += 16) {
+        f32x4 a[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) a[b] = *reinterpret_cast<const f32x4*>(fx + b * 16 * kF32Row + k);
+        const f32x4 g = *reinterpret_cast<const f32x4*>(fg + k);
+        const f32x4 u = *reinterpret_cast<const f32x4*>(fu + k);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            acc_g[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b][i], g[i], acc_g[b], 0, 0, 0);
+            acc_u[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b][i], u[i], acc_u[b], 0, 0, 0);
+          }
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc_g[i][j] = fmaf(xr[i], gr[j], acc_g[i][j]);
-          acc_u[i][j] = fmaf(xr[i], ur[j], acc_u[i][j]);
-        }
     }
   }
-  if constexpr (EPI != kEpiStats) {  // per token row: hidden activations (float32 here) or the plain products
+
+  // accumulator element i of a lane: token row 4*quarter + i of the 16-row block, channel col
+  const int c = n0 + wave_n * 16 + col;
+  float kept = 1.0f;
+  if constexpr (EPI == kEpiHidden) kept = (c >= d_ff || ep.keep == nullptr || ep.keep[(int64_t)e * d_ff + c]) ? 1.0f : 0.0f;
+  float sum = 0.0f, mx = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
-      if (col >= d_ff) continue;
-      float kept = 1.0f;
-      if constexpr (EPI == kEpiHidden) kept = (ep.keep == nullptr || ep.keep[(int64_t)e * d_ff + col]) ? 1.0f : 0.0f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = ty * 4 + i;
-        if (row >= m_len) continue;
-        const int64_t out_row = row_first + row;
-        if constexpr (EPI == kEpiHidden) {
-          static_cast<float*>(ep.hidden)[out_row * ep.ld_hidden + col] = s_a[row] * silu_f32(acc_g[i][j]) * acc_u[i][j] * kept;
-        } else {
-          ep.product[out_row * ep.ld_product + col] = acc_g[i][j];
-          ep.product[out_row * ep.ld_product + col + ep.col_gap] = acc_u[i][j];
-        }
-      }
-    }
-  } else {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    float sum = 0.0f, mx = 0.0f;
+  for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float lam = s_a[ty * 4 + i] * silu_f32(acc_g[i][j]) * acc_u[i][j];
-      sum += lam * lam;
-      mx = fmaxf(mx, lam * lam);
+      const int row = wave_m * 32 + b * 16 + quarter * 4 + i;
+      const int64_t out_row = row_first + row;
+      if constexpr (EPI == kEpiProduct) {
+        if (row < m_len && c < d_ff) {
+          ep.product[out_row * ep.ld_product + c] = acc_g[b][i];
+          ep.product[out_row * ep.ld_product + c + ep.col_gap] = acc_u[b][i];
+        }
+      } else {
+        const float lam = s_a[row] * silu_f32(acc_g[b][i]) * acc_u[b][i];
+        if constexpr (EPI == kEpiHidden) {
+          if (row < m_len && c < d_ff) static_cast<float*>(ep.hidden)[out_row * ep.ld_hidden + c] = lam * kept;
+        } else {
+          const float sq = row < m_len ? lam * lam : 0.0f;
+          sum += sq;
+          mx = fmaxf(mx, sq);
+        }
+      }
     }
-    s_red[0][ty][tx * 4 + j] = sum;
-    s_red[1][ty][tx * 4 + j] = mx;
-  }
-  __syncthreads();
-  if (tid < F32_BN && n0 + tid < d_ff) {
-    float sum = 0.0f, mx = 0.0f;
-    for (int r = 0; r < 16; ++r) {  // fixed order
-      sum += s_red[0][r][tid];
-      mx = fmaxf(mx, s_red[1][r][tid]);
+  if constexpr (EPI == kEpiStats) {
+    sum += __shfl_xor(sum, 16);
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    sum += __shfl_xor(sum, 32);
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    if (quarter == 0) {
+      s_red[0][wave_m][wave_n * 16 + col] = sum;
+      s_red[1][wave_m][wave_n * 16 + col] = mx;
     }
-    ep.part_phi2[(int64_t)slot * d_ff + n0 + tid] = sum;
-    ep.part_max[(int64_t)slot * d_ff + n0 + tid] = mx;
+    __syncthreads();
+    if (tid < F32_BN && n0 + tid < d_ff) {
+      ep.part_phi2[(int64_t)slot * d_ff + n0 + tid] = s_red[0][0][tid] + s_red[0][1][tid];
+      ep.part_max[(int64_t)slot * d_ff + n0 + tid] = fmaxf(s_red[1][0][tid], s_red[1][1][tid]);
+    }
   }
-  }  // statistics epilogue
 }
 
 // Shape of the bf16 kernel: waves (M x N), 32x32 blocks per wave (M x N), K tile, stages of the token ring, stages
@@ -1204,12 +1232,13 @@ hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int
         return hipErrorInvalidValue;
     }
   }
-  dim3 grid((unsigned)((d_ff + F32_BN - 1) / F32_BN), (unsigned)max_tiles);
+  const int64_t n_blocks = (max_tiles * ((d_ff + F32_BN - 1) / F32_BN) + kXcds - 1) / kXcds * kXcds;
+  if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   auto kern = e.mode == GemmEpilogue::kStats    ? grouped_gemm_f32_kernel<kEpiStats>
               : e.mode == GemmEpilogue::kHidden ? grouped_gemm_f32_kernel<kEpiHidden>
                                                 : grouped_gemm_f32_kernel<kEpiProduct>;
   if (e.mode < GemmEpilogue::kStats || e.mode > GemmEpilogue::kProduct) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, static_cast<const float*>(X), ldx, (int)d_model, (int)d_ff,
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_blocks), dim3(256), 0, stream, static_cast<const float*>(X), ldx, (int)d_model, (int)d_ff,
                      static_cast<const float*>(W_gate), static_cast<const float*>(W_up), stride_gu, t.offsets,
                      t.tile_offset, t.tile_expert, t.perm, t.w_perm, n_experts, ep);
   return hipGetLastError();

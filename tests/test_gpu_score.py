@@ -59,6 +59,22 @@ CASES = [
 ]
 
 
+# edges of the float32 tiles: 64 tokens (two waves of 32) x 32 channels (two waves of 16) x 32 of K
+F32_EDGES = [dict(n_tokens=n, d_model=d, d_ff=f) for n, d, f in
+             [(1, 4, 1), (32, 32, 16), (33, 36, 17), (64, 28, 32), (65, 64, 33), (97, 132, 95)]]
+
+
+@pytest.mark.parametrize("case", F32_EDGES, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_f32_tile_edges_match_oracle(cam, case):
+    cfg = small(dtype="f32", n_experts=2, top_k=2, outlier_channels=0, **case)  # every expert holds every token
+    layer = inputs.make_layer(cfg, 0)
+    dev = H.to_dev(layer)
+    _, idx_o, w_o, _ = H.oracle_route(layer, cfg.top_k)
+    w32 = w_o.astype(np.float32)
+    want = H.oracle_score(layer, orc.dense_routing(idx_o, w32, cfg.n_experts), cfg.alpha)
+    compare_scores(score_on_gpu(cam, dev, idx_o, w32, cfg.alpha), want, TOL["f32"])
+
+
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()) or "base")
 def test_route_and_score_match_oracle(cam, case):
     cfg = small(**case)
