@@ -210,38 +210,79 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
                   topk_w + (tok0 + t_local) * top_k);
 }
 
-// float32: four waves per block, 32 tokens, each wave 8 tokens; lanes stride over d_model.
+// float32: 8 tokens per block; its four waves deal the experts among them, EG at a time.  A wave's lanes stride over
+// d_model with 8 x EG partial dot products in registers, so a row of R fetched once serves 8 tokens and a token fetched
+// once EG experts.  What bounds it is the latency of one wave's loads, so blocks are small: 512 tokens are 64 of them.
+// The partials of the 64 lanes are added by halving: at distance m a lane hands over half of its sums and keeps the
+// other half, 8 * EG shuffles in all instead of 6 for each sum.  The order of the additions is a lane's K positions in
+// turn and then lane distances 32, 16, ... 1: one float32 chain of d_model / 64 terms and a tree, which matters for ties.
+// One token by one expert at a time and 32 tokens per block, as it was before, against this:
+//   512 tokens, 8 experts, 256 wide     26 -> 5.7 us
+//   1499 tokens, 12 experts, 772 wide   79 -> 11 us
+constexpr int kTokensF32 = 8;
+template <int EG>
 __global__ __launch_bounds__(256) void route_f32_kernel(const float* __restrict__ X, int64_t n, int d_model,
                                                         int64_t ldx, const float* __restrict__ R, int64_t ldr,
                                                         const float* __restrict__ bias, int n_experts, int top_k,
                                                         int renorm, int32_t* __restrict__ topk_idx,
                                                         float* __restrict__ topk_w) {
-  __shared__ float s_logit[kTokens][CAMERA_MAX_EXPERTS + 1];
+  __shared__ float s_logit[kTokensF32][CAMERA_MAX_EXPERTS + 1];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int64_t tok0 = (int64_t)blockIdx.x * kTokens;
-  for (int t = 0; t < 8; ++t) {
-    const int64_t tok = tok0 + wave * 8 + t;
-    if (tok >= n) break;  // wave-uniform
-    const float* x = X + tok * ldx;
-    for (int e = 0; e < n_experts; ++e) {
-      const float* rr = R + (int64_t)e * ldr;
-      float s = 0.0f;
-      for (int c = lane * 4; c < d_model; c += kWave * 4) {  // d_model is a multiple of 4
-        const float4 xv = *reinterpret_cast<const float4*>(x + c);
-        const float4 rv = *reinterpret_cast<const float4*>(rr + c);
-        s = fmaf(xv.x, rv.x, s);
-        s = fmaf(xv.y, rv.y, s);
-        s = fmaf(xv.z, rv.z, s);
-        s = fmaf(xv.w, rv.w, s);
-      }
+  const int64_t tok0 = (int64_t)blockIdx.x * kTokensF32;
+  const float* x[kTokensF32];
 #pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
-      if (lane == 0) s_logit[wave * 8 + t][e] = s + (bias ? bias[e] : 0.0f);
+  for (int t = 0; t < kTokensF32; ++t) x[t] = X + min(tok0 + t, n - 1) * ldx;  // tokens past the end repeat the last one
+  for (int e0 = wave * EG; e0 < n_experts; e0 += 4 * EG) {
+    const float* r[EG];
+#pragma unroll
+    for (int j = 0; j < EG; ++j) r[j] = R + (int64_t)min(e0 + j, n_experts - 1) * ldr;
+    float s[kTokensF32 * EG];
+#pragma unroll
+    for (int i = 0; i < kTokensF32 * EG; ++i) s[i] = 0.0f;
+#pragma unroll 2
+    for (int c = lane * 4; c < d_model; c += kWave * 4) {  // d_model is a multiple of 4
+      float4 rv[EG];
+#pragma unroll
+      for (int j = 0; j < EG; ++j) rv[j] = *reinterpret_cast<const float4*>(r[j] + c);
+#pragma unroll
+      for (int t = 0; t < kTokensF32; ++t) {
+        const float4 xv = *reinterpret_cast<const float4*>(x[t] + c);
+#pragma unroll
+        for (int j = 0; j < EG; ++j) {
+          float v = s[t * EG + j];
+          v = fmaf(xv.x, rv[j].x, v);
+          v = fmaf(xv.y, rv[j].y, v);
+          v = fmaf(xv.z, rv[j].z, v);
+          s[t * EG + j] = fmaf(xv.w, rv[j].w, v);
+        }
+      }
     }
+    // After the step at distance m a lane holds the sums whose index has the lane's bit m in the place of that step.
+    int held = 0;  // index of the one sum the lane ends with
+    static_for<0, 6>([&](auto step) {
+      constexpr int k = decltype(step)::value;
+      constexpr int m = 32 >> k;
+      constexpr int half = (kTokensF32 * EG) >> (k + 1);
+      if constexpr (half >= 1) {
+        const bool high = (lane & m) != 0;
+        held += high ? half : 0;
+#pragma unroll
+        for (int i = 0; i < half; ++i) {
+          const float keep = high ? s[i + half] : s[i];
+          const float give = high ? s[i] : s[i + half];
+          s[i] = keep + __shfl_xor(give, m);
+        }
+      } else {
+        s[0] += __shfl_xor(s[0], m);
+      }
+    });
+    constexpr int kCopies = kWave / (kTokensF32 * EG);  // lanes that end with the same sum
+    const int t = held / EG, e = e0 + held % EG;
+    if (lane % kCopies == 0 && e < n_experts) s_logit[t][e] = s[0] + (bias ? bias[e] : 0.0f);
   }
   __syncthreads();
-  const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;  // 256 threads = 32 tokens x 8 lanes
-  if (tok0 + t_local < n)
+  const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;  // one wave = 8 tokens x 8 lanes
+  if (t_local < kTokensF32 && tok0 + t_local < n)
     topk_of_token(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
                   topk_w + (tok0 + t_local) * top_k);
 }
@@ -274,7 +315,9 @@ hipError_t launch_route_topk(hipStream_t stream, const void* X, int dtype, int64
     else CAMERA_ROUTE_CASE(8);
 #undef CAMERA_ROUTE_CASE
   } else {
-    hipLaunchKernelGGL(route_f32_kernel, dim3((unsigned)n_blocks), dim3(256), 0, stream,
+    // two experts at a time where that is what keeps all four waves busy (up to 8 experts), four beyond
+    auto kern = n_experts <= 8 ? route_f32_kernel<2> : route_f32_kernel<4>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((n + kTokensF32 - 1) / kTokensF32)), dim3(256), 0, stream,
                        static_cast<const float*>(X), n, (int)d_model, ldx, static_cast<const float*>(W_r), ldr,
                        bias, n_experts, top_k, renorm, topk_idx, topk_w);
   }

@@ -125,6 +125,19 @@ def test_route_variants(cam):
     assert torch.equal(idx_s, idx_c) and torch.equal(w_s, w_c)
 
 
+@pytest.mark.parametrize("n_tokens,n_experts,d_model,top_k", [
+    (1, 1, 4, 1), (7, 2, 256, 2), (8, 8, 260, 3), (9, 9, 772, 4), (33, 33, 516, 8), (70, 256, 1028, 8),
+])
+def test_route_f32_edges(cam, n_tokens, n_experts, d_model, top_k):
+    """Token and expert groups that are not full, rows shorter and longer than a wave's stride."""
+    cfg = small(n_tokens=n_tokens, d_model=d_model, n_experts=n_experts, top_k=top_k, dtype="f32", outlier_channels=0)
+    layer = inputs.make_layer(cfg, 3)
+    dev = H.to_dev(layer)
+    L, idx_o, w_o, _ = H.oracle_route(layer, top_k)
+    idx_g, w_g = cam.route_topk(dev["X"], dev["W_r"], dev["bias"], top_k)
+    H.check_routing(L, idx_o, w_o, idx_g.cpu().numpy(), w_g.cpu().numpy(), top_k)
+
+
 def test_shared_expert_dense_call(cam):
     cfg = inputs.scaled(inputs.CONFIGS["qwen2-57b-a14b"], n_tokens=333, d_model=96, d_ff=64, n_experts=4, top_k=2,
                         n_shared=2, d_ff_shared=264, n_layers=1)
