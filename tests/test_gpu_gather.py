@@ -155,3 +155,25 @@ def test_gather_full_size_layer(cam, name):
             pos += cnt[e]
         seg_pos += n_e
         idx_pos += n_idx
+
+
+@pytest.mark.parametrize("dtype,d_ff,n_experts,d_model", [
+    (torch.bfloat16, 8192, 2, 24),      # the widest row taken four at a time
+    (torch.bfloat16, 8200, 2, 24),      # two at a time, vector loads
+    (torch.bfloat16, 9001, 2, 24),      # two at a time, element loads
+    (torch.bfloat16, 13656, 1, 8),      # one at a time
+    (torch.float32, 4548, 2, 12),       # float32: four, two and one, the last workgroup without its full rows
+    (torch.float32, 4556, 2, 12),
+    (torch.float32, 8196, 1, 20),
+    (torch.bfloat16, 40, 96, 344),      # 16 rows per workgroup and a last one of 8
+])
+def test_gather_cols_edges_of_the_row_sets(cam, dtype, d_ff, n_experts, d_model):
+    Wg, Wu, Wd = weights(n_experts, d_ff, d_model, dtype, seed=d_ff)
+    rng = np.random.default_rng(d_ff)
+    index, count = [], []
+    for e in range(n_experts):
+        kept = rng.permutation(d_ff)[:d_ff if e == 1 else d_ff * (e + 1) // (n_experts + 2)]
+        index.append(e * d_ff + kept)
+        count.append(len(kept))
+    for align in (1, 8, 64):
+        check(cam, Wg, Wu, Wd, np.concatenate(index), count, align=align)
