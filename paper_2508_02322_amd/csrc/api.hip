@@ -765,8 +765,8 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   }
   {
     Bracket b(ctx, stream, CAMERA_K_COMBINE);
-    CAMERA_HIP(camera::launch_compact_combine(stream, product, tab_down, t, n, terms, d_model, n_pairs,
-                                              (flags & CAMERA_ACCUMULATE) ? 1 : 0, Y),
+    CAMERA_HIP(camera::launch_compact_combine(stream, product, tab_down, t, topk_idx, n, terms, top_k, n_experts, d_model,
+                                              n_pairs, (flags & CAMERA_ACCUMULATE) ? 1 : 0, Y),
                "compact combine launch");
   }
   return CAMERA_OK;

@@ -176,10 +176,11 @@ hipError_t launch_compact_hidden(hipStream_t stream, const void* X, int64_t ldx,
 hipError_t launch_compact_down(hipStream_t stream, const void* hidden, int ldh, const void* W_down, int64_t d_model,
                                const CompactDown& tab, const BucketTables& t, int token_groups, int64_t n_slots,
                                float* partial);
-// Y[token] (+)= the partial rows of the token's slots (experts in k order, chunks in chunk order).
+// Y[token] (+)= the partial rows of the token's slots (experts in k order, chunks in chunk order).  topk_idx: the
+// routing the bucket order was made from (unused for dense layers).
 hipError_t launch_compact_combine(hipStream_t stream, const float* partial, const CompactDown& tab,
-                                  const BucketTables& t, int64_t n, int terms, int64_t d_model, int64_t n_slots,
-                                  int accumulate, float* Y);
+                                  const BucketTables& t, const int32_t* topk_idx, int64_t n, int terms, int top_k,
+                                  int n_routed, int64_t d_model, int64_t n_slots, int accumulate, float* Y);
 
 // The two contractions of the compacted layer in the grouped MFMA kernel (gemm.hip), for batches large enough
 // to fill its 256-row tiles.  d_model must be a multiple of 16 and the rows of the W_down blocks a multiple of 8

@@ -387,39 +387,66 @@ __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(3)))
 }
 
 // ---- y_token (+)= its partial rows -------------------------------------------------------------------------
-// One thread per (token, four output columns).  Routed: the token's slots are slot_of[token * terms + k], the
-// expert of a slot is found in `offsets`; dense (slot_of == nullptr): expert k, slot k * n + token.
+// grid: x = tokens, y = blockDim.x vectors of four columns each.  Routed: the token's slots are
+// slot_of[token * terms + k], of expert topk_idx[token][k] for k < top_k and n_routed + k - top_k beyond; dense
+// (slot_of == nullptr): expert k, slot k * n + token.  A workgroup has one token, so slots, experts and chunk counts are
+// scalar loads; the first chunks of eight terms are in flight together, then the further chunks of a term.  (One thread
+// per output that searched the expert of every slot in turn was a chain of some sixty dependent loads:
+// 1 token 12 -> 6 us, 64 tokens of the Qwen2 shape 21 -> 10 us, 397 of the Qwen3 shape 22 -> 8 us.)
+constexpr int kTerms = 8;
+__device__ __forceinline__ void add4(float4& s, const float4& p) {
+  s.x += p.x;
+  s.y += p.y;
+  s.z += p.z;
+  s.w += p.w;
+}
 __global__ __launch_bounds__(256) void compact_combine_kernel(const float4* __restrict__ partial,
                                                               const int32_t* __restrict__ slot_of,
-                                                              const int32_t* __restrict__ offsets, CompactDown tab,
-                                                              int64_t n, int terms, int vecs, int64_t n_slots,
-                                                              int accumulate, float4* __restrict__ Y) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= n * vecs) return;
-  const int64_t tok = id / vecs;
-  const int v = (int)(id - tok * vecs);
-  float4 s = accumulate ? Y[id] : make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int k = 0; k < terms; ++k) {
-    int64_t slot;
-    int e;
-    if (slot_of) {
-      slot = slot_of[tok * terms + k];
-      if (slot < 0) continue;  // a pair with an expert id outside the group
-      e = find_segment(offsets, tab.n_experts, (int)slot);
-    } else {
-      slot = (int64_t)k * n + tok;
-      e = k;
+                                                              const int32_t* __restrict__ topk_idx, CompactDown tab,
+                                                              int64_t n, int terms, int top_k, int n_routed, int vecs,
+                                                              int64_t n_slots, int accumulate, float4* __restrict__ Y) {
+  const int64_t tok = blockIdx.x;
+  const int v = (int)(blockIdx.y * blockDim.x + threadIdx.x);
+  if (v >= vecs) return;
+  float4 s = accumulate ? Y[tok * vecs + v] : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int k0 = 0; k0 < terms; k0 += kTerms) {
+    int64_t slot[kTerms];
+    int chunks[kTerms];
+    float4 p[kTerms];
+#pragma unroll
+    for (int u = 0; u < kTerms; ++u) {
+      const int k = k0 + u;
+      chunks[u] = 0;
+      slot[u] = -1;
+      if (k >= terms) continue;
+      int e = k;
+      if (slot_of) {
+        slot[u] = slot_of[tok * terms + k];
+        e = k < top_k ? topk_idx[tok * top_k + k] : n_routed + k - top_k;
+      } else {
+        slot[u] = (int64_t)k * n + tok;
+      }
+      if (slot[u] >= 0) chunks[u] = tab.chunk_off[e + 1] - tab.chunk_off[e];  // below 0: an expert id outside the group
     }
-    const int chunks = tab.chunk_off[e + 1] - tab.chunk_off[e];
-    for (int c = 0; c < chunks; ++c) {
-      const float4 p = partial[((int64_t)c * n_slots + slot) * vecs + v];
-      s.x += p.x;
-      s.y += p.y;
-      s.z += p.z;
-      s.w += p.w;
+#pragma unroll
+    for (int u = 0; u < kTerms; ++u)
+      if (chunks[u] > 0) p[u] = partial[slot[u] * vecs + v];
+#pragma unroll
+    for (int u = 0; u < kTerms; ++u) {
+      if (chunks[u] <= 0) continue;
+      add4(s, p[u]);
+      if (chunks[u] > 1) {
+        float4 q[kCompactMaxChunks];
+#pragma unroll
+        for (int c = 1; c < kCompactMaxChunks; ++c)
+          if (c < chunks[u]) q[c] = partial[((int64_t)c * n_slots + slot[u]) * vecs + v];
+#pragma unroll
+        for (int c = 1; c < kCompactMaxChunks; ++c)
+          if (c < chunks[u]) add4(s, q[c]);
+      }
     }
   }
-  Y[id] = s;
+  Y[tok * vecs + v] = s;
 }
 
 // ---- bucket order of a decoding batch ----------------------------------------------------------------------
@@ -577,13 +604,13 @@ hipError_t launch_compact_down(hipStream_t stream, const void* hidden, int ldh, 
 }
 
 hipError_t launch_compact_combine(hipStream_t stream, const float* partial, const CompactDown& tab,
-                                  const BucketTables& t, int64_t n, int terms, int64_t d_model, int64_t n_slots,
-                                  int accumulate, float* Y) {
+                                  const BucketTables& t, const int32_t* topk_idx, int64_t n, int terms, int top_k,
+                                  int n_routed, int64_t d_model, int64_t n_slots, int accumulate, float* Y) {
   const int vecs = (int)(d_model / 4);
-  const int64_t threads = n * vecs;
-  compact_combine_kernel<<<(unsigned)((threads + 255) / 256), 256, 0, stream>>>(
-      reinterpret_cast<const float4*>(partial), t.slot_of, t.offsets, tab, n, terms, vecs, n_slots, accumulate,
-      reinterpret_cast<float4*>(Y));
+  const int threads = vecs < 256 ? (vecs + kWave - 1) / kWave * kWave : 256;
+  compact_combine_kernel<<<dim3((unsigned)n, (unsigned)((vecs + threads - 1) / threads)), threads, 0, stream>>>(
+      reinterpret_cast<const float4*>(partial), t.slot_of, topk_idx, tab, n, terms, top_k, n_routed, vecs, n_slots,
+      accumulate, reinterpret_cast<float4*>(Y));
   return hipGetLastError();
 }
 
