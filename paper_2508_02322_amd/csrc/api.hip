@@ -634,6 +634,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     return fail(ctx, CAMERA_EINVAL, "down_row_align: must be in [1, %d]", CAMERA_MAX_ROW_ALIGN);
   camera::CompactRows tab;
   camera::CompactDown tab_down;
+  camera::CompactWork tiles_of;                   // per token group, for the decoding kernels
   tab.n_experts = tab_down.n_experts = total;
   tab_down.k_round = down_row_align % 64 == 0 ? 64 : 8;
   int64_t rows = 0, tiles = 0, widest = 0, chunks = 0, ld_rows = 0;
@@ -650,6 +651,8 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     tiles += (count[e] + 31) / 32;
     chunks += camera::compact_chunks(count[e]);
     most_chunks = std::max(most_chunks, camera::compact_chunks(count[e]));
+    tiles_of.hidden_tiles[e] = (int32_t)((count[e] + 31ll) / 32);
+    tiles_of.down_tiles[e] = (int32_t)(camera::compact_chunks(count[e]) * ((d_model + 31) / 32));
     widest = std::max<int64_t>(widest, count[e]);
     if (ld_rows >= (int64_t(1) << 31) - 1024) return fail(ctx, CAMERA_ESHAPE, "sum of count: too large");
   }
@@ -658,7 +661,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     tab.tile_off[e] = (int32_t)tiles;
     tab_down.ld_off[e] = (int32_t)ld_rows;
     tab_down.chunk_off[e] = (int32_t)chunks;
-    if (e < CAMERA_MAX_EXPERTS) tab_down.count[e] = 0;
+    if (e < CAMERA_MAX_EXPERTS) tab_down.count[e] = tiles_of.hidden_tiles[e] = tiles_of.down_tiles[e] = 0;
   }
   if (rows > 0 && (W_gate_c == nullptr || W_up_c == nullptr || W_down_c == nullptr))
     return fail(ctx, CAMERA_EINVAL, "W_gate_c / W_up_c / W_down_c: NULL");
@@ -676,8 +679,6 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     return fail(ctx, CAMERA_ESHAPE, "n_experts * d_model: too large");
   if (n == 0) return CAMERA_OK;
 
-  // grid rows of 32 tokens per expert; the last row also takes what lies beyond it
-  const int token_groups = (int)std::min<int64_t>((n + 31) / 32, 64);
   // From about 64 tokens per expert on, the tiles of the grouped MFMA kernel are worth filling: the weights are
   // then read once per 256 tokens of an expert instead of once per 32.  Its 16-byte tile loads need W_down rows
   // that are a multiple of 8 elements long and the two halves of d_model to be multiples of 8.
@@ -698,7 +699,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   const size_t o_w_aug = cv.take(append ? sizeof(float) * n_pairs : 0);
   const size_t o_hidden = cv.take(2 * (size_t)n_pairs * ldh);
   const size_t o_product = cv.take(sizeof(float) * (size_t)(mfma ? 1 : most_chunks) * n_pairs * d_model);
-  const size_t o_work = cv.take(sizeof(int32_t) * camera::kCompactGemmScratchWords);
+  const size_t o_work = cv.take(sizeof(int32_t) * (mfma ? camera::kCompactGemmScratchWords : camera::kCompactWorkWords));
 
   DeviceGuard guard;
   CAMERA_HIP(guard.enter(ctx->device), "hipSetDevice");
@@ -707,6 +708,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   const camera::BucketTables t = plan.bind(ws, ctx->zeros);
   void* hidden = ws + o_hidden;
   float* product = reinterpret_cast<float*>(ws + o_product);
+  int32_t* work = reinterpret_cast<int32_t*>(ws + o_work);
 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   {
@@ -714,7 +716,8 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     if (dense) {
       CAMERA_HIP(camera::launch_dense_tables(stream, n, n_experts, tile_m, max_tiles, t), "dense tables launch");
     } else if (small) {
-      CAMERA_HIP(camera::launch_compact_bucket_small(stream, topk_idx, topk_w, n, top_k, n_experts, n_shared, t),
+      CAMERA_HIP(camera::launch_compact_bucket_small(stream, topk_idx, topk_w, n, top_k, n_experts, n_shared, tiles_of, t,
+                                                     work),
                  "small bucket launch");
     } else {
       const int32_t* idx = topk_idx;
@@ -730,18 +733,18 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
       }
       CAMERA_HIP(camera::launch_bucket(stream, idx, wts, n, terms, total, tile_m, max_tiles, t), "bucket launch");
     }
+    if (!mfma && !small) CAMERA_HIP(camera::launch_compact_items(stream, tiles_of, total, t, work), "work items launch");
   }
   if (mfma) {
-    int32_t* work_off = reinterpret_cast<int32_t*>(ws + o_work);
     {
       Bracket b(ctx, stream, CAMERA_K_GEMM);
       CAMERA_HIP(camera::launch_compact_hidden_gemm(stream, X, ldx, d_model, W_gate_c, W_up_c, tab, (int)widest, max_tiles,
-                                                    t, work_off, hidden, k_round),
+                                                    t, work, hidden, k_round),
                  "compact hidden gemm launch");
     }
     {
       Bracket b(ctx, stream, CAMERA_K_DOWN_GEMM);
-      CAMERA_HIP(camera::launch_compact_down_gemm(stream, hidden, d_model, W_down_c, tab_down, max_tiles, t, work_off,
+      CAMERA_HIP(camera::launch_compact_down_gemm(stream, hidden, d_model, W_down_c, tab_down, max_tiles, t, work,
                                                   product),
                  "compact down gemm launch");
     }
@@ -751,16 +754,17 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
                "combine launch");
     return CAMERA_OK;
   }
+  const int n_routed = dense ? 0 : n_experts;
   {
     Bracket b(ctx, stream, CAMERA_K_COMPACT_HIDDEN);
-    CAMERA_HIP(camera::launch_compact_hidden(stream, X, ldx, d_model, W_gate_c, W_up_c, tab, t, token_groups, hidden,
-                                             (int)ldh),
+    CAMERA_HIP(camera::launch_compact_hidden(stream, X, ldx, d_model, W_gate_c, W_up_c, tab, tiles_of, n_routed, top_k,
+                                             n, t, work, hidden, (int)ldh),
                "compact hidden launch");
   }
   {
     Bracket b(ctx, stream, CAMERA_K_COMPACT_DOWN);
-    CAMERA_HIP(camera::launch_compact_down(stream, hidden, (int)ldh, W_down_c, d_model, tab_down, t, token_groups, n_pairs,
-                                           product),
+    CAMERA_HIP(camera::launch_compact_down(stream, hidden, (int)ldh, W_down_c, d_model, tab_down, tiles_of, n_routed,
+                                           top_k, n, t, work, n_pairs, product),
                "compact down launch");
   }
   {

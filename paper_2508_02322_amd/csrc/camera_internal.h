@@ -151,6 +151,12 @@ struct CompactDown {                          // W_down_c
                                               // expert e's block starts at element d_model * ld_off[e]
   int32_t chunk_off[CAMERA_MAX_EXPERTS + 1];  // first K chunk of each expert
 };
+// Work items of the decoding kernels per group of 32 tokens of an expert.
+struct CompactWork {
+  int32_t hidden_tiles[CAMERA_MAX_EXPERTS];   // 32-row tiles of its kept rows
+  int32_t down_tiles[CAMERA_MAX_EXPERTS];     // K chunks times 32-row tiles of d_model
+};
+constexpr int kCompactWorkWords = 2 * (CAMERA_MAX_EXPERTS + 1);  // the prefixes over the experts, one per contraction
 // K chunks of an expert with `count` kept micro-experts in the second contraction: chunks of at most
 // kCompactChunk elements, at most kCompactMaxChunks of them (0 for an expert that keeps nothing).
 constexpr int kCompactChunk = 3072;
@@ -160,22 +166,28 @@ inline int compact_chunks(int count) {
   return c > kCompactMaxChunks ? kCompactMaxChunks : c;
 }
 // Bucket tables (counts, offsets, perm, w_perm, slot_of) of the pairs (token, routed choice k < top_k) and
-// (token, appended expert n_experts + s, weight 1), in one launch; n * (top_k + n_shared) <= kCompactSmallPairs.
+// (token, appended expert n_experts + s, weight 1) and the work items, in one launch; n * (top_k + n_shared) <=
+// kCompactSmallPairs.
 constexpr int kCompactSmallPairs = 2048;
 hipError_t launch_compact_bucket_small(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n,
-                                       int top_k, int n_experts, int n_shared, const BucketTables& t);
+                                       int top_k, int n_experts, int n_shared, const CompactWork& tab,
+                                       const BucketTables& t, int32_t* work);
+// The work items from the counts of the other bucket orders.
+hipError_t launch_compact_items(hipStream_t stream, const CompactWork& tab, int total, const BucketTables& t,
+                                int32_t* work);
 // idx_aug / w_aug [n][top_k + n_shared]: the routed choices followed by the appended experts with weight 1.
 hipError_t launch_compact_append_shared(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n,
                                         int top_k, int n_experts, int n_shared, int32_t* idx_aug, float* w_aug);
-// token_groups: grid rows of 32 tokens per expert; the last one also takes what lies beyond.
+// n_routed experts share the n * top_k routed pairs; the ones behind them (all, n_routed = 0, without routing) have
+// every token.
 // hidden [slots][ldh] bf16 <- a silu(x w_gate) (x w_up) on the kept rows; columns [count, round8(count)) zero.
 hipError_t launch_compact_hidden(hipStream_t stream, const void* X, int64_t ldx, int64_t d_model, const void* W_gate,
-                                 const void* W_up, const CompactRows& tab, const BucketTables& t, int token_groups,
-                                 void* hidden, int ldh);
+                                 const void* W_up, const CompactRows& tab, const CompactWork& tiles, int n_routed,
+                                 int top_k, int64_t n, const BucketTables& t, const int32_t* work, void* hidden, int ldh);
 // partial [chunk within its expert][n_slots][d_model] float32 <- hidden times the chunk of the expert's W_down block.
 hipError_t launch_compact_down(hipStream_t stream, const void* hidden, int ldh, const void* W_down, int64_t d_model,
-                               const CompactDown& tab, const BucketTables& t, int token_groups, int64_t n_slots,
-                               float* partial);
+                               const CompactDown& tab, const CompactWork& tiles, int n_routed, int top_k, int64_t n,
+                               const BucketTables& t, const int32_t* work, int64_t n_slots, float* partial);
 // Y[token] (+)= the partial rows of the token's slots (experts in k order, chunks in chunk order).  topk_idx: the
 // routing the bucket order was made from (unused for dense layers).
 hipError_t launch_compact_combine(hipStream_t stream, const float* partial, const CompactDown& tab,

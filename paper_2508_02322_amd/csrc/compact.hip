@@ -13,10 +13,9 @@
 // launch has several times more workgroups than the chip holds at once and its
 // last round does not leave most compute units idle:
 //   - the K extent of a workgroup is split between its waves;
-//   - the 32-token groups of an expert go to different workgroups (grid y),
-//     which read the same weights at about the same time (the second read is
-//     served by the caches); the workgroups of groups an expert does not have
-//     leave at once;
+//   - the 32-token groups of an expert go to different workgroups, eight apart
+//     in the launch: on the same XCD and at about the same time, so that its L2
+//     serves the weights to all but the first of them;
 //   - in the second contraction an expert with many kept micro-experts (a
 //     large shared expert) is cut into K chunks that go to different
 //     workgroups, each writing its own partial product rows; the chunks are
@@ -179,14 +178,73 @@ __device__ __forceinline__ KRange k_range(int full_blocks, bool has_tail, int wa
   return k;
 }
 
-// Last index e in [0, n) with off[e] <= x, for a rising table with off[0] <= x < off[n].
-__device__ __forceinline__ int find_segment(const int32_t* off, int n, int x) {
-  int lo = 0, hi = n;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (off[mid] <= x) lo = mid; else hi = mid;
+// ---- work items -----------------------------------------------------------------------------------------------
+// A work item is one weight tile of one expert with one group of kTokens of the expert's tokens.  work_off[e], the items
+// of the experts before e (work_off[n_experts]: all items), is made on the device with the bucket order, because only
+// there the groups of an expert are known; the host launches an upper bound.  (A grid of tiles x token groups of the
+// batch is mostly workgroups of groups that an expert does not have: 23 of 24 at 397 tokens and 128 experts, and
+// starting them cost more than a fifth of the two kernels.)
+struct WorkItem {
+  int e, tile, group;  // tile inside the expert
+};
+// All lanes of a wave call it with the same id < work_off[n_experts]: lane l looks at experts l, l + 64, ...
+__device__ __forceinline__ int find_expert(const int32_t* __restrict__ work_off, int n_experts, int id) {
+  const int lane = threadIdx.x & 63;
+  int e = 0;
+#pragma unroll
+  for (int i = 0; i < CAMERA_MAX_EXPERTS / kWave; ++i) {
+    const int at = i * kWave + lane + 1;
+    e += __popcll(__ballot(at < n_experts && work_off[min(at, n_experts)] <= id));
   }
-  return lo;
+  return __builtin_amdgcn_readfirstlane(e);
+}
+// Eight tiles, then the next group of the same eight: workgroup ids go round the eight XCDs, so the groups of a tile
+// stay on one.
+__device__ __forceinline__ WorkItem item_of(int e, int local, int tiles, int groups) {
+  constexpr int kXcds = 8;
+  WorkItem w;
+  w.e = e;
+  const int block = local / (kXcds * groups);
+  const int width = min(kXcds, tiles - block * kXcds);  // the last tiles of an expert may be fewer than eight
+  const int in = local - block * kXcds * groups;
+  w.group = in / width;
+  w.tile = block * kXcds + in - w.group * width;
+  return w;
+}
+__device__ __forceinline__ int groups_of(int m) { return (m + kTokens - 1) / kTokens; }
+
+// Exclusive prefix over the threads of a workgroup of WAVES waves.  s_total: one entry per wave.
+template <int WAVES>
+__device__ __forceinline__ int block_prefix(int mine, int32_t* s_total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int incl = mine;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int up = __shfl_up(incl, d);
+    if (lane >= d) incl += up;
+  }
+  __syncthreads();  // s_total may hold an earlier call's totals
+  if (lane == kWave - 1) s_total[wave] = incl;
+  __syncthreads();
+  int first = incl - mine;
+  for (int w = 0; w < wave; ++w) first += s_total[w];
+  return first;
+}
+// work [2][CAMERA_MAX_EXPERTS + 1]: the items of the first contraction (32-row tiles of the kept rows), then of the
+// second (K chunks x 32-row tiles of d_model).  Thread e < total has expert e with m tokens.
+template <int WAVES>
+__device__ __forceinline__ void write_work(const CompactWork& tab, int total, int m, int32_t* s_total,
+                                           int32_t* __restrict__ work) {
+  const int e = threadIdx.x;
+  const int g = e < total ? groups_of(m) : 0;
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    const int mine = e < total ? g * (which ? tab.down_tiles[e] : tab.hidden_tiles[e]) : 0;
+    const int first = block_prefix<WAVES>(mine, s_total);
+    int32_t* out = work + which * (CAMERA_MAX_EXPERTS + 1);
+    if (e < total) out[e] = first;
+    if (e == total - 1) out[total] = first + mine;
+  }
 }
 
 // ---- Lambda = a silu(X W_gate^T) (X W_up^T) on the kept rows ----------------------------------------------
@@ -225,38 +283,33 @@ __device__ __forceinline__ void hidden_pass(const __bf16* __restrict__ wg, const
   }
 }
 
-// grid: x = 32-row tiles of all experts (exactly tab.tile_off[tab.n_experts]), y = 32-token groups.  The
-// workgroups of the last group also take any further groups of their expert (an expert can hold more tokens
-// than the batch has only if a token names it twice).
+// Workgroups take the items blockIdx.x, blockIdx.x + gridDim.x, ...
 template <int KS>
 __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(2))) void compact_hidden_kernel(
     const __bf16* __restrict__ X, int64_t ldx, int d_model, const __bf16* __restrict__ W_gate,
-    const __bf16* __restrict__ W_up, CompactRows tab, const int32_t* __restrict__ counts,
-    const int32_t* __restrict__ offsets, const int32_t* __restrict__ perm, const float* __restrict__ w_perm,
-    __bf16* __restrict__ H, int ldh) {
+    const __bf16* __restrict__ W_up, CompactRows tab, const int32_t* __restrict__ work_off,
+    const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets, const int32_t* __restrict__ perm,
+    const float* __restrict__ w_perm, __bf16* __restrict__ H, int ldh) {
   __shared__ float red_mem[KS][2][16][kWave];  // gate and up
   const Reduce<KS, 2> red{red_mem};
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int tile = blockIdx.x;
-  const int e = find_segment(tab.tile_off, tab.n_experts, tile);
-  const int m = __builtin_amdgcn_readfirstlane(counts[e]);
-  const int t_first = (int)blockIdx.y * kTokens;
-  if (t_first >= m) return;  // no token (of this group) selected the expert: the whole workgroup leaves, nothing is read
-  const bool last_group = blockIdx.y + 1 == gridDim.y;
-  const int slot0 = __builtin_amdgcn_readfirstlane(offsets[e]);
-  const int cnt = tab.row_off[e + 1] - tab.row_off[e];
-  const int cnt8 = (cnt + 7) & ~7;
-  const int c0 = (tile - tab.tile_off[e]) * kRows;
   const int r = lane & 31, h = lane >> 5;
-  const int row = min(c0 + r, cnt - 1);  // rows past the expert's end repeat its last row; their results are dropped
-  const int64_t w_off = ((int64_t)tab.row_off[e] + row) * d_model + h * 32;
-  const __bf16* wg = W_gate + w_off;
-  const __bf16* wu = W_up + w_off;
   const KRange kr = k_range<KS>(d_model / kKBlock, d_model % kKBlock != 0, wave);
-
-  for (int t0 = t_first; t0 < m; t0 += kTokens) {
-    const int t = t0 + r;
+  const int n_items = work_off[tab.n_experts];
+  for (int id = blockIdx.x; id < n_items; id += gridDim.x) {
+    const int e = find_expert(work_off, tab.n_experts, id);
+    const int m = __builtin_amdgcn_readfirstlane(counts[e]);
+    const int slot0 = __builtin_amdgcn_readfirstlane(offsets[e]);
+    const WorkItem w = item_of(e, id - work_off[e], tab.tile_off[e + 1] - tab.tile_off[e], groups_of(m));
+    const int cnt = tab.row_off[e + 1] - tab.row_off[e];
+    const int cnt8 = (cnt + 7) & ~7;
+    const int c0 = w.tile * kRows;
+    const int row = min(c0 + r, cnt - 1);  // rows past the expert's end repeat its last row; their results are dropped
+    const int64_t w_off = ((int64_t)tab.row_off[e] + row) * d_model + h * 32;
+    const __bf16* wg = W_gate + w_off;
+    const __bf16* wu = W_up + w_off;
+    const int t = w.group * kTokens + r;
     const int tc = min(t, m - 1);  // clamped: columns past m are dropped
     const int64_t tok = perm ? perm[slot0 + tc] : tc;
     const __bf16* x = X + tok * ldx + h * 32;
@@ -287,8 +340,7 @@ __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(2)))
         *reinterpret_cast<bf16x4*>(H + slot * ldh + c) = out;
       }
     }
-    if (!last_group) break;
-    if constexpr (KS > 1) __syncthreads();  // the next pass writes the same LDS
+    if constexpr (KS > 1) __syncthreads();  // the next item writes the same LDS
   }
 }
 
@@ -327,40 +379,37 @@ __device__ __forceinline__ int chunk_length(int cnt, int n_chunks) {
   return ((cnt + n_chunks - 1) / n_chunks + kKBlock - 1) & ~(kKBlock - 1);
 }
 
-// grid: x = (K chunk of an expert, 32-row tile of d_model): tab.chunk_off[tab.n_experts] * row_tiles workgroups,
-// y = 32-token groups.  partial is [chunk within the expert][n_slots][d_model].
+// The tiles of an expert are (K chunk, 32-row tile of d_model).  partial is [chunk within the expert][n_slots][d_model].
 template <int KS>
 __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(3))) void compact_down_kernel(
     const __bf16* __restrict__ H, int ldh, const __bf16* __restrict__ W_down, int d_model, CompactDown tab,
-    const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets, int64_t n_slots,
+    const int32_t* __restrict__ work_off, const int32_t* __restrict__ counts, const int32_t* __restrict__ offsets, int64_t n_slots,
     float* __restrict__ partial) {
   __shared__ float red_mem[KS][1][16][kWave];
   const Reduce<KS, 1> red{red_mem};
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int row_tiles = (d_model + kRows - 1) / kRows;
-  const int chunk = blockIdx.x / row_tiles;
-  const int r0 = ((int)blockIdx.x - chunk * row_tiles) * kRows;
-  const int e = find_segment(tab.chunk_off, tab.n_experts, chunk);
-  const int m = __builtin_amdgcn_readfirstlane(counts[e]);
-  const int t_first = (int)blockIdx.y * kTokens;
-  if (t_first >= m) return;
-  const bool last_group = blockIdx.y + 1 == gridDim.y;
-  const int slot0 = __builtin_amdgcn_readfirstlane(offsets[e]);
-  const int cnt = tab.count[e];
-  const int ld = tab.ld_off[e + 1] - tab.ld_off[e];  // row length of the expert's block (cnt and zero padding)
-  const int chunk_in = chunk - tab.chunk_off[e];
-  const int len = chunk_length(cnt, tab.chunk_off[e + 1] - tab.chunk_off[e]);
-  const int k0 = min(chunk_in * len, cnt);
-  const int k_len = min(len, cnt - k0);
   const int r = lane & 31, h = lane >> 5;
-  const int row = min(r0 + r, d_model - 1);
-  const __bf16* wd = W_down + (int64_t)tab.ld_off[e] * d_model + (int64_t)row * ld + k0 + h * 32;
-  const KRange kr = k_range<KS>(k_len / kKBlock, k_len % kKBlock != 0, wave);
-  float* out_chunk = partial + (int64_t)chunk_in * n_slots * d_model;
-
-  for (int t0 = t_first; t0 < m; t0 += kTokens) {
-    const int t = t0 + r;
+  const int n_items = work_off[tab.n_experts];
+  for (int id = blockIdx.x; id < n_items; id += gridDim.x) {
+    const int e = find_expert(work_off, tab.n_experts, id);
+    const int m = __builtin_amdgcn_readfirstlane(counts[e]);
+    const int slot0 = __builtin_amdgcn_readfirstlane(offsets[e]);
+    const int n_chunks = tab.chunk_off[e + 1] - tab.chunk_off[e];
+    const WorkItem w = item_of(e, id - work_off[e], n_chunks * row_tiles, groups_of(m));
+    const int cnt = tab.count[e];
+    const int ld = tab.ld_off[e + 1] - tab.ld_off[e];  // row length of the expert's block (cnt and zero padding)
+    const int chunk_in = w.tile / row_tiles;
+    const int r0 = (w.tile - chunk_in * row_tiles) * kRows;
+    const int len = chunk_length(cnt, n_chunks);
+    const int k0 = min(chunk_in * len, cnt);
+    const int k_len = min(len, cnt - k0);
+    const int row = min(r0 + r, d_model - 1);
+    const __bf16* wd = W_down + (int64_t)tab.ld_off[e] * d_model + (int64_t)row * ld + k0 + h * 32;
+    const KRange kr = k_range<KS>(k_len / kKBlock, k_len % kKBlock != 0, wave);
+    float* out_chunk = partial + (int64_t)chunk_in * n_slots * d_model;
+    const int t = w.group * kTokens + r;
     const __bf16* hrow = H + (int64_t)(slot0 + min(t, m - 1)) * ldh + k0 + h * 32;
     f32x16 p = {};
     down_pass(wd, hrow, k_len, cnt, kr, p);
@@ -381,8 +430,7 @@ __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(3)))
         *reinterpret_cast<float4*>(out + rr) = make_float4(v[0], v[1], v[2], v[3]);
       }
     }
-    if (!last_group) break;
-    if constexpr (KS > 1) __syncthreads();
+    if constexpr (KS > 1) __syncthreads();  // the next item writes the same LDS
   }
 }
 
@@ -463,13 +511,14 @@ static_assert(kSmallThreads <= 1024, "one workgroup");
 
 __global__ __launch_bounds__(kSmallThreads) void compact_bucket_small_kernel(
     const int32_t* __restrict__ topk_idx, const float* __restrict__ topk_w, int n, int top_k, int n_experts,
-    int n_shared, int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
-    float* __restrict__ w_perm, int32_t* __restrict__ slot_of) {
+    int n_shared, CompactWork tab, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ perm, float* __restrict__ w_perm, int32_t* __restrict__ slot_of, int32_t* __restrict__ work) {
   __shared__ __attribute__((aligned(16))) int16_t ids[kCompactSmallPairs];  // expert of every pair, -1: none
   __shared__ int16_t token[kCompactSmallPairs];                             // its token
   __shared__ float weight[kCompactSmallPairs];                              // and its weight
   __shared__ int32_t wave_total[kSmallThreads / kWave];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ int32_t s_count[CAMERA_MAX_EXPERTS];
+  const int tid = threadIdx.x, lane = tid & 63;
   const int kk = top_k + n_shared, total = n_experts + n_shared, n_pairs = n * kk;
   const int padded = (n_pairs + 7) & ~7;
   for (int p = tid; p < padded; p += kSmallThreads) {
@@ -503,22 +552,12 @@ __global__ __launch_bounds__(kSmallThreads) void compact_bucket_small_kernel(
       for (int i = 0; i < 8; ++i) mine += v[i] == e;
     }
   }
-  // exclusive prefix of `mine` over the threads: inside the wave by shuffles, then the totals of the waves before
-  int incl = mine;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int up = __shfl_up(incl, d);
-    if (lane >= d) incl += up;
-  }
-  if (lane == kWave - 1) wave_total[wave] = incl;
-  __syncthreads();
-  int first = incl - mine;
-  for (int w = 0; w < wave; ++w) first += wave_total[w];
+  const int first = block_prefix<kSmallThreads / kWave>(mine, wave_total);
   const int first_of_expert = __shfl(first, lane & ~(kQuarters - 1));  // the four threads of an expert are neighbours
   if (e < total) {
     if (quarter == 0) offsets[e] = first;
     if (quarter == kQuarters - 1) {
-      counts[e] = first + mine - first_of_expert;
+      counts[e] = s_count[e] = first + mine - first_of_expert;
       if (e == total - 1) offsets[total] = first + mine;
     }
     int slot = first;
@@ -535,6 +574,37 @@ __global__ __launch_bounds__(kSmallThreads) void compact_bucket_small_kernel(
       }
     }
   }
+  __syncthreads();
+  write_work<kSmallThreads / kWave>(tab, total, tid < total ? s_count[tid] : 0, wave_total, work);
+}
+
+// The work items where the bucket order comes from the general counting sort, or every expert has every token.
+__global__ __launch_bounds__(CAMERA_MAX_EXPERTS) void compact_items_kernel(CompactWork tab, int total,
+                                                                           const int32_t* __restrict__ counts,
+                                                                           int32_t* __restrict__ work) {
+  __shared__ int32_t wave_total[CAMERA_MAX_EXPERTS / kWave];
+  const int e = threadIdx.x;
+  write_work<CAMERA_MAX_EXPERTS / kWave>(tab, total, e < total ? counts[e] : 0, wave_total, work);
+}
+
+// Upper bound of the work items of a contraction with tiles[e] per expert: of the n * top_k routed pairs, an expert with
+// m of them has at most 1 + (m - 1) / 32 groups, so the first groups are at most one per expert (or pair) and the others
+// one per 32 pairs; every appended (or dense) expert has all n tokens.  At most 2^22 workgroups (2^32 threads is the
+// limit of a launch); they take further items in turn.
+unsigned work_blocks(const int32_t* tiles, int n_routed, int total, int64_t n, int top_k) {
+  int64_t sum = 0, widest = 0, all = 0;
+  for (int e = 0; e < total; ++e) {
+    if (e < n_routed) {
+      sum += tiles[e];
+      widest = widest > tiles[e] ? widest : tiles[e];
+    } else {
+      all += tiles[e] * ((n + kTokens - 1) / kTokens);
+    }
+  }
+  const int64_t pairs = n * top_k;
+  const int64_t first = sum < widest * pairs ? sum : widest * pairs;
+  const int64_t blocks = first + widest * (pairs / kTokens) + all;
+  return (unsigned)(blocks < (int64_t(1) << 22) ? blocks : (int64_t(1) << 22));
 }
 
 // The same pairs written out, for the general counting sort: idx_aug / w_aug [n][top_k + n_shared].
@@ -559,9 +629,16 @@ __global__ void compact_append_shared_kernel(const int32_t* __restrict__ topk_id
 }  // namespace
 
 hipError_t launch_compact_bucket_small(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n,
-                                       int top_k, int n_experts, int n_shared, const BucketTables& t) {
-  compact_bucket_small_kernel<<<1, kSmallThreads, 0, stream>>>(topk_idx, topk_w, (int)n, top_k, n_experts, n_shared,
-                                                               t.counts, t.offsets, t.perm, t.w_perm, t.slot_of);
+                                       int top_k, int n_experts, int n_shared, const CompactWork& tab,
+                                       const BucketTables& t, int32_t* work) {
+  compact_bucket_small_kernel<<<1, kSmallThreads, 0, stream>>>(topk_idx, topk_w, (int)n, top_k, n_experts, n_shared, tab,
+                                                               t.counts, t.offsets, t.perm, t.w_perm, t.slot_of, work);
+  return hipGetLastError();
+}
+
+hipError_t launch_compact_items(hipStream_t stream, const CompactWork& tab, int total, const BucketTables& t,
+                                int32_t* work) {
+  compact_items_kernel<<<1, CAMERA_MAX_EXPERTS, 0, stream>>>(tab, total, t.counts, work);
   return hipGetLastError();
 }
 
@@ -574,32 +651,33 @@ hipError_t launch_compact_append_shared(hipStream_t stream, const int32_t* topk_
 }
 
 hipError_t launch_compact_hidden(hipStream_t stream, const void* X, int64_t ldx, int64_t d_model, const void* W_gate,
-                                 const void* W_up, const CompactRows& tab, const BucketTables& t, int token_groups,
-                                 void* hidden, int ldh) {
-  const int tiles = tab.tile_off[tab.n_experts];
-  if (tiles <= 0) return hipSuccess;
-  compact_hidden_kernel<kSplitHidden><<<dim3(tiles, token_groups), kWave * kSplitHidden, 0, stream>>>(
+                                 const void* W_up, const CompactRows& tab, const CompactWork& tiles, int n_routed,
+                                 int top_k, int64_t n, const BucketTables& t, const int32_t* work, void* hidden, int ldh) {
+  const unsigned blocks = work_blocks(tiles.hidden_tiles, n_routed, tab.n_experts, n, top_k);
+  if (blocks == 0) return hipSuccess;
+  compact_hidden_kernel<kSplitHidden><<<blocks, kWave * kSplitHidden, 0, stream>>>(
       static_cast<const __bf16*>(X), ldx, (int)d_model, static_cast<const __bf16*>(W_gate),
-      static_cast<const __bf16*>(W_up), tab, t.counts, t.offsets, t.perm, t.w_perm, static_cast<__bf16*>(hidden), ldh);
+      static_cast<const __bf16*>(W_up), tab, work, t.counts, t.offsets, t.perm, t.w_perm, static_cast<__bf16*>(hidden),
+      ldh);
   return hipGetLastError();
 }
 
 hipError_t launch_compact_down(hipStream_t stream, const void* hidden, int ldh, const void* W_down, int64_t d_model,
-                               const CompactDown& tab, const BucketTables& t, int token_groups, int64_t n_slots,
-                               float* partial) {
-  const int64_t blocks = (int64_t)tab.chunk_off[tab.n_experts] * ((d_model + kRows - 1) / kRows);
-  if (blocks <= 0) return hipSuccess;
+                               const CompactDown& tab, const CompactWork& tiles, int n_routed, int top_k, int64_t n,
+                               const BucketTables& t, const int32_t* work, int64_t n_slots, float* partial) {
+  const unsigned blocks = work_blocks(tiles.down_tiles, n_routed, tab.n_experts, n, top_k);
+  if (blocks == 0) return hipSuccess;
+  work += CAMERA_MAX_EXPERTS + 1;
   int64_t kept = 0;
   for (int e = 0; e < tab.n_experts; ++e) kept += tab.count[e];
-  const dim3 grid((unsigned)blocks, token_groups);
   if (kept >= (int64_t)kDownFourWavesFrom * tab.chunk_off[tab.n_experts])  // mean chunk length
-    compact_down_kernel<4><<<grid, kWave * 4, 0, stream>>>(static_cast<const __bf16*>(hidden), ldh,
-                                                           static_cast<const __bf16*>(W_down), (int)d_model, tab,
-                                                           t.counts, t.offsets, n_slots, partial);
+    compact_down_kernel<4><<<blocks, kWave * 4, 0, stream>>>(static_cast<const __bf16*>(hidden), ldh,
+                                                             static_cast<const __bf16*>(W_down), (int)d_model, tab, work,
+                                                             t.counts, t.offsets, n_slots, partial);
   else
-    compact_down_kernel<2><<<grid, kWave * 2, 0, stream>>>(static_cast<const __bf16*>(hidden), ldh,
-                                                           static_cast<const __bf16*>(W_down), (int)d_model, tab,
-                                                           t.counts, t.offsets, n_slots, partial);
+    compact_down_kernel<2><<<blocks, kWave * 2, 0, stream>>>(static_cast<const __bf16*>(hidden), ldh,
+                                                             static_cast<const __bf16*>(W_down), (int)d_model, tab, work,
+                                                             t.counts, t.offsets, n_slots, partial);
   return hipGetLastError();
 }
 

@@ -264,3 +264,38 @@ def test_seeded_shapes_inside_the_limits(cam, seed):
     err, counts = run_and_check(cam, cfg, float(rng.uniform(0.05, 1.0)), align, seed=seed)
     print(f"seed {seed}: {cfg.n_tokens} tokens, d_model {cfg.d_model}, d_ff {cfg.d_ff}, {cfg.n_experts} experts top-{cfg.top_k}, "
           f"{cfg.n_shared} shared of {cfg.d_ff_shared}, align {align}: rel err {err:.2e}")
+
+
+@pytest.mark.parametrize("n_tokens,top_k,d_ff,experts,align", [
+    (48, 4, 296, [2, 2, 2, 2], 64),     # every choice of every token is one expert: six token groups of a 48-token batch
+    (33, 2, 20, [7, 7], 1),             # one tile only, and the last expert
+    (130, 1, 264, [0], 64),             # one above eight tiles, five groups
+    (600, 4, 40, [5, 0, 5, 5], 1),      # more pairs than the one-workgroup bucket order takes, unaligned rows
+    (16, 1, 64, [3], 8),                # exactly one token tile, and one token more
+    (17, 1, 64, [3], 8),
+])
+def test_work_items_of_skewed_routing(cam, n_tokens, top_k, d_ff, experts, align):
+    """All tokens on one or two of eight experts, some of them named more than once by a token: the numbers of token
+    groups at their largest.  The layer is not pruned, so the uncompacted layer's output is the same up to the order of
+    float32 sums and the bf16 rounding of the hidden values (the bound of the uncompacted output's own test)."""
+    cfg = small(n_tokens=n_tokens, d_ff=d_ff + (-d_ff) % 8, n_experts=8, top_k=top_k, n_shared=0)
+    layer = inputs.make_layer(cfg, 0, device="cpu")
+    dev = H.to_dev(layer)
+    keep = np.ones(cfg.n_experts * cfg.d_ff, dtype=np.uint8)
+    keep.reshape(cfg.n_experts, cfg.d_ff)[:, d_ff:] = 0
+    count, gate_c, up_c, down_c = compact(cam, dev, "W", keep, cfg.n_experts, cfg.d_ff, align=align)
+    idx = torch.tensor(experts, dtype=torch.int32, device="cuda").expand(n_tokens, top_k).contiguous()
+    w = torch.rand((n_tokens, top_k), generator=torch.Generator().manual_seed(1)).cuda()
+    Y = cam.layer_forward_compact(dev["X"], idx, w, count, gate_c, up_c, down_c, down_row_align=align)
+    torch.cuda.synchronize()
+    # the sum of the token's weights on each expert, per expert: the same layer to float32 rounding of the weights
+    gate, up, down = expert_lists(layer, "W")
+    X64 = H.f64(layer["X"])
+    want = np.zeros((n_tokens, cfg.d_model))
+    term = None
+    for k in range(top_k):
+        A = dense_A(idx[:, k:k + 1].cpu().numpy().astype(np.int64), w[:, k:k + 1].cpu().numpy().astype(np.float64), 8)
+        want += orc.layer_forward(X64, A, gate, up, down, keep=keep, round_hidden=orc.round_to_bf16)
+        t = largest_term(X64, A, gate, up, down, keep)
+        term = t if term is None else np.maximum(term, t)
+    check_output(Y, want, term * top_k)
