@@ -7,8 +7,8 @@
 // activated expert's weights once, so no operand is tiled through LDS: a
 // workgroup owns 32 weight rows and up to 32 tokens of one expert, its waves
 // split the K extent between them and stream their share from HBM straight
-// into MFMA operand registers (v_mfma_f32_32x32x16_bf16: the weight rows are
-// the M side, the tokens the N side); the partial sums of the waves meet in
+// into MFMA operand registers (the weight rows are the M side, the tokens the
+// N side); the partial sums of the waves meet in
 // LDS, added in wave order.  Work items are kept small and alike, so that a
 // launch has several times more workgroups than the chip holds at once and its
 // last round does not leave most compute units idle:
@@ -20,10 +20,14 @@
 //     large shared expert) is cut into K chunks that go to different
 //     workgroups, each writing its own partial product rows; the chunks are
 //     added, in chunk order, when the token's experts are summed.
-// Inside a 64-element K block lane (row, half) holds the 32 consecutive
-// elements [32*half, 32*half + 32) of its row as four 16-byte loads, so the two
-// lanes of a row read one full 128-byte line; the token operand uses the same
-// K order, which a sum over K does not care about.  Experts that no token of
+// Operands are those of v_mfma_f32_16x16x32_bf16, two weight-row tiles by one or
+// two token tiles per wave: lane (row, quarter) loads 16 bytes and the four
+// lanes of a row read one whole 64-byte sector, so that a sector is asked for
+// by one instruction only.  (With 32x32x16 operands two lanes share a row and a
+// 128-byte line is put together from four instructions, between which the
+// waves of a CU together bring in several times the 32 KiB of its vector cache:
+// 64 tokens of the Qwen2 shape took 341 + 220 us, now 314 + 194 us.)  A group of at
+// most 16 tokens leaves out the second token tile.  Experts that no token of
 // the batch selected are skipped before any weight is read.
 //
 //   hidden  : Lambda[slot][c] = a silu(x w_gate,c) (x w_up,c), bf16, for the c < count[e] kept micro-experts
@@ -41,7 +45,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
 typedef __attribute__((ext_vector_type(8))) int16_t i16x8;
 
@@ -55,9 +59,10 @@ static_assert(kSplitHidden == 1 || kSplitHidden == 2 || kSplitHidden == 4, "1, 2
 // The second contraction's K extent is the expert's kept count, which shrinks with the pruning ratio: four
 // waves while a K chunk gives each of them at least five K blocks, two below that (measured 3-8 % apart).
 constexpr int kDownFourWavesFrom = 1280;
-constexpr int kRows = 32;    // weight rows per workgroup (the MFMA's M)
-constexpr int kTokens = 32;  // tokens per workgroup (the MFMA's N)
-constexpr int kKBlock = 64;  // K elements per step: 4 MFMAs of K = 16
+constexpr int kTile = 16;    // rows and columns of an MFMA
+constexpr int kRows = 32;    // weight rows per workgroup: two M tiles
+constexpr int kTokens = 32;  // tokens per workgroup: one or two N tiles
+constexpr int kKBlock = 64;  // K elements per step: 2 MFMAs of K = 32 per pair of tiles
 
 __device__ __forceinline__ float silu_f32(float g) {
   return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f));
@@ -79,15 +84,16 @@ __device__ __forceinline__ bf16x8 load8_unaligned(const __bf16* p) {
   return v;
 }
 
-// One lane's share of a 64-element K block: chunk j covers elements [8j, 8j + 8) of the lane's 32.
+// One lane's share of a 64-element K block of two 16-row tiles: c[i][s] covers elements [32 s + 8 q, 32 s + 8 q + 8) of
+// row 16 i + r, for lane = 16 q + r.
 struct Frag {
-  bf16x8 c[4];
+  bf16x8 c[2][2];
 };
-
+// p: the row's first element of the block (for s = 0) of this lane's quarter
 template <bool ALIGNED>
-__device__ __forceinline__ void load_frag(Frag& f, const __bf16* p) {
+__device__ __forceinline__ void load_rows(bf16x8 (&c)[2], const __bf16* p) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) f.c[j] = ALIGNED ? load8(p + 8 * j) : load8_unaligned(p + 8 * j);
+  for (int s = 0; s < 2; ++s) c[s] = ALIGNED ? load8(p + 32 * s) : load8_unaligned(p + 32 * s);
 }
 
 // out[i] = w[i + d] for i + d < 8, else 0 (1 <= d <= 7, the same for the whole wave)
@@ -114,44 +120,55 @@ __device__ __forceinline__ bf16x8 shift_down(bf16x8 w, int d) {
 //            that; shorter rows are read element by element)
 enum TailMode { kWhole, kPadded, kRagged };
 template <bool ALIGNED, TailMode MODE>
-__device__ __forceinline__ void load_frag_tail(Frag& f, const __bf16* p, int k, int k_full, int row_k) {
+__device__ __forceinline__ void load_rows_tail(bf16x8 (&c)[2], const __bf16* p, int k, int k_full, int row_k) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int kj = k + 8 * j;
+  for (int j = 0; j < 2; ++j) {
+    const int kj = k + 32 * j;
+    const __bf16* pj = p + 32 * j;
     if (kj + 8 <= k_full || (MODE == kPadded && kj < k_full)) {
-      f.c[j] = ALIGNED ? load8(p + 8 * j) : load8_unaligned(p + 8 * j);
+      c[j] = ALIGNED ? load8(pj) : load8_unaligned(pj);
     } else if (MODE == kRagged && kj < k_full) {
       const int valid = k_full - kj;  // 1..7, the same for every lane that gets here
       if (row_k >= 8) {
-        f.c[j] = shift_down(load8_unaligned(p + 8 * j + valid - 8), 8 - valid);
+        c[j] = shift_down(load8_unaligned(pj + valid - 8), 8 - valid);
       } else {
         u64x2 o = {0, 0};
 #pragma unroll 1
         for (int i = 0; i < valid; ++i) {
-          const uint64_t x = __builtin_bit_cast(uint16_t, p[8 * j + i]);
+          const uint64_t x = __builtin_bit_cast(uint16_t, pj[i]);
           o[i >> 2] |= x << (16 * (i & 3));
         }
-        f.c[j] = __builtin_bit_cast(bf16x8, o);
+        c[j] = __builtin_bit_cast(bf16x8, o);
       }
     } else {
-      f.c[j] = zero8();
+      c[j] = zero8();
     }
   }
 }
 
-__device__ __forceinline__ void mfma4(f32x16& acc, const Frag& a, const Frag& b) {
+// acc.t[i][n]: weight tile i by token tile n.  Element e of a lane: weight row 16 i + 4 (lane / 16) + e, token 16 n + lane % 16.
+struct Acc {
+  f32x4 t[2][2] = {};
+};
+template <int NT>
+__device__ __forceinline__ void multiply(Acc& acc, const Frag& a, const Frag& b) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.c[j], b.c[j], acc, 0, 0, 0);
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+        acc.t[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.c[i][s], b.c[n][s], acc.t[i][n], 0, 0, 0);
 }
 
 // ---- partial sums of the waves ------------------------------------------------------------------------------
-// red[wave][tile][i][lane]: accumulator element i of `lane`.  With one wave per workgroup nothing goes through LDS.
+// red[wave][m][4 g + e][lane]: element e of `lane` in group g = 2 i + n of product m.  With one wave per workgroup nothing goes through LDS.
 template <int KS, int TILES>
 struct Reduce {
   float (*red)[TILES][16][kWave];
-  __device__ __forceinline__ void put(int wave, int tile, const f32x16& acc, int lane) const {
+  __device__ __forceinline__ void put(int wave, int tile, const Acc& acc, int lane) const {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) red[wave][tile][i][lane] = acc[i];
+    for (int i = 0; i < 16; ++i) red[wave][tile][i][lane] = acc.t[i / 8][i / 4 % 2][i % 4];
   }
   __device__ __forceinline__ float get(int tile, int i, int lane) const {
     float s = red[0][tile][i][lane];
@@ -160,7 +177,7 @@ struct Reduce {
     return s;
   }
 };
-// The groups of four accumulator elements (q = i / 4) that `wave` finishes after the reduction.
+// The groups of four accumulator elements that `wave` finishes after the reduction.
 template <int KS>
 __device__ __forceinline__ bool owns_group(int wave, int q) { return (q * KS) / 4 == wave; }
 
@@ -248,38 +265,45 @@ __device__ __forceinline__ void write_work(const CompactWork& tab, int total, in
 }
 
 // ---- Lambda = a silu(X W_gate^T) (X W_up^T) on the kept rows ----------------------------------------------
-__device__ __forceinline__ void hidden_pass(const __bf16* __restrict__ wg, const __bf16* __restrict__ wu,
-                                            const __bf16* __restrict__ x, int d_model, KRange kr, f32x16& g,
-                                            f32x16& u) {
+// wg, wu, x: the two rows of a lane (of tiles 0 and 1), at the lane's quarter of the first K block
+template <int NT>
+__device__ __forceinline__ void hidden_pass(const __bf16* const (&wg)[2], const __bf16* const (&wu)[2],
+                                            const __bf16* const (&x)[2], int d_model, KRange kr, Acc& g, Acc& u) {
   Frag ag[2], au[2], b[2];
   auto fetch = [&](int buf, int kb) {
     const int off = kb * kKBlock;
-    load_frag<true>(ag[buf], wg + off);
-    load_frag<true>(au[buf], wu + off);
-    load_frag<true>(b[buf], x + off);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      load_rows<true>(ag[buf].c[i], wg[i] + off);
+      load_rows<true>(au[buf].c[i], wu[i] + off);
+      if (i < NT) load_rows<true>(b[buf].c[i], x[i] + off);
+    }
   };
-  auto multiply = [&](int buf) {
-    mfma4(g, ag[buf], b[buf]);
-    mfma4(u, au[buf], b[buf]);
+  auto both = [&](int buf) {
+    multiply<NT>(g, ag[buf], b[buf]);
+    multiply<NT>(u, au[buf], b[buf]);
   };
   int kb = kr.kb0;
   if (kb < kr.kb1) fetch(0, kb);
   for (; kb + 2 <= kr.kb1; kb += 2) {  // the loads of the next block are in flight while this one multiplies
     fetch(1, kb + 1);
-    multiply(0);
+    both(0);
     if (kb + 2 < kr.kb1) fetch(0, kb + 2);
-    multiply(1);
+    both(1);
   }
-  if (kb < kr.kb1) multiply(0);
+  if (kb < kr.kb1) both(0);
   if (kr.tail) {
     const int full = d_model / kKBlock;
-    const int rem = d_model - full * kKBlock;         // a multiple of 8
-    const int half_k = (threadIdx.x & 63) >> 5 << 5;  // K index of the lane's first element inside the block
+    const int rem = d_model - full * kKBlock;     // a multiple of 8
+    const int k = (threadIdx.x & 63) / kTile * 8;  // K index of the lane's first element inside the block
     const int off = full * kKBlock;
-    load_frag_tail<true, kWhole>(ag[0], wg + off, half_k, rem, d_model);
-    load_frag_tail<true, kWhole>(au[0], wu + off, half_k, rem, d_model);
-    load_frag_tail<true, kWhole>(b[0], x + off, half_k, rem, d_model);
-    multiply(0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      load_rows_tail<true, kWhole>(ag[0].c[i], wg[i] + off, k, rem, d_model);
+      load_rows_tail<true, kWhole>(au[0].c[i], wu[i] + off, k, rem, d_model);
+      if (i < NT) load_rows_tail<true, kWhole>(b[0].c[i], x[i] + off, k, rem, d_model);
+    }
+    both(0);
   }
 }
 
@@ -294,7 +318,7 @@ __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(2)))
   const Reduce<KS, 2> red{red_mem};
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int r = lane & 31, h = lane >> 5;
+  const int r = lane % kTile, q = lane / kTile;
   const KRange kr = k_range<KS>(d_model / kKBlock, d_model % kKBlock != 0, wave);
   const int n_items = work_off[tab.n_experts];
   for (int id = blockIdx.x; id < n_items; id += gridDim.x) {
@@ -305,37 +329,45 @@ __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(2)))
     const int cnt = tab.row_off[e + 1] - tab.row_off[e];
     const int cnt8 = (cnt + 7) & ~7;
     const int c0 = w.tile * kRows;
-    const int row = min(c0 + r, cnt - 1);  // rows past the expert's end repeat its last row; their results are dropped
-    const int64_t w_off = ((int64_t)tab.row_off[e] + row) * d_model + h * 32;
-    const __bf16* wg = W_gate + w_off;
-    const __bf16* wu = W_up + w_off;
-    const int t = w.group * kTokens + r;
-    const int tc = min(t, m - 1);  // clamped: columns past m are dropped
-    const int64_t tok = perm ? perm[slot0 + tc] : tc;
-    const __bf16* x = X + tok * ldx + h * 32;
-    f32x16 g = {}, u = {};
-    hidden_pass(wg, wu, x, d_model, kr, g, u);
+    const int t0 = w.group * kTokens;
+    const __bf16 *wg[2], *wu[2], *x[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = min(c0 + kTile * i + r, cnt - 1);  // rows past the expert's end repeat its last row, columns past m
+      const int tc = min(t0 + kTile * i + r, m - 1);     // its last token; their results are dropped
+      const int64_t w_at = ((int64_t)tab.row_off[e] + row) * d_model + q * 8;
+      wg[i] = W_gate + w_at;
+      wu[i] = W_up + w_at;
+      x[i] = X + (int64_t)(perm ? perm[slot0 + tc] : tc) * ldx + q * 8;
+    }
+    Acc g, u;
+    if (m - t0 > kTile)
+      hidden_pass<2>(wg, wu, x, d_model, kr, g, u);
+    else
+      hidden_pass<1>(wg, wu, x, d_model, kr, g, u);
     if constexpr (KS > 1) {
       red.put(wave, 0, g, lane);
       red.put(wave, 1, u, lane);
       __syncthreads();
     }
-    // accumulator element i of a lane: weight row 8*(i/4) + 4*h + i%4, token column r
-    if (t < m) {
-      const int64_t slot = slot0 + t;
-      const float a = w_perm ? w_perm[slot] : 1.0f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (!owns_group<KS>(wave, q)) continue;
-        const int c = c0 + 8 * q + 4 * h;
-        if (c >= cnt8) continue;  // columns [cnt, cnt8) are written as zeros: the down kernel reads whole chunks
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const int group = 2 * i + n;
+        const int t = t0 + kTile * n + r;
+        const int c = c0 + kTile * i + 4 * q;
+        // columns [cnt, cnt8) are written as zeros: the down kernel reads whole chunks
+        if (!owns_group<KS>(wave, group) || t >= m || c >= cnt8) continue;
+        const int64_t slot = slot0 + t;
+        const float a = w_perm ? w_perm[slot] : 1.0f;
         bf16x4 out;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float gv = KS > 1 ? red.get(0, 4 * q + i, lane) : g[4 * q + i];
-          const float uv = KS > 1 ? red.get(1, 4 * q + i, lane) : u[4 * q + i];
+        for (int k = 0; k < 4; ++k) {
+          const float gv = KS > 1 ? red.get(0, 4 * group + k, lane) : g.t[i][n][k];
+          const float uv = KS > 1 ? red.get(1, 4 * group + k, lane) : u.t[i][n][k];
           const float lam = a * silu_f32(gv) * uv;
-          out[i] = (__bf16)(c + i < cnt ? lam : 0.0f);
+          out[k] = (__bf16)(c + k < cnt ? lam : 0.0f);
         }
         *reinterpret_cast<bf16x4*>(H + slot * ldh + c) = out;
       }
@@ -345,32 +377,41 @@ __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(2)))
 }
 
 // ---- partial = Lambda W_down_e^T over one K chunk ----------------------------------------------------------
-// wd, hrow point at the first element of the chunk; k_len its length; row_k the valid length of the whole row.
-__device__ __forceinline__ void down_pass(const __bf16* __restrict__ wd, const __bf16* __restrict__ hrow, int k_len,
-                                          int row_k, KRange kr, f32x16& p) {
+// wd, hrow: the two rows of a lane, at the lane's quarter of the chunk's first K block; k_len: the chunk's length; row_k:
+// the valid length of the whole row.
+template <int NT>
+__device__ __forceinline__ void down_pass(const __bf16* const (&wd)[2], const __bf16* const (&hrow)[2], int k_len,
+                                          int row_k, KRange kr, Acc& p) {
   Frag a[2], b[2];
   auto fetch = [&](int buf, int kb) {
     const int off = kb * kKBlock;
-    load_frag<false>(a[buf], wd + off);
-    load_frag<true>(b[buf], hrow + off);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      load_rows<false>(a[buf].c[i], wd[i] + off);
+      if (i < NT) load_rows<true>(b[buf].c[i], hrow[i] + off);
+    }
   };
   int kb = kr.kb0;
   if (kb < kr.kb1) fetch(0, kb);
   for (; kb + 2 <= kr.kb1; kb += 2) {
     fetch(1, kb + 1);
-    mfma4(p, a[0], b[0]);
+    multiply<NT>(p, a[0], b[0]);
     if (kb + 2 < kr.kb1) fetch(0, kb + 2);
-    mfma4(p, a[1], b[1]);
+    multiply<NT>(p, a[1], b[1]);
   }
-  if (kb < kr.kb1) mfma4(p, a[0], b[0]);
+  if (kb < kr.kb1) multiply<NT>(p, a[0], b[0]);
   if (kr.tail) {
     const int full = k_len / kKBlock;
     const int rem = k_len - full * kKBlock;
-    const int half_k = (threadIdx.x & 63) >> 5 << 5;
+    const int k = (threadIdx.x & 63) / kTile * 8;
     const int off = full * kKBlock;
-    load_frag_tail<false, kRagged>(a[0], wd + off, half_k, rem, row_k);   // never past the end of the weight row
-    load_frag_tail<true, kPadded>(b[0], hrow + off, half_k, rem, row_k);  // Lambda rows are zero-filled up to a multiple of 8
-    mfma4(p, a[0], b[0]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      load_rows_tail<false, kRagged>(a[0].c[i], wd[i] + off, k, rem, row_k);  // never past the end of the weight row
+      // Lambda rows are zero-filled up to a multiple of 8
+      if (i < NT) load_rows_tail<true, kPadded>(b[0].c[i], hrow[i] + off, k, rem, row_k);
+    }
+    multiply<NT>(p, a[0], b[0]);
   }
 }
 
@@ -390,7 +431,7 @@ __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(3)))
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int row_tiles = (d_model + kRows - 1) / kRows;
-  const int r = lane & 31, h = lane >> 5;
+  const int r = lane % kTile, q = lane / kTile;
   const int n_items = work_off[tab.n_experts];
   for (int id = blockIdx.x; id < n_items; id += gridDim.x) {
     const int e = find_expert(work_off, tab.n_experts, id);
@@ -405,29 +446,38 @@ __global__ __launch_bounds__(kWave * KS) __attribute__((amdgpu_waves_per_eu(3)))
     const int len = chunk_length(cnt, n_chunks);
     const int k0 = min(chunk_in * len, cnt);
     const int k_len = min(len, cnt - k0);
-    const int row = min(r0 + r, d_model - 1);
-    const __bf16* wd = W_down + (int64_t)tab.ld_off[e] * d_model + (int64_t)row * ld + k0 + h * 32;
     const KRange kr = k_range<KS>(k_len / kKBlock, k_len % kKBlock != 0, wave);
     float* out_chunk = partial + (int64_t)chunk_in * n_slots * d_model;
-    const int t = w.group * kTokens + r;
-    const __bf16* hrow = H + (int64_t)(slot0 + min(t, m - 1)) * ldh + k0 + h * 32;
-    f32x16 p = {};
-    down_pass(wd, hrow, k_len, cnt, kr, p);
+    const int t0 = w.group * kTokens;
+    const __bf16 *wd[2], *hrow[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = min(r0 + kTile * i + r, d_model - 1);
+      wd[i] = W_down + (int64_t)tab.ld_off[e] * d_model + (int64_t)row * ld + k0 + q * 8;
+      hrow[i] = H + (int64_t)(slot0 + min(t0 + kTile * i + r, m - 1)) * ldh + k0 + q * 8;
+    }
+    Acc p;
+    if (m - t0 > kTile)
+      down_pass<2>(wd, hrow, k_len, cnt, kr, p);
+    else
+      down_pass<1>(wd, hrow, k_len, cnt, kr, p);
     if constexpr (KS > 1) {
       red.put(wave, 0, p, lane);
       __syncthreads();
     }
-    if (t < m) {
-      float* out = out_chunk + (int64_t)(slot0 + t) * d_model;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (!owns_group<KS>(wave, q)) continue;
-        const int rr = r0 + 8 * q + 4 * h;
-        if (rr >= d_model) continue;  // d_model is a multiple of 8: a group of four is inside or outside as a whole
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const int group = 2 * i + n;
+        const int t = t0 + kTile * n + r;
+        const int rr = r0 + kTile * i + 4 * q;
+        // d_model is a multiple of 8: four rows are inside or outside as a whole
+        if (!owns_group<KS>(wave, group) || t >= m || rr >= d_model) continue;
         float v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = KS > 1 ? red.get(0, 4 * q + i, lane) : p[4 * q + i];
-        *reinterpret_cast<float4*>(out + rr) = make_float4(v[0], v[1], v[2], v[3]);
+        for (int k = 0; k < 4; ++k) v[k] = KS > 1 ? red.get(0, 4 * group + k, lane) : p.t[i][n][k];
+        *reinterpret_cast<float4*>(out_chunk + (int64_t)(slot0 + t) * d_model + rr) = make_float4(v[0], v[1], v[2], v[3]);
       }
     }
     if constexpr (KS > 1) __syncthreads();  // the next item writes the same LDS
