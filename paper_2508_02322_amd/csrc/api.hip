@@ -17,7 +17,7 @@ struct camera_ctx {
   char err[512] = {0};
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  void* zeros = nullptr;                         // 256 zero bytes, made on first use
+  void* zeros = nullptr;                         // 256 zero bytes, then the routing scratch; made on first use
   void* rank_state = nullptr;                    // persistent select state of the ranking kernels (zero when made, self-cleaning)
   bool rank_dirty = false;                       // a ranking call failed between its passes: clear the state before the next
   bool profiling = false;
@@ -126,10 +126,12 @@ struct BucketPlan {
   }
 };
 
+constexpr size_t kZeroBytes = 256;
+
 int ensure_workspace(camera_ctx* ctx, size_t bytes) {
   if (ctx->zeros == nullptr) {
-    hipError_t e = hipMalloc(&ctx->zeros, 256);
-    if (e == hipSuccess) e = hipMemset(ctx->zeros, 0, 256);
+    hipError_t e = hipMalloc(&ctx->zeros, kZeroBytes + camera::kRouteScratchBytes);
+    if (e == hipSuccess) e = hipMemset(ctx->zeros, 0, kZeroBytes);
     if (e == hipSuccess) e = hipDeviceSynchronize();  // once: visible to every stream from here on
     if (e != hipSuccess) {
       if (ctx->zeros) (void)hipFree(ctx->zeros);
@@ -377,7 +379,9 @@ int camera_route_topk(camera_ctx* ctx, void* stream_, const void* X, int dtype, 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   Bracket b(ctx, stream, CAMERA_K_ROUTE);
   CAMERA_HIP(camera::launch_route_topk(stream, X, dtype, n, d_model, ldx, W_r, ldr, bias, n_experts, top_k, renorm,
-                                       ctx->zeros, topk_idx, topk_w),
+                                       ctx->zeros,
+                                       reinterpret_cast<float*>(static_cast<char*>(ctx->zeros) + kZeroBytes), topk_idx,
+                                       topk_w),
              "route_topk launch");
   return CAMERA_OK;
 }

@@ -210,6 +210,96 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
                   topk_w + (tok0 + t_local) * top_k);
 }
 
+// bf16, few tokens: a block per 32 tokens is one or two workgroups for a decoding batch, which fetch the whole router matrix
+// in a chain of chunks, a latency each.  So the K extent is
+// split over workgroups too: 16 tokens x one of `splits` K ranges each, its four waves taking blocks of 32 elements straight
+// from memory into the operands of v_mfma_f32_16x16x32_bf16 (the four lanes of a row read a 64-byte sector).  The waves'
+// partial logits are added in wave order, the ranges' in range order by route_pick_kernel.  ET: tiles of 16 experts.
+// A call of 1 / 64 / 397 tokens: 64 experts, 2048 wide 19 / 20 / 20 -> 15 / 17 / 19 us; 128 experts, 2048 wide
+// 36 / 37 / 37 -> 29 / 33 / 36 us; 8 experts, 4096 wide 14 -> 7 / 8 / 9 us.
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+constexpr int kTokensSmall = 16, kWavesSmall = 4;
+template <int ET>
+__global__ __launch_bounds__(kWave * kWavesSmall) void route_bf16_split_kernel(
+    const __hip_bfloat16* __restrict__ X, int64_t n, int d_model, int64_t ldx, const __hip_bfloat16* __restrict__ R,
+    int64_t ldr, int n_experts, const __hip_bfloat16* __restrict__ zeros, float* __restrict__ part) {
+  constexpr int kFlight = ET <= 8 ? 4 : 2;  // K blocks of a wave in flight
+  __shared__ float s_part[kWavesSmall][kTokensSmall][ET * 16];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int row = lane % 16, quarter = lane / 16;
+  const int64_t tok0 = (int64_t)blockIdx.x * kTokensSmall;
+  const __hip_bfloat16* x = X + min(tok0 + row, n - 1) * ldx;  // rows outside repeat the last one; never used
+  const __hip_bfloat16* r[ET];
+#pragma unroll
+  for (int t = 0; t < ET; ++t) r[t] = R + (int64_t)min(t * 16 + row, n_experts - 1) * ldr;
+  f32x4 acc[ET];
+#pragma unroll
+  for (int t = 0; t < ET; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int n_blocks = (d_model + 31) / 32;
+  const int kb_begin = (int)((int64_t)n_blocks * blockIdx.y / gridDim.y);
+  const int kb_end = (int)((int64_t)n_blocks * (blockIdx.y + 1) / gridDim.y);
+  for (int kb = kb_begin + wave; kb < kb_end; kb += kWavesSmall * kFlight) {
+    bf16x8 xv[kFlight], rv[kFlight][ET];
+#pragma unroll
+    for (int u = 0; u < kFlight; ++u) {
+      const int at = kb + u * kWavesSmall;
+      const int k = at * 32 + quarter * 8;
+      const bool k_ok = at < kb_end && k < d_model;  // d_model is a multiple of 8
+      xv[u] = *reinterpret_cast<const bf16x8*>(k_ok ? x + k : zeros);
+#pragma unroll
+      for (int t = 0; t < ET; ++t) rv[u][t] = *reinterpret_cast<const bf16x8*>(k_ok ? r[t] + k : zeros);
+    }
+#pragma unroll
+    for (int u = 0; u < kFlight; ++u)
+#pragma unroll
+      for (int t = 0; t < ET; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[u], rv[u][t], acc[t], 0, 0, 0);
+  }
+  // accumulator element i of a lane: token 4 * quarter + i, expert `row` of the tile
+#pragma unroll
+  for (int t = 0; t < ET; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s_part[wave][4 * quarter + i][t * 16 + row] = acc[t][i];
+  __syncthreads();
+  for (int i = threadIdx.x; i < kTokensSmall * ET * 16; i += kWave * kWavesSmall) {
+    const int t = i / (ET * 16), e = i % (ET * 16);
+    float s = s_part[0][t][e];
+#pragma unroll
+    for (int w = 1; w < kWavesSmall; ++w) s += s_part[w][t][e];
+    if (tok0 + t < n && e < n_experts) part[((int64_t)blockIdx.y * n + tok0 + t) * n_experts + e] = s;
+  }
+}
+
+// part [splits][n][n_experts].  8 tokens per block: their logits, then the top-k with eight lanes per token.
+constexpr int kTokensPick = 8;
+__global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict__ part, int splits, int64_t n,
+                                                         const float* __restrict__ bias, int n_experts, int top_k,
+                                                         int renorm, int32_t* __restrict__ topk_idx,
+                                                         float* __restrict__ topk_w) {
+  __shared__ float s_logit[kTokensPick][CAMERA_MAX_EXPERTS + 1];
+  const int64_t tok0 = (int64_t)blockIdx.x * kTokensPick;
+  const int tokens = (int)min((int64_t)kTokensPick, n - tok0);
+  const int64_t stride = n * n_experts;
+  for (int i = threadIdx.x; i < tokens * n_experts; i += 256) {
+    const float* p = part + tok0 * n_experts + i;
+    const int t = i / n_experts, e = i - t * n_experts;
+    float s = 0.0f;
+    for (int k0 = 0; k0 < splits; k0 += 8) {  // eight ranges in flight, added in order
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[min(k0 + u, splits - 1) * stride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (k0 + u < splits) s += v[u];
+    }
+    s_logit[t][e] = s + (bias ? bias[e] : 0.0f);
+  }
+  __syncthreads();
+  const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;
+  if (t_local < tokens)
+    topk_of_token(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
+                  topk_w + (tok0 + t_local) * top_k);
+}
+
 // float32: 8 tokens per block; its four waves deal the experts among them, EG at a time.  A wave's lanes stride over
 // d_model with 8 x EG partial dot products in registers, so a row of R fetched once serves 8 tokens and a token fetched
 // once EG experts.  What bounds it is the latency of one wave's loads, so blocks are small: 512 tokens are 64 of them.
@@ -297,14 +387,53 @@ void launch_bf16(hipStream_t stream, int64_t n_blocks, const void* X, int64_t n,
                      static_cast<const __hip_bfloat16*>(zeros), topk_idx, topk_w);
 }
 
+// K ranges of a split call: about 512 workgroups, no range shorter than one block per wave, and the partial logits inside
+// the scratch.  At most kSplitTokens tokens: there a range is 2 (256 experts) to 4 workgroups per tile of tokens.
+constexpr int64_t kSplitTokens = 2048;
+static_assert(2 * kSplitTokens * CAMERA_MAX_EXPERTS * (int64_t)sizeof(float) <= (int64_t)kRouteScratchBytes, "two ranges fit");
+int route_splits(int64_t n, int64_t d_model, int n_experts) {
+  const int64_t tiles = (n + kTokensSmall - 1) / kTokensSmall;
+  const int64_t by_k = ((d_model + 31) / 32 + kWavesSmall - 1) / kWavesSmall;
+  const int64_t by_room = (int64_t)kRouteScratchBytes / (n * n_experts * (int64_t)sizeof(float));
+  int64_t s = (512 + tiles - 1) / tiles;
+  if (s > by_k) s = by_k;
+  if (s > by_room) s = by_room;
+  return (int)(s < 1 ? 1 : s);
+}
+
+template <int ET>
+void launch_bf16_split(hipStream_t stream, const void* X, int64_t n, int64_t d_model, int64_t ldx, const void* W_r,
+                       int64_t ldr, const float* bias, int n_experts, int top_k, int renorm, const void* zeros,
+                       float* scratch, int32_t* topk_idx, float* topk_w) {
+  const int splits = route_splits(n, d_model, n_experts);
+  hipLaunchKernelGGL(route_bf16_split_kernel<ET>, dim3((unsigned)((n + kTokensSmall - 1) / kTokensSmall), (unsigned)splits),
+                     dim3(kWave * kWavesSmall), 0, stream, static_cast<const __hip_bfloat16*>(X), n, (int)d_model, ldx,
+                     static_cast<const __hip_bfloat16*>(W_r), ldr, n_experts, static_cast<const __hip_bfloat16*>(zeros),
+                     scratch);
+  hipLaunchKernelGGL(route_pick_kernel, dim3((unsigned)((n + kTokensPick - 1) / kTokensPick)), dim3(256), 0, stream, scratch,
+                     splits, n, bias, n_experts, top_k, renorm, topk_idx, topk_w);
+}
+
 }  // namespace
 
 hipError_t launch_route_topk(hipStream_t stream, const void* X, int dtype, int64_t n, int64_t d_model,
                              int64_t ldx, const void* W_r, int64_t ldr, const float* bias, int n_experts,
-                             int top_k, int renorm, const void* zeros, int32_t* topk_idx, float* topk_w) {
+                             int top_k, int renorm, const void* zeros, float* scratch, int32_t* topk_idx,
+                             float* topk_w) {
   if (n <= 0) return hipSuccess;
   const int64_t n_blocks = (n + kTokens - 1) / kTokens;
   if (dtype == CAMERA_BF16) {
+    if (n <= kSplitTokens) {
+#define CAMERA_ROUTE_SPLIT(ET)                                                                                          \
+  launch_bf16_split<ET>(stream, X, n, d_model, ldx, W_r, ldr, bias, n_experts, top_k, renorm, zeros, scratch, topk_idx, \
+                        topk_w)
+      if (n_experts <= 16) CAMERA_ROUTE_SPLIT(1);
+      else if (n_experts <= 64) CAMERA_ROUTE_SPLIT(4);
+      else if (n_experts <= 128) CAMERA_ROUTE_SPLIT(8);
+      else CAMERA_ROUTE_SPLIT(16);
+#undef CAMERA_ROUTE_SPLIT
+      return hipGetLastError();
+    }
     const int nt = (n_experts + 31) / 32;
 #define CAMERA_ROUTE_CASE(NT)                                                                                        \
   launch_bf16<NT>(stream, n_blocks, X, n, d_model, ldx, W_r, ldr, bias, n_experts, top_k, renorm, zeros, topk_idx, \

@@ -138,6 +138,21 @@ def test_route_f32_edges(cam, n_tokens, n_experts, d_model, top_k):
     H.check_routing(L, idx_o, w_o, idx_g.cpu().numpy(), w_g.cpu().numpy(), top_k)
 
 
+@pytest.mark.parametrize("n_tokens,n_experts,d_model,top_k", [
+    (1, 1, 8, 1), (15, 16, 40, 3), (16, 17, 1032, 4), (17, 64, 2048, 6), (400, 65, 520, 8), (33, 129, 264, 8),
+    (2048, 256, 264, 8), (2049, 16, 264, 2),
+])
+def test_route_bf16_small_batches(cam, n_tokens, n_experts, d_model, top_k):
+    """Batches whose K extent is split over workgroups (up to 2048 tokens) and the first that is not: partial token and
+    expert tiles, K tails, one range and many."""
+    cfg = small(n_tokens=n_tokens, d_model=d_model, n_experts=n_experts, top_k=top_k, outlier_channels=0)
+    layer = inputs.make_layer(cfg, 3)
+    dev = H.to_dev(layer)
+    L, idx_o, w_o, _ = H.oracle_route(layer, top_k)
+    idx_g, w_g = cam.route_topk(dev["X"], dev["W_r"], dev["bias"], top_k)
+    H.check_routing(L, idx_o, w_o, idx_g.cpu().numpy(), w_g.cpu().numpy(), top_k)
+
+
 def test_shared_expert_dense_call(cam):
     cfg = inputs.scaled(inputs.CONFIGS["qwen2-57b-a14b"], n_tokens=333, d_model=96, d_ff=64, n_experts=4, top_k=2,
                         n_shared=2, d_ff_shared=264, n_layers=1)
