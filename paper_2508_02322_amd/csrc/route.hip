@@ -35,32 +35,43 @@ __device__ __forceinline__ void static_for(F&& f) {
 constexpr int kTokens = 32;  // tokens per block
 constexpr int kSub = 8;      // lanes that share one token in the top-k stage
 
-// Top-k of one token by kSub consecutive lanes: lane `sub` scans experts sub, sub + kSub, ...; each
-// round takes the largest logit not yet taken (ties: lower index) and the lanes agree on it with
-// three xor-shuffles.  s_row[0 .. n_experts) are the token's logits.
-__device__ void topk_of_token(const float* s_row, int n_experts, int top_k, int renorm, int sub,
-                              int32_t* idx_out, float* w_out) {
+// Top-k of one token by kSub consecutive lanes: lane `sub` has experts sub, sub + kSub, ... of at most NE, read once into
+// registers (a round that reads them from LDS again waits for each; 8192 tokens, 64 experts, 2048 wide: 24 -> 21 us, 16384
+// tokens, 128 experts: 56 -> 48 us, 1 token, 256 experts: 47 -> 34 us); each round takes the
+// largest logit not yet taken (ties: lower index) and the lanes agree on it with three xor-shuffles.  s_row[0 .. n_experts)
+// are the token's logits.  The lane `sub` keeps the weight of round `sub` until the denominator is known.
+template <int NE>
+__device__ __forceinline__ void topk_of_token(const float* s_row, int n_experts, int top_k, int renorm, int sub,
+                                              int32_t* idx_out, float* w_out) {
+  constexpr int kPer = NE / kSub;
+  float v[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) v[i] = s_row[min(sub + i * kSub, n_experts - 1)];
   float row_max = -INFINITY;
-  for (int e = sub; e < n_experts; e += kSub) row_max = fmaxf(row_max, s_row[e]);
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) row_max = fmaxf(row_max, v[i]);  // a repeated last expert does not change it
 #pragma unroll
   for (int m = kSub / 2; m >= 1; m >>= 1) row_max = fmaxf(row_max, __shfl_xor(row_max, m));
   float denom = 0.0f;
   if (!renorm) {
-    for (int e = sub; e < n_experts; e += kSub) denom += __expf(s_row[e] - row_max);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if (sub + i * kSub < n_experts) denom += __expf(v[i] - row_max);
 #pragma unroll
     for (int m = kSub / 2; m >= 1; m >>= 1) denom += __shfl_xor(denom, m);
   }
   float prev_v = INFINITY;
   int prev_i = -1;
-  float kept_sum = 0.0f;
+  float kept_sum = 0.0f, mine = 0.0f;
   for (int r = 0; r < top_k; ++r) {
     float best_v = -INFINITY;
     int best_i = 0x7fffffff;
-    for (int e = sub; e < n_experts; e += kSub) {
-      const float v = s_row[e];
-      const bool not_taken = v < prev_v || (v == prev_v && e > prev_i);
-      if (not_taken && (v > best_v || (v == best_v && e < best_i))) {
-        best_v = v;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = sub + i * kSub;
+      const bool not_taken = e < n_experts && (v[i] < prev_v || (v[i] == prev_v && e > prev_i));
+      if (not_taken && (v[i] > best_v || (v[i] == best_v && e < best_i))) {
+        best_v = v[i];
         best_i = e;
       }
     }
@@ -74,18 +85,20 @@ __device__ void topk_of_token(const float* s_row, int n_experts, int top_k, int 
       }
     }
     const float p = __expf(best_v - row_max);
-    if (sub == 0) {
-      idx_out[r] = best_i;
+    if (r < kSub) {
+      if (sub == r) mine = p;
+    } else if (sub == 0) {
       w_out[r] = p;
     }
+    if (sub == 0) idx_out[r] = best_i;
     kept_sum += p;
     prev_v = best_v;
     prev_i = best_i;
   }
-  if (sub == 0) {
-    const float inv = 1.0f / (renorm ? kept_sum : denom);
-    for (int r = 0; r < top_k; ++r) w_out[r] *= inv;
-  }
+  const float inv = 1.0f / (renorm ? kept_sum : denom);
+  if (sub < top_k) w_out[sub] = mine * inv;
+  if (sub == 0)
+    for (int r = kSub; r < top_k; ++r) w_out[r] *= inv;
 }
 
 // bf16: 32 tokens per block, NT tiles of 32 experts, K in chunks of KC elements that go through LDS.
@@ -206,8 +219,8 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
   }
   const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;  // 256 threads = 32 tokens x 8 lanes
   if (tok0 + t_local < n)
-    topk_of_token(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
-                  topk_w + (tok0 + t_local) * top_k);
+    topk_of_token<NT * 32>(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
+                     topk_w + (tok0 + t_local) * top_k);
 }
 
 // bf16, few tokens: a block per 32 tokens is one or two workgroups for a decoding batch, which fetch the whole router matrix
@@ -215,8 +228,9 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
 // split over workgroups too: 16 tokens x one of `splits` K ranges each, its four waves taking blocks of 32 elements straight
 // from memory into the operands of v_mfma_f32_16x16x32_bf16 (the four lanes of a row read a 64-byte sector).  The waves'
 // partial logits are added in wave order, the ranges' in range order by route_pick_kernel.  ET: tiles of 16 experts.
-// A call of 1 / 64 / 397 tokens: 64 experts, 2048 wide 19 / 20 / 20 -> 15 / 17 / 19 us; 128 experts, 2048 wide
-// 36 / 37 / 37 -> 29 / 33 / 36 us; 8 experts, 4096 wide 14 -> 7 / 8 / 9 us.
+// A call of 1 / 64 / 397 tokens, before the split / with it: 64 experts, 2048 wide 19 / 20 / 20 -> 15 / 17 / 19 us; 128
+// experts, 2048 wide 36 / 37 / 37 -> 29 / 33 / 36 us; 8 experts, 4096 wide 14 -> 7 / 8 / 9 us (with the top-k in registers
+// 12 / 14 / 16, 21 / 25 / 28 and 7 / 7 / 8 us).
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 constexpr int kTokensSmall = 16, kWavesSmall = 4;
 template <int ET>
@@ -271,11 +285,12 @@ __global__ __launch_bounds__(kWave * kWavesSmall) void route_bf16_split_kernel(
 
 // part [splits][n][n_experts].  8 tokens per block: their logits, then the top-k with eight lanes per token.
 constexpr int kTokensPick = 8;
+template <int NE>
 __global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict__ part, int splits, int64_t n,
                                                          const float* __restrict__ bias, int n_experts, int top_k,
                                                          int renorm, int32_t* __restrict__ topk_idx,
                                                          float* __restrict__ topk_w) {
-  __shared__ float s_logit[kTokensPick][CAMERA_MAX_EXPERTS + 1];
+  __shared__ float s_logit[kTokensPick][NE + 1];
   const int64_t tok0 = (int64_t)blockIdx.x * kTokensPick;
   const int tokens = (int)min((int64_t)kTokensPick, n - tok0);
   const int64_t stride = n * n_experts;
@@ -296,8 +311,8 @@ __global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict
   __syncthreads();
   const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;
   if (t_local < tokens)
-    topk_of_token(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
-                  topk_w + (tok0 + t_local) * top_k);
+    topk_of_token<NE>(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
+                     topk_w + (tok0 + t_local) * top_k);
 }
 
 // float32: 8 tokens per block; its four waves deal the experts among them, EG at a time.  A wave's lanes stride over
@@ -307,16 +322,16 @@ __global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict
 // other half, 8 * EG shuffles in all instead of 6 for each sum.  The order of the additions is a lane's K positions in
 // turn and then lane distances 32, 16, ... 1: one float32 chain of d_model / 64 terms and a tree, which matters for ties.
 // One token by one expert at a time and 32 tokens per block, as it was before, against this:
-//   512 tokens, 8 experts, 256 wide     26 -> 5.7 us
-//   1499 tokens, 12 experts, 772 wide   79 -> 11 us
+//   512 tokens, 8 experts, 256 wide     26 -> 4.9 us
+//   1499 tokens, 12 experts, 772 wide   79 -> 9.9 us
 constexpr int kTokensF32 = 8;
-template <int EG>
+template <int EG, int NE>
 __global__ __launch_bounds__(256) void route_f32_kernel(const float* __restrict__ X, int64_t n, int d_model,
                                                         int64_t ldx, const float* __restrict__ R, int64_t ldr,
                                                         const float* __restrict__ bias, int n_experts, int top_k,
                                                         int renorm, int32_t* __restrict__ topk_idx,
                                                         float* __restrict__ topk_w) {
-  __shared__ float s_logit[kTokensF32][CAMERA_MAX_EXPERTS + 1];
+  __shared__ float s_logit[kTokensF32][NE + 1];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int64_t tok0 = (int64_t)blockIdx.x * kTokensF32;
   const float* x[kTokensF32];
@@ -373,8 +388,8 @@ __global__ __launch_bounds__(256) void route_f32_kernel(const float* __restrict_
   __syncthreads();
   const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;  // one wave = 8 tokens x 8 lanes
   if (t_local < kTokensF32 && tok0 + t_local < n)
-    topk_of_token(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
-                  topk_w + (tok0 + t_local) * top_k);
+    topk_of_token<NE>(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
+                     topk_w + (tok0 + t_local) * top_k);
 }
 
 template <int NT>
@@ -410,7 +425,7 @@ void launch_bf16_split(hipStream_t stream, const void* X, int64_t n, int64_t d_m
                      dim3(kWave * kWavesSmall), 0, stream, static_cast<const __hip_bfloat16*>(X), n, (int)d_model, ldx,
                      static_cast<const __hip_bfloat16*>(W_r), ldr, n_experts, static_cast<const __hip_bfloat16*>(zeros),
                      scratch);
-  hipLaunchKernelGGL(route_pick_kernel, dim3((unsigned)((n + kTokensPick - 1) / kTokensPick)), dim3(256), 0, stream, scratch,
+  hipLaunchKernelGGL(route_pick_kernel<ET * 16>, dim3((unsigned)((n + kTokensPick - 1) / kTokensPick)), dim3(256), 0, stream, scratch,
                      splits, n, bias, n_experts, top_k, renorm, topk_idx, topk_w);
 }
 
@@ -445,7 +460,10 @@ hipError_t launch_route_topk(hipStream_t stream, const void* X, int dtype, int64
 #undef CAMERA_ROUTE_CASE
   } else {
     // two experts at a time where that is what keeps all four waves busy (up to 8 experts), four beyond
-    auto kern = n_experts <= 8 ? route_f32_kernel<2> : route_f32_kernel<4>;
+    auto kern = n_experts <= 8     ? route_f32_kernel<2, 8>
+                : n_experts <= 64  ? route_f32_kernel<4, 64>
+                : n_experts <= 128 ? route_f32_kernel<4, 128>
+                                   : route_f32_kernel<4, CAMERA_MAX_EXPERTS>;
     hipLaunchKernelGGL(kern, dim3((unsigned)((n + kTokensF32 - 1) / kTokensF32)), dim3(256), 0, stream,
                        static_cast<const float*>(X), n, (int)d_model, ldx, static_cast<const float*>(W_r), ldr,
                        bias, n_experts, top_k, renorm, topk_idx, topk_w);
