@@ -299,18 +299,18 @@ __device__ __forceinline__ void segment_walk(const float* __restrict__ E, const 
     uint32_t before[kMaxCuts], mine[kMaxCuts];
 #pragma unroll
     for (int q = 0; q < kMaxCuts; ++q) before[q] = mine[q] = 0u;
-    for (int i0 = 0; i0 < begin; i0 += U * kRankThreads) {
+    for (int64_t i0 = threadIdx.x; i0 < begin; i0 += U * kRankThreads) {  // 64 bits: `begin` may be within a step of 2^31
       uint32_t k[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int i = i0 + u * kRankThreads + (int)threadIdx.x;
+        const int64_t i = i0 + u * kRankThreads;
         k[u] = i < begin ? key_of(E[i]) : 0u;
       }
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int q = 0; q < kMaxCuts; ++q)
-          before[q] += (i0 + u * kRankThreads + (int)threadIdx.x < begin && k[u] == cut.key[q]) ? 1u : 0u;
+          before[q] += (i0 + u * kRankThreads < begin && k[u] == cut.key[q]) ? 1u : 0u;
     }
     for (int i0 = w_begin; i0 < w_end; i0 += kWave) {
       const bool valid = i0 + lane < w_end;

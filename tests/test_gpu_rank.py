@@ -171,3 +171,16 @@ def test_keys_that_share_their_upper_bits(cam, n, n_seg):
     for E in (one_prefix, two_groups, signed):
         check_decisions_one_pass(cam, E, seg, [0.1, 0.45, 0.55], [4, 3, 2, 1], [0.25, 0.25, 0.25, 0.25])
         check_select(cam, E, seg, 0.3, want_rank=False)
+
+
+def test_ties_before_a_segment_close_to_the_size_limit(cam):
+    """The largest vector the ranking takes, all energies equal, so the order is by index alone: the last segment begins
+    within one step (4096) of 2^31, and counting the equal keys before it has to end there."""
+    n = (1 << 31) - 1025
+    E = torch.zeros(n, device="cuda")
+    n_keep = 500
+    ratio = (n - n_keep) / n
+    assert orc.prune_count(ratio, n) == n - n_keep
+    keep, per, _, _ = cam.select_prune(E, [0, n - 900, n], ratio)
+    assert per.tolist() == [0, n_keep]
+    assert int(torch.count_nonzero(keep)) == n_keep and bool(keep[n - n_keep:].all())
