@@ -147,12 +147,10 @@ __device__ __forceinline__ Pick pick_2level(const uint32_t* coarse, const uint32
   return {c.bin * kCoarse + f.bin, f.rest};
 }
 
-constexpr int kTopLds = kFine * 2 + kCoarse * 4;
-
 __global__ __launch_bounds__(kRankThreads) void rank_top_kernel(const float* __restrict__ E, int64_t n, int key_blocks,
                                                                 int n_cuts, RankState* __restrict__ st) {
-  extern __shared__ __align__(16) uint32_t hist[];  // [kFine / 2] pairs of 16-bit counters, then [kCoarse]
-  uint32_t* coarse = hist + kFine / 2;
+  __shared__ __align__(16) uint32_t hist[kFine / 2];  // pairs of 16-bit counters
+  __shared__ uint32_t coarse[kCoarse];
   const int tid = threadIdx.x;
   const bool has_keys = (int)blockIdx.x < key_blocks;
   Keys8 keys;
@@ -662,16 +660,9 @@ hipError_t launch_rank_decisions(hipStream_t stream, const float* energy, int64_
   bool select = false;
   for (int q = 0; q < cuts.n_cuts; ++q) select |= cut_mode(cuts, q, n_micro) == kCutSelect;
   if (select) {
-    static bool attr_set = false;
-    if (!attr_set) {
-      const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_top_kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kTopLds);
-      if (err != hipSuccess) return err;
-      attr_set = true;
-    }
     const int blocks = (int)((n_micro + kKeysPerBlock - 1) / kKeysPerBlock);
     hipLaunchKernelGGL(rank_top_kernel, dim3((unsigned)(blocks > kMinTopBlocks ? blocks : kMinTopBlocks)), dim3(kRankThreads),
-                       kTopLds, stream, energy, n_micro, blocks, cuts.n_cuts, st);
+                       0, stream, energy, n_micro, blocks, cuts.n_cuts, st);
     hipLaunchKernelGGL(rank_low_kernel, dim3((unsigned)blocks), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, st);
   }
   if (seg.n_seg > 0)
