@@ -5,12 +5,32 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/camera.h"
 
 namespace camera {
 
 // ---- device-side helpers used by several kernels ---------------------------
 constexpr int kWave = 64;
+
+// ---- host-side helpers used by several launchers ----------------------------
+// A setting that belongs to a device (a kernel's function attribute): set(), which must be repeatable, is called until it
+// has succeeded once for that device.  Any host thread, any device; devices beyond the 64 bits are set on every call.
+class OncePerDevice {
+ public:
+  template <class F>
+  hipError_t operator()(int device, F&& set) {
+    const uint64_t bit = device >= 0 && device < 64 ? uint64_t(1) << device : 0;
+    if (done_.load(std::memory_order_acquire) & bit) return hipSuccess;
+    const hipError_t err = set();
+    if (err == hipSuccess) done_.fetch_or(bit, std::memory_order_release);
+    return err;
+  }
+
+ private:
+  std::atomic<uint64_t> done_{0};
+};
 
 // Tables that describe how the routed (token, expert) pairs are laid out after
 // bucketing.  All live in the context workspace.

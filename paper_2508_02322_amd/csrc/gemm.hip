@@ -1189,6 +1189,13 @@ int gemm_tile_m(int dtype, int64_t d_ff) {
   return dtype == CAMERA_BF16 ? Bf16Cfg::BM : F32_BM;
 }
 
+// Lets `kernel` have `bytes` of dynamic LDS on the current device (the context's: the entry points have made it current).
+static hipError_t allow_lds(OncePerDevice& once, const void* kernel, int bytes) {
+  int device = -1;
+  if (hipError_t err = hipGetDevice(&device); err != hipSuccess) return err;
+  return once(device, [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
+
 template <int EPI>
 static hipError_t launch_bf16(hipStream_t stream, const void* X, int64_t ldx, int64_t d_model, int64_t d_ff,
                               int n_experts, const void* W_gate, const void* W_up, int64_t stride_gu, int max_tiles,
@@ -1197,13 +1204,8 @@ static hipError_t launch_bf16(hipStream_t stream, const void* X, int64_t ldx, in
   // token rows lie below max_tiles * BM (every token, and every bucket slot, belongs to some tile)
   const bool tail = d_model % C::KT != 0 || !fits_32bit_offsets((int64_t)max_tiles * C::BM, ldx, d_ff, d_model);
   auto kern = tail ? grouped_gemm_bf16_kernel<C, true, EPI> : grouped_gemm_bf16_kernel<C, false, EPI>;
-  static bool attr_set[2] = {false, false};
-  if (!attr_set[tail]) {
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, C::kSmemBytes);
-    if (err != hipSuccess) return err;
-    attr_set[tail] = true;
-  }
+  static OncePerDevice lds_allowed[2];
+  if (hipError_t err = allow_lds(lds_allowed[tail], reinterpret_cast<const void*>(kern), C::kSmemBytes); err != hipSuccess) return err;
   const int64_t n_tiles_n = (d_ff + C::BN - 1) / C::BN;
   const int64_t n_blocks = (max_tiles * n_tiles_n + kXcds - 1) / kXcds * kXcds;
   if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
@@ -1264,13 +1266,8 @@ static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx,
   tail = tail || !fits_32bit_offsets((int64_t)max_tiles * C::BM, a_ld, b_rows, b_ld);
   auto kern = tail ? grouped_gemm_bf16_compact_kernel<C, true, EPI, TABLE>
                    : grouped_gemm_bf16_compact_kernel<C, false, EPI, TABLE>;
-  static bool attr_set[2] = {false, false};
-  if (!attr_set[tail]) {
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, C::kSmemBytes);
-    if (err != hipSuccess) return err;
-    attr_set[tail] = true;
-  }
+  static OncePerDevice lds_allowed[2];
+  if (hipError_t err = allow_lds(lds_allowed[tail], reinterpret_cast<const void*>(kern), C::kSmemBytes); err != hipSuccess) return err;
   hipLaunchKernelGGL((compact_work_kernel<TABLE>), dim3(1), dim3(CAMERA_MAX_EXPERTS), 0, stream, tab, (int)d_model, C::BN, C::KT, k_round,
                      t.offsets, t.tile_offset, scratch);
   // an upper bound of the tile count, shared evenly between the XCDs: a workgroup walks on through its XCD's
