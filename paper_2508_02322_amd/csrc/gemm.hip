@@ -1040,8 +1040,9 @@ __global__ __launch_bounds__(256, 6) void grouped_gemm_f32_kernel(
   const int n_tiles_n = (d_ff + F32_BN - 1) / F32_BN;
   const int total = tile_offset[n_experts] * n_tiles_n;
   const int per_xcd = (total + kXcds - 1) / kXcds;
-  const int seq = blockIdx.x / kXcds;
-  const int logical = (blockIdx.x % kXcds) * per_xcd + seq;
+  const int block = linear_block();
+  const int seq = block / kXcds;
+  const int logical = (block % kXcds) * per_xcd + seq;
   if (seq >= per_xcd || logical >= total) return;
   const int e = tile_expert[logical / n_tiles_n];
   const int m_e = tile_offset[e + 1] - tile_offset[e];
@@ -1240,8 +1241,8 @@ hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int
               : e.mode == GemmEpilogue::kHidden ? grouped_gemm_f32_kernel<kEpiHidden>
                                                 : grouped_gemm_f32_kernel<kEpiProduct>;
   if (e.mode < GemmEpilogue::kStats || e.mode > GemmEpilogue::kProduct) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_blocks), dim3(256), 0, stream, static_cast<const float*>(X), ldx, (int)d_model, (int)d_ff,
-                     static_cast<const float*>(W_gate), static_cast<const float*>(W_up), stride_gu, t.offsets,
+  hipLaunchKernelGGL(kern, launch_grid(n_blocks), dim3(256), 0, stream, static_cast<const float*>(X), ldx, (int)d_model,
+                     (int)d_ff, static_cast<const float*>(W_gate), static_cast<const float*>(W_up), stride_gu, t.offsets,
                      t.tile_offset, t.tile_expert, t.perm, t.w_perm, n_experts, ep);
   return hipGetLastError();
 }

@@ -110,3 +110,27 @@ def test_one_step_past_each_limit_is_refused(cam):
     with pytest.raises(binding.CameraError):
         cam.gather_micro_experts(W, W, Wd, torch.zeros(4, dtype=torch.int32, device="cuda"),
                                  torch.tensor([4], dtype=torch.int32, device="cuda"))   # W_down row of 65552 bytes
+
+
+@pytest.mark.parametrize("dtype,tile_m,tile_n,d_model", [("f32", 64, 32, 4)])
+def test_more_tiles_than_one_grid_dimension_holds(dtype, tile_m, tile_n, d_model):
+    """2^24 workgroups of 256 threads are 2^32 threads, one more than a launch takes in a dimension: a call with just
+    more tiles than that.  Columns of the first, a middle and the last channel tiles against float64."""
+    n, d_ff = 4096 * tile_m, 4097 * tile_n
+    g = torch.Generator(device="cuda").manual_seed(5)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    X = torch.randn((n, d_model), generator=g, device="cuda").to(t)
+    Wg, Wu = (torch.randn((1, d_ff, d_model), generator=g, device="cuda").to(t) for _ in range(2))
+    out = {k: torch.full((d_ff,), -1.0, device="cuda") for k in ("phi2", "phi_inf")}
+    own = binding.Camera(device=0)                    # gives its gigabytes of partial statistics back
+    try:
+        own.score_layer(X, None, None, Wg, Wu, None, 0.95, flags=binding.NO_FINALIZE, out=out)
+        torch.cuda.synchronize()
+    finally:
+        own.close()
+    cols = torch.cat([torch.arange(lo, lo + tile_n) for lo in (0, d_ff // 2, d_ff - tile_n)]).cuda()
+    G, U = (X.double() @ W[0, cols].double().t() for W in (Wg, Wu))
+    lam2 = (torch.nn.functional.silu(G) * U) ** 2
+    for got, want in ((out["phi2"], lam2.sum(dim=0)), (out["phi_inf"], lam2.amax(dim=0))):
+        assert float(((got[cols].double() - want).abs() / want).max()) <= TOL[dtype]
+        assert bool((got > 0).all())                  # every other channel was computed too
