@@ -784,8 +784,9 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   const int n_tiles_n = (d_ff + BN - 1) / BN;
   const int total = tile_offset[n_experts] * n_tiles_n;
   const int per_xcd = (total + kXcds - 1) / kXcds;
-  const int seq = blockIdx.x / kXcds;
-  const int logical = (blockIdx.x % kXcds) * per_xcd + seq;
+  const int block = linear_block();
+  const int seq = block / kXcds;
+  const int logical = (block % kXcds) * per_xcd + seq;
   if (seq >= per_xcd || logical >= total) return;  // block-uniform: nothing here
   const int e = tile_expert[logical / n_tiles_n];  // expert e owns logical ids tile_offset[e] * n_tiles_n ..
   const int m_e = tile_offset[e + 1] - tile_offset[e];
@@ -1210,8 +1211,7 @@ static hipError_t launch_bf16(hipStream_t stream, const void* X, int64_t ldx, in
   const int64_t n_tiles_n = (d_ff + C::BN - 1) / C::BN;
   const int64_t n_blocks = (max_tiles * n_tiles_n + kXcds - 1) / kXcds * kXcds;
   if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-  dim3 grid((unsigned)n_blocks);
-  hipLaunchKernelGGL(kern, grid, dim3(C::kThreads), C::kSmemBytes, stream, static_cast<const __hip_bfloat16*>(X), ldx,
+  hipLaunchKernelGGL(kern, launch_grid(n_blocks), dim3(C::kThreads), C::kSmemBytes, stream, static_cast<const __hip_bfloat16*>(X), ldx,
                      (int)d_model, (int)d_ff, static_cast<const __hip_bfloat16*>(W_gate),
                      static_cast<const __hip_bfloat16*>(W_up), stride_gu, t.offsets, t.tile_offset, t.tile_expert,
                      t.perm, t.w_perm, n_experts, static_cast<const __hip_bfloat16*>(t.zeros), ep);
@@ -1273,8 +1273,8 @@ static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx,
                      t.offsets, t.tile_offset, scratch);
   // an upper bound of the tile count, shared evenly between the XCDs: a workgroup walks on through its XCD's
   // range where the cuts by cost give that XCD more (cheaper) tiles than that
-  const int64_t n_blocks = (max_tiles * n_tiles_n_max + kXcds - 1) / kXcds * kXcds;
-  if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  constexpr int64_t kMaxBlocks = int64_t(1) << 22;  // a launch takes fewer than 2^32 threads per dimension
+  const int64_t n_blocks = std::min(kMaxBlocks, (max_tiles * n_tiles_n_max + kXcds - 1) / kXcds * kXcds);
   if (n_blocks == 0) return hipGetLastError();
   hipLaunchKernelGGL(kern, dim3((unsigned)n_blocks), dim3(C::kThreads), C::kSmemBytes, stream,
                      static_cast<const __hip_bfloat16*>(X), ldx, (int)d_model, static_cast<const __hip_bfloat16*>(Wg),

@@ -112,7 +112,7 @@ def test_one_step_past_each_limit_is_refused(cam):
                                  torch.tensor([4], dtype=torch.int32, device="cuda"))   # W_down row of 65552 bytes
 
 
-@pytest.mark.parametrize("dtype,tile_m,tile_n,d_model", [("f32", 64, 32, 4)])
+@pytest.mark.parametrize("dtype,tile_m,tile_n,d_model", [("f32", 64, 32, 4), ("bf16", 256, 128, 8)])
 def test_more_tiles_than_one_grid_dimension_holds(dtype, tile_m, tile_n, d_model):
     """2^24 workgroups of 256 threads are 2^32 threads, one more than a launch takes in a dimension: a call with just
     more tiles than that.  Columns of the first, a middle and the last channel tiles against float64."""
