@@ -333,7 +333,8 @@ __global__ __launch_bounds__(256) void route_f32_kernel(const float* __restrict_
                                                         float* __restrict__ topk_w) {
   __shared__ float s_logit[kTokensF32][NE + 1];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int64_t tok0 = (int64_t)blockIdx.x * kTokensF32;
+  const int64_t tok0 = (int64_t)linear_block() * kTokensF32;
+  if (tok0 >= n) return;  // block-uniform: the last row of a large grid is longer than needed
   const float* x[kTokensF32];
 #pragma unroll
   for (int t = 0; t < kTokensF32; ++t) x[t] = X + min(tok0 + t, n - 1) * ldx;  // tokens past the end repeat the last one
@@ -464,7 +465,7 @@ hipError_t launch_route_topk(hipStream_t stream, const void* X, int dtype, int64
                 : n_experts <= 64  ? route_f32_kernel<4, 64>
                 : n_experts <= 128 ? route_f32_kernel<4, 128>
                                    : route_f32_kernel<4, CAMERA_MAX_EXPERTS>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((n + kTokensF32 - 1) / kTokensF32)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(kern, launch_grid((n + kTokensF32 - 1) / kTokensF32), dim3(256), 0, stream,
                        static_cast<const float*>(X), n, (int)d_model, ldx, static_cast<const float*>(W_r), ldr,
                        bias, n_experts, top_k, renorm, topk_idx, topk_w);
   }

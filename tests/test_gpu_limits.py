@@ -134,3 +134,17 @@ def test_more_tiles_than_one_grid_dimension_holds(dtype, tile_m, tile_n, d_model
     for got, want in ((out["phi2"], lam2.sum(dim=0)), (out["phi_inf"], lam2.amax(dim=0))):
         assert float(((got[cols].double() - want).abs() / want).max()) <= TOL[dtype]
         assert bool((got > 0).all())                  # every other channel was computed too
+
+
+@pytest.mark.parametrize("dtype,n,d_model", [("f32", (1 << 27) + 5, 4)])
+def test_routing_of_more_tokens_than_one_grid_dimension_holds(cam, dtype, n, d_model):
+    """A router that asks for the sign of the first element (so the choice is exact), over more tokens than the
+    workgroups of one grid dimension take."""
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    X = torch.zeros((n, d_model), dtype=t, device="cuda")
+    X[:, 0] = torch.randint(1, 9, (n,), device="cuda", dtype=torch.int8, generator=torch.Generator(device="cuda").manual_seed(3)) - 4.5
+    W_r = torch.zeros((2, d_model), dtype=t, device="cuda")
+    W_r[0, 0], W_r[1, 0] = 1.0, -1.0
+    idx, w = cam.route_topk(X, W_r, None, 1)
+    assert torch.equal(idx[:, 0] == 1, X[:, 0] < 0)
+    assert bool((w == 1.0).all())
