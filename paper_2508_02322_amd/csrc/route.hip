@@ -136,7 +136,8 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
   float (*s_logit)[NT * 32 + 1] = reinterpret_cast<float (*)[NT * 32 + 1]>(s_raw);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int frag_row = lane % 32, frag_half = lane / 32;
-  const int64_t tok0 = (int64_t)blockIdx.x * kTokens;
+  const int64_t tok0 = (int64_t)linear_block() * kTokens;
+  if (tok0 >= n) return;  // block-uniform: the last row of a large grid is longer than needed
 
   // fetch side: this thread's vector of every row it brings in
   const int vec = threadIdx.x % kVecs, row0 = threadIdx.x / kVecs;
@@ -397,7 +398,7 @@ template <int NT>
 void launch_bf16(hipStream_t stream, int64_t n_blocks, const void* X, int64_t n, int64_t d_model, int64_t ldx,
                  const void* W_r, int64_t ldr, const float* bias, int n_experts, int top_k, int renorm,
                  const void* zeros, int32_t* topk_idx, float* topk_w) {
-  hipLaunchKernelGGL(route_bf16_kernel<NT>, dim3((unsigned)n_blocks), dim3(256), 0, stream,
+  hipLaunchKernelGGL(route_bf16_kernel<NT>, launch_grid(n_blocks), dim3(256), 0, stream,
                      static_cast<const __hip_bfloat16*>(X), n, (int)d_model, ldx,
                      static_cast<const __hip_bfloat16*>(W_r), ldr, bias, n_experts, top_k, renorm,
                      static_cast<const __hip_bfloat16*>(zeros), topk_idx, topk_w);

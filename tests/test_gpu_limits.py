@@ -136,7 +136,7 @@ def test_more_tiles_than_one_grid_dimension_holds(dtype, tile_m, tile_n, d_model
         assert bool((got > 0).all())                  # every other channel was computed too
 
 
-@pytest.mark.parametrize("dtype,n,d_model", [("f32", (1 << 27) + 5, 4)])
+@pytest.mark.parametrize("dtype,n,d_model", [("f32", (1 << 27) + 5, 4), ("bf16", (1 << 29) + 33, 8)])
 def test_routing_of_more_tokens_than_one_grid_dimension_holds(cam, dtype, n, d_model):
     """A router that asks for the sign of the first element (so the choice is exact), over more tokens than the
     workgroups of one grid dimension take."""
