@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kThreads) void output_error_kernel(const float* __r
                                                                 int64_t d_model, int64_t ldy, int64_t ldh,
                                                                 float* __restrict__ per_token) {
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int64_t tok = (int64_t)blockIdx.x * kTokensPerBlock + wave;
+  const int64_t tok = (int64_t)linear_block() * kTokensPerBlock + wave;
   if (tok >= n) return;
   const float* y = Y + tok * ldy;
   const float* h = Y_hat + tok * ldh;
@@ -102,7 +102,7 @@ hipError_t launch_output_error(hipStream_t stream, const float* Y, const float* 
                                int64_t ldy, int64_t ldh, float* per_token) {
   if (n <= 0) return hipSuccess;
   const int64_t blocks = (n + kTokensPerBlock - 1) / kTokensPerBlock;
-  hipLaunchKernelGGL(output_error_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, Y, Y_hat, n, d_model, ldy,
+  hipLaunchKernelGGL(output_error_kernel, launch_grid(blocks), dim3(kThreads), 0, stream, Y, Y_hat, n, d_model, ldy,
                      ldh, per_token);
   return hipGetLastError();
 }

@@ -148,3 +148,11 @@ def test_routing_of_more_tokens_than_one_grid_dimension_holds(cam, dtype, n, d_m
     idx, w = cam.route_topk(X, W_r, None, 1)
     assert torch.equal(idx[:, 0] == 1, X[:, 0] < 0)
     assert bool((w == 1.0).all())
+
+
+def test_output_error_of_more_tokens_than_one_grid_dimension_holds(cam):
+    n = (1 << 26) + 3
+    Y = torch.randint(-3, 4, (n, 1), device="cuda", dtype=torch.int8, generator=torch.Generator(device="cuda").manual_seed(4)).float()
+    Z = Y.roll(1, 0)
+    got = cam.output_error(Y, Z)
+    assert torch.equal(got, torch.cat([(Y - Z) ** 2, Y * Y, Z * Z, Y * Z], dim=1))     # small integers: exact
