@@ -99,7 +99,8 @@ int camera_version(void);
  *   topk_w   [n x top_k] float32 out: softmax probability (over all n_experts)
  *            of each kept expert; with renorm != 0 divided by the sum of the
  *            kept probabilities ("Norm"), so each row sums to 1
- * Logits are accumulated in float32.  1 <= top_k <= n_experts <= CAMERA_MAX_EXPERTS.
+ * Logits are accumulated in float32, in an order that does not depend on n: a token gets the same experts and the
+ * same weights, bit for bit, in whatever batch it is.  1 <= top_k <= n_experts <= CAMERA_MAX_EXPERTS.
  * n == 0 is accepted and does nothing.
  */
 int camera_route_topk(camera_ctx* ctx, void* stream,

@@ -57,7 +57,7 @@ struct BucketTables {
 
 // ---- route.hip --------------------------------------------------------------
 // scratch: kRouteScratchBytes of device memory for the partial logits of small batches, 16-byte aligned.
-constexpr size_t kRouteScratchBytes = 4 << 20;
+constexpr size_t kRouteScratchBytes = 8 << 20;
 hipError_t launch_route_topk(hipStream_t stream, const void* X, int dtype, int64_t n, int64_t d_model,
                              int64_t ldx, const void* W_r, int64_t ldr, const float* bias, int n_experts,
                              int top_k, int renorm, const void* zeros /* 16 readable zero bytes */, float* scratch,

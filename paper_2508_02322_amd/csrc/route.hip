@@ -2,11 +2,16 @@
 // (Algorithm 1, line 2; the weights A_i(x) of Eq. 2).
 //
 // Logits L[j, e] = <x_j, R_e> (+ bias_e) are accumulated in float32: for bf16 on
-// v_mfma_f32_32x32x16_bf16 (a block = 32 tokens x all experts, K chunks staged
-// through LDS, its four waves split each chunk -- R is small and stays in L2),
-// for float32 with FMA and a wave reduction.  The logits of a
-// block's tokens go through LDS so that eight lanes can walk the experts of
-// one token: top_k rounds of "largest remaining logit, lower index on ties".
+// v_mfma_f32_16x16x32_bf16, for float32 with FMA and a wave reduction.  The
+// logits of a block's tokens go through LDS so that eight lanes can walk the
+// experts of one token: top_k rounds of "largest remaining logit, lower index on
+// ties".
+// The bits of a bf16 token's logits do not depend on the batch it is in, so
+// neither does its choice of experts: both bf16 kernels add in one order, which
+// follows from d_model alone.  Blocks of 32 K elements are dealt to four chains
+// in turn; a chain adds its eight blocks of every range of 1024 elements one MFMA
+// after the other, starting from zero, then its ranges in order; the logit is
+// (((chain 0 + bias) + chain 1) + chain 2) + chain 3.
 // Selection is on the logits (softmax is increasing, so this is the top-k of
 // the probabilities); the kept weights are exp(L - max) over the softmax
 // denominator, renormalised over the kept ones.
@@ -20,7 +25,7 @@ namespace camera {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 // f(integral_constant<int, LO>), ..., f(integral_constant<int, HI - 1>)
@@ -34,6 +39,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 constexpr int kTokens = 32;  // tokens per block
 constexpr int kSub = 8;      // lanes that share one token in the top-k stage
+constexpr int kChains = 4;   // bf16: the order of additions, see above
+constexpr int kBlockK = 32;
+constexpr int kRangeBlocks = 32;
+constexpr int kRangeK = kRangeBlocks * kBlockK;
 
 // Top-k of one token by kSub consecutive lanes: lane `sub` has experts sub, sub + kSub, ... of at most NE, read once into
 // registers (a round that reads them from LDS again waits for each; 8192 tokens, 64 experts, 2048 wide: 24 -> 21 us, 16384
@@ -101,32 +110,42 @@ __device__ __forceinline__ void topk_of_token(const float* s_row, int n_experts,
     for (int r = kSub; r < top_k; ++r) w_out[r] *= inv;
 }
 
-// bf16: 32 tokens per block, NT tiles of 32 experts, K in chunks of KC elements that go through LDS.
+// bf16: 32 tokens per block, NT tiles of 32 experts, K in chunks of four blocks, one for each chain, that go through LDS.
 // The MFMA operand layout (lane = row, 8 consecutive K elements) makes neighbouring lanes read different rows, i.e.
 // a different cache line per lane; fetched that way from global memory a wave instruction costs four times the
 // address cycles of a coalesced one.  So the block fetches each chunk coalesced (a row's KC elements by KC / 8
 // neighbouring threads, 16 bytes each), PF chunks ahead in registers (a block is alone on its CU for most sizes:
 // what hides the latency of HBM is the number of its own loads in flight), stores it to LDS with rows padded by
-// 16 bytes (conflict-free fragment reads), and the four waves split the chunk's K steps.
+// 16 bytes (conflict-free fragment reads), and four waves take the chunk's four blocks.  From two expert tiles on a second
+// four waves take half of the experts: half the accumulators and running sums per wave, so that 128 experts fit 128
+// registers and two workgroups a CU.  Against four waves that chained all of K (one accumulator, no ranges), us per call:
+//   2048 wide, 64 experts:  2049 / 8192 / 65536 tokens 17.4 / 19.8 / 98 -> 16.5 / 19.3 / 96
+//              128 experts: 2049 / 16384 / 65536       31 / 46 / 157 -> 30 / 43 / 157
+//              256 experts: 2049 / 16384 / 65536       57 / 120 / 473 -> 50 / 110 / 433
 // No load is conditional: a thread whose token, expert or K position lies outside reads a valid address all the
-// same (row 0, or a page of zeros for the K tail); what it brings in is never used.  Partial logits of the four
-// waves are added through LDS in wave order.
+// same (row 0, or a page of zeros for the K tail); what it brings in is never used.  The chains of the
+// waves are added through LDS in chain order.
 template <int NT>
-__global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* __restrict__ X, int64_t n,
-                                                         int d_model, int64_t ldx,
-                                                         const __hip_bfloat16* __restrict__ R, int64_t ldr,
-                                                         const float* __restrict__ bias, int n_experts,
-                                                         int top_k, int renorm,
-                                                         const __hip_bfloat16* __restrict__ zeros,
-                                                         int32_t* __restrict__ topk_idx,
-                                                         float* __restrict__ topk_w) {
-  constexpr int KC = NT <= 4 ? 128 : 64;            // K elements per chunk
+constexpr int kRouteThreads = NT == 1 ? 256 : 512;
+template <int NT>
+__global__ __launch_bounds__(kRouteThreads<NT>, NT == 4 ? 4 : 1) void route_bf16_kernel(const __hip_bfloat16* __restrict__ X, int64_t n,
+                                                                       int d_model, int64_t ldx,
+                                                                       const __hip_bfloat16* __restrict__ R, int64_t ldr,
+                                                                       const float* __restrict__ bias, int n_experts,
+                                                                       int top_k, int renorm,
+                                                                       const __hip_bfloat16* __restrict__ zeros,
+                                                                       int32_t* __restrict__ topk_idx,
+                                                                       float* __restrict__ topk_w) {
+  constexpr int kThreads = kRouteThreads<NT>;
+  constexpr int KC = kChains * kBlockK;             // K elements per chunk
+  constexpr int kRangeChunks = kRangeK / KC;
   constexpr int kRowB = KC * 2 + 16;                // bytes of a padded LDS row
   constexpr int kVecs = KC / 8;                     // 16-byte vectors per row
-  constexpr int kRowsPerPass = 256 / kVecs;         // rows the block fetches per pass
+  constexpr int kRowsPerPass = kThreads / kVecs;    // rows the block fetches per pass
   constexpr int kXPasses = kTokens / kRowsPerPass;
   constexpr int kRPasses = NT * 32 / kRowsPerPass;
-  constexpr int kStepsPerWave = KC / 16 / 4;        // MFMA K steps of a chunk per wave
+  constexpr int kParts = kThreads / (kChains * kWave);  // parts of the experts, a chain's waves take one each
+  constexpr int TN = NT * 2 / kParts;               // tiles of 16 experts per wave
   constexpr int kTileBytes = (kTokens + NT * 32) * kRowB;
   constexpr int kLogitBytes = kTokens * (NT * 32 + 1) * 4;
   // the logits of the block's tokens lie over the chunk buffers: they are written after the last chunk was read
@@ -135,7 +154,8 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
   unsigned char* s_r = s_raw + kTokens * kRowB;
   float (*s_logit)[NT * 32 + 1] = reinterpret_cast<float (*)[NT * 32 + 1]>(s_raw);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int frag_row = lane % 32, frag_half = lane / 32;
+  const int chain = wave % kChains, part = wave / kChains;
+  const int row = lane % 16, quarter = lane / 16;
   const int64_t tok0 = (int64_t)linear_block() * kTokens;
   if (tok0 >= n) return;  // block-uniform: the last row of a large grid is longer than needed
 
@@ -153,7 +173,8 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
     const int e = row0 + p * kRowsPerPass;
     r_src[p] = R + (int64_t)(e < n_experts ? e : 0) * ldr + vec * 8;
   }
-  constexpr int PF = NT <= 2 ? 4 : 2;               // chunks in flight
+  constexpr int PF = NT <= 2 ? 4 : 1;               // chunks in flight
+  static_assert(kRangeChunks % PF == 0, "a range ends with the last slot");
   u32x4 xv[PF][kXPasses], rv[PF][kRPasses];
   auto fetch = [&](auto slot, int k0) {              // chunks past the end read the zero page
     constexpr int u = decltype(slot)::value;
@@ -173,13 +194,23 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
       *reinterpret_cast<u32x4*>(s_r + (row0 + p * kRowsPerPass) * kRowB + vec * 16) = rv[u][p];
   };
 
-  f32x16 acc[NT];
+  f32x4 acc[2][TN], sum[2][TN];  // of 2 x 16 tokens: the range that runs, the ranges before it
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
+  for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+    for (int t = 0; t < TN; ++t) acc[m][t] = sum[m][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto end_range = [&] {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int t = 0; t < TN; ++t) {
+        sum[m][t] += acc[m][t];
+        acc[m][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+  };
 
   const int n_chunks = (d_model + KC - 1) / KC;
+  const int col = (chain * kBlockK + quarter * 8) * 2;  // byte column of this lane's K elements
   static_for<0, PF>([&](auto u) { fetch(u, decltype(u)::value * KC); });
   for (int c0 = 0; c0 < n_chunks; c0 += PF) {
     static_for<0, PF>([&](auto u) {
@@ -188,106 +219,97 @@ __global__ __launch_bounds__(256) void route_bf16_kernel(const __hip_bfloat16* _
         stage(u);          // waits for this slot's loads only: the younger chunks stay in flight
         __syncthreads();
         fetch(u, (c + PF) * KC);
+        bf16x8 a[2];
 #pragma unroll
-        for (int i = 0; i < kStepsPerWave; ++i) {
-          const int col = ((wave * kStepsPerWave + i) * 16 + frag_half * 8) * 2;  // byte column of this lane's K elements
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(s_x + frag_row * kRowB + col);
+        for (int m = 0; m < 2; ++m) a[m] = *reinterpret_cast<const bf16x8*>(s_x + (m * 16 + row) * kRowB + col);
 #pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            const bf16x8 b = *reinterpret_cast<const bf16x8*>(s_r + (t * 32 + frag_row) * kRowB + col);
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[t], 0, 0, 0);
-          }
+        for (int t = 0; t < TN; ++t) {
+          const bf16x8 b = *reinterpret_cast<const bf16x8*>(s_r + ((part * TN + t) * 16 + row) * kRowB + col);
+#pragma unroll
+          for (int m = 0; m < 2; ++m) acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][t], 0, 0, 0);
         }
+        if (decltype(u)::value == PF - 1 && (c + 1) % kRangeChunks == 0) end_range();  // block-uniform
         __syncthreads();  // every wave has read the chunk (after the last one: the logits may overwrite it)
       }
     });
   }
-  // accumulator register r of lane l: token row 8*(r/4) + 4*(l/32) + (r%4), expert column l % 32
-  for (int w = 0; w < 4; ++w) {  // fixed order: wave 0 stores (with the bias), waves 1..3 add
-    if (wave == w) {
+  if (n_chunks % kRangeChunks != 0) end_range();
+  // accumulator element i of a lane: token 4 * quarter + i, expert `row` of the tile
+  for (int w = 0; w < kChains; ++w) {  // fixed order: chain 0 stores (with the bias), chains 1..3 add
+    if (chain == w) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int e = t * 32 + frag_row;
+      for (int t = 0; t < TN; ++t) {
+        const int e = (part * TN + t) * 16 + row;
         const float b = (w == 0 && bias && e < n_experts) ? bias[e] : 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float* dst = &s_logit[(r / 4) * 8 + frag_half * 4 + (r % 4)][e];
-          *dst = (w == 0 ? 0.0f : *dst) + acc[t][r] + b;
-        }
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float* dst = &s_logit[m * 16 + 4 * quarter + i][e];
+            *dst = (w == 0 ? 0.0f : *dst) + sum[m][t][i] + b;
+          }
       }
     }
     __syncthreads();
   }
   const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;  // 256 threads = 32 tokens x 8 lanes
-  if (tok0 + t_local < n)
+  if (t_local < kTokens && tok0 + t_local < n)
     topk_of_token<NT * 32>(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
                      topk_w + (tok0 + t_local) * top_k);
 }
 
 // bf16, few tokens: a block per 32 tokens is one or two workgroups for a decoding batch, which fetch the whole router matrix
-// in a chain of chunks, a latency each.  So the K extent is
-// split over workgroups too: 16 tokens x one of `splits` K ranges each, its four waves taking blocks of 32 elements straight
-// from memory into the operands of v_mfma_f32_16x16x32_bf16 (the four lanes of a row read a 64-byte sector).  The waves'
-// partial logits are added in wave order, the ranges' in range order by route_pick_kernel.  ET: tiles of 16 experts.
-// A call of 1 / 64 / 397 tokens, before the split / with it: 64 experts, 2048 wide 19 / 20 / 20 -> 15 / 17 / 19 us; 128
-// experts, 2048 wide 36 / 37 / 37 -> 29 / 33 / 36 us; 8 experts, 4096 wide 14 -> 7 / 8 / 9 us (with the top-k in registers
-// 12 / 14 / 16, 21 / 25 / 28 and 7 / 7 / 8 us).
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-constexpr int kTokensSmall = 16, kWavesSmall = 4;
+// in a sequence of chunks, a latency each.  So the ranges of K go to workgroups of their own, and so do groups of ET tiles of
+// 16 experts (blockIdx.z): 16 tokens each, a wave per chain, its eight blocks straight from memory into the operands of
+// v_mfma_f32_16x16x32_bf16 (the four lanes of a row read a 64-byte sector).  part [range][chain][n][n_experts] goes to memory
+// as it is and route_pick_kernel adds it up.
+constexpr int kTokensSmall = 16;
 template <int ET>
-__global__ __launch_bounds__(kWave * kWavesSmall) void route_bf16_split_kernel(
+__global__ __launch_bounds__(kWave * kChains) void route_bf16_split_kernel(
     const __hip_bfloat16* __restrict__ X, int64_t n, int d_model, int64_t ldx, const __hip_bfloat16* __restrict__ R,
     int64_t ldr, int n_experts, const __hip_bfloat16* __restrict__ zeros, float* __restrict__ part) {
-  constexpr int kFlight = ET <= 8 ? 4 : 2;  // K blocks of a wave in flight
-  __shared__ float s_part[kWavesSmall][kTokensSmall][ET * 16];
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  constexpr int kBlocks = kRangeBlocks / kChains;  // of a wave, all in flight
+  const int lane = threadIdx.x % kWave, chain = threadIdx.x / kWave;
   const int row = lane % 16, quarter = lane / 16;
   const int64_t tok0 = (int64_t)blockIdx.x * kTokensSmall;
+  const int e0 = blockIdx.z * ET * 16 + row;
   const __hip_bfloat16* x = X + min(tok0 + row, n - 1) * ldx;  // rows outside repeat the last one; never used
   const __hip_bfloat16* r[ET];
 #pragma unroll
-  for (int t = 0; t < ET; ++t) r[t] = R + (int64_t)min(t * 16 + row, n_experts - 1) * ldr;
+  for (int t = 0; t < ET; ++t) r[t] = R + (int64_t)min(e0 + t * 16, n_experts - 1) * ldr;
   f32x4 acc[ET];
 #pragma unroll
   for (int t = 0; t < ET; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  const int n_blocks = (d_model + 31) / 32;
-  const int kb_begin = (int)((int64_t)n_blocks * blockIdx.y / gridDim.y);
-  const int kb_end = (int)((int64_t)n_blocks * (blockIdx.y + 1) / gridDim.y);
-  for (int kb = kb_begin + wave; kb < kb_end; kb += kWavesSmall * kFlight) {
-    bf16x8 xv[kFlight], rv[kFlight][ET];
+  bf16x8 xv[kBlocks], rv[kBlocks][ET];
 #pragma unroll
-    for (int u = 0; u < kFlight; ++u) {
-      const int at = kb + u * kWavesSmall;
-      const int k = at * 32 + quarter * 8;
-      const bool k_ok = at < kb_end && k < d_model;  // d_model is a multiple of 8
-      xv[u] = *reinterpret_cast<const bf16x8*>(k_ok ? x + k : zeros);
+  for (int u = 0; u < kBlocks; ++u) {
+    const int k = ((int)blockIdx.y * kRangeBlocks + u * kChains + chain) * kBlockK + quarter * 8;
+    const bool k_ok = k < d_model;  // d_model is a multiple of 8
+    xv[u] = *reinterpret_cast<const bf16x8*>(k_ok ? x + k : zeros);
 #pragma unroll
-      for (int t = 0; t < ET; ++t) rv[u][t] = *reinterpret_cast<const bf16x8*>(k_ok ? r[t] + k : zeros);
-    }
-#pragma unroll
-    for (int u = 0; u < kFlight; ++u)
-#pragma unroll
-      for (int t = 0; t < ET; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[u], rv[u][t], acc[t], 0, 0, 0);
+    for (int t = 0; t < ET; ++t) rv[u][t] = *reinterpret_cast<const bf16x8*>(k_ok ? r[t] + k : zeros);
   }
+#pragma unroll
+  for (int u = 0; u < kBlocks; ++u)
+#pragma unroll
+    for (int t = 0; t < ET; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[u], rv[u][t], acc[t], 0, 0, 0);
   // accumulator element i of a lane: token 4 * quarter + i, expert `row` of the tile
+  float* out = part + ((int64_t)blockIdx.y * kChains + chain) * n * n_experts;
 #pragma unroll
-  for (int t = 0; t < ET; ++t)
+  for (int t = 0; t < ET; ++t) {
+    const int e = e0 + t * 16;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s_part[wave][4 * quarter + i][t * 16 + row] = acc[t][i];
-  __syncthreads();
-  for (int i = threadIdx.x; i < kTokensSmall * ET * 16; i += kWave * kWavesSmall) {
-    const int t = i / (ET * 16), e = i % (ET * 16);
-    float s = s_part[0][t][e];
-#pragma unroll
-    for (int w = 1; w < kWavesSmall; ++w) s += s_part[w][t][e];
-    if (tok0 + t < n && e < n_experts) part[((int64_t)blockIdx.y * n + tok0 + t) * n_experts + e] = s;
+    for (int i = 0; i < 4; ++i) {
+      const int64_t tok = tok0 + 4 * quarter + i;
+      if (tok < n && e < n_experts) out[tok * n_experts + e] = acc[t][i];
+    }
   }
 }
 
-// part [splits][n][n_experts].  8 tokens per block: their logits, then the top-k with eight lanes per token.
+// part [ranges][kChains][n][n_experts].  8 tokens per block: their logits, then the top-k with eight lanes per token.
 constexpr int kTokensPick = 8;
 template <int NE>
-__global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict__ part, int splits, int64_t n,
+__global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict__ part, int ranges, int64_t n,
                                                          const float* __restrict__ bias, int n_experts, int top_k,
                                                          int renorm, int32_t* __restrict__ topk_idx,
                                                          float* __restrict__ topk_w) {
@@ -298,16 +320,23 @@ __global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict
   for (int i = threadIdx.x; i < tokens * n_experts; i += 256) {
     const float* p = part + tok0 * n_experts + i;
     const int t = i / n_experts, e = i - t * n_experts;
-    float s = 0.0f;
-    for (int k0 = 0; k0 < splits; k0 += 8) {  // eight ranges in flight, added in order
-      float v[8];
+    float sum[kChains] = {};
+    for (int s0 = 0; s0 < ranges; s0 += 4) {  // the chains of four ranges in flight, added in range order
+      float v[4][kChains];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p[min(k0 + u, splits - 1) * stride];
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (k0 + u < splits) s += v[u];
+        for (int w = 0; w < kChains; ++w) v[u][w] = p[(min(s0 + u, ranges - 1) * kChains + w) * stride];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int w = 0; w < kChains; ++w)
+          if (s0 + u < ranges) sum[w] += v[u][w];
     }
-    s_logit[t][e] = s + (bias ? bias[e] : 0.0f);
+    float logit = sum[0] + (bias ? bias[e] : 0.0f);
+#pragma unroll
+    for (int w = 1; w < kChains; ++w) logit += sum[w];
+    s_logit[t][e] = logit;
   }
   __syncthreads();
   const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;
@@ -398,37 +427,39 @@ template <int NT>
 void launch_bf16(hipStream_t stream, int64_t n_blocks, const void* X, int64_t n, int64_t d_model, int64_t ldx,
                  const void* W_r, int64_t ldr, const float* bias, int n_experts, int top_k, int renorm,
                  const void* zeros, int32_t* topk_idx, float* topk_w) {
-  hipLaunchKernelGGL(route_bf16_kernel<NT>, launch_grid(n_blocks), dim3(256), 0, stream,
+  hipLaunchKernelGGL(route_bf16_kernel<NT>, launch_grid(n_blocks), dim3(kRouteThreads<NT>), 0, stream,
                      static_cast<const __hip_bfloat16*>(X), n, (int)d_model, ldx,
                      static_cast<const __hip_bfloat16*>(W_r), ldr, bias, n_experts, top_k, renorm,
                      static_cast<const __hip_bfloat16*>(zeros), topk_idx, topk_w);
 }
 
-// K ranges of a split call: about 512 workgroups, no range shorter than one block per wave, and the partial logits inside
-// the scratch.  At most kSplitTokens tokens: there a range is 2 (256 experts) to 4 workgroups per tile of tokens.
-constexpr int64_t kSplitTokens = 2048;
-static_assert(2 * kSplitTokens * CAMERA_MAX_EXPERTS * (int64_t)sizeof(float) <= (int64_t)kRouteScratchBytes, "two ranges fit");
-int route_splits(int64_t n, int64_t d_model, int n_experts) {
-  const int64_t tiles = (n + kTokensSmall - 1) / kTokensSmall;
-  const int64_t by_k = ((d_model + 31) / 32 + kWavesSmall - 1) / kWavesSmall;
-  const int64_t by_room = (int64_t)kRouteScratchBytes / (n * n_experts * (int64_t)sizeof(float));
-  int64_t s = (512 + tiles - 1) / tiles;
-  if (s > by_k) s = by_k;
-  if (s > by_room) s = by_room;
-  return (int)(s < 1 ? 1 : s);
+// Whether a call goes range by range, then: it needs two ranges, room for their partial logits, and few enough tokens.  The
+// block kernel's time hardly depends on the batch below 8192 tokens; that of the two launches grows with what they hand
+// over, 16 bytes per logit and range.  us per call, block kernel / range by range:
+//   8 experts, 4096 wide:     1 token 13.2 / 5.3,  1024 15.0 / 7.2,  4096 16.7 / 12.7
+//   64 experts, 2048 wide:    1 token 15.3 / 11.7, 1024 16.4 / 14.5, 2048 16.5 / 18.8
+//   128 experts, 2048 wide:   1 token 26.5 / 20.0, 1024 29.5 / 28.0, 2048 29.8 / 34.6
+//   256 experts, 2048 wide:   1 token 46 / 31,     1024 49.1 / 49.2, 2048 49 / 59
+// so the line is at 1024 tokens from 64 experts on, and below that where as many logits are, in whole tiles of 16 experts.
+constexpr int64_t kSplitLogits = 1024 * 64;
+bool route_split(int64_t n, int64_t ranges, int n_experts) {
+  const int64_t experts = n_experts < 16 ? 16 : (n_experts > 64 ? 64 : n_experts);
+  return ranges > 1 && n * experts <= kSplitLogits &&
+         ranges * kChains * n * n_experts * (int64_t)sizeof(float) <= (int64_t)kRouteScratchBytes;
 }
 
-template <int ET>
+template <int NE>
 void launch_bf16_split(hipStream_t stream, const void* X, int64_t n, int64_t d_model, int64_t ldx, const void* W_r,
                        int64_t ldr, const float* bias, int n_experts, int top_k, int renorm, const void* zeros,
                        float* scratch, int32_t* topk_idx, float* topk_w) {
-  const int splits = route_splits(n, d_model, n_experts);
-  hipLaunchKernelGGL(route_bf16_split_kernel<ET>, dim3((unsigned)((n + kTokensSmall - 1) / kTokensSmall), (unsigned)splits),
-                     dim3(kWave * kWavesSmall), 0, stream, static_cast<const __hip_bfloat16*>(X), n, (int)d_model, ldx,
-                     static_cast<const __hip_bfloat16*>(W_r), ldr, n_experts, static_cast<const __hip_bfloat16*>(zeros),
-                     scratch);
-  hipLaunchKernelGGL(route_pick_kernel<ET * 16>, dim3((unsigned)((n + kTokensPick - 1) / kTokensPick)), dim3(256), 0, stream, scratch,
-                     splits, n, bias, n_experts, top_k, renorm, topk_idx, topk_w);
+  constexpr int ET = NE <= 16 ? 1 : 2;
+  const int ranges = (int)((d_model + kRangeK - 1) / kRangeK);
+  hipLaunchKernelGGL(route_bf16_split_kernel<ET>, dim3((unsigned)((n + kTokensSmall - 1) / kTokensSmall), (unsigned)ranges,
+                     (unsigned)((n_experts + ET * 16 - 1) / (ET * 16))), dim3(kWave * kChains), 0, stream,
+                     static_cast<const __hip_bfloat16*>(X), n, (int)d_model, ldx, static_cast<const __hip_bfloat16*>(W_r), ldr,
+                     n_experts, static_cast<const __hip_bfloat16*>(zeros), scratch);
+  hipLaunchKernelGGL(route_pick_kernel<NE>, dim3((unsigned)((n + kTokensPick - 1) / kTokensPick)), dim3(256), 0, stream, scratch,
+                     ranges, n, bias, n_experts, top_k, renorm, topk_idx, topk_w);
 }
 
 }  // namespace
@@ -440,14 +471,14 @@ hipError_t launch_route_topk(hipStream_t stream, const void* X, int dtype, int64
   if (n <= 0) return hipSuccess;
   const int64_t n_blocks = (n + kTokens - 1) / kTokens;
   if (dtype == CAMERA_BF16) {
-    if (n <= kSplitTokens) {
-#define CAMERA_ROUTE_SPLIT(ET)                                                                                          \
-  launch_bf16_split<ET>(stream, X, n, d_model, ldx, W_r, ldr, bias, n_experts, top_k, renorm, zeros, scratch, topk_idx, \
+    if (route_split(n, (d_model + kRangeK - 1) / kRangeK, n_experts)) {
+#define CAMERA_ROUTE_SPLIT(NE)                                                                                          \
+  launch_bf16_split<NE>(stream, X, n, d_model, ldx, W_r, ldr, bias, n_experts, top_k, renorm, zeros, scratch, topk_idx, \
                         topk_w)
-      if (n_experts <= 16) CAMERA_ROUTE_SPLIT(1);
-      else if (n_experts <= 64) CAMERA_ROUTE_SPLIT(4);
-      else if (n_experts <= 128) CAMERA_ROUTE_SPLIT(8);
-      else CAMERA_ROUTE_SPLIT(16);
+      if (n_experts <= 16) CAMERA_ROUTE_SPLIT(16);
+      else if (n_experts <= 64) CAMERA_ROUTE_SPLIT(64);
+      else if (n_experts <= 128) CAMERA_ROUTE_SPLIT(128);
+      else CAMERA_ROUTE_SPLIT(256);
 #undef CAMERA_ROUTE_SPLIT
       return hipGetLastError();
     }

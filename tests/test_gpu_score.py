@@ -140,10 +140,10 @@ def test_route_f32_edges(cam, n_tokens, n_experts, d_model, top_k):
 
 @pytest.mark.parametrize("n_tokens,n_experts,d_model,top_k", [
     (1, 1, 8, 1), (15, 16, 40, 3), (16, 17, 1032, 4), (17, 64, 2048, 6), (400, 65, 520, 8), (33, 129, 264, 8),
-    (2048, 256, 264, 8), (2049, 16, 264, 2),
+    (2048, 256, 264, 8), (2049, 16, 264, 2), (1, 1, 1032, 1), (400, 65, 1544, 8), (33, 129, 2056, 8),
 ])
 def test_route_bf16_small_batches(cam, n_tokens, n_experts, d_model, top_k):
-    """Batches whose K extent is split over workgroups (up to 2048 tokens) and the first that is not: partial token and
+    """Batches whose K extent is split over workgroups (more than 1024 wide) and ones that are not: partial token and
     expert tiles, K tails, one range and many."""
     cfg = small(n_tokens=n_tokens, d_model=d_model, n_experts=n_experts, top_k=top_k, outlier_channels=0)
     layer = inputs.make_layer(cfg, 3)
@@ -151,6 +151,34 @@ def test_route_bf16_small_batches(cam, n_tokens, n_experts, d_model, top_k):
     L, idx_o, w_o, _ = H.oracle_route(layer, top_k)
     idx_g, w_g = cam.route_topk(dev["X"], dev["W_r"], dev["bias"], top_k)
     H.check_routing(L, idx_o, w_o, idx_g.cpu().numpy(), w_g.cpu().numpy(), top_k)
+
+
+@pytest.mark.parametrize("dtype,n_experts,d_model,top_k,largest", [
+    ("bf16", 8, 4096, 2, 4097),       # four ranges of 1024, the last batch size that goes range by range and the one above
+    ("bf16", 16, 1544, 4, 4097),      # a range that ends inside a block
+    ("bf16", 33, 1032, 8, 2000),      # one block in the second range
+    ("bf16", 64, 2048, 6, 1025),
+    ("bf16", 128, 4104, 8, 1025),     # more partial logits than there is room for above 819 tokens
+    ("bf16", 200, 2048, 8, 1025),
+    ("bf16", 64, 1024, 6, 100),       # one range: one kernel for all
+    ("f32", 12, 772, 3, 1025),
+])
+def test_routing_gives_a_token_the_same_bits_in_every_batch(cam, dtype, n_experts, d_model, top_k, largest):
+    """The order of additions does not depend on the number of tokens: expert choices (near ties among them: the router's
+    rows are in pairs that differ in one element) and weights are those of the largest call, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(n_experts)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    X = torch.randn((largest, d_model), generator=g, device="cuda").to(t)
+    R = torch.randn((n_experts, d_model), generator=g, device="cuda")
+    R[1::2] = R[:n_experts - n_experts % 2:2]
+    R[1::2, d_model // 2] += 2.0 ** -12
+    R = (R * 0.02).to(t)
+    bias = torch.randn(n_experts, generator=g, device="cuda") * 0.1
+    bias[1::2] = bias[:n_experts - n_experts % 2:2]
+    idx, w = cam.route_topk(X, R, bias, top_k)
+    for lo, n in ((0, 1), (largest - 1, 1), (3, 7), (5, 16), (11, 33), (0, 64), (1, largest // 2), (0, largest - 1)):
+        part_idx, part_w = cam.route_topk(X[lo:lo + n], R, bias, top_k)
+        assert torch.equal(part_idx, idx[lo:lo + n]) and torch.equal(part_w, w[lo:lo + n]), (lo, n)
 
 
 def test_shared_expert_dense_call(cam):
