@@ -717,8 +717,10 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   {
     Bracket b(ctx, stream, CAMERA_K_BUCKET);
-    if (dense) {
+    if (dense && mfma) {
       CAMERA_HIP(camera::launch_dense_tables(stream, n, n_experts, tile_m, max_tiles, t), "dense tables launch");
+    } else if (dense) {
+      CAMERA_HIP(camera::launch_compact_dense_items(stream, tiles_of, total, n, t, work), "dense work items launch");
     } else if (small) {
       CAMERA_HIP(camera::launch_compact_bucket_small(stream, topk_idx, topk_w, n, top_k, n_experts, n_shared, tiles_of, t,
                                                      work),
@@ -737,7 +739,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
       }
       CAMERA_HIP(camera::launch_bucket(stream, idx, wts, n, terms, total, tile_m, max_tiles, t), "bucket launch");
     }
-    if (!mfma && !small) CAMERA_HIP(camera::launch_compact_items(stream, tiles_of, total, t, work), "work items launch");
+    if (!dense && !mfma && !small) CAMERA_HIP(camera::launch_compact_items(stream, tiles_of, total, t, work), "work items launch");
   }
   if (mfma) {
     {

@@ -203,9 +203,12 @@ constexpr int kCompactSmallPairs = 2048;
 hipError_t launch_compact_bucket_small(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n,
                                        int top_k, int n_experts, int n_shared, const CompactWork& tab,
                                        const BucketTables& t, int32_t* work);
-// The work items from the counts of the other bucket orders.
+// The work items from the counts of the general counting sort.
 hipError_t launch_compact_items(hipStream_t stream, const CompactWork& tab, int total, const BucketTables& t,
                                 int32_t* work);
+// Without routing: the tables (counts, offsets; every expert has the tokens 0 .. n-1) and the work items.
+hipError_t launch_compact_dense_items(hipStream_t stream, const CompactWork& tab, int total, int64_t n,
+                                      const BucketTables& t, int32_t* work);
 // idx_aug / w_aug [n][top_k + n_shared]: the routed choices followed by the appended experts with weight 1.
 hipError_t launch_compact_append_shared(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n,
                                         int top_k, int n_experts, int n_shared, int32_t* idx_aug, float* w_aug);

@@ -628,13 +628,27 @@ __global__ __launch_bounds__(kSmallThreads) void compact_bucket_small_kernel(
   write_work<kSmallThreads / kWave>(tab, total, tid < total ? s_count[tid] : 0, wave_total, work);
 }
 
-// The work items where the bucket order comes from the general counting sort, or every expert has every token.
+// The work items where the bucket order comes from the general counting sort.
 __global__ __launch_bounds__(CAMERA_MAX_EXPERTS) void compact_items_kernel(CompactWork tab, int total,
                                                                            const int32_t* __restrict__ counts,
                                                                            int32_t* __restrict__ work) {
   __shared__ int32_t wave_total[CAMERA_MAX_EXPERTS / kWave];
   const int e = threadIdx.x;
   write_work<CAMERA_MAX_EXPERTS / kWave>(tab, total, e < total ? counts[e] : 0, wave_total, work);
+}
+// Where every expert has every token: the order too, in the one launch that the order alone would take.
+__global__ __launch_bounds__(CAMERA_MAX_EXPERTS) void compact_dense_items_kernel(CompactWork tab, int total, int n,
+                                                                                 int32_t* __restrict__ counts,
+                                                                                 int32_t* __restrict__ offsets,
+                                                                                 int32_t* __restrict__ work) {
+  __shared__ int32_t wave_total[CAMERA_MAX_EXPERTS / kWave];
+  const int e = threadIdx.x;
+  if (e < total) {
+    counts[e] = n;
+    offsets[e] = e * n;
+    if (e == total - 1) offsets[total] = total * n;
+  }
+  write_work<CAMERA_MAX_EXPERTS / kWave>(tab, total, e < total ? n : 0, wave_total, work);
 }
 
 // Upper bound of the work items of a contraction with tiles[e] per expert: of the n * top_k routed pairs, an expert with
@@ -689,6 +703,12 @@ hipError_t launch_compact_bucket_small(hipStream_t stream, const int32_t* topk_i
 hipError_t launch_compact_items(hipStream_t stream, const CompactWork& tab, int total, const BucketTables& t,
                                 int32_t* work) {
   compact_items_kernel<<<1, CAMERA_MAX_EXPERTS, 0, stream>>>(tab, total, t.counts, work);
+  return hipGetLastError();
+}
+
+hipError_t launch_compact_dense_items(hipStream_t stream, const CompactWork& tab, int total, int64_t n,
+                                      const BucketTables& t, int32_t* work) {
+  compact_dense_items_kernel<<<1, CAMERA_MAX_EXPERTS, 0, stream>>>(tab, total, (int)n, t.counts, t.offsets, work);
   return hipGetLastError();
 }
 
