@@ -41,6 +41,7 @@ __device__ __forceinline__ uint32_t key_of(float v) {
 //            1/128 of an octave), so they go to global memory one by one
 //   segment  one workgroup per segment: class of every element, output bytes, counts and the stable partition by level
 //   compact  (optional) ascending list of the kept indices
+//   label, finish   instead of these two where a segment is long: a workgroup per part of one
 // No workgroup picks for the others: `low` and `segment` begin with every workgroup reading the histogram of the pass
 // before for itself -- a wave per cut, 256 coarse counters (8 bits) and then the 256 fine ones under the bin it found,
 // two dependent loads -- so nothing needs a fence, a ticket or a last workgroup, and a kernel boundary is the only
@@ -56,6 +57,7 @@ constexpr int kRankThreads = 1024;
 constexpr int kRankWaves = kRankThreads / kWave;
 constexpr int kKeysPerBlock = kRankThreads * 8;  // a counter of the LDS histogram cannot overflow its 16 bits
 constexpr int kFine = 1 << 16, kCoarse = 1 << 8;
+constexpr int kMaxParts = CAMERA_MAX_SEGMENTS + 1024;
 constexpr int kMinTopBlocks = 64;                // workgroups that clear for `low` (0.25 MB per cut) when the keys are few
 static_assert(kMaxCuts <= kRankWaves, "a wave per cut in the pick");
 
@@ -68,6 +70,8 @@ struct RankState {  // persistent, see above
   } low[kMaxCuts];
   uint32_t prefix[kMaxCuts];              // bits 31..16 of the cut element
   uint32_t rest[kMaxCuts];                // its rank among the keys that share them
+  uint32_t part_class[kMaxParts][CAMERA_MAX_LEVELS];  // of a part of a segment: its members by class (written by `label`)
+  uint32_t part_ties[kMaxParts][kMaxCuts];            // and the keys before it that equal each cut's, where a cut has ties
 };
 
 // The 8 keys of this thread: two float4 of consecutive keys, kKeysPerBlock / 2 apart.  Both loads are issued together.
@@ -249,6 +253,15 @@ __global__ __launch_bounds__(kRankThreads) void rank_low_kernel(const float* __r
 
 __device__ __forceinline__ int nibble(uint32_t packed, int c) { return (int)((packed >> (4 * c)) & 15u); }
 
+// A segment of more keys than this goes in parts of kPartKeys or more: one workgroup walks some 1300 keys a microsecond, the
+// parts cost a launch and, with a partition, two more walks.  us per call, whole / in parts (one pruning mask with its index
+// list; three masks and bits; bits and partition):
+//   64 segments of 2560, one of 20480   33 / 32    30 / 28    37 / 44
+//   one of 32768                        39 / 28    34 / 24    45 / 41
+//   one of 2^20                         802 / 54   563 / 48   992 / 65
+constexpr int kWholeSegment = 24576;
+constexpr int kPartKeys = 8192;
+
 // The cuts as the walk sees them.
 struct CutKeys {
   uint32_t key[kMaxCuts];   // key of the cut element; 0 where nothing, 0xffffffff where everything lies below (with all set)
@@ -274,29 +287,31 @@ __device__ __forceinline__ int class_of(const CutKeys& c, uint32_t k, bool valid
   return below;
 }
 
-template <bool ANY_TIES>
-__device__ __forceinline__ void segment_walk(const float* __restrict__ E, const CutKeys& cut, int begin, int end,
-                                             uint64_t out_table, uint64_t out2_table, const SegOutputs& out, int n_seg,
-                                             uint8_t* __restrict__ byte_out, uint8_t* __restrict__ byte_out2,
-                                             uint32_t (*s_cnt)[CAMERA_MAX_LEVELS], uint32_t (*s_lvl)[CAMERA_MAX_LEVELS],
-                                             uint32_t (*s_tie)[kRankWaves]) {
-  const int s = blockIdx.x;
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const uint64_t lower = (1ull << lane) - 1ull;
+// A wave's range of [begin, end): the waves have consecutive ones, whole steps of kWave.
+struct WaveRange {
+  int begin, end;
+};
+__device__ __forceinline__ WaveRange wave_range(int begin, int end) {
+  const int wave = threadIdx.x / kWave;
   const int span = ((end - begin + kRankWaves * kWave - 1) / (kRankWaves * kWave)) * kWave;
-  const int w_begin = min(end, begin + wave * span);
-  const int w_end = min(end, w_begin + span);
-  constexpr int U = 4;  // steps whose loads are in flight together
+  WaveRange r;
+  r.begin = min(end, begin + wave * span);
+  r.end = min(end, r.begin + span);
+  return r;
+}
+constexpr int kSteps = 4;  // steps of a walk whose loads are in flight together
 
-  uint32_t tie_base[kMaxCuts];
+// tie_base[q]: keys equal to cut q's at lower indices than the wave's range.  COUNT_BEFORE: those before `begin` are
+// counted here, by all threads, and left in s_before (all of the workgroup's waves call it); otherwise s_before has them.
+template <bool COUNT_BEFORE>
+__device__ __forceinline__ void count_ties(const float* __restrict__ E, const CutKeys& cut, int begin, WaveRange r,
+                                           uint32_t* s_before, uint32_t (*s_tie)[kRankWaves], uint32_t (&tie_base)[kMaxCuts]) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  uint32_t before[kMaxCuts], mine[kMaxCuts];
 #pragma unroll
-  for (int q = 0; q < kMaxCuts; ++q) tie_base[q] = 0u;
-  if constexpr (ANY_TIES) {
-    // equal keys before this wave: in the segments before this one (counted here by all threads) and in the earlier
-    // waves of this one
-    uint32_t before[kMaxCuts], mine[kMaxCuts];
-#pragma unroll
-    for (int q = 0; q < kMaxCuts; ++q) before[q] = mine[q] = 0u;
+  for (int q = 0; q < kMaxCuts; ++q) before[q] = mine[q] = 0u;
+  if constexpr (COUNT_BEFORE) {
+    constexpr int U = kSteps;
     for (int64_t i0 = threadIdx.x; i0 < begin; i0 += U * kRankThreads) {  // 64 bits: `begin` may be within a step of 2^31
       uint32_t k[U];
 #pragma unroll
@@ -310,75 +325,187 @@ __device__ __forceinline__ void segment_walk(const float* __restrict__ E, const 
         for (int q = 0; q < kMaxCuts; ++q)
           before[q] += (i0 + u * kRankThreads < begin && k[u] == cut.key[q]) ? 1u : 0u;
     }
-    for (int i0 = w_begin; i0 < w_end; i0 += kWave) {
-      const bool valid = i0 + lane < w_end;
-      const uint32_t k = valid ? key_of(E[i0 + lane]) : 0u;
+  }
+  for (int i0 = r.begin; i0 < r.end; i0 += kWave) {
+    const bool valid = i0 + lane < r.end;
+    const uint32_t k = valid ? key_of(E[i0 + lane]) : 0u;
 #pragma unroll
-      for (int q = 0; q < kMaxCuts; ++q) mine[q] += __popcll(__ballot(valid && k == cut.key[q]));
-    }
+    for (int q = 0; q < kMaxCuts; ++q) mine[q] += __popcll(__ballot(valid && k == cut.key[q]));
+  }
 #pragma unroll
-    for (int q = 0; q < kMaxCuts; ++q) {
+  for (int q = 0; q < kMaxCuts; ++q) {
+    if constexpr (COUNT_BEFORE) {
 #pragma unroll
       for (int m = 32; m >= 1; m >>= 1) before[q] += __shfl_xor(before[q], m);
-      if (lane == 0) {
-        s_tie[q][wave] = mine[q];
-        s_tie[kMaxCuts + q][wave] = before[q];
-      }
     }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kMaxCuts; ++q) {
-      uint32_t run = 0;
-      for (int w = 0; w < kRankWaves; ++w) run += s_tie[kMaxCuts + q][w] + (w < wave ? s_tie[q][w] : 0u);
-      tie_base[q] = run;
+    if (lane == 0) {
+      s_tie[q][wave] = mine[q];
+      s_tie[kMaxCuts + q][wave] = before[q];
     }
   }
-
-  // first walk: output bytes and class sizes
-  uint32_t cnt[CAMERA_MAX_LEVELS], tie_run[kMaxCuts];
+  __syncthreads();
+  if (COUNT_BEFORE && threadIdx.x < kMaxCuts) {
+    uint32_t all = 0;
+    for (int w = 0; w < kRankWaves; ++w) all += s_tie[kMaxCuts + threadIdx.x][w];
+    s_before[threadIdx.x] = all;
+  }
+  __syncthreads();
 #pragma unroll
-  for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) cnt[m] = 0u;
+  for (int q = 0; q < kMaxCuts; ++q) {
+    uint32_t run = s_before[q];
+    for (int w = 0; w < wave; ++w) run += s_tie[q][w];
+    tie_base[q] = run;
+  }
+}
+
+// f(index, valid, class) for the elements of the wave's range, in index order, all lanes together.
+template <bool ANY_TIES, class F>
+__device__ __forceinline__ void walk(const float* __restrict__ E, const CutKeys& cut, WaveRange r,
+                                     const uint32_t (&tie_base)[kMaxCuts], F&& f) {
+  const int lane = threadIdx.x % kWave;
+  const uint64_t lower = (1ull << lane) - 1ull;
+  uint32_t tie_run[kMaxCuts];
 #pragma unroll
   for (int q = 0; q < kMaxCuts; ++q) tie_run[q] = tie_base[q];
-  for (int i0 = w_begin; i0 < w_end; i0 += U * kWave) {
-    float v[U];
+  for (int i0 = r.begin; i0 < r.end; i0 += kSteps * kWave) {
+    float v[kSteps];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < kSteps; ++u) {
       const int i = i0 + u * kWave + lane;
-      v[u] = i < w_end ? E[i] : 0.0f;
+      v[u] = i < r.end ? E[i] : 0.0f;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < kSteps; ++u) {
       const int i = i0 + u * kWave + lane;
-      const bool valid = i < w_end;
-      const int c = class_of<ANY_TIES>(cut, key_of(v[u]), valid, lower, tie_run);
-      if (valid) {
-        byte_out[i] = (uint8_t)(out_table >> (8 * c));
-        if (byte_out2) byte_out2[i] = (uint8_t)(out2_table >> (8 * c));
+      const bool valid = i < r.end;
+      f(i, valid, class_of<ANY_TIES>(cut, key_of(v[u]), valid, lower, tie_run));
+    }
+  }
+}
+
+// The cuts' keys from the counts of the `low` pass, by every workgroup for itself.
+__device__ __forceinline__ void load_cuts(const RankCuts& cuts, int64_t n, const RankState* __restrict__ st, uint32_t* s_key,
+                                          uint32_t* s_ties, CutKeys* cut, bool* any_ties) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  if (wave < kMaxCuts) {
+    Pick p = {0u, 0u};
+    if (cut_mode(cuts, wave, n) == kCutSelect) {
+      p = pick_2level(st->low[wave].coarse, st->low[wave].fine, st->rest[wave]);
+      p.bin |= st->prefix[wave] << 16;
+    }
+    if (lane == 0) {
+      s_key[wave] = p.bin;
+      s_ties[wave] = p.rest;
+    }
+  }
+  __syncthreads();
+  cut->all = 0u;
+  *any_ties = false;
+#pragma unroll
+  for (int q = 0; q < kMaxCuts; ++q) {
+    cut->key[q] = __builtin_amdgcn_readfirstlane(s_key[q]);
+    cut->ties[q] = __builtin_amdgcn_readfirstlane(s_ties[q]);
+    *any_ties |= cut->ties[q] != 0;
+    if (cut_mode(cuts, q, n) == kCutAll) cut->all |= 1u << q;
+  }
+}
+// Leaves the counters of the `top` pass as the next call needs them; nobody reads them any more.
+__device__ __forceinline__ void clear_top(RankState* __restrict__ st) {
+  uint4* top = reinterpret_cast<uint4*>(st->top_coarse);
+  static_assert(offsetof(RankState, top_fine) == kCoarse * 4, "coarse and fine counters lie side by side");
+  for (int i = blockIdx.x * kRankThreads + threadIdx.x; i < (kCoarse + kFine) / 4; i += gridDim.x * kRankThreads)
+    top[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+struct OutTables {
+  uint64_t first, second;  // output bytes by class
+};
+__device__ __forceinline__ OutTables out_tables(const RankCuts& cuts) {
+  OutTables t = {0, 0};
+#pragma unroll
+  for (int c = 0; c <= kMaxCuts; ++c) {
+    t.first |= (uint64_t)cuts.out_of_below[c] << (8 * c);
+    t.second |= (uint64_t)cuts.out2_of_below[c] << (8 * c);
+  }
+  return t;
+}
+
+// Output bytes of the wave's elements; s_cnt[wave]: its members by class.
+template <bool ANY_TIES>
+__device__ __forceinline__ void label(const float* __restrict__ E, const CutKeys& cut, WaveRange r,
+                                      const uint32_t (&tie_base)[kMaxCuts], const OutTables& t, int n_classes,
+                                      uint8_t* __restrict__ byte_out, uint8_t* __restrict__ byte_out2,
+                                      uint32_t (*s_cnt)[CAMERA_MAX_LEVELS]) {
+  uint32_t cnt[CAMERA_MAX_LEVELS];
+#pragma unroll
+  for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) cnt[m] = 0u;
+  walk<ANY_TIES>(E, cut, r, tie_base, [&](int i, bool valid, int c) {
+    if (valid && byte_out) {
+      byte_out[i] = (uint8_t)(t.first >> (8 * c));
+      if (byte_out2) byte_out2[i] = (uint8_t)(t.second >> (8 * c));
+    }
+#pragma unroll
+    for (int m = 0; m < CAMERA_MAX_LEVELS; ++m)
+      if (m < n_classes) cnt[m] += __popcll(__ballot(valid && c == m));
+  });
+  if (threadIdx.x % kWave == 0) {
+#pragma unroll
+    for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) s_cnt[threadIdx.x / kWave][m] = cnt[m];
+  }
+}
+// Members of level m among the classes counted in cnt.
+__device__ __forceinline__ uint32_t of_level(const SegOutputs& out, const uint32_t* cnt, int m) {
+  uint32_t total = 0;
+  for (int c = 0; c < out.n_classes; ++c)
+    if (nibble(out.level_of_class, c) == m) total += cnt[c];
+  return total;
+}
+// Kept at ratio k: the members of the classes that lie below at most n_ratios - 1 - k of the pruning cuts.
+__device__ __forceinline__ bool class_kept(const SegOutputs& out, int c, int k) {
+  return nibble(out.prune_cuts_of_class, c) <= out.n_ratios - 1 - k;
+}
+// The stable partition by level: slot[m] is the first place of the wave's members of level m.
+template <bool ANY_TIES>
+__device__ __forceinline__ void partition(const float* __restrict__ E, const CutKeys& cut, WaveRange r,
+                                          const uint32_t (&tie_base)[kMaxCuts], const SegOutputs& out,
+                                          uint32_t (&slot)[CAMERA_MAX_LEVELS]) {
+  const uint64_t lower = (1ull << (threadIdx.x % kWave)) - 1ull;
+  walk<ANY_TIES>(E, cut, r, tie_base, [&](int i, bool valid, int c) {
+    const int lv = nibble(out.level_of_class, c);
+#pragma unroll
+    for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) {
+      if (m < out.n_levels) {
+        const uint64_t b = __ballot(valid && lv == m);
+        if (valid && lv == m) out.perm[slot[m] + __popcll(b & lower)] = i;
+        slot[m] += __popcll(b);
       }
-#pragma unroll
-      for (int m = 0; m < CAMERA_MAX_LEVELS; ++m)
-        if (m < out.n_classes) cnt[m] += __popcll(__ballot(valid && c == m));
     }
-  }
-  if (lane == 0) {
+  });
+}
+
+// One workgroup per segment.  low_counted: the select passes ran (some cut has keys on both sides).
+template <bool ANY_TIES>
+__device__ __forceinline__ void whole_segment(const float* __restrict__ E, const CutKeys& cut, int begin, int end,
+                                              const OutTables& t, const SegOutputs& out, int n_seg,
+                                              uint8_t* __restrict__ byte_out, uint8_t* __restrict__ byte_out2,
+                                              uint32_t (*s_cnt)[CAMERA_MAX_LEVELS], uint32_t (*s_lvl)[CAMERA_MAX_LEVELS],
+                                              uint32_t (*s_tie)[kRankWaves], uint32_t* s_before) {
+  const int s = blockIdx.x, wave = threadIdx.x / kWave;
+  const WaveRange r = wave_range(begin, end);
+  uint32_t tie_base[kMaxCuts];
 #pragma unroll
-    for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) s_cnt[wave][m] = cnt[m];
-  }
+  for (int q = 0; q < kMaxCuts; ++q) tie_base[q] = 0u;
+  if constexpr (ANY_TIES) count_ties<true>(E, cut, begin, r, s_before, s_tie, tie_base);
+  label<ANY_TIES>(E, cut, r, tie_base, t, out.n_classes, byte_out, byte_out2, s_cnt);
   __syncthreads();
   if (threadIdx.x < kRankWaves * CAMERA_MAX_LEVELS) {  // (wave w, level m): members of level m in wave w's range
     const int w = threadIdx.x / CAMERA_MAX_LEVELS, m = threadIdx.x % CAMERA_MAX_LEVELS;
-    uint32_t total = 0;
-    for (int c = 0; c < out.n_classes; ++c)
-      if (nibble(out.level_of_class, c) == m) total += s_cnt[w][c];
-    s_lvl[w][m] = total;
+    s_lvl[w][m] = of_level(out, s_cnt[w], m);
   }
   if (threadIdx.x >= 512 && threadIdx.x < 512 + out.n_ratios) {
-    // kept at ratio k: the members of the classes that lie below at most n_ratios - 1 - k of the pruning cuts
     const int k = threadIdx.x - 512;
     uint32_t total = 0;
     for (int c = 0; c < out.n_classes; ++c)
-      if (nibble(out.prune_cuts_of_class, c) <= out.n_ratios - 1 - k)
+      if (class_kept(out, c, k))
         for (int w = 0; w < kRankWaves; ++w) total += s_cnt[w][c];
     out.kept[k * n_seg + s] = (int32_t)total;
   }
@@ -389,8 +516,7 @@ __device__ __forceinline__ void segment_walk(const float* __restrict__ E, const 
     out.level_count[s * out.n_levels + threadIdx.x] = (int32_t)total;
   }
   if (out.perm == nullptr) return;  // block-uniform
-
-  // second walk: first slot of level m for this wave = segment start + all earlier levels + earlier waves
+  // first slot of level m for this wave = segment start + all earlier levels + earlier waves
   uint32_t slot[CAMERA_MAX_LEVELS];
   uint32_t run = (uint32_t)begin;
 #pragma unroll
@@ -403,82 +529,167 @@ __device__ __forceinline__ void segment_walk(const float* __restrict__ E, const 
       }
     }
   }
-#pragma unroll
-  for (int q = 0; q < kMaxCuts; ++q) tie_run[q] = tie_base[q];
-  for (int i0 = w_begin; i0 < w_end; i0 += U * kWave) {
-    float v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = i0 + u * kWave + lane;
-      v[u] = i < w_end ? E[i] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = i0 + u * kWave + lane;
-      const bool valid = i < w_end;
-      const int lv = nibble(out.level_of_class, class_of<ANY_TIES>(cut, key_of(v[u]), valid, lower, tie_run));
-#pragma unroll
-      for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) {
-        if (m < out.n_levels) {
-          const uint64_t b = __ballot(valid && lv == m);
-          if (valid && lv == m) out.perm[slot[m] + __popcll(b & lower)] = i;
-          slot[m] += __popcll(b);
-        }
-      }
-    }
-  }
+  partition<ANY_TIES>(E, cut, r, tie_base, out, slot);
 }
 
-// One workgroup per segment (a shared expert can be a 20 480-element segment: 16 waves walk it).
-// low_counted: the select passes ran (some cut has keys on both sides).
 __global__ __launch_bounds__(kRankThreads) void rank_segment_kernel(const float* __restrict__ E, int64_t n, RankCuts cuts,
                                                                    SegTable seg, SegOutputs out, int low_counted,
                                                                    RankState* __restrict__ st, uint8_t* __restrict__ byte_out,
                                                                    uint8_t* __restrict__ byte_out2 /*or NULL*/) {
-  __shared__ uint32_t s_key[kMaxCuts], s_ties[kMaxCuts];
+  __shared__ uint32_t s_key[kMaxCuts], s_ties[kMaxCuts], s_before[kMaxCuts];
   __shared__ uint32_t s_cnt[kRankWaves][CAMERA_MAX_LEVELS];   // per wave and class
   __shared__ uint32_t s_lvl[kRankWaves][CAMERA_MAX_LEVELS];   // per wave and level
   __shared__ uint32_t s_tie[2 * kMaxCuts][kRankWaves];
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  if (wave < kMaxCuts) {
-    Pick p = {0u, 0u};
-    if (cut_mode(cuts, wave, n) == kCutSelect) {
-      p = pick_2level(st->low[wave].coarse, st->low[wave].fine, st->rest[wave]);
-      p.bin |= st->prefix[wave] << 16;
-    }
-    if (lane == 0) {
-      s_key[wave] = p.bin;
-      s_ties[wave] = p.rest;
-    }
-  }
-  if (low_counted) {  // leave the state as the next call needs it: nobody reads these counters any more
-    uint4* top = reinterpret_cast<uint4*>(st->top_coarse);
-    static_assert(offsetof(RankState, top_fine) == kCoarse * 4, "coarse and fine counters lie side by side");
-    for (int i = blockIdx.x * kRankThreads + tid; i < (kCoarse + kFine) / 4; i += gridDim.x * kRankThreads)
-      top[i] = make_uint4(0u, 0u, 0u, 0u);
-  }
-  __syncthreads();
+  if (low_counted) clear_top(st);
   CutKeys cut;
-  cut.all = 0u;
-  bool any_ties = false;
-  uint64_t out_table = 0, out2_table = 0;
-#pragma unroll
-  for (int q = 0; q < kMaxCuts; ++q) {
-    cut.key[q] = __builtin_amdgcn_readfirstlane(s_key[q]);
-    cut.ties[q] = __builtin_amdgcn_readfirstlane(s_ties[q]);
-    any_ties |= cut.ties[q] != 0;
-    if (cut_mode(cuts, q, n) == kCutAll) cut.all |= 1u << q;
-  }
-#pragma unroll
-  for (int c = 0; c <= kMaxCuts; ++c) {
-    out_table |= (uint64_t)cuts.out_of_below[c] << (8 * c);
-    out2_table |= (uint64_t)cuts.out2_of_below[c] << (8 * c);
-  }
+  bool any_ties;
+  load_cuts(cuts, n, st, s_key, s_ties, &cut, &any_ties);
+  const OutTables t = out_tables(cuts);
   const int begin = seg.off[blockIdx.x], end = seg.off[blockIdx.x + 1];
   if (any_ties)  // block-uniform
-    segment_walk<true>(E, cut, begin, end, out_table, out2_table, out, seg.n_seg, byte_out, byte_out2, s_cnt, s_lvl, s_tie);
+    whole_segment<true>(E, cut, begin, end, t, out, seg.n_seg, byte_out, byte_out2, s_cnt, s_lvl, s_tie, s_before);
   else
-    segment_walk<false>(E, cut, begin, end, out_table, out2_table, out, seg.n_seg, byte_out, byte_out2, s_cnt, s_lvl, s_tie);
+    whole_segment<false>(E, cut, begin, end, t, out, seg.n_seg, byte_out, byte_out2, s_cnt, s_lvl, s_tie, s_before);
+}
+
+// Long segments go in parts of `len` keys, a workgroup each, in two launches: `label` writes the output bytes and counts a
+// part's members by class, `finish` adds the parts up and places their members.  off[s]: the parts before segment s; a
+// segment without keys has one part.
+struct Parts {
+  int32_t len;
+  uint16_t off[CAMERA_MAX_SEGMENTS + 1];
+};
+static_assert(kMaxParts < 65536, "part numbers fit 16 bits");
+struct PartRange {
+  int seg, begin, end;
+};
+__device__ __forceinline__ PartRange part_range(const Parts& parts, const SegTable& seg, int* s_seg) {
+  const int b = blockIdx.x;
+  if ((int)threadIdx.x < seg.n_seg && parts.off[threadIdx.x] <= b && b < parts.off[threadIdx.x + 1]) *s_seg = threadIdx.x;
+  __syncthreads();
+  PartRange p;
+  p.seg = __builtin_amdgcn_readfirstlane(*s_seg);
+  const int64_t begin = seg.off[p.seg] + (int64_t)(b - parts.off[p.seg]) * parts.len;
+  p.begin = (int)begin;
+  p.end = (int)min(begin + parts.len, (int64_t)seg.off[p.seg + 1]);
+  return p;
+}
+
+__global__ __launch_bounds__(kRankThreads) void rank_label_kernel(const float* __restrict__ E, int64_t n, RankCuts cuts,
+                                                                 SegTable seg, Parts parts, int n_classes, int low_counted,
+                                                                 RankState* __restrict__ st, uint8_t* __restrict__ byte_out,
+                                                                 uint8_t* __restrict__ byte_out2 /*or NULL*/) {
+  __shared__ uint32_t s_key[kMaxCuts], s_ties[kMaxCuts], s_before[kMaxCuts];
+  __shared__ uint32_t s_cnt[kRankWaves][CAMERA_MAX_LEVELS];
+  __shared__ uint32_t s_tie[2 * kMaxCuts][kRankWaves];
+  __shared__ int s_seg;
+  if (low_counted) clear_top(st);
+  const PartRange p = part_range(parts, seg, &s_seg);
+  CutKeys cut;
+  bool any_ties;
+  load_cuts(cuts, n, st, s_key, s_ties, &cut, &any_ties);
+  const OutTables t = out_tables(cuts);
+  const WaveRange r = wave_range(p.begin, p.end);
+  uint32_t tie_base[kMaxCuts];
+#pragma unroll
+  for (int q = 0; q < kMaxCuts; ++q) tie_base[q] = 0u;
+  if (any_ties) {  // block-uniform
+    count_ties<true>(E, cut, p.begin, r, s_before, s_tie, tie_base);
+    if (threadIdx.x < kMaxCuts) st->part_ties[blockIdx.x][threadIdx.x] = s_before[threadIdx.x];
+    label<true>(E, cut, r, tie_base, t, n_classes, byte_out, byte_out2, s_cnt);
+  } else {
+    label<false>(E, cut, r, tie_base, t, n_classes, byte_out, byte_out2, s_cnt);
+  }
+  __syncthreads();
+  if (threadIdx.x < CAMERA_MAX_LEVELS) {
+    uint32_t total = 0;
+    for (int w = 0; w < kRankWaves; ++w) total += s_cnt[w][threadIdx.x];
+    st->part_class[blockIdx.x][threadIdx.x] = total;
+  }
+}
+
+// kept_idx as in rank_compact_kernel.
+template <bool ANY_TIES>
+__device__ __forceinline__ void place_part(const float* __restrict__ E, const CutKeys& cut, const PartRange& p,
+                                           const SegOutputs& out, const uint32_t* s_total, const uint32_t* s_earlier,
+                                           uint32_t first_kept, int32_t* __restrict__ kept_idx,
+                                           uint32_t (*s_cnt)[CAMERA_MAX_LEVELS], uint32_t (*s_tie)[kRankWaves],
+                                           uint32_t* s_before, int seg_begin) {
+  const int wave = threadIdx.x / kWave;
+  const uint64_t lower = (1ull << (threadIdx.x % kWave)) - 1ull;
+  const WaveRange r = wave_range(p.begin, p.end);
+  uint32_t tie_base[kMaxCuts];
+#pragma unroll
+  for (int q = 0; q < kMaxCuts; ++q) tie_base[q] = 0u;
+  if constexpr (ANY_TIES) count_ties<false>(E, cut, p.begin, r, s_before, s_tie, tie_base);
+  label<ANY_TIES>(E, cut, r, tie_base, OutTables{0, 0}, out.n_classes, nullptr, nullptr, s_cnt);  // counts only
+  __syncthreads();
+  if (out.perm) {
+    uint32_t slot[CAMERA_MAX_LEVELS];
+    uint32_t run = (uint32_t)seg_begin;
+#pragma unroll
+    for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) {
+      slot[m] = 0;
+      if (m < out.n_levels) {
+        slot[m] = run + of_level(out, s_earlier, m);
+        for (int w = 0; w < wave; ++w) slot[m] += of_level(out, s_cnt[w], m);
+        run += of_level(out, s_total, m);
+      }
+    }
+    partition<ANY_TIES>(E, cut, r, tie_base, out, slot);
+  }
+  if (kept_idx) {
+    uint32_t pos = first_kept;
+    for (int w = 0; w < wave; ++w) pos += s_cnt[w][0];
+    walk<ANY_TIES>(E, cut, r, tie_base, [&](int i, bool valid, int c) {
+      const uint64_t b = __ballot(valid && c == 0);
+      if (valid && c == 0) kept_idx[pos + __popcll(b & lower)] = i;
+      pos += __popcll(b);
+    });
+  }
+}
+
+__global__ __launch_bounds__(kRankThreads) void rank_finish_kernel(const float* __restrict__ E, int64_t n, RankCuts cuts,
+                                                                  SegTable seg, Parts parts, SegOutputs out,
+                                                                  const RankState* __restrict__ st,
+                                                                  int32_t* __restrict__ kept_idx /*or NULL*/) {
+  __shared__ uint32_t s_key[kMaxCuts], s_ties[kMaxCuts], s_before[kMaxCuts];
+  __shared__ uint32_t s_cnt[kRankWaves][CAMERA_MAX_LEVELS];
+  __shared__ uint32_t s_tie[2 * kMaxCuts][kRankWaves];
+  __shared__ uint32_t s_total[CAMERA_MAX_LEVELS], s_earlier[CAMERA_MAX_LEVELS];  // of the segment, of its earlier parts
+  __shared__ uint32_t s_kept;                                                    // before this part, in all segments
+  __shared__ int s_seg;
+  const int b = blockIdx.x, tid = threadIdx.x;
+  if (tid < CAMERA_MAX_LEVELS) s_total[tid] = s_earlier[tid] = 0u;
+  if (tid == 0) s_kept = 0u;
+  const PartRange p = part_range(parts, seg, &s_seg);
+  for (int i = parts.off[p.seg] + tid / CAMERA_MAX_LEVELS; i < parts.off[p.seg + 1]; i += kRankThreads / CAMERA_MAX_LEVELS) {
+    const int c = tid % CAMERA_MAX_LEVELS;
+    const uint32_t v = st->part_class[i][c];
+    if (v == 0u) continue;
+    atomicAdd(&s_total[c], v);
+    if (i < b) atomicAdd(&s_earlier[c], v);
+  }
+  if (kept_idx) {
+    for (int i = tid; i < b; i += kRankThreads) atomicAdd(&s_kept, st->part_class[i][0]);
+  }
+  if (tid < kMaxCuts) s_before[tid] = st->part_ties[b][tid];
+  CutKeys cut;
+  bool any_ties;
+  load_cuts(cuts, n, st, s_key, s_ties, &cut, &any_ties);
+  if (b == parts.off[p.seg]) {
+    if (tid < out.n_ratios) {
+      uint32_t total = 0;
+      for (int c = 0; c < out.n_classes; ++c) total += class_kept(out, c, tid) ? s_total[c] : 0u;
+      out.kept[tid * seg.n_seg + p.seg] = (int32_t)total;
+    }
+    if (tid < out.n_levels) out.level_count[p.seg * out.n_levels + tid] = (int32_t)of_level(out, s_total, tid);
+  }
+  if (out.perm == nullptr && kept_idx == nullptr) return;  // block-uniform
+  if (any_ties)  // block-uniform
+    place_part<true>(E, cut, p, out, s_total, s_earlier, s_kept, kept_idx, s_cnt, s_tie, s_before, seg.off[p.seg]);
+  else
+    place_part<false>(E, cut, p, out, s_total, s_earlier, s_kept, kept_idx, s_cnt, s_tie, s_before, seg.off[p.seg]);
 }
 
 // Ascending list of the kept indices (keep byte 1), one workgroup per segment; kept [n_seg]: how many each segment keeps.
@@ -665,12 +876,31 @@ hipError_t launch_rank_decisions(hipStream_t stream, const float* energy, int64_
                        0, stream, energy, n_micro, blocks, cuts.n_cuts, st);
     hipLaunchKernelGGL(rank_low_kernel, dim3((unsigned)blocks), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, st);
   }
-  if (seg.n_seg > 0)
+  int widest = 0;
+  for (int i = 0; i < seg.n_seg; ++i) widest = seg.off[i + 1] - seg.off[i] > widest ? seg.off[i + 1] - seg.off[i] : widest;
+  if (widest <= kWholeSegment) {
     hipLaunchKernelGGL(rank_segment_kernel, dim3((unsigned)seg.n_seg), dim3(kRankThreads), 0, stream, energy, n_micro, cuts,
                        seg, out, select ? 1 : 0, st, byte_out, byte_out2);
-  if (kept_idx && n_micro > 0)
-    hipLaunchKernelGGL(rank_compact_kernel, dim3((unsigned)seg.n_seg), dim3(kRankThreads), 0, stream, byte_out, seg, out.kept,
-                       kept_idx);
+    if (kept_idx && n_micro > 0)
+      hipLaunchKernelGGL(rank_compact_kernel, dim3((unsigned)seg.n_seg), dim3(kRankThreads), 0, stream, byte_out, seg, out.kept,
+                         kept_idx);
+    return hipGetLastError();
+  }
+  Parts parts;
+  const int64_t most = kMaxParts - CAMERA_MAX_SEGMENTS;  // a part begins at every segment and after `len` keys
+  const int64_t len = ((n_micro + most - 1) / most + kRankThreads - 1) / kRankThreads * kRankThreads;
+  parts.len = (int32_t)(len > kPartKeys ? len : kPartKeys);
+  int n_parts = 0;
+  for (int i = 0; i < seg.n_seg; ++i) {
+    parts.off[i] = (uint16_t)n_parts;
+    const int64_t keys = seg.off[i + 1] - seg.off[i];
+    n_parts += keys > 0 ? (int)((keys + parts.len - 1) / parts.len) : 1;
+  }
+  for (int i = seg.n_seg; i <= CAMERA_MAX_SEGMENTS; ++i) parts.off[i] = (uint16_t)n_parts;
+  hipLaunchKernelGGL(rank_label_kernel, dim3((unsigned)n_parts), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, seg, parts,
+                     out.n_classes, select ? 1 : 0, st, byte_out, byte_out2);
+  hipLaunchKernelGGL(rank_finish_kernel, dim3((unsigned)n_parts), dim3(kRankThreads), 0, stream, energy, n_micro, cuts, seg,
+                     parts, out, st, kept_idx);
   return hipGetLastError();
 }
 

@@ -24,6 +24,18 @@ def check_select(cam, E, seg, ratio, want_rank=True):
         np.testing.assert_array_equal(rank.cpu().numpy().astype(np.int64), o_rank)
 
 
+def check_select_noalloc(cam, E, seg, ratio):
+    n = E.numel()
+    keep = torch.empty(n, dtype=torch.uint8, device="cuda")
+    per = torch.empty(len(seg) - 1, dtype=torch.int32, device="cuda")
+    kept_idx = torch.empty(n, dtype=torch.int32, device="cuda")
+    cam.select_prune_noalloc(E.cuda(), seg, ratio, keep, per, kept_idx)
+    o_keep, o_per, o_idx, _ = orc.select_prune(E.numpy(), seg, ratio)
+    np.testing.assert_array_equal(keep.cpu().numpy(), o_keep)
+    np.testing.assert_array_equal(per.cpu().numpy(), o_per)
+    np.testing.assert_array_equal(kept_idx.cpu().numpy()[:o_idx.size], o_idx)
+
+
 @pytest.mark.parametrize("n", [1, 5, 255, 256, 257, 1000, 4096, 16385, 98304, 184320, 200001])
 def test_select_sizes(cam, n):
     E = inputs.energy_like(n, seed=n)
@@ -171,6 +183,30 @@ def test_keys_that_share_their_upper_bits(cam, n, n_seg):
     for E in (one_prefix, two_groups, signed):
         check_decisions_one_pass(cam, E, seg, [0.1, 0.45, 0.55], [4, 3, 2, 1], [0.25, 0.25, 0.25, 0.25])
         check_select(cam, E, seg, 0.3, want_rank=False)
+
+
+@pytest.mark.parametrize("widths", [
+    [24576],                                # the longest segment that one workgroup walks
+    [24577],                                # and the first that goes in parts of 8192
+    [0, 32768, 0, 0],                       # whole parts, empty segments around them
+    [100, 40000, 0, 33, 24575, 8193],
+    [3] * 511 + [70001],                    # as many segments as there may be
+    [1 << 20],                              # as many keys as the call without allocations takes
+    [(1 << 23) + 5, 1000],                  # parts longer than 8192
+], ids=lambda w: f"{len(w)}x{max(w)}")
+def test_long_segments_in_parts(cam, widths):
+    seg = [0]
+    for w in widths:
+        seg.append(seg[-1] + w)
+    n = seg[-1]
+    cases = [inputs.energy_like(n, seed=n)]
+    if n <= 1 << 20:
+        cases.append(inputs.energy_like(n, seed=n + 1, zero_fraction=0.3, tie_fraction=0.3))
+    for E in cases:
+        check_select(cam, E, seg, 0.4, want_rank=False)
+        check_decisions_one_pass(cam, E, seg, [0.2, 0.25, 0.6], [4, 3, 2, 1], [0.25, 0.25, 0.25, 0.25])
+        if n <= 1 << 20:
+            check_select_noalloc(cam, E, seg, 0.6)
 
 
 def test_ties_before_a_segment_close_to_the_size_limit(cam):
