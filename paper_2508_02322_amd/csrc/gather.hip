@@ -235,7 +235,8 @@ static hipError_t launch_cols_of(hipStream_t stream, const void* W_down, int64_t
   if (err != hipSuccess) return err;
   // 16 rows share a column list; 8 where 16 would leave the chip short of workgroups (one wide shared expert)
   const int rows = n_experts * d_model >= 16 * 2048 ? 16 : 8;
-  const int threads = smem <= 40 * 1024 ? kThreads : 4 * kThreads;  // few workgroups fit a CU: larger ones fill it
+  // few workgroups fit a CU: larger ones fill it; a row of one wave's elements leaves the other waves idle
+  const int threads = d_ff <= kWave ? kWave : (smem <= 40 * 1024 ? kThreads : 4 * kThreads);
   dim3 grid((unsigned)n_experts, (unsigned)((d_model + rows - 1) / rows));
   hipLaunchKernelGGL(kern, grid, dim3(threads), smem, stream, static_cast<const T*>(W_down), stride_down, (int)d_ff,
                      (int)d_model, index, n_index, index_base, off, off_ld, rows,
