@@ -45,7 +45,7 @@ __device__ __forceinline__ uint32_t key_of(float v) {
 // No workgroup picks for the others: `low` and `segment` begin with every workgroup reading the histogram of the pass
 // before for itself -- a wave per cut, 256 coarse counters (8 bits) and then the 256 fine ones under the bin it found,
 // two dependent loads -- so nothing needs a fence, a ticket or a last workgroup, and a kernel boundary is the only
-// synchronisation.  Measured for 98 304 keys and five cuts: 28 us in 3 launches (7 + 12 + 9); with three passes of
+// synchronisation.  Measured for 98 304 keys and five cuts: 26 us in 3 launches (7 + 10 + 9); with three passes of
 // 11 + 11 + 10 bits over all keys and all cuts, each closed by a last workgroup that picked, 82 us in 5 launches, 53 of
 // them in two passes' atomics and picks.  A call on 4096 keys: 18 us against 61.
 // The select state cleans itself: it starts as zeros (the library clears it when it makes it), `top` clears what `low`
@@ -264,7 +264,7 @@ constexpr int kPartKeys = 8192;
 
 // The cuts as the walk sees them.
 struct CutKeys {
-  uint32_t key[kMaxCuts];   // key of the cut element; 0 where nothing, 0xffffffff where everything lies below (with all set)
+  uint32_t key[kMaxCuts];   // key of the cut element; 0, which no key is below, where nothing or everything lies below
   uint32_t ties[kMaxCuts];  // how many keys equal to it lie below the cut
   uint32_t all;             // bit q: everything lies below cut q
 };
@@ -301,8 +301,12 @@ __device__ __forceinline__ WaveRange wave_range(int begin, int end) {
 }
 constexpr int kSteps = 4;  // steps of a walk whose loads are in flight together
 
-// tie_base[q]: keys equal to cut q's at lower indices than the wave's range.  COUNT_BEFORE: those before `begin` are
-// counted here, by all threads, and left in s_before (all of the workgroup's waves call it); otherwise s_before has them.
+// A cut runs through equal keys in one call of ten or so (two adjacent keys of 180 000 are equal with a chance of 2 %): those
+// before a segment are counted with 16-byte loads, four in flight per thread (one mask of 64 segments of 2560 and one of 20480
+// with one such pair: 56 us, with 4-byte loads and every cut compared 89, without a tie 33).
+// tie_base[q]: keys equal to cut q's at lower indices than the wave's range, where the cut has ties.  COUNT_BEFORE: those
+// before `begin` are counted here, by all threads, and left in s_before (all of the workgroup's waves call it); otherwise
+// s_before has them.
 template <bool COUNT_BEFORE>
 __device__ __forceinline__ void count_ties(const float* __restrict__ E, const CutKeys& cut, int begin, WaveRange r,
                                            uint32_t* s_before, uint32_t (*s_tie)[kRankWaves], uint32_t (&tie_base)[kMaxCuts]) {
@@ -310,27 +314,45 @@ __device__ __forceinline__ void count_ties(const float* __restrict__ E, const Cu
   uint32_t before[kMaxCuts], mine[kMaxCuts];
 #pragma unroll
   for (int q = 0; q < kMaxCuts; ++q) before[q] = mine[q] = 0u;
+  // Only cuts that run through equal keys are counted (block-uniform): with more it is the comparisons that take the time.
   if constexpr (COUNT_BEFORE) {
     constexpr int U = kSteps;
-    for (int64_t i0 = threadIdx.x; i0 < begin; i0 += U * kRankThreads) {  // 64 bits: `begin` may be within a step of 2^31
-      uint32_t k[U];
+    const int64_t vecs = begin / 4;  // E is 16-byte aligned
+    for (int64_t i0 = threadIdx.x; i0 < vecs; i0 += U * kRankThreads) {  // 64 bits: an index may be within a step of 2^31
+      uint4 k[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int64_t i = i0 + u * kRankThreads;
-        k[u] = i < begin ? key_of(E[i]) : 0u;
+        const float4 v = reinterpret_cast<const float4*>(E)[min(i0 + u * kRankThreads, vecs - 1)];
+        k[u] = make_uint4(key_of(v.x), key_of(v.y), key_of(v.z), key_of(v.w));
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int q = 0; q < kMaxCuts; ++q) {
+        if (cut.ties[q] == 0) continue;
+        const uint32_t want = cut.key[q];
 #pragma unroll
-        for (int q = 0; q < kMaxCuts; ++q)
-          before[q] += (i0 + u * kRankThreads < begin && k[u] == cut.key[q]) ? 1u : 0u;
+        for (int u = 0; u < U; ++u)
+          if (i0 + u * kRankThreads < vecs)
+            before[q] += (k[u].x == want ? 1u : 0u) + (k[u].y == want ? 1u : 0u) + (k[u].z == want ? 1u : 0u) + (k[u].w == want ? 1u : 0u);
+      }
+    }
+    const int64_t rest = vecs * 4 + threadIdx.x;
+    if (rest < begin) {
+      const uint32_t k = key_of(E[rest]);
+#pragma unroll
+      for (int q = 0; q < kMaxCuts; ++q) before[q] += cut.ties[q] != 0 && k == cut.key[q] ? 1u : 0u;
     }
   }
-  for (int i0 = r.begin; i0 < r.end; i0 += kWave) {
-    const bool valid = i0 + lane < r.end;
-    const uint32_t k = valid ? key_of(E[i0 + lane]) : 0u;
+  for (int i0 = r.begin; i0 < r.end; i0 += kSteps * kWave) {
+    float v[kSteps];
 #pragma unroll
-    for (int q = 0; q < kMaxCuts; ++q) mine[q] += __popcll(__ballot(valid && k == cut.key[q]));
+    for (int u = 0; u < kSteps; ++u) v[u] = E[min(i0 + u * kWave + lane, r.end - 1)];
+#pragma unroll
+    for (int q = 0; q < kMaxCuts; ++q) {
+      if (cut.ties[q] == 0) continue;
+#pragma unroll
+      for (int u = 0; u < kSteps; ++u)
+        mine[q] += __popcll(__ballot(i0 + u * kWave + lane < r.end && key_of(v[u]) == cut.key[q]));
+    }
   }
 #pragma unroll
   for (int q = 0; q < kMaxCuts; ++q) {
@@ -429,8 +451,8 @@ __device__ __forceinline__ OutTables out_tables(const RankCuts& cuts) {
   return t;
 }
 
-// Output bytes of the wave's elements; s_cnt[wave]: its members by class.
-template <bool ANY_TIES>
+// Output bytes of the wave's elements (WRITE); s_cnt[wave]: its members by class.
+template <bool ANY_TIES, bool WRITE>
 __device__ __forceinline__ void label(const float* __restrict__ E, const CutKeys& cut, WaveRange r,
                                       const uint32_t (&tie_base)[kMaxCuts], const OutTables& t, int n_classes,
                                       uint8_t* __restrict__ byte_out, uint8_t* __restrict__ byte_out2,
@@ -439,7 +461,7 @@ __device__ __forceinline__ void label(const float* __restrict__ E, const CutKeys
 #pragma unroll
   for (int m = 0; m < CAMERA_MAX_LEVELS; ++m) cnt[m] = 0u;
   walk<ANY_TIES>(E, cut, r, tie_base, [&](int i, bool valid, int c) {
-    if (valid && byte_out) {
+    if (WRITE && valid) {
       byte_out[i] = (uint8_t)(t.first >> (8 * c));
       if (byte_out2) byte_out2[i] = (uint8_t)(t.second >> (8 * c));
     }
@@ -495,7 +517,7 @@ __device__ __forceinline__ void whole_segment(const float* __restrict__ E, const
 #pragma unroll
   for (int q = 0; q < kMaxCuts; ++q) tie_base[q] = 0u;
   if constexpr (ANY_TIES) count_ties<true>(E, cut, begin, r, s_before, s_tie, tie_base);
-  label<ANY_TIES>(E, cut, r, tie_base, t, out.n_classes, byte_out, byte_out2, s_cnt);
+  label<ANY_TIES, true>(E, cut, r, tie_base, t, out.n_classes, byte_out, byte_out2, s_cnt);
   __syncthreads();
   if (threadIdx.x < kRankWaves * CAMERA_MAX_LEVELS) {  // (wave w, level m): members of level m in wave w's range
     const int w = threadIdx.x / CAMERA_MAX_LEVELS, m = threadIdx.x % CAMERA_MAX_LEVELS;
@@ -596,9 +618,9 @@ __global__ __launch_bounds__(kRankThreads) void rank_label_kernel(const float* _
   if (any_ties) {  // block-uniform
     count_ties<true>(E, cut, p.begin, r, s_before, s_tie, tie_base);
     if (threadIdx.x < kMaxCuts) st->part_ties[blockIdx.x][threadIdx.x] = s_before[threadIdx.x];
-    label<true>(E, cut, r, tie_base, t, n_classes, byte_out, byte_out2, s_cnt);
+    label<true, true>(E, cut, r, tie_base, t, n_classes, byte_out, byte_out2, s_cnt);
   } else {
-    label<false>(E, cut, r, tie_base, t, n_classes, byte_out, byte_out2, s_cnt);
+    label<false, true>(E, cut, r, tie_base, t, n_classes, byte_out, byte_out2, s_cnt);
   }
   __syncthreads();
   if (threadIdx.x < CAMERA_MAX_LEVELS) {
@@ -622,7 +644,7 @@ __device__ __forceinline__ void place_part(const float* __restrict__ E, const Cu
 #pragma unroll
   for (int q = 0; q < kMaxCuts; ++q) tie_base[q] = 0u;
   if constexpr (ANY_TIES) count_ties<false>(E, cut, p.begin, r, s_before, s_tie, tie_base);
-  label<ANY_TIES>(E, cut, r, tie_base, OutTables{0, 0}, out.n_classes, nullptr, nullptr, s_cnt);  // counts only
+  label<ANY_TIES, false>(E, cut, r, tie_base, OutTables{0, 0}, out.n_classes, nullptr, nullptr, s_cnt);
   __syncthreads();
   if (out.perm) {
     uint32_t slot[CAMERA_MAX_LEVELS];
