@@ -5,43 +5,16 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <atomic>
-
 #include "../../include/camera.h"
+#include "host_launch.h"
 
 namespace camera {
 
 // ---- device-side helpers used by several kernels ---------------------------
 constexpr int kWave = 64;
 
-// ---- host-side helpers used by several launchers ----------------------------
-// A grid of at least `blocks` (< 2^31) workgroups of at most 512 threads, numbered by linear_block().  A launch takes fewer
-// than 2^32 threads per dimension, so beyond 2^22 workgroups the numbering goes on in y; the last row may be longer than
-// needed.  2^22 is a multiple of the number of XCDs, so consecutive numbers go round them as in a one-dimensional grid.  The
-// width is a constant, so that nothing has to be loaded before a workgroup knows its tile.
-constexpr int kGridWidthLog2 = 22;
-inline dim3 launch_grid(int64_t blocks) {
-  constexpr int64_t kWidth = int64_t(1) << kGridWidthLog2;
-  return blocks <= kWidth ? dim3((unsigned)blocks) : dim3((unsigned)kWidth, (unsigned)((blocks + kWidth - 1) / kWidth));
-}
+// Number of this workgroup in a grid of launch_grid() (host_launch.h).
 __device__ __forceinline__ int linear_block() { return (int)((blockIdx.y << kGridWidthLog2) + blockIdx.x); }
-
-// A setting that belongs to a device (a kernel's function attribute): set(), which must be repeatable, is called until it
-// has succeeded once for that device.  Any host thread, any device; devices beyond the 64 bits are set on every call.
-class OncePerDevice {
- public:
-  template <class F>
-  hipError_t operator()(int device, F&& set) {
-    const uint64_t bit = device >= 0 && device < 64 ? uint64_t(1) << device : 0;
-    if (done_.load(std::memory_order_acquire) & bit) return hipSuccess;
-    const hipError_t err = set();
-    if (err == hipSuccess) done_.fetch_or(bit, std::memory_order_release);
-    return err;
-  }
-
- private:
-  std::atomic<uint64_t> done_{0};
-};
 
 // Tables that describe how the routed (token, expert) pairs are laid out after
 // bucketing.  All live in the context workspace.

@@ -51,14 +51,15 @@ def test_host_code_is_clean_under_asan_and_ubsan():
     assert "ERROR: AddressSanitizer" not in res.stderr and "runtime error" not in res.stderr
 
 
-def test_device_attribute_memory_is_clean_under_tsan(tmp_path):
-    """Kernel attributes are set per device, from any host thread: the helper that remembers them, host code only."""
+def test_launch_helpers_under_tsan(tmp_path):
+    """Kernel attributes are set per device, from any host thread, and grids stay inside a launch's limits: the helpers of
+    the launchers, host code only."""
     clang = "/opt/rocm/lib/llvm/bin/clang++"
     if not os.path.exists(clang):
         pytest.skip("clang++ not available")
-    exe = str(tmp_path / "once_per_device")
+    exe = str(tmp_path / "host_launch_checks")
     _run([clang, "-O1", "-g", "-std=c++17", "-pthread", "-fsanitize=thread", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
-          os.path.join(ROOT, "tests", "native", "once_per_device.cpp"), "-o", exe])
+          os.path.join(ROOT, "tests", "native", "host_launch_checks.cpp"), "-o", exe])
     res = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
     assert "all passed" in res.stdout and "WARNING: ThreadSanitizer" not in res.stderr
