@@ -135,7 +135,7 @@ int camera_route_topk(camera_ctx* ctx, void* stream,
  *             be NULL).
  *   phi2, phi_inf, omega2, energy   float32 [n_experts * d_ff] out
  * Contractions run on bf16 MFMA with float32 accumulation (CAMERA_BF16) or in
- * float32 FMA (CAMERA_F32); the result does not depend on launch order (no
+ * float32 MFMA (CAMERA_F32); the result does not depend on launch order (no
  * floating-point atomics).  n == 0 gives phi2 = phi_inf = 0 (or leaves them
  * unchanged under CAMERA_ACCUMULATE).
  */

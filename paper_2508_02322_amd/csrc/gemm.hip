@@ -18,7 +18,7 @@
 // ((row >> 1) & 7): the LDS has 64 four-byte banks, so two 128-byte tile rows
 // fill one bank row and 16 consecutive rows reading the same K chunk (one
 // quarter of a fragment read) then hit 16 different 16-byte bank groups.
-// fp32: v_mfma_f32_32x32x2_f32 tiles (float32 layers only).
+// fp32: v_mfma_f32_16x16x4_f32 in tiles of 64 x 32 (float32 layers only).
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
@@ -1019,13 +1019,14 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
 // ---------------------------------------------------------------------------
 // fp32 kernel: 64 tokens x 32 channels x {gate, up} per workgroup of four waves on v_mfma_f32_16x16x4_f32, each wave
 // 32 tokens x 16 channels of either product.  The instruction multiplies and accumulates in float32 and runs at twice
-// the rate of the vector FMA; a float32 contraction is bound by it.  K advances 32 elements per tile; the tile after
+// the rate of the unpacked vector FMA (a large float32 product reaches 153 TFLOP/s on it); a float32 contraction is bound by it.  K advances 32 elements per tile; the tile after
 // the one being multiplied is in flight in registers.  An instruction takes four K elements, one from each quarter of
 // the lanes, and a sum over K does not care which: quarter q holds elements [4q, 4q + 4) of every sixteen, so a
 // fragment is one 16-byte LDS read for four instructions and the tiles stay K-contiguous (rows padded by 16 bytes:
 // at most two-way conflicts).  The tiles are small because float32 layers are: 64 x 64 ones leave five per CU at the
 // shape below and the last of them run alone (195 us).  1499 tokens x top 3 of 12 experts, d_model 772, d_ff 1033:
-// 311 us with vector FMA, 172 us now (83 TFLOP/s); the matrix pipe is busy 64 % of that.
+// 311 us with vector FMA, 172 us now alone and 181 us in a scoring pass (83 and 79 TFLOP/s); the matrix pipe is busy 64 %
+// of that: one tile in LDS, two barriers per 32 of K.
 // ---------------------------------------------------------------------------
 constexpr int F32_BM = 64, F32_BN = 32, F32_KT = 32;
 constexpr int kF32Row = F32_KT + 4;  // floats per padded tile row

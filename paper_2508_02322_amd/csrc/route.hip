@@ -45,8 +45,8 @@ constexpr int kRangeBlocks = 32;
 constexpr int kRangeK = kRangeBlocks * kBlockK;
 
 // Top-k of one token by kSub consecutive lanes: lane `sub` has experts sub, sub + kSub, ... of at most NE, read once into
-// registers (a round that reads them from LDS again waits for each; 8192 tokens, 64 experts, 2048 wide: 24 -> 21 us, 16384
-// tokens, 128 experts: 56 -> 48 us, 1 token, 256 experts: 47 -> 34 us); each round takes the
+// registers (a round that reads them from LDS again waits for each: with the other kernels of that time, graph replays of 8192
+// tokens and 64 experts 24 -> 21 us, of one token and 256 experts 47 -> 34 us); each round takes the
 // largest logit not yet taken (ties: lower index) and the lanes agree on it with three xor-shuffles.  s_row[0 .. n_experts)
 // are the token's logits.  The lane `sub` keeps the weight of round `sub` until the denominator is known.
 template <int NE>
