@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3       # MI355X fp32 vector
+PEAK_F32_TFLOPS = 157.3       # MI355X fp32, vector and matrix
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 
 # Decisions taken per layer after scoring: CAMERA-P ratios and CAMERA-Q (bits, ratios) settings.
@@ -41,7 +41,7 @@ PMC_TRAFFIC = {"qwen2-57b-a14b": (6.000e9, "profiles/grouped_gemm_bf16_qwen2-57b
 PMC_NORM_TRAFFIC = {"qwen2-57b-a14b": (6.651e8, "profiles/down_norm_qwen2-57b-a14b_hbm_traffic.txt")}
 # The same for the two streaming kernels of the compacted layer on a 64-token batch, unpruned
 # (profiles/compact_layer_decode_hbm_traffic.txt): read + written bytes per call.
-PMC_DECODE_TRAFFIC_BYTES = {"deepseek-moe-16b": 777.0e6 + 392.5e6 + 5.6e6, "qwen2-57b-a14b": 2976.9e6 + 1522.0e6 + 19.0e6}
+PMC_DECODE_TRAFFIC_BYTES = {"deepseek-moe-16b": 775.5e6 + 392.4e6 + 5.6e6, "qwen2-57b-a14b": 2693.6e6 + 1389.9e6 + 19.0e6}
 
 
 def parse_args():
