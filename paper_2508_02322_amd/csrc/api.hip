@@ -893,7 +893,7 @@ int launch_rank(camera_ctx* ctx, hipStream_t stream, const float* energy, int64_
   camera::SegOutputs seg_out;
   plan_cuts(r, n_micro, &cuts, &seg_out);
   if (*state_dirty) {  // an earlier call failed between its passes: start from a clean state again
-    CAMERA_HIP(hipMemsetAsync(state, 0, camera::rank_state_bytes(), stream), "hipMemsetAsync(select state)");
+    CAMERA_HIP(camera::launch_rank_clear(stream, state), "select state clear launch");
     *state_dirty = false;
   }
   uint8_t* first = r.n_ratios > 0 ? r.keep_out : r.bit_of;

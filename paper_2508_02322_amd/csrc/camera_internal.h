@@ -121,6 +121,8 @@ struct SegOutputs {
 // Bytes of the persistent select state (zero when made, self-cleaning afterwards) and the int32 words of
 // per-call workspace that a call for the full rank needs for n_micro keys.
 size_t rank_state_bytes();
+// Clears the state, by a kernel: the call may be captured, and graphs hold no memset nodes here.
+hipError_t launch_rank_clear(hipStream_t stream, void* state);
 int64_t rank_workspace_words(int64_t n_micro, int want_rank);
 // byte_out[i] = out_of_below[k] for an element i below k cuts, byte_out2 (optional) likewise from out2_of_below; the
 // per-segment outputs of `out`.  kept_idx (optional, with one pruning ratio): ascending indices of the elements below

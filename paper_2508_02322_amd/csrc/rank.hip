@@ -758,6 +758,11 @@ __global__ __launch_bounds__(kRankThreads) void rank_compact_kernel(const uint8_
   });
 }
 
+__global__ __launch_bounds__(kRankThreads) void rank_clear_kernel(uint4* __restrict__ state, int vecs) {
+  for (int i = blockIdx.x * kRankThreads + threadIdx.x; i < vecs; i += gridDim.x * kRankThreads)
+    state[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // ---------------------------------------------------------------------------
 // full rank: LSD radix sort of (key, index), 8 bits per pass
 // ---------------------------------------------------------------------------
@@ -878,7 +883,13 @@ static_assert(kSortThreads == kDigits, "one thread per digit in the scatter prol
 
 }  // namespace
 
-size_t rank_state_bytes() { return sizeof(RankState); }
+size_t rank_state_bytes() { return (sizeof(RankState) + 15) & ~size_t(15); }
+
+hipError_t launch_rank_clear(hipStream_t stream, void* state) {
+  hipLaunchKernelGGL(rank_clear_kernel, dim3(kMinTopBlocks), dim3(kRankThreads), 0, stream, static_cast<uint4*>(state),
+                     (int)(rank_state_bytes() / 16));
+  return hipGetLastError();
+}
 
 int64_t rank_workspace_words(int64_t n_micro, int want_rank) {
   if (!want_rank) return 0;

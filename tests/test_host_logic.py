@@ -111,3 +111,12 @@ def test_binding_refuses_layouts_the_library_cannot_see():
     assert "energy" in refused(cam.alloc_bits, torch.zeros(32, dtype=torch.float64), [0, 32], [3, 2], [0.5, 0.5])
     assert "Y" in refused(cam.layer_forward, X, idx, w, Wg, Wg, Wd, Y=torch.zeros((32, 16)).t())
     cam.close()
+
+
+def test_the_library_records_no_memset_into_a_captured_stream():
+    """Entry points may be called on a stream under graph capture: what they clear there, they clear with kernels."""
+    csrc = os.path.join(ROOT, "paper_2508_02322_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        if name.endswith((".hip", ".h")):
+            with open(os.path.join(csrc, name)) as f:
+                assert "hipMemsetAsync" not in f.read(), name
