@@ -306,10 +306,12 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   // and an instruction advances K by 32.  With random operand values this instruction holds a shader clock about
   // 10 % higher than the 32x32x16 one at the same flops (the chip is power-limited), which is why it is used.
   // Which way round a 16 x 16 sub-block lies in the registers.  Statistics: a lane owns one channel and four
-  // consecutive token rows (the column reduction starts in the lane).  The epilogues that write per token row take
-  // the transposed form, a lane owning one token row and four consecutive channels: its four values are 16
-  // contiguous bytes of the output row (8 for bf16), one store instead of four.
-  constexpr bool kSwap = EPI != kEpiStats;
+  // consecutive token rows (the column reduction starts in the lane).  Product: the same, and the channels of a lane in
+  // its four sub-blocks are consecutive (tile_channel).  Hidden rows take the transposed form, a lane owning one token row
+  // and four consecutive channels: one routing weight per row block to hold through the K loop instead of four (dealt like
+  // the product's channels, the compacted layer's kernel spills and takes 425 us where this one takes 412: 8192 tokens of
+  // the DeepSeek shape, 40 % pruned).
+  constexpr bool kSwap = EPI == kEpiHidden;
   f32x4 acc_g[NA][TN][2][2], acc_u[NA][TN][2][2];
 #pragma unroll
   for (int i = 0; i < NA; ++i)
@@ -555,11 +557,44 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   if constexpr (C::kAliasAux && EPI == kEpiStats) __syncthreads();  // the column reduction lies over the ring: every wave has read its last fragments
 
   // Epilogue.  Accumulator register r of lane l in sub-block (a, b) of block (i, j) is output row
-  // 32*block + 16a + 4*(l/16) + r, column 32*block + 16b + l % 16: a lane owns two channels per channel block.
+  // 32*block + 16a + 4*(l/16) + r, channel tile_channel(32*j + 16b + l % 16) of the wave's.
   // Transposed (kSwap): row 32*block + 16a + l % 16, columns 32*block + 16b + 4*(l/16) + r.
   const int lane_col = st.frag_row, lane_rows = st.frag_half * 4;  // l % 16, 4 * (l / 16)
-  if constexpr (EPI != kEpiStats) {
-    const int pad_end = (EPI == kEpiHidden && ep.pad_hidden) ? (d_ff + ep.pad_hidden - 1) / ep.pad_hidden * ep.pad_hidden : d_ff;
+  if constexpr (EPI == kEpiProduct) {
+    static_assert(TN == 2, "a lane's channels of the four sub-blocks are consecutive");
+    const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four channels
+    if (col0 < d_ff) {
+      const bool whole = col0 + 3 < d_ff;  // all four inside: one vector store
+#pragma unroll
+      for (int i = 0; i < ACT; ++i)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = (WM * i + st.wave_m) * 32 + a * 16 + lane_rows + r;
+            if (row >= st.m_len) continue;
+            f32x4 g, u;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              g[s] = acc_g[i][s / 2][a][s % 2][r];
+              u[s] = acc_u[i][s / 2][a][s % 2][r];
+            }
+            float* dst = ep.product + (int64_t)(st.row_first + row) * ep.ld_product + col0;
+            if (whole) {  // output rows and both column halves are multiples of 4 floats: 16-byte aligned
+              *reinterpret_cast<f32x4*>(dst) = g;
+              *reinterpret_cast<f32x4*>(dst + ep.col_gap) = u;
+            } else {
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+                if (col0 + s < d_ff) {
+                  dst[s] = g[s];
+                  dst[s + ep.col_gap] = u[s];
+                }
+            }
+          }
+    }
+  } else if constexpr (EPI == kEpiHidden) {
+    const int pad_end = ep.pad_hidden ? (d_ff + ep.pad_hidden - 1) / ep.pad_hidden * ep.pad_hidden : d_ff;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
 #pragma unroll
@@ -568,12 +603,10 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
         if (col0 >= pad_end) continue;
         const bool whole = col0 + 3 < d_ff;  // all four inside: one vector store
         float kept[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-        if constexpr (EPI == kEpiHidden) {
-          if (ep.keep != nullptr) {
+        if (ep.keep != nullptr) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              kept[r] = (col0 + r < d_ff && ep.keep[(int64_t)st.expert * d_ff + col0 + r]) ? 1.0f : 0.0f;
-          }
+          for (int r = 0; r < 4; ++r)
+            kept[r] = (col0 + r < d_ff && ep.keep[(int64_t)st.expert * d_ff + col0 + r]) ? 1.0f : 0.0f;
         }
 #pragma unroll
         for (int i = 0; i < ACT; ++i)
@@ -581,37 +614,21 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
           for (int a = 0; a < 2; ++a) {
             const int row = (WM * i + st.wave_m) * 32 + a * 16 + lane_col;
             if (row >= st.m_len) continue;
-            const int64_t out_row = st.row_first + row;
-            if constexpr (EPI == kEpiHidden) {
-              __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(ep.hidden) + out_row * ep.ld_hidden + col0;
-              const float a_tok = a_of(i, a, 0, row);
-              __hip_bfloat16 lam[4];
+            __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(ep.hidden) + (int64_t)(st.row_first + row) * ep.ld_hidden + col0;
+            const float a_tok = a_of(i, a, 0, row);
+            __hip_bfloat16 lam[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              lam[r] = __float2bfloat16(a_tok * silu_f32(acc_g[i][j][a][b][r]) * acc_u[i][j][a][b][r] * kept[r]);
+            if (whole) {  // rows of the hidden buffer are multiples of 8 elements long: 8-byte aligned
+              uint2 v;
+              v.x = (uint32_t)__builtin_bit_cast(uint16_t, lam[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[1]) << 16);
+              v.y = (uint32_t)__builtin_bit_cast(uint16_t, lam[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[3]) << 16);
+              *reinterpret_cast<uint2*>(dst) = v;
+            } else {  // the last channels of the expert, then the K padding of the contraction that reads these rows
 #pragma unroll
               for (int r = 0; r < 4; ++r)
-                lam[r] = __float2bfloat16(a_tok * silu_f32(acc_g[i][j][a][b][r]) * acc_u[i][j][a][b][r] * kept[r]);
-              if (whole) {  // rows of the hidden buffer are multiples of 8 elements long: 8-byte aligned
-                uint2 v;
-                v.x = (uint32_t)__builtin_bit_cast(uint16_t, lam[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[1]) << 16);
-                v.y = (uint32_t)__builtin_bit_cast(uint16_t, lam[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[3]) << 16);
-                *reinterpret_cast<uint2*>(dst) = v;
-              } else {  // the last channels of the expert, then the K padding of the contraction that reads these rows
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  if (col0 + r < pad_end) dst[r] = col0 + r < d_ff ? lam[r] : __float2bfloat16(0.0f);
-              }
-            } else {
-              float* dst = ep.product + out_row * ep.ld_product + col0;
-              if (whole) {  // output rows and both column halves are multiples of 4 floats: 16-byte aligned
-                *reinterpret_cast<f32x4*>(dst) = acc_g[i][j][a][b];
-                *reinterpret_cast<f32x4*>(dst + ep.col_gap) = acc_u[i][j][a][b];
-              } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  if (col0 + r < d_ff) {
-                    dst[r] = acc_g[i][j][a][b][r];
-                    dst[r + ep.col_gap] = acc_u[i][j][a][b][r];
-                  }
-              }
+                if (col0 + r < pad_end) dst[r] = col0 + r < d_ff ? lam[r] : __float2bfloat16(0.0f);
             }
           }
       }
@@ -659,6 +676,20 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
       }
     }
   }  // statistics epilogue
+}
+
+// The channel (of the tile's BN) whose weight row lies in row `row` of the LDS tile.  A lane's accumulators belong to tile
+// rows 16 apart.  The product epilogue deals the channels of a wave (32 TN) to its 16-row sub-blocks one at a time, so that a
+// lane owns 2 TN = 4 consecutive channels, one per sub-block: the 16 lanes that a store instruction serves at a time then
+// write 256 bytes of one token row side by side.  (With a lane per token row, transposed, they wrote 16 bytes of 16 rows
+// each, and memory took 1.31 bytes for every byte of the product: 8192 tokens of the DeepSeek shape, 40 % pruned, 537 MB of
+// product rows, K of 14 tiles: 361 -> 288 us; without any store it is 208.)
+template <class C, int EPI>
+__device__ __forceinline__ int tile_channel(int row) {
+  if constexpr (EPI != kEpiProduct) return row;
+  constexpr int kSub = 2 * C::TN, kOfWave = 16 * kSub;
+  const int in = row % kOfWave;
+  return row - in + in % 16 * kSub + in / 16;
 }
 
 // What a workgroup has to do: tile (slot, n0 / BN) of expert e.
@@ -729,7 +760,7 @@ __device__ __forceinline__ void run_tile(const TileWork& w, const __hip_bfloat16
   for (int j = 0; j < C::kBDma; ++j) {
     const int row = b_row0 + j * C::kDmaRows + lane / C::kChunks;
     const int ck = (lane % C::kChunks) ^ swizzle_key<C>(row);
-    const int c = min(n0 + row, d_ff - 1);  // channels past d_ff read the last channel again; never written
+    const int c = min(n0 + tile_channel<C, EPI>(row), d_ff - 1);  // channels past d_ff read the last channel again; never written
     const int64_t off = (int64_t)e * stride_gu + (int64_t)c * ldw + ck * 8;
     st.b_k[j] = ck * 8;
     st.g_src[j] = Wg + off - (j % 4) * 512;

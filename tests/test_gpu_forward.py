@@ -108,6 +108,19 @@ def test_layer_output_matches_oracle_with_and_without_a_mask(cam, case):
     print(f"{case}: rel err full {err_full:.2e}, masked {err_kept:.2e}")
 
 
+@pytest.mark.parametrize("n_tokens,d_model", [(1, 8), (257, 120), (33, 128), (300, 136), (255, 248), (256, 264), (513, 520)])
+def test_output_columns_at_the_edges_of_a_lane_a_wave_and_a_tile(cam, n_tokens, d_model):
+    """The second contraction's columns: half of d_model below, at and past the 4 of a lane, the 64 of a wave, the 128 of a
+    tile, with token counts around its 256 rows.  One expert, so that every row of a tile is in use."""
+    cfg = small(n_tokens=n_tokens, d_model=d_model, d_ff=72, n_experts=1, top_k=1, outlier_channels=0)
+    layer = inputs.make_layer(cfg, 0, device="cpu")
+    dev = H.to_dev(layer)
+    Y = cam.layer_forward(dev["X"], None, None, dev["W_gate"], dev["W_up"], dev["W_down"])
+    gate, up, down = expert_lists(layer, "W")
+    X64, A = H.f64(layer["X"]), np.ones((n_tokens, 1))
+    check_output(Y, orc.layer_forward(X64, A, gate, up, down, round_hidden=orc.round_to_bf16), largest_term(X64, A, gate, up, down))
+
+
 def test_nothing_kept_gives_zero_and_accumulate_adds_the_shared_experts(cam):
     cfg = small(n_shared=1, d_ff_shared=256)
     layer = inputs.make_layer(cfg, 0, device="cpu")
