@@ -572,6 +572,7 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   const camera::BucketTables t = plan.bind(ws, ctx->zeros);
   void* hidden = ws + o_hidden;
   float* product = reinterpret_cast<float*>(ws + o_product);
+  const bool streams = camera::product_streams(n_pairs, d_model);
 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   {
@@ -602,6 +603,7 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
     ep.product = product;
     ep.ld_product = d_model;
     ep.col_gap = (int)half;
+    ep.stream_product = streams;
     const char* wd = static_cast<const char*>(W_down);
     CAMERA_HIP(camera::launch_grouped_gemm(stream, dtype, hidden, d_ff, d_ff, half, n_experts, wd,
                                            wd + es * half * d_ff, stride_down, max_tiles, t, ep),
@@ -610,7 +612,7 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   {
     Bracket b(ctx, stream, CAMERA_K_COMBINE);
     CAMERA_HIP(camera::launch_combine(stream, product, t.slot_of, n, top_k, n_experts, d_model,
-                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, Y),
+                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, Y),
                "combine launch");
   }
   return CAMERA_OK;
@@ -742,6 +744,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     if (!dense && !mfma && !small) CAMERA_HIP(camera::launch_compact_items(stream, tiles_of, total, t, work), "work items launch");
   }
   if (mfma) {
+    const bool streams = camera::product_streams(n_pairs, d_model);
     {
       Bracket b(ctx, stream, CAMERA_K_GEMM);
       CAMERA_HIP(camera::launch_compact_hidden_gemm(stream, X, ldx, d_model, W_gate_c, W_up_c, tab, (int)widest, max_tiles,
@@ -751,12 +754,12 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     {
       Bracket b(ctx, stream, CAMERA_K_DOWN_GEMM);
       CAMERA_HIP(camera::launch_compact_down_gemm(stream, hidden, d_model, W_down_c, tab_down, max_tiles, t, work,
-                                                  product),
+                                                  product, streams),
                  "compact down gemm launch");
     }
     Bracket b(ctx, stream, CAMERA_K_COMBINE);
     CAMERA_HIP(camera::launch_combine(stream, product, t.slot_of, n, terms, n_experts, d_model,
-                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, Y),
+                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, Y),
                "combine launch");
     return CAMERA_OK;
   }

@@ -71,7 +71,13 @@ struct GemmEpilogue {
   float* product = nullptr;
   int64_t ld_product = 0;
   int col_gap = 0;
+  bool stream_product = false;
 };
+// Whether the product rows of `pairs` slots go past the caches on their way out (second contraction) and back in
+// (combine): from 256 MiB on, which is what the memory-side cache holds, they only displace each other in it.  Second
+// contraction + combine, us, through the caches / past them: 537 MB 291 + 128 / 280 + 107 (8192 tokens of the DeepSeek
+// shape, 40 % pruned), below the line 197 MB 338 + 106 / 335 + 114, 79 MB 74 + 30 / 70 + 35.
+inline bool product_streams(int64_t pairs, int64_t d_model) { return pairs * d_model * 4 >= (int64_t(256) << 20); }
 hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int64_t ldx, int64_t d_model,
                                int64_t d_ff, int n_experts, const void* W_gate, const void* W_up,
                                int64_t stride_gu, int max_tiles, const BucketTables& t, const GemmEpilogue& ep);
@@ -137,8 +143,9 @@ hipError_t launch_full_rank(hipStream_t stream, const float* energy, int64_t n_m
 // ---- forward.hip -----------------------------------------------------------
 // Y[token] (+)= sum of the product rows of the token's slots (routed: slot_of[token*top_k + k], k ascending;
 // slot_of == nullptr: rows e*n + token for e ascending).  product is [pairs][d_model] float32, Y [n][d_model].
+// stream_product: the rows are read once, past the caches (see product_streams).
 hipError_t launch_combine(hipStream_t stream, const float* product, const int32_t* slot_of, int64_t n, int top_k,
-                          int n_experts, int64_t d_model, int accumulate, float* Y);
+                          int n_experts, int64_t d_model, int accumulate, bool stream_product, float* Y);
 // per_token [n][4] = ||y - y_hat||^2, ||y||^2, ||y_hat||^2, <y, y_hat>
 hipError_t launch_output_error(hipStream_t stream, const float* Y, const float* Y_hat, int64_t n, int64_t d_model,
                                int64_t ldy, int64_t ldh, float* per_token);
@@ -218,7 +225,7 @@ hipError_t launch_compact_hidden_gemm(hipStream_t stream, const void* X, int64_t
                                       int k_round);
 hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int64_t d_model, const void* W_down,
                                     const CompactDown& tab, int max_tiles, const BucketTables& t, int32_t* scratch,
-                                    float* product);
+                                    float* product, bool stream_product);
 
 // Gather of kept micro-experts (gather.hip).  off: [n_experts + 1] exclusive prefix of the per-expert
 // entry counts (count == nullptr: d_ff each), off_ld: the same of the counts rounded up to a multiple of

@@ -21,18 +21,21 @@ constexpr int kTokensPerBlock = kThreads / kWave;  // one wave per token
 // loads, and the rows of eight terms are in flight together: waiting for each row in turn is what a wave per token
 // spent its time on.  8192 tokens, 8 terms, 2048 wide: 143 -> 127 us; 2048 tokens, 2 terms, 4096 wide: 44 -> 19 us.
 constexpr int kTerms = 8;
-__global__ __launch_bounds__(kThreads) void combine_kernel(const float4* __restrict__ product,
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+template <bool STREAM>
+__global__ __launch_bounds__(kThreads) void combine_kernel(const f32x4* __restrict__ product,
                                                            const int32_t* __restrict__ slot_of, int64_t n, int top_k,
                                                            int n_experts, int vecs, int accumulate,
-                                                           float4* __restrict__ Y) {
+                                                           f32x4* __restrict__ Y) {
   const int64_t tok = blockIdx.x;
   const int v = (int)(blockIdx.y * blockDim.x + threadIdx.x);
   if (v >= vecs) return;
   const int terms = slot_of ? top_k : n_experts;
-  float4 s = accumulate ? Y[tok * vecs + v] : make_float4(0.f, 0.f, 0.f, 0.f);
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  if (accumulate) s = Y[tok * vecs + v];
   for (int k0 = 0; k0 < terms; k0 += kTerms) {
     int64_t row[kTerms];
-    float4 p[kTerms];
+    f32x4 p[kTerms];
 #pragma unroll
     for (int u = 0; u < kTerms; ++u) {
       const int k = k0 + u;
@@ -40,14 +43,11 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const float4* __restr
     }
 #pragma unroll
     for (int u = 0; u < kTerms; ++u)
-      if (row[u] >= 0) p[u] = product[row[u] * vecs + v];  // below 0: past the last term, or an expert id outside the group
+      if (row[u] >= 0)  // below 0: past the last term, or an expert id outside the group
+        p[u] = STREAM ? __builtin_nontemporal_load(product + row[u] * vecs + v) : product[row[u] * vecs + v];
 #pragma unroll
     for (int u = 0; u < kTerms; ++u) {
-      if (row[u] < 0) continue;
-      s.x += p[u].x;
-      s.y += p[u].y;
-      s.z += p[u].z;
-      s.w += p[u].w;
+      if (row[u] >= 0) s += p[u];
     }
   }
   Y[tok * vecs + v] = s;
@@ -88,13 +88,13 @@ __global__ __launch_bounds__(kThreads) void output_error_kernel(const float* __r
 }  // namespace
 
 hipError_t launch_combine(hipStream_t stream, const float* product, const int32_t* slot_of, int64_t n, int top_k,
-                          int n_experts, int64_t d_model, int accumulate, float* Y) {
+                          int n_experts, int64_t d_model, int accumulate, bool stream_product, float* Y) {
   if (n <= 0) return hipSuccess;
   const int vecs = (int)(d_model / 4);
   const int threads = vecs < kThreads ? (vecs + kWave - 1) / kWave * kWave : kThreads;
-  hipLaunchKernelGGL(combine_kernel, dim3((unsigned)n, (unsigned)((vecs + threads - 1) / threads)), dim3(threads), 0,
-                     stream, reinterpret_cast<const float4*>(product), slot_of, n, top_k, n_experts, vecs, accumulate,
-                     reinterpret_cast<float4*>(Y));
+  hipLaunchKernelGGL(stream_product ? combine_kernel<true> : combine_kernel<false>, dim3((unsigned)n, (unsigned)((vecs + threads - 1) / threads)), dim3(threads), 0,
+                     stream, reinterpret_cast<const f32x4*>(product), slot_of, n, top_k, n_experts, vecs, accumulate,
+                     reinterpret_cast<f32x4*>(Y));
   return hipGetLastError();
 }
 

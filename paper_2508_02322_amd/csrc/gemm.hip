@@ -105,6 +105,7 @@ struct EpiArgs {
   int col_gap;
   int64_t ld_hidden;       // row stride of hidden (d_ff when every expert has the same width)
   int pad_hidden;          // != 0: columns from d_ff up to the next multiple of it are written as zeros (8 or 64)
+  int stream_product;      // != 0: product rows go past the caches (see product_streams)
 };
 
 // One wave instruction of the direct global -> LDS path: lane l's 16 bytes at p (+ IMM) go to LDS bytes
@@ -563,7 +564,7 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   if constexpr (EPI == kEpiProduct) {
     static_assert(TN == 2, "a lane's channels of the four sub-blocks are consecutive");
     const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four channels
-    if (col0 < d_ff) {
+    auto write = [&](auto stream) {
       const bool whole = col0 + 3 < d_ff;  // all four inside: one vector store
 #pragma unroll
       for (int i = 0; i < ACT; ++i)
@@ -581,8 +582,13 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
             }
             float* dst = ep.product + (int64_t)(st.row_first + row) * ep.ld_product + col0;
             if (whole) {  // output rows and both column halves are multiples of 4 floats: 16-byte aligned
-              *reinterpret_cast<f32x4*>(dst) = g;
-              *reinterpret_cast<f32x4*>(dst + ep.col_gap) = u;
+              if constexpr (decltype(stream)::value) {
+                __builtin_nontemporal_store(g, reinterpret_cast<f32x4*>(dst));
+                __builtin_nontemporal_store(u, reinterpret_cast<f32x4*>(dst + ep.col_gap));
+              } else {
+                *reinterpret_cast<f32x4*>(dst) = g;
+                *reinterpret_cast<f32x4*>(dst + ep.col_gap) = u;
+              }
             } else {
 #pragma unroll
               for (int s = 0; s < 4; ++s)
@@ -592,6 +598,10 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
                 }
             }
           }
+    };
+    if (col0 < d_ff) {
+      if (ep.stream_product) write(std::true_type{});
+      else write(std::false_type{});
     }
   } else if constexpr (EPI == kEpiHidden) {
     const int pad_end = ep.pad_hidden ? (d_ff + ep.pad_hidden - 1) / ep.pad_hidden * ep.pad_hidden : d_ff;
@@ -1254,7 +1264,7 @@ hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int
                                int64_t d_ff, int n_experts, const void* W_gate, const void* W_up,
                                int64_t stride_gu, int max_tiles, const BucketTables& t, const GemmEpilogue& e) {
   if (max_tiles <= 0) return hipSuccess;
-  EpiArgs ep{e.part_phi2, e.part_max, e.hidden, e.keep, e.product, e.ld_product, e.col_gap, d_ff, 0};
+  EpiArgs ep{e.part_phi2, e.part_max, e.hidden, e.keep, e.product, e.ld_product, e.col_gap, d_ff, 0, e.stream_product ? 1 : 0};
   if (dtype == CAMERA_BF16) {
     switch (e.mode) {
       case GemmEpilogue::kStats:
@@ -1319,16 +1329,16 @@ hipError_t launch_compact_hidden_gemm(hipStream_t stream, const void* X, int64_t
                                       const void* W_gate, const void* W_up, const CompactRows& tab, int widest,
                                       int max_tiles, const BucketTables& t, int32_t* scratch, void* hidden,
                                       int k_round) {
-  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, 0, 0, 0, k_round};
+  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, 0, 0, 0, k_round, 0};
   return launch_compact<kEpiHidden>(stream, X, ldx, d_model, W_gate, W_up, tab, k_round, d_model % Bf16Cfg::KT != 0,
                                     (widest + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep);
 }
 
 hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int64_t d_model, const void* W_down,
                                     const CompactDown& tab, int max_tiles, const BucketTables& t, int32_t* scratch,
-                                    float* product) {
+                                    float* product, bool stream_product) {
   const int64_t half = d_model / 2;
-  EpiArgs ep{nullptr, nullptr, nullptr, nullptr, product, d_model, (int)half, 0, 0};
+  EpiArgs ep{nullptr, nullptr, nullptr, nullptr, product, d_model, (int)half, 0, 0, stream_product ? 1 : 0};
   return launch_compact<kEpiProduct>(stream, hidden, 0, d_model, W_down, W_down, tab, tab.k_round,
                                      tab.k_round % Bf16Cfg::KT != 0, (half + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t,
                                      scratch, ep);

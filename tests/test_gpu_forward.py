@@ -121,6 +121,27 @@ def test_output_columns_at_the_edges_of_a_lane_a_wave_and_a_tile(cam, n_tokens, 
     check_output(Y, orc.layer_forward(X64, A, gate, up, down, round_hidden=orc.round_to_bf16), largest_term(X64, A, gate, up, down))
 
 
+@pytest.mark.parametrize("compact", [False, True])
+def test_product_rows_past_the_caches(cam, compact):
+    """From 256 MiB of product rows on they are stored and read past the caches.  A token's output does not depend on the
+    batch, so the call on all tokens equals the calls on their halves (below the line) bit for bit."""
+    cfg = small(n_tokens=9001, d_model=1032 if not compact else 1040, d_ff=64, n_experts=9, top_k=8, outlier_channels=0)
+    assert cfg.n_tokens * cfg.top_k * cfg.d_model * 4 >= 256 << 20 > (cfg.n_tokens // 2 + 1) * cfg.top_k * cfg.d_model * 4
+    dev = inputs.make_layer(cfg, 0, device="cuda")
+    X = dev["X"]
+    idx, w = cam.route_topk(X, dev["W_r"], dev["bias"], cfg.top_k)
+
+    def forward(lo, hi):
+        args = X[lo:hi], idx[lo:hi], w[lo:hi]
+        if not compact:
+            return cam.layer_forward(*args, dev["W_gate"], dev["W_up"], dev["W_down"])
+        return cam.layer_forward_compact(*args, [cfg.d_ff] * cfg.n_experts, dev["W_gate"].flatten(0, 1), dev["W_up"].flatten(0, 1),
+                                         dev["W_down"].flatten(), down_row_align=64)
+    whole, half = forward(0, cfg.n_tokens), cfg.n_tokens // 2
+    assert torch.isfinite(whole).all() and whole.abs().max() > 0
+    assert torch.equal(whole, torch.cat([forward(0, half), forward(half, cfg.n_tokens)]))
+
+
 def test_nothing_kept_gives_zero_and_accumulate_adds_the_shared_experts(cam):
     cfg = small(n_shared=1, d_ff_shared=256)
     layer = inputs.make_layer(cfg, 0, device="cpu")
