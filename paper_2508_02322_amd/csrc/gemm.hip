@@ -306,13 +306,8 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   // v_mfma_f32_16x16x32_bf16: a 32 x 32 block of the wave's tile is four 16 x 16 sub-blocks (a: rows, b: columns)
   // and an instruction advances K by 32.  With random operand values this instruction holds a shader clock about
   // 10 % higher than the 32x32x16 one at the same flops (the chip is power-limited), which is why it is used.
-  // Which way round a 16 x 16 sub-block lies in the registers.  Statistics: a lane owns one channel and four
-  // consecutive token rows (the column reduction starts in the lane).  Product: the same, and the channels of a lane in
-  // its four sub-blocks are consecutive (tile_channel).  Hidden rows take the transposed form, a lane owning one token row
-  // and four consecutive channels: one routing weight per row block to hold through the K loop instead of four (dealt like
-  // the product's channels, the compacted layer's kernel spills and takes 425 us where this one takes 412: 8192 tokens of
-  // the DeepSeek shape, 40 % pruned).
-  constexpr bool kSwap = EPI == kEpiHidden;
+  // In the registers a lane owns one channel and four consecutive token rows of a 16 x 16 sub-block (tile_channel says
+  // which channel).
   f32x4 acc_g[NA][TN][2][2], acc_u[NA][TN][2][2];
 #pragma unroll
   for (int i = 0; i < NA; ++i)
@@ -372,14 +367,8 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   auto mfma_one = [&](const FragA& fa, const FragB& fb, auto b_index, auto m_index) {
     constexpr int b = decltype(b_index)::value, m = decltype(m_index)::value;
     constexpr int gu = m % 2, j = (m / 2) % TN, a = (m / (2 * TN)) % 2, i = m / (4 * TN);
-    // kSwap: the weight fragment takes the first operand's place, which transposes the accumulator tile
-    if constexpr (gu == 0) {
-      if constexpr (kSwap) mfma_pinned(acc_g[i][j][a][b], fb.g[j], fa.v[i][a]);
-      else mfma_pinned(acc_g[i][j][a][b], fa.v[i][a], fb.g[j]);
-    } else {
-      if constexpr (kSwap) mfma_pinned(acc_u[i][j][a][b], fb.u[j], fa.v[i][a]);
-      else mfma_pinned(acc_u[i][j][a][b], fa.v[i][a], fb.u[j]);
-    }
+    if constexpr (gu == 0) mfma_pinned(acc_g[i][j][a][b], fa.v[i][a], fb.g[j]);
+    else mfma_pinned(acc_u[i][j][a][b], fa.v[i][a], fb.u[j]);
   };
 
   // Ring schedule.  Token tiles and weight tiles each cycle through their own ring of LDS stages; the barrier of
@@ -413,18 +402,27 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   // Routing weight of the lane's output rows.  They stay in registers when the per-tile arrays lie over the ring:
   // the first tile load may overwrite them, so every wave must have taken its copy (and finished with the token
   // ids) before any load is issued.
-  float a_rows[NA][2][4];
+  // (The hidden rows' epilogue is long enough for two more barriers: one weight per thread goes through the loop and back
+  // to LDS behind it, which leaves the compacted layer's kernel without spills.)
+  float a_rows[NA][2][4], a_mine = 0.0f;
   if constexpr (C::kAliasAux) {
+    if constexpr (EPI == kEpiHidden) {
+      a_mine = st.s_a[threadIdx.x];
+    } else {
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
+      for (int i = 0; i < NA; ++i)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          a_rows[i][a][r] = st.s_a[(WM * i + st.wave_m) * 32 + a * 16 + (kSwap ? st.frag_row : st.frag_half * 4 + r)];
+          for (int r = 0; r < 4; ++r)
+            a_rows[i][a][r] = st.s_a[(WM * i + st.wave_m) * 32 + a * 16 + st.frag_half * 4 + r];
+    }
     __syncthreads();
   }
-  auto a_of = [&](int i, int a, int r, int row) { return C::kAliasAux ? a_rows[i][a][r] : st.s_a[row]; };
+  static_assert(!C::kAliasAux || C::kThreads == C::BM, "one routing weight per thread");
+  auto a_of = [&](int i, int a, int r, int row) {
+    return C::kAliasAux && EPI != kEpiHidden ? a_rows[i][a][r] : st.s_a[row];
+  };
 
   // Prologue: whole tiles 0 .. SB - 2 (token rows: 0 .. SA - 2), then what the phase behind a barrier would issue
   // of the first fill (token tile SA - 1, weight tile SB - 1).
@@ -555,11 +553,14 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be writing LDS at exit
   mfma_drain();                                      // the last MFMAs have written their accumulators
-  if constexpr (C::kAliasAux && EPI == kEpiStats) __syncthreads();  // the column reduction lies over the ring: every wave has read its last fragments
+  if constexpr (C::kAliasAux && EPI != kEpiProduct) __syncthreads();  // the per-tile arrays lie over the ring: every wave has read its last fragments
+  if constexpr (C::kAliasAux && EPI == kEpiHidden) {
+    const_cast<float*>(st.s_a)[threadIdx.x] = a_mine;
+    __syncthreads();
+  }
 
   // Epilogue.  Accumulator register r of lane l in sub-block (a, b) of block (i, j) is output row
   // 32*block + 16a + 4*(l/16) + r, channel tile_channel(32*j + 16b + l % 16) of the wave's.
-  // Transposed (kSwap): row 32*block + 16a + l % 16, columns 32*block + 16b + 4*(l/16) + r.
   const int lane_col = st.frag_row, lane_rows = st.frag_half * 4;  // l % 16, 4 * (l / 16)
   if constexpr (EPI == kEpiProduct) {
     static_assert(TN == 2, "a lane's channels of the four sub-blocks are consecutive");
@@ -605,31 +606,29 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
     }
   } else if constexpr (EPI == kEpiHidden) {
     const int pad_end = ep.pad_hidden ? (d_ff + ep.pad_hidden - 1) / ep.pad_hidden * ep.pad_hidden : d_ff;
+    const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four channels
+    if (col0 < pad_end) {
+      const bool whole = col0 + 3 < d_ff;  // all four inside: one vector store
+      float kept[4] = {1.0f, 1.0f, 1.0f, 1.0f};
+      if (ep.keep != nullptr) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
+        for (int s = 0; s < 4; ++s)
+          kept[s] = (col0 + s < d_ff && ep.keep[(int64_t)st.expert * d_ff + col0 + s]) ? 1.0f : 0.0f;
+      }
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int col0 = n0 + st.wave_n * TN * 32 + j * 32 + b * 16 + lane_rows;  // this lane's four channels
-        if (col0 >= pad_end) continue;
-        const bool whole = col0 + 3 < d_ff;  // all four inside: one vector store
-        float kept[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-        if (ep.keep != nullptr) {
+      for (int i = 0; i < ACT; ++i)
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            kept[r] = (col0 + r < d_ff && ep.keep[(int64_t)st.expert * d_ff + col0 + r]) ? 1.0f : 0.0f;
-        }
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int i = 0; i < ACT; ++i)
-#pragma unroll
-          for (int a = 0; a < 2; ++a) {
-            const int row = (WM * i + st.wave_m) * 32 + a * 16 + lane_col;
+          for (int r = 0; r < 4; ++r) {
+            const int row = (WM * i + st.wave_m) * 32 + a * 16 + lane_rows + r;
             if (row >= st.m_len) continue;
             __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(ep.hidden) + (int64_t)(st.row_first + row) * ep.ld_hidden + col0;
-            const float a_tok = a_of(i, a, 0, row);
+            const float a_tok = a_of(i, a, r, row);
             __hip_bfloat16 lam[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              lam[r] = __float2bfloat16(a_tok * silu_f32(acc_g[i][j][a][b][r]) * acc_u[i][j][a][b][r] * kept[r]);
+            for (int s = 0; s < 4; ++s)
+              lam[s] = __float2bfloat16(a_tok * silu_f32(acc_g[i][s / 2][a][s % 2][r]) * acc_u[i][s / 2][a][s % 2][r] * kept[s]);
             if (whole) {  // rows of the hidden buffer are multiples of 8 elements long: 8-byte aligned
               uint2 v;
               v.x = (uint32_t)__builtin_bit_cast(uint16_t, lam[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[1]) << 16);
@@ -637,11 +636,10 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
               *reinterpret_cast<uint2*>(dst) = v;
             } else {  // the last channels of the expert, then the K padding of the contraction that reads these rows
 #pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if (col0 + r < pad_end) dst[r] = col0 + r < d_ff ? lam[r] : __float2bfloat16(0.0f);
+              for (int s = 0; s < 4; ++s)
+                if (col0 + s < pad_end) dst[s] = col0 + s < d_ff ? lam[s] : __float2bfloat16(0.0f);
             }
           }
-      }
     }
   } else {
 #pragma unroll
@@ -689,14 +687,15 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
 }
 
 // The channel (of the tile's BN) whose weight row lies in row `row` of the LDS tile.  A lane's accumulators belong to tile
-// rows 16 apart.  The product epilogue deals the channels of a wave (32 TN) to its 16-row sub-blocks one at a time, so that a
-// lane owns 2 TN = 4 consecutive channels, one per sub-block: the 16 lanes that a store instruction serves at a time then
-// write 256 bytes of one token row side by side.  (With a lane per token row, transposed, they wrote 16 bytes of 16 rows
-// each, and memory took 1.31 bytes for every byte of the product: 8192 tokens of the DeepSeek shape, 40 % pruned, 537 MB of
-// product rows, K of 14 tiles: 361 -> 288 us; without any store it is 208.)
+// rows 16 apart.  The epilogues that write per token row deal the channels of a wave (32 TN) to its 16-row sub-blocks one at a
+// time, so that a lane owns 2 TN = 4 consecutive channels, one per sub-block: the 16 lanes that a store instruction serves at
+// a time then write one token row side by side, 256 bytes of float32 or 128 of bf16.  With a lane per token row, transposed,
+// they wrote 16 (8) bytes of 16 rows each, and memory took 1.31 bytes for every byte of the product.  Second contraction,
+// 8192 tokens of the DeepSeek shape, 40 % pruned, 537 MB of product rows, K of 14 tiles: 361 -> 288 us (208 without any
+// store); first contraction of the Mixtral shape, 2048 tokens: 825 -> 815 us.
 template <class C, int EPI>
 __device__ __forceinline__ int tile_channel(int row) {
-  if constexpr (EPI != kEpiProduct) return row;
+  if constexpr (EPI == kEpiStats) return row;
   constexpr int kSub = 2 * C::TN, kOfWave = 16 * kSub;
   const int in = row % kOfWave;
   return row - in + in % 16 * kSub + in / 16;
@@ -990,21 +989,29 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   const CompactScratch sc = compact_scratch(scratch, n_experts);
   const int32_t* work_off = sc.work_off;
   const int32_t* xcd_first = sc.xcd_first;
-  const int xcd = blockIdx.x % kXcds;
-  const int stride = gridDim.x / kXcds;  // workgroups per XCD: a workgroup takes every stride-th tile of its XCD's range
-  const int last = xcd_first[xcd + 1];
-  for (int logical = xcd_first[xcd] + (int)(blockIdx.x / kXcds); logical < last; logical += stride) {
-  __syncthreads();  // the previous tile's per-tile arrays in LDS are no longer read
+  const int block = linear_block();
+  const int xcd = block % kXcds;
+  // A workgroup takes every stride-th tile of its XCD's range.  In the first contraction every tile costs the same, the
+  // ranges are an eighth of the tiles each, and the grid has a workgroup for each of them: no loop, whose state would
+  // have to be kept over the K loop, which leaves no register free for it.
+  constexpr bool kWalk = !std::is_same<TABLE, CompactRows>::value;
+  const int stride = gridDim.x / kXcds;  // kWalk: the grid is one-dimensional
+  const int last = __builtin_amdgcn_readfirstlane(xcd_first[xcd + 1]);
+  const int first = __builtin_amdgcn_readfirstlane(xcd_first[xcd]);
+  for (int logical = first + block / kXcds; logical < last; logical += stride) {
+  if constexpr (kWalk) __syncthreads();  // the previous tile's per-tile arrays in LDS are no longer read
   int lo = 0, hi = n_experts;                      // work_off[lo] <= logical < work_off[hi]
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
     if (work_off[mid] <= logical) lo = mid; else hi = mid;
   }
-  const int e = lo;
+  const int e = __builtin_amdgcn_readfirstlane(lo);
   const ExpertGeom g = expert_geom(tab, e, d_model);
   // the expert's rows of the hidden buffer: row of bucket slot s at hid_e + s * hid_ld
   const int64_t hid_ld = hidden_ld(tab, e, k_round);
-  const int64_t hid_e = sc.hid_off[e] - (int64_t)offsets[e] * hid_ld;
+  const uint64_t hid_off = (uint64_t)sc.hid_off[e];
+  const int64_t hid_e = (int64_t)((uint64_t)__builtin_amdgcn_readfirstlane((int)(hid_off >> 32)) << 32 |
+                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)hid_off)) - (int64_t)offsets[e] * hid_ld;
   EpiArgs ep = ep_launch;
   const __hip_bfloat16* A = X;
   int64_t lda = ldx;
@@ -1017,7 +1024,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   }
   const int n_tiles_n = (g.n_ext + BN - 1) / BN;  // >= 1: an expert without N tiles owns no logical id
   const int m_e = tile_offset[e + 1] - tile_offset[e];
-  const int local = logical - work_off[e];
+  const int local = logical - __builtin_amdgcn_readfirstlane(work_off[e]);
   // the tile order of grouped_gemm_bf16_kernel inside the expert
   const int chunk_m = m_e <= kChunkMax ? m_e : kChunkM;
   const int group_n = max(1, kPatch / chunk_m);
@@ -1054,6 +1061,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   w.tok_first = tile_in_expert * BM;
   constexpr int kAux = C::kAliasAux ? 0 : C::kRingBytes;  // the per-tile arrays
   run_tile<C, TAIL, EPI, kAux>(w, A, lda, g.k_ext, g.n_ext, Wg + g.g_off, Wu + g.u_off, 0, g.ldw, perm, w_perm, zeros, ep);
+  if constexpr (!kWalk) break;
   }
 }
 
@@ -1313,12 +1321,13 @@ static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx,
   if (hipError_t err = allow_lds(lds_allowed[tail], reinterpret_cast<const void*>(kern), C::kSmemBytes); err != hipSuccess) return err;
   hipLaunchKernelGGL((compact_work_kernel<TABLE>), dim3(1), dim3(CAMERA_MAX_EXPERTS), 0, stream, tab, (int)d_model, C::BN, C::KT, k_round,
                      t.offsets, t.tile_offset, scratch);
-  // an upper bound of the tile count, shared evenly between the XCDs: a workgroup walks on through its XCD's
-  // range where the cuts by cost give that XCD more (cheaper) tiles than that
-  constexpr int64_t kMaxBlocks = int64_t(1) << 22;  // a launch takes fewer than 2^32 threads per dimension
-  const int64_t n_blocks = std::min(kMaxBlocks, (max_tiles * n_tiles_n_max + kXcds - 1) / kXcds * kXcds);
+  // an upper bound of the tile count, shared evenly between the XCDs.  In the second contraction a workgroup walks on through
+  // its XCD's range where the cuts by cost give that XCD more (cheaper) tiles than that, or the grid ends at one row.
+  int64_t n_blocks = (max_tiles * n_tiles_n_max + kXcds - 1) / kXcds * kXcds;
   if (n_blocks == 0) return hipGetLastError();
-  hipLaunchKernelGGL(kern, dim3((unsigned)n_blocks), dim3(C::kThreads), C::kSmemBytes, stream,
+  if (!std::is_same<TABLE, CompactRows>::value) n_blocks = std::min(int64_t(1) << kGridWidthLog2, n_blocks);
+  if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kern, launch_grid(n_blocks), dim3(C::kThreads), C::kSmemBytes, stream,
                      static_cast<const __hip_bfloat16*>(X), ldx, (int)d_model, static_cast<const __hip_bfloat16*>(Wg),
                      static_cast<const __hip_bfloat16*>(Wu), tab, k_round, t.offsets, t.tile_offset, scratch, t.perm,
                      t.w_perm, static_cast<const __hip_bfloat16*>(t.zeros), ep);
