@@ -689,7 +689,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   // then read once per 256 tokens of an expert instead of once per 32.  Its 16-byte tile loads need W_down rows
   // that are a multiple of 8 elements long and the two halves of d_model to be multiples of 8.
   const bool mfma = n_pairs / total > 64 && down_row_align % 8 == 0 && d_model % 16 == 0;
-  const bool small = !dense && !mfma && n_pairs <= camera::kCompactSmallPairs;  // one-workgroup bucket order, no M-tile tables
+  const bool small = !dense && !mfma && n_pairs <= camera::kBucketSmallPairs;  // one-workgroup bucket order, no M-tile tables
   const int tile_m = camera::gemm_tile_m(dtype, widest);  // M tiles of the MFMA path; otherwise only the bucket order is used
   const int64_t max_tiles64 = dense ? n_experts * ((n + tile_m - 1) / tile_m) : n_pairs / tile_m + total;
   if (max_tiles64 > 65535)

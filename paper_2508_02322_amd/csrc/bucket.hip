@@ -12,6 +12,7 @@
 //             ballots (one per bit of the expert id gives the lanes of equal
 //             expert) and popcounts of the lower lanes, so equal experts keep
 //             their pair order (stable, deterministic).
+// Up to kBucketSmallPairs pairs one workgroup does all of it in one launch.
 #include "camera_internal.h"
 
 namespace camera {
@@ -132,6 +133,17 @@ __global__ __launch_bounds__(kScanThreads) void bucket_scan_kernel(int32_t* __re
   }
 }
 
+// The lanes of a wave that hold the same expert id as this one (e < 0: none), from one ballot per bit: ids are below 256.
+__device__ __forceinline__ uint64_t lanes_of_expert(int e) {
+  uint64_t same = __ballot(e >= 0);
+#pragma unroll
+  for (int bit = 0; bit < 8; ++bit) {
+    const uint64_t ones = __ballot((e >> bit) & 1);
+    same &= ((e >> bit) & 1) ? ones : ~ones;
+  }
+  return same;
+}
+
 __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(const int32_t* __restrict__ topk_idx,
                                                                   const float* __restrict__ topk_w,
                                                                   int64_t n_pairs, int top_k, int n_experts,
@@ -180,12 +192,7 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(const int32_t*
     // The lanes that hold the same expert, from one ballot per bit of the id (eight bits: ids are below 256):
     // a lane keeps the lanes that agree with it on every bit.  Its slot is the expert's next free one plus the
     // number of such lanes below it; the lowest lane of every group then moves the expert's counter on.
-    uint64_t same = __ballot(e >= 0);
-#pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const uint64_t ones = __ballot((e >> bit) & 1);
-      same &= ((e >> bit) & 1) ? ones : ~ones;
-    }
+    const uint64_t same = lanes_of_expert(e);
     int slot = -1;
     if (e >= 0) slot = next[wave][e] + __popcll(same & lower_lanes);
     // every lane has read next[] before the first lane of its group moves it on
@@ -197,6 +204,138 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(const int32_t*
       if (topk_w) w_perm[slot] = topk_w[p];
     }
     if (slot_of != nullptr && p < n_pairs) slot_of[p] = e >= 0 ? slot : -1;
+  }
+}
+
+// At most kBucketSmallPairs pairs, one workgroup: a launch and the loads behind it cost more than the counting, which the
+// general sort does in three (and a decoding batch needs its work items and appended experts on top).  A wave takes 64
+// consecutive pairs, one per lane, and up to four such chunks; the ballots give a pair its place among those of its expert
+// in the chunk and the chunk's count; the thread of an expert turns the counts of the chunks into exclusive bases (LDS,
+// all loads of a thread in flight); prefixes over the experts follow, pairs and tiles or work items in one pass.
+// Replaced, us: the three launches, 1024 pairs of 8 experts 9.6 -> 4.8 (and two gaps), 3176 pairs of 128 experts with the work
+// items 19 -> 11; four threads per expert that walked over the pairs, as decoding batches had it, 8 pairs 4.9 -> 4.0, 576
+// pairs of 65 experts 14.5 -> 5.0, 1600 of 128 30.7 -> 7.5.  Beyond 4096 pairs the general sort's workgroups are worth their
+// launches (a lone one takes 3 us for every thousand).
+// COMPACT: pair token * (top_k + n_shared) + k is routed choice k, or for k >= top_k the appended expert n_experts + k - top_k
+// with weight 1; work [2][CAMERA_MAX_EXPERTS + 1] gets the work items.  Otherwise: the M-tile tables.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallChunks = kBucketSmallPairs / kWave;
+constexpr int kSmallSteps = kBucketSmallPairs / kSmallThreads;
+template <bool COMPACT>
+__global__ __launch_bounds__(kSmallThreads) void bucket_small_kernel(
+    const int32_t* __restrict__ topk_idx, const float* __restrict__ topk_w, int n_pairs, int top_k, int n_experts,
+    int n_shared, CompactWork tab, int tile_m, int max_tiles, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ tile_offset, int32_t* __restrict__ tile_expert, int32_t* __restrict__ perm,
+    float* __restrict__ w_perm, int32_t* __restrict__ slot_of, int32_t* __restrict__ work) {
+  __shared__ uint16_t hist[kSmallChunks][CAMERA_MAX_EXPERTS];  // pairs of an expert in a chunk, then in the chunks before it
+  __shared__ int32_t first_slot[CAMERA_MAX_EXPERTS];
+  constexpr int kExpertWaves = CAMERA_MAX_EXPERTS / kWave;
+  __shared__ int32_t wave_total[3][kExpertWaves];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int kk = top_k + n_shared, total = n_experts + n_shared;
+  const int n_chunks = (n_pairs + kWave - 1) / kWave;
+  for (int i = tid; i < n_chunks * CAMERA_MAX_EXPERTS / 2; i += kSmallThreads) reinterpret_cast<uint32_t*>(&hist[0][0])[i] = 0;
+  int expert[kSmallSteps], token[kSmallSteps], place[kSmallSteps];
+  float weight[kSmallSteps];
+  // pairs past the end have no expert; no early exit, the ballots take whole waves
+#pragma unroll
+  for (int s = 0; s < kSmallSteps; ++s) {
+    const int p = s * kSmallThreads + tid;
+    expert[s] = -1;
+    weight[s] = 1.0f;
+    token[s] = 0;
+    if (p < n_pairs) {
+      token[s] = p / kk;
+      const int k = p - token[s] * kk;
+      if (k < top_k) {
+        const int e = topk_idx[token[s] * top_k + k];
+        if (topk_w) weight[s] = topk_w[token[s] * top_k + k];
+        if (e >= 0 && e < n_experts) expert[s] = e;  // an id of the appended experts is not a routed choice
+      } else {
+        expert[s] = n_experts + k - top_k;
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < kSmallSteps; ++s) {
+    const int chunk = s * (kSmallThreads / kWave) + wave;
+    if (chunk >= n_chunks) break;  // wave-uniform
+    const uint64_t same = lanes_of_expert(expert[s]);
+    place[s] = __popcll(same & ((1ull << lane) - 1ull));
+    if (expert[s] >= 0 && place[s] == 0) hist[chunk][expert[s]] = (uint16_t)__popcll(same);
+  }
+  __syncthreads();
+  int32_t value[3] = {0, 0, 0}, incl[3];  // of this thread's expert: pairs; tiles or items of either contraction
+  if (tid < total) {
+    int run = 0;
+    for (int c0 = 0; c0 < n_chunks; c0 += 16) {
+      int v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = c0 + u < n_chunks ? hist[c0 + u][tid] : 0;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        if (c0 + u < n_chunks) hist[c0 + u][tid] = (uint16_t)run;
+        run += v[u];
+      }
+    }
+    value[0] = run;
+    if constexpr (COMPACT) {
+      const int groups = (run + kCompactTokens - 1) / kCompactTokens;
+      value[1] = groups * tab.hidden_tiles[tid];
+      value[2] = groups * tab.down_tiles[tid];
+    } else {
+      value[1] = (run + tile_m - 1) / tile_m;
+    }
+  }
+  if (wave < kExpertWaves) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      incl[i] = value[i];
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int up = __shfl_up(incl[i], d);
+        if (lane >= d) incl[i] += up;
+      }
+      if (lane == kWave - 1) wave_total[i][wave] = incl[i];
+    }
+  }
+  __syncthreads();
+  if (tid < total) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      for (int w = 0; w < wave; ++w) incl[i] += wave_total[i][w];
+    first_slot[tid] = incl[0] - value[0];
+    counts[tid] = value[0];
+    offsets[tid] = incl[0] - value[0];
+    if (tid == total - 1) offsets[total] = incl[0];
+    if constexpr (COMPACT) {
+      int32_t* work2 = work + CAMERA_MAX_EXPERTS + 1;
+      work[tid] = incl[1] - value[1];
+      work2[tid] = incl[2] - value[2];
+      if (tid == total - 1) {
+        work[total] = incl[1];
+        work2[total] = incl[2];
+      }
+    } else {
+      const int first = incl[1] - value[1];
+      tile_offset[tid] = first;
+      if (tid == total - 1) tile_offset[total] = min(incl[1], max_tiles);
+      for (int t = first; t < min(incl[1], max_tiles); ++t) tile_expert[t] = tid;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < kSmallSteps; ++s) {
+    const int p = s * kSmallThreads + tid;
+    if (p >= n_pairs) break;
+    const int e = expert[s];
+    const int slot = e < 0 ? -1 : first_slot[e] + hist[s * (kSmallThreads / kWave) + wave][e] + place[s];
+    if (e >= 0) {
+      perm[slot] = token[s];
+      if (topk_w) w_perm[slot] = weight[s];
+    }
+    if (slot_of) slot_of[p] = slot;
   }
 }
 
@@ -218,6 +357,12 @@ __global__ void dense_tables_kernel(int64_t n, int n_experts, int tile_m, int ma
 hipError_t launch_bucket(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n, int top_k,
                          int n_experts, int tile_m, int max_tiles, const BucketTables& t) {
   const int64_t n_pairs = n * top_k;
+  if (n_pairs <= kBucketSmallPairs) {
+    hipLaunchKernelGGL(bucket_small_kernel<false>, dim3(1), dim3(kSmallThreads), 0, stream, topk_idx, topk_w, (int)n_pairs, top_k,
+                       n_experts, 0, CompactWork{}, tile_m, max_tiles, t.counts, t.offsets, t.tile_offset, t.tile_expert, t.perm,
+                       t.w_perm, t.slot_of, nullptr);
+    return hipGetLastError();
+  }
   const int n_blocks = (int)bucket_blocks(n_pairs);
   if (n_blocks > 0)
     hipLaunchKernelGGL(bucket_count_kernel, dim3(n_blocks), dim3(kThreads), 0, stream, topk_idx, n_pairs, n_experts,
@@ -227,6 +372,15 @@ hipError_t launch_bucket(hipStream_t stream, const int32_t* topk_idx, const floa
   if (n_blocks > 0)
     hipLaunchKernelGGL(bucket_scatter_kernel, dim3(n_blocks), dim3(kThreads), 0, stream, topk_idx, topk_w, n_pairs,
                        top_k, n_experts, t.block_hist, t.offsets, t.perm, t.w_perm, t.slot_of);
+  return hipGetLastError();
+}
+
+hipError_t launch_compact_bucket_small(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n,
+                                       int top_k, int n_experts, int n_shared, const CompactWork& tab,
+                                       const BucketTables& t, int32_t* work) {
+  hipLaunchKernelGGL(bucket_small_kernel<true>, dim3(1), dim3(kSmallThreads), 0, stream, topk_idx, topk_w,
+                     (int)(n * (top_k + n_shared)), top_k, n_experts, n_shared, tab, 0, 0, t.counts, t.offsets, nullptr, nullptr,
+                     t.perm, t.w_perm, t.slot_of, work);
   return hipGetLastError();
 }
 

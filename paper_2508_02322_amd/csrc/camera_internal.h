@@ -43,6 +43,9 @@ hipError_t launch_route_topk(hipStream_t stream, const void* X, int dtype, int64
 constexpr int kBucketChunk = 1024;
 inline int64_t bucket_blocks(int64_t n_pairs) { return (n_pairs + kBucketChunk - 1) / kBucketChunk; }
 
+// Up to this many pairs one workgroup sorts them in one launch.
+constexpr int kBucketSmallPairs = 4096;
+
 // Stable counting sort of the n*top_k pairs by expert, then the M-tile tables
 // for tiles of `tile_m` rows.
 // (topk_w may be NULL: w_perm is then left unwritten.)
@@ -166,7 +169,8 @@ struct CompactDown {                          // W_down_c
                                               // expert e's block starts at element d_model * ld_off[e]
   int32_t chunk_off[CAMERA_MAX_EXPERTS + 1];  // first K chunk of each expert
 };
-// Work items of the decoding kernels per group of 32 tokens of an expert.
+// Work items of the decoding kernels per group of kCompactTokens tokens of an expert.
+constexpr int kCompactTokens = 32;
 struct CompactWork {
   int32_t hidden_tiles[CAMERA_MAX_EXPERTS];   // 32-row tiles of its kept rows
   int32_t down_tiles[CAMERA_MAX_EXPERTS];     // K chunks times 32-row tiles of d_model
@@ -181,9 +185,8 @@ inline int compact_chunks(int count) {
   return c > kCompactMaxChunks ? kCompactMaxChunks : c;
 }
 // Bucket tables (counts, offsets, perm, w_perm, slot_of) of the pairs (token, routed choice k < top_k) and
-// (token, appended expert n_experts + s, weight 1) and the work items, in one launch; n * (top_k + n_shared) <=
-// kCompactSmallPairs.
-constexpr int kCompactSmallPairs = 2048;
+// (token, appended expert n_experts + s, weight 1) and the work items, in one launch (bucket.hip); n * (top_k + n_shared) <=
+// kBucketSmallPairs.
 hipError_t launch_compact_bucket_small(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n,
                                        int top_k, int n_experts, int n_shared, const CompactWork& tab,
                                        const BucketTables& t, int32_t* work);

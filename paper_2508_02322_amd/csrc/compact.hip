@@ -50,7 +50,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
-typedef __attribute__((ext_vector_type(8))) int16_t i16x8;
 
 // Waves of a workgroup, each with its share of the K blocks (1, 2 or 4: the four accumulator groups of a lane
 // are dealt to them after the reduction).  The first contraction's K extent is d_model.
@@ -64,7 +63,7 @@ static_assert(kSplitHidden == 1 || kSplitHidden == 2 || kSplitHidden == 4, "1, 2
 constexpr int kDownFourWavesFrom = 1280;
 constexpr int kTile = 16;    // rows and columns of an MFMA
 constexpr int kRows = 32;    // weight rows per workgroup: two M tiles
-constexpr int kTokens = 32;  // tokens per workgroup: one or two N tiles
+constexpr int kTokens = kCompactTokens;  // tokens per workgroup: one or two N tiles
 constexpr int kKBlock = 64;  // K elements per step: 2 MFMAs of K = 32 per pair of tiles
 
 __device__ __forceinline__ float silu_f32(float g) {
@@ -550,87 +549,7 @@ __global__ __launch_bounds__(256) void compact_combine_kernel(const float4* __re
   Y[tok * vecs + v] = s;
 }
 
-// ---- bucket order of a decoding batch ----------------------------------------------------------------------
-// Pair p = token * (top_k + n_shared) + k: for k < top_k the routed expert topk_idx[token][k] with weight
-// topk_w[token][k], for k >= top_k the appended expert n_experts + k - top_k with weight 1.
-//
-// One workgroup does what the three launches of the general counting sort do, for at most kCompactSmallPairs
-// pairs.  Four threads per expert, each with a quarter of the pair range: a thread counts the pairs of its
-// expert in its quarter, an exclusive prefix over the threads (expert-major, quarter-minor: the stable order)
-// gives its first slot, and it places its pairs in pair order.
-constexpr int kQuarters = 4;
-constexpr int kSmallThreads = CAMERA_MAX_EXPERTS * kQuarters;
-static_assert(kSmallThreads <= 1024, "one workgroup");
-
-__global__ __launch_bounds__(kSmallThreads) void compact_bucket_small_kernel(
-    const int32_t* __restrict__ topk_idx, const float* __restrict__ topk_w, int n, int top_k, int n_experts,
-    int n_shared, CompactWork tab, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ perm, float* __restrict__ w_perm, int32_t* __restrict__ slot_of, int32_t* __restrict__ work) {
-  __shared__ __attribute__((aligned(16))) int16_t ids[kCompactSmallPairs];  // expert of every pair, -1: none
-  __shared__ int16_t token[kCompactSmallPairs];                             // its token
-  __shared__ float weight[kCompactSmallPairs];                              // and its weight
-  __shared__ int32_t wave_total[kSmallThreads / kWave];
-  __shared__ int32_t s_count[CAMERA_MAX_EXPERTS];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int kk = top_k + n_shared, total = n_experts + n_shared, n_pairs = n * kk;
-  const int padded = (n_pairs + 7) & ~7;
-  for (int p = tid; p < padded; p += kSmallThreads) {
-    int e = -1, j = 0;
-    float a = 1.0f;
-    if (p < n_pairs) {
-      j = p / kk;
-      const int k = p - j * kk;
-      if (k < top_k) {
-        e = topk_idx[j * top_k + k];
-        a = topk_w[j * top_k + k];
-        if (e < 0 || e >= n_experts) e = -1;
-      } else {
-        e = n_experts + k - top_k;
-      }
-      if (e < 0) slot_of[p] = -1;
-    }
-    ids[p] = (int16_t)e;
-    token[p] = (int16_t)j;
-    weight[p] = a;
-  }
-  __syncthreads();
-  const int e = tid / kQuarters, quarter = tid % kQuarters;
-  const int groups = padded / 8;
-  const int p_begin = groups * quarter / kQuarters * 8, p_end = groups * (quarter + 1) / kQuarters * 8;
-  int mine = 0;
-  if (e < total) {
-    for (int p = p_begin; p < p_end; p += 8) {
-      const i16x8 v = *reinterpret_cast<const i16x8*>(&ids[p]);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) mine += v[i] == e;
-    }
-  }
-  const int first = block_prefix<kSmallThreads / kWave>(mine, wave_total);
-  const int first_of_expert = __shfl(first, lane & ~(kQuarters - 1));  // the four threads of an expert are neighbours
-  if (e < total) {
-    if (quarter == 0) offsets[e] = first;
-    if (quarter == kQuarters - 1) {
-      counts[e] = s_count[e] = first + mine - first_of_expert;
-      if (e == total - 1) offsets[total] = first + mine;
-    }
-    int slot = first;
-    for (int p = p_begin; p < p_end; p += 8) {
-      const i16x8 v = *reinterpret_cast<const i16x8*>(&ids[p]);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (v[i] != e) continue;
-        const int q = p + i;
-        perm[slot] = token[q];
-        w_perm[slot] = weight[q];
-        slot_of[q] = slot;
-        ++slot;
-      }
-    }
-  }
-  __syncthreads();
-  write_work<kSmallThreads / kWave>(tab, total, tid < total ? s_count[tid] : 0, wave_total, work);
-}
-
+// ---- work items and pairs of batches that the general counting sort puts in order -------------------------------
 // The work items where the bucket order comes from the general counting sort.
 __global__ __launch_bounds__(CAMERA_MAX_EXPERTS) void compact_items_kernel(CompactWork tab, int total,
                                                                            const int32_t* __restrict__ counts,
@@ -694,14 +613,6 @@ __global__ void compact_append_shared_kernel(const int32_t* __restrict__ topk_id
 }
 
 }  // namespace
-
-hipError_t launch_compact_bucket_small(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n,
-                                       int top_k, int n_experts, int n_shared, const CompactWork& tab,
-                                       const BucketTables& t, int32_t* work) {
-  compact_bucket_small_kernel<<<1, kSmallThreads, 0, stream>>>(topk_idx, topk_w, (int)n, top_k, n_experts, n_shared, tab,
-                                                               t.counts, t.offsets, t.perm, t.w_perm, t.slot_of, work);
-  return hipGetLastError();
-}
 
 hipError_t launch_compact_items(hipStream_t stream, const CompactWork& tab, int total, const BucketTables& t,
                                 int32_t* work) {

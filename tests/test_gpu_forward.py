@@ -121,6 +121,38 @@ def test_output_columns_at_the_edges_of_a_lane_a_wave_and_a_tile(cam, n_tokens, 
     check_output(Y, orc.layer_forward(X64, A, gate, up, down, round_hidden=orc.round_to_bf16), largest_term(X64, A, gate, up, down))
 
 
+@pytest.mark.parametrize("top_k,experts,n_shared", [(8, 100, 0), (3, 256, 0), (4, 63, 0), (6, 96, 1), (7, 250, 2)])
+@pytest.mark.parametrize("compact", [False, True])
+def test_bucket_order_in_one_launch(cam, compact, top_k, experts, n_shared):
+    """Up to 4096 pairs one workgroup makes the bucket order, beyond them the general sort does.  A token's output does not
+    depend on the batch: the call on all tokens (more pairs) equals the calls on parts of them with 1 token, a chunk of
+    64 pairs and its neighbours, a whole step of 1024, and the rest, bit for bit.  Some choices are no expert's."""
+    n_shared = n_shared if compact else 0
+    terms = top_k + n_shared
+    n_tokens = 4096 // terms + 1
+    cfg = small(n_tokens=n_tokens, d_model=64, d_ff=40, n_experts=experts, top_k=top_k, n_shared=n_shared,
+                d_ff_shared=48 if n_shared else 0, outlier_channels=0)
+    dev = inputs.make_layer(cfg, 0, device="cuda")
+    X = dev["X"]
+    idx, w = cam.route_topk(X, dev["W_r"], dev["bias"], top_k)
+    idx[::7, 0] = -1
+    idx[3::11, top_k - 1] = experts  # of an appended expert: not a routed choice
+
+    def forward(lo, hi):
+        args = X[lo:hi], idx[lo:hi], w[lo:hi]
+        if not compact:
+            return cam.layer_forward(*args, dev["W_gate"], dev["W_up"], dev["W_down"])
+        parts = [[dev[p + m].flatten(0, 1) if m != "_down" else dev[p + m].flatten() for p in ("W", "Ws")[:1 + (cfg.n_shared > 0)]]
+                 for m in ("_gate", "_up", "_down")]
+        return cam.layer_forward_compact(*args, [cfg.d_ff] * experts + [cfg.d_ff_shared] * cfg.n_shared,
+                                         *[torch.cat(p) for p in parts], n_shared=cfg.n_shared, down_row_align=8)
+    whole = forward(0, n_tokens)
+    assert whole.abs().max() > 0
+    for size in (1, 64 // terms, 64 // terms + 1, 1024 // terms + 1, 4096 // terms):
+        for lo in (0, n_tokens - size):
+            assert torch.equal(forward(lo, lo + size), whole[lo:lo + size]), (size, lo)
+
+
 @pytest.mark.parametrize("compact", [False, True])
 def test_product_rows_past_the_caches(cam, compact):
     """From 256 MiB of product rows on they are stored and read past the caches.  A token's output does not depend on the
