@@ -44,6 +44,16 @@ constexpr int kBlockK = 32;
 constexpr int kRangeBlocks = 32;
 constexpr int kRangeK = kRangeBlocks * kBlockK;
 
+// The value of another of the eight lanes that share a token (all or none of them active): after the steps 0, 1 and 2 every
+// lane has met all eight.  0 and 1 are the lanes at distance 1 and 2; 2 is the mirror image in the eight, which will do
+// for the distance 4 because the lanes of a quad agree by then.  (Data-parallel primitives: a few cycles, where a shuffle
+// goes through the LDS crossbar.)
+template <int STEP, class T>
+__device__ __forceinline__ T lane_of_eight(T v) {
+  constexpr int kCtrl = STEP == 0 ? 0xb1 : (STEP == 1 ? 0x4e : 0x141);  // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror
+  return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, true));
+}
+
 // Top-k of one token by kSub consecutive lanes: lane `sub` has experts sub, sub + kSub, ... of at most NE, read once into
 // registers (a round that reads them from LDS again waits for each: with the other kernels of that time, graph replays of 8192
 // tokens and 64 experts 24 -> 21 us, of one token and 256 experts 47 -> 34 us); each round takes the
@@ -59,8 +69,8 @@ __device__ __forceinline__ void topk_of_token(const float* s_row, int n_experts,
   float row_max = -INFINITY;
 #pragma unroll
   for (int i = 0; i < kPer; ++i) row_max = fmaxf(row_max, v[i]);  // a repeated last expert does not change it
-#pragma unroll
-  for (int m = kSub / 2; m >= 1; m >>= 1) row_max = fmaxf(row_max, __shfl_xor(row_max, m));
+  static_assert(kSub == 8, "lane_of_eight");
+  static_for<0, 3>([&](auto step) { row_max = fmaxf(row_max, lane_of_eight<decltype(step)::value>(row_max)); });
   float denom = 0.0f;
   if (!renorm) {
 #pragma unroll
@@ -84,15 +94,14 @@ __device__ __forceinline__ void topk_of_token(const float* s_row, int n_experts,
         best_i = e;
       }
     }
-#pragma unroll
-    for (int m = kSub / 2; m >= 1; m >>= 1) {
-      const float ov = __shfl_xor(best_v, m);
-      const int oi = __shfl_xor(best_i, m);
+    static_for<0, 3>([&](auto step) {
+      const float ov = lane_of_eight<decltype(step)::value>(best_v);
+      const int oi = lane_of_eight<decltype(step)::value>(best_i);
       if (ov > best_v || (ov == best_v && oi < best_i)) {
         best_v = ov;
         best_i = oi;
       }
-    }
+    });
     const float p = __expf(best_v - row_max);
     if (r < kSub) {
       if (sub == r) mine = p;
@@ -306,20 +315,29 @@ __global__ __launch_bounds__(kWave * kChains) void route_bf16_split_kernel(
   }
 }
 
-// part [ranges][kChains][n][n_experts].  8 tokens per block: their logits, then the top-k with eight lanes per token.
-constexpr int kTokensPick = 8;
+// part [ranges][kChains][n][n_experts].  A thread has one logit, a block 256 / NE tokens, so that what it reads is one round
+// of loads.  A thread counts the logits of its token that come before its own (larger, or equal with a lower index): that is
+// its place in the top-k, without rounds that wait for each other.  The weights are those of topk_of_token bit for bit: the
+// same exponentials, added in the same order.  (8 tokens per block and their top-k in rounds, against this, us, top 8 or 6:
+// 1 token of 64 experts 7.9 / 5.2, 64 of 64 11.2 / 5.8, 16 of 128 18.3 / 8.5, 397 of 128 19.2 / 8.9, 250 of 256 (top 4) 20.8 / 15.0.)
+template <int NE>
+constexpr int kTokensPick = 256 / NE;
 template <int NE>
 __global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict__ part, int ranges, int64_t n,
                                                          const float* __restrict__ bias, int n_experts, int top_k,
                                                          int renorm, int32_t* __restrict__ topk_idx,
                                                          float* __restrict__ topk_w) {
-  __shared__ float s_logit[kTokensPick][NE + 1];
-  const int64_t tok0 = (int64_t)blockIdx.x * kTokensPick;
-  const int tokens = (int)min((int64_t)kTokensPick, n - tok0);
-  const int64_t stride = n * n_experts;
-  for (int i = threadIdx.x; i < tokens * n_experts; i += 256) {
-    const float* p = part + tok0 * n_experts + i;
-    const int t = i / n_experts, e = i - t * n_experts;
+  constexpr int T = kTokensPick<NE>;
+  __shared__ __align__(16) float s_logit[T][NE + 4];
+  __shared__ float s_v[T][NE], s_p[T][NE];  // logits by place, then their exponentials
+  __shared__ int s_i[T][NE];
+  const int t = threadIdx.x / NE, e = threadIdx.x % NE;
+  const int64_t tok = (int64_t)blockIdx.x * T + t;
+  const bool valid = tok < n && e < n_experts;
+  float logit = __builtin_nanf("");  // of no expert: comes before none
+  if (valid) {
+    const int64_t stride = n * n_experts;
+    const float* p = part + tok * n_experts + e;
     float sum[kChains] = {};
     for (int s0 = 0; s0 < ranges; s0 += 4) {  // the chains of four ranges in flight, added in range order
       float v[4][kChains];
@@ -333,16 +351,47 @@ __global__ __launch_bounds__(256) void route_pick_kernel(const float* __restrict
         for (int w = 0; w < kChains; ++w)
           if (s0 + u < ranges) sum[w] += v[u][w];
     }
-    float logit = sum[0] + (bias ? bias[e] : 0.0f);
+    logit = sum[0] + (bias ? bias[e] : 0.0f);
 #pragma unroll
     for (int w = 1; w < kChains; ++w) logit += sum[w];
-    s_logit[t][e] = logit;
+  }
+  s_logit[t][e] = logit;
+  s_v[t][e] = -INFINITY;  // what a place holds that no logit takes (a token with NaN logits)
+  s_i[t][e] = 0x7fffffff;
+  __syncthreads();
+  if (valid && logit == logit) {
+    int place = 0;
+#pragma unroll 8
+    for (int j = 0; j < NE; j += 4) {
+      const f32x4 o = *reinterpret_cast<const f32x4*>(&s_logit[t][j]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) place += (o[u] > logit || (o[u] == logit && j + u < e)) ? 1 : 0;
+    }
+    if (place < top_k) {
+      s_v[t][place] = logit;
+      s_i[t][place] = e;
+    }
   }
   __syncthreads();
-  const int t_local = threadIdx.x / kSub, sub = threadIdx.x % kSub;
-  if (t_local < tokens)
-    topk_of_token<NE>(s_logit[t_local], n_experts, top_k, renorm, sub, topk_idx + (tok0 + t_local) * top_k,
-                     topk_w + (tok0 + t_local) * top_k);
+  const float row_max = s_v[t][0];
+  const float kept = __expf(s_v[t][e] - row_max);  // of place e
+  s_p[t][e] = renorm ? kept : __expf(logit - row_max);
+  __syncthreads();
+  if (tok >= n || e >= top_k) return;
+  float total = 0.0f;
+  if (renorm) {
+    for (int r = 0; r < top_k; ++r) total += s_p[t][r];
+  } else {  // the sums of kSub lanes that take every kSub-th expert, then these at distances 4, 2, 1
+    float sub[kSub];
+#pragma unroll
+    for (int q = 0; q < kSub; ++q) {
+      sub[q] = 0.0f;
+      for (int i = q; i < n_experts; i += kSub) sub[q] += s_p[t][i];
+    }
+    total = ((sub[0] + sub[4]) + (sub[2] + sub[6])) + ((sub[1] + sub[5]) + (sub[3] + sub[7]));
+  }
+  topk_idx[tok * top_k + e] = s_i[t][e];
+  topk_w[tok * top_k + e] = kept * (1.0f / total);
 }
 
 // float32: 8 tokens per block; its four waves deal the experts among them, EG at a time.  A wave's lanes stride over
@@ -458,7 +507,7 @@ void launch_bf16_split(hipStream_t stream, const void* X, int64_t n, int64_t d_m
                      (unsigned)((n_experts + ET * 16 - 1) / (ET * 16))), dim3(kWave * kChains), 0, stream,
                      static_cast<const __hip_bfloat16*>(X), n, (int)d_model, ldx, static_cast<const __hip_bfloat16*>(W_r), ldr,
                      n_experts, static_cast<const __hip_bfloat16*>(zeros), scratch);
-  hipLaunchKernelGGL(route_pick_kernel<NE>, dim3((unsigned)((n + kTokensPick - 1) / kTokensPick)), dim3(256), 0, stream, scratch,
+  hipLaunchKernelGGL(route_pick_kernel<NE>, dim3((unsigned)((n + kTokensPick<NE> - 1) / kTokensPick<NE>)), dim3(256), 0, stream, scratch,
                      ranges, n, bias, n_experts, top_k, renorm, topk_idx, topk_w);
 }
 

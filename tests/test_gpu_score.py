@@ -1,6 +1,8 @@
 """GPU parity of camera_route_topk and camera_score_layer against the fp64 oracle on
 seeded inputs small enough for the full oracle, with ragged sizes and the degenerate
 cases of the method."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -179,6 +181,30 @@ def test_routing_gives_a_token_the_same_bits_in_every_batch(cam, dtype, n_expert
     for lo, n in ((0, 1), (largest - 1, 1), (3, 7), (5, 16), (11, 33), (0, 64), (1, largest // 2), (0, largest - 1)):
         part_idx, part_w = cam.route_topk(X[lo:lo + n], R, bias, top_k)
         assert torch.equal(part_idx, idx[lo:lo + n]) and torch.equal(part_w, w[lo:lo + n]), (lo, n)
+
+
+@pytest.mark.parametrize("n_experts", [16, 17, 64, 65, 128, 129, 256])
+def test_top_k_by_counting_equals_top_k_in_rounds(cam, n_experts):
+    """Small batches count how many logits of a token come before each, large ones take the largest in rounds: the same
+    choices and weights bit for bit, with exact ties, infinities of either sign and NaN among the logits, for one expert
+    and for all of them, with and without renormalisation."""
+    d_model, many = 1032, 2049
+    g = torch.Generator(device="cuda").manual_seed(n_experts)
+    X = torch.randn((many, d_model), generator=g, device="cuda").bfloat16()
+    R = (torch.randn((n_experts, d_model), generator=g, device="cuda") * 0.02).bfloat16()
+    R[1::3] = R[:1]                                            # a third of the experts tie
+    plain = torch.zeros(n_experts, device="cuda")
+    biases = [plain, plain.clone(), plain.clone(), torch.full_like(plain, -math.inf)]
+    biases[1][::2] = -math.inf
+    biases[2][1::4], biases[2][2::5] = math.nan, math.inf
+    for bias in biases:
+        for top_k in (1, min(9, n_experts), n_experts):
+            for renorm in (True, False):
+                idx, w = cam.route_topk(X, R, bias, top_k, renorm)
+                for n in (1, 5, 300 if n_experts <= 128 else 60):
+                    idx_n, w_n = cam.route_topk(X[:n], R, bias, top_k, renorm)
+                    assert torch.equal(idx_n, idx[:n])
+                    assert torch.equal(w_n.nan_to_num(nan=-1.0), w[:n].nan_to_num(nan=-1.0))
 
 
 def test_shared_expert_dense_call(cam):
