@@ -564,6 +564,9 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   const size_t es = dtype == CAMERA_BF16 ? 2 : 4;
   const size_t o_hidden = cv.take(es * (size_t)n_pairs * d_ff);
   const size_t o_product = cv.take(sizeof(float) * (size_t)n_pairs * d_model);
+  const bool by_list = keep_mask != nullptr && dtype == CAMERA_BF16 && camera::masks_by_list(n_pairs, d_model, d_ff);
+  const size_t o_kept = cv.take(by_list ? sizeof(int32_t) * (size_t)(n_micro + n_experts) : 0);
+  const size_t o_work = cv.take(by_list ? sizeof(int32_t) * camera::kCompactGemmScratchWords : 0);
 
   DeviceGuard guard;
   CAMERA_HIP(guard.enter(ctx->device), "hipSetDevice");
@@ -583,7 +586,13 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
       CAMERA_HIP(camera::launch_bucket(stream, topk_idx, topk_w, n, top_k, n_experts, tile_m, max_tiles, t),
                  "bucket launch");
   }
-  {
+  if (by_list) {
+    Bracket b(ctx, stream, CAMERA_K_GEMM);
+    CAMERA_HIP(camera::launch_kept_hidden_gemm(stream, X, ldx, d_model, d_ff, n_experts, W_gate, W_up, stride_gu, keep_mask,
+                                               max_tiles, n_pairs, t, reinterpret_cast<int32_t*>(ws + o_kept),
+                                               reinterpret_cast<int32_t*>(ws + o_work), hidden),
+               "kept hidden gemm launch");
+  } else {
     Bracket b(ctx, stream, CAMERA_K_GEMM);
     camera::GemmEpilogue ep;
     ep.mode = camera::GemmEpilogue::kHidden;

@@ -226,6 +226,20 @@ hipError_t launch_compact_hidden_gemm(hipStream_t stream, const void* X, int64_t
                                       const void* W_gate, const void* W_up, const CompactRows& tab, int widest,
                                       int max_tiles, const BucketTables& t, int32_t* scratch, void* hidden,
                                       int k_round);
+// The first contraction of a masked layer over its kept micro-experts only (keep [n_experts * d_ff], 0 = pruned); hidden
+// rows are d_ff long, zero where nothing is kept.  kept: n_experts * (d_ff + 1) int32 words, scratch as above.
+hipError_t launch_kept_hidden_gemm(hipStream_t stream, const void* X, int64_t ldx, int64_t d_model, int64_t d_ff,
+                                   int n_experts, const void* W_gate, const void* W_up, int64_t stride_gu,
+                                   const uint8_t* keep, int max_tiles, int64_t n_pairs, const BucketTables& t, int32_t* kept,
+                                   int32_t* scratch, void* hidden);
+// When that pays: the lists, the zeros and the work table are three launches before it (25-33 us), and a launch with few more
+// tiles than compute units gains little from fewer.  Masked call, first contraction + these, us, against computing every
+// micro-expert and zeroing the pruned ones: 2.4e11 products of 40 % pruned 815 -> 575 + 32, of 20 % 808 -> 757 + 33, of nothing
+// pruned 800 -> 805 + 21; 6.9e10 (40 %) 288 -> 212 + 29; 4.7e10 (60 %) 278 -> 155 + 20; below the line 2.5e10 (40 %) 124 -> 107 + 19,
+// (20 %) 109 -> 112 + 20.
+inline bool masks_by_list(int64_t n_pairs, int64_t d_model, int64_t d_ff) {
+  return (double)n_pairs * d_model * d_ff >= 4e10;
+}
 hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int64_t d_model, const void* W_down,
                                     const CompactDown& tab, int max_tiles, const BucketTables& t, int32_t* scratch,
                                     float* product, bool stream_product);

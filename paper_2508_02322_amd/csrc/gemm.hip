@@ -94,12 +94,16 @@ constexpr int kChunkM = 4;     // otherwise this many
 //   kEpiHidden  : the same Lambda, times the keep flag of its micro-expert, rounded to bf16 -> hidden[slot row][channel]
 //   kEpiProduct : the plain products -> product[slot row][column] (first B matrix) and [column + col_gap] (second);
 //                 the token rows of this mode are the bucket slots themselves (A = the hidden activations)
-enum { kEpiStats = 0, kEpiHidden = 1, kEpiProduct = 2 };
+//   kEpiListed  : kEpiHidden over the kept micro-experts only: tile channel i of the expert is micro-expert list[i], whose
+//                 weight rows it reads and whose column of the (zeroed) hidden row it writes
+enum { kEpiStats = 0, kEpiHidden = 1, kEpiProduct = 2, kEpiListed = 3 };
+constexpr bool epi_hidden(int epi) { return epi == kEpiHidden || epi == kEpiListed; }
 struct EpiArgs {
   float* part_phi2;
   float* part_max;
   void* hidden;            // [pairs][ld_hidden], bf16 (MFMA kernel) or float32 (FMA kernel)
-  const uint8_t* keep;     // [n_experts * d_ff] or nullptr (all kept)
+  const uint8_t* keep;     // kEpiHidden: [n_experts * d_ff] or nullptr (all kept)
+  const int32_t* list;     // kEpiListed: the kept micro-experts of the tile's expert
   float* product;          // [pairs][ld_product]
   int64_t ld_product;
   int col_gap;
@@ -406,7 +410,7 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   // to LDS behind it, which leaves the compacted layer's kernel without spills.)
   float a_rows[NA][2][4], a_mine = 0.0f;
   if constexpr (C::kAliasAux) {
-    if constexpr (EPI == kEpiHidden) {
+    if constexpr (epi_hidden(EPI)) {
       a_mine = st.s_a[threadIdx.x];
     } else {
 #pragma unroll
@@ -421,7 +425,7 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   }
   static_assert(!C::kAliasAux || C::kThreads == C::BM, "one routing weight per thread");
   auto a_of = [&](int i, int a, int r, int row) {
-    return C::kAliasAux && EPI != kEpiHidden ? a_rows[i][a][r] : st.s_a[row];
+    return C::kAliasAux && !epi_hidden(EPI) ? a_rows[i][a][r] : st.s_a[row];
   };
 
   // Prologue: whole tiles 0 .. SB - 2 (token rows: 0 .. SA - 2), then what the phase behind a barrier would issue
@@ -554,7 +558,7 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be writing LDS at exit
   mfma_drain();                                      // the last MFMAs have written their accumulators
   if constexpr (C::kAliasAux && EPI != kEpiProduct) __syncthreads();  // the per-tile arrays lie over the ring: every wave has read its last fragments
-  if constexpr (C::kAliasAux && EPI == kEpiHidden) {
+  if constexpr (C::kAliasAux && epi_hidden(EPI)) {
     const_cast<float*>(st.s_a)[threadIdx.x] = a_mine;
     __syncthreads();
   }
@@ -604,16 +608,49 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
       if (ep.stream_product) write(std::true_type{});
       else write(std::false_type{});
     }
+  } else if constexpr (EPI == kEpiListed) {
+    const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four entries of the list
+    if (col0 < d_ff) {
+      int at[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) at[s] = col0 + s < d_ff ? ep.list[col0 + s] : -1;
+      const bool whole = at[3] - at[0] == 3 && at[0] % 4 == 0;  // neighbours, 8-byte aligned: one vector store
+#pragma unroll
+      for (int i = 0; i < ACT; ++i)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = (WM * i + st.wave_m) * 32 + a * 16 + lane_rows + r;
+            if (row >= st.m_len) continue;
+            __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(ep.hidden) + (int64_t)(st.row_first + row) * ep.ld_hidden;
+            const float a_tok = a_of(i, a, r, row);
+            __hip_bfloat16 lam[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+              lam[s] = __float2bfloat16(a_tok * silu_f32(acc_g[i][s / 2][a][s % 2][r]) * acc_u[i][s / 2][a][s % 2][r]);
+            if (whole) {
+              uint2 v;
+              v.x = (uint32_t)__builtin_bit_cast(uint16_t, lam[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[1]) << 16);
+              v.y = (uint32_t)__builtin_bit_cast(uint16_t, lam[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[3]) << 16);
+              *reinterpret_cast<uint2*>(dst + at[0]) = v;
+            } else {
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+                if (at[s] >= 0) dst[at[s]] = lam[s];
+            }
+          }
+    }
   } else if constexpr (EPI == kEpiHidden) {
     const int pad_end = ep.pad_hidden ? (d_ff + ep.pad_hidden - 1) / ep.pad_hidden * ep.pad_hidden : d_ff;
     const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four channels
     if (col0 < pad_end) {
       const bool whole = col0 + 3 < d_ff;  // all four inside: one vector store
-      float kept[4] = {1.0f, 1.0f, 1.0f, 1.0f};
+      bool kept[4] = {true, true, true, true};
       if (ep.keep != nullptr) {
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-          kept[s] = (col0 + s < d_ff && ep.keep[(int64_t)st.expert * d_ff + col0 + s]) ? 1.0f : 0.0f;
+          kept[s] = col0 + s < d_ff && ep.keep[(int64_t)st.expert * d_ff + col0 + s] != 0;
       }
 #pragma unroll
       for (int i = 0; i < ACT; ++i)
@@ -628,7 +665,7 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
             __hip_bfloat16 lam[4];
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-              lam[s] = __float2bfloat16(a_tok * silu_f32(acc_g[i][s / 2][a][s % 2][r]) * acc_u[i][s / 2][a][s % 2][r] * kept[s]);
+              lam[s] = __float2bfloat16(kept[s] ? a_tok * silu_f32(acc_g[i][s / 2][a][s % 2][r]) * acc_u[i][s / 2][a][s % 2][r] : 0.0f);
             if (whole) {  // rows of the hidden buffer are multiples of 8 elements long: 8-byte aligned
               uint2 v;
               v.x = (uint32_t)__builtin_bit_cast(uint16_t, lam[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[1]) << 16);
@@ -769,7 +806,8 @@ __device__ __forceinline__ void run_tile(const TileWork& w, const __hip_bfloat16
   for (int j = 0; j < C::kBDma; ++j) {
     const int row = b_row0 + j * C::kDmaRows + lane / C::kChunks;
     const int ck = (lane % C::kChunks) ^ swizzle_key<C>(row);
-    const int c = min(n0 + tile_channel<C, EPI>(row), d_ff - 1);  // channels past d_ff read the last channel again; never written
+    int c = min(n0 + tile_channel<C, EPI>(row), d_ff - 1);  // channels past d_ff read the last channel again; never written
+    if constexpr (EPI == kEpiListed) c = ep.list[c];
     const int64_t off = (int64_t)e * stride_gu + (int64_t)c * ldw + ck * 8;
     st.b_k[j] = ck * 8;
     st.g_src[j] = Wg + off - (j % 4) * 512;
@@ -882,6 +920,18 @@ __device__ __forceinline__ ExpertGeom expert_geom(const CompactDown& t, int e, i
   return {d_model / 2, k_ext, ld, base, base + (int64_t)(d_model / 2) * ld};
 }
 
+// A masked layer's first contraction over its kept micro-experts: their number and list on the device (keep_list_kernel),
+// the matrices as they are.
+struct KeptRows {
+  int n_experts, d_ff;
+  int64_t stride_gu;
+  const int32_t* count;  // [n_experts]
+  const int32_t* list;   // [n_experts][d_ff], ascending
+};
+__device__ __forceinline__ ExpertGeom expert_geom(const KeptRows& t, int e, int d_model) {
+  return {t.count[e], d_model, d_model, e * t.stride_gu, e * t.stride_gu};
+}
+
 // Scratch of a compacted-layer launch, written by compact_work_kernel:
 //   work_off  [n_experts + 1]  first logical tile id of every expert
 //   xcd_first [kXcds + 1]      XCD x runs the logical ids xcd_first[x] .. xcd_first[x + 1].  The cuts are placed by
@@ -907,6 +957,7 @@ __host__ __device__ inline CompactScratch compact_scratch(int32_t* base, int n_e
 __device__ __forceinline__ int hidden_ld(const CompactRows& t, int e, int k_round) {
   return (t.row_off[e + 1] - t.row_off[e] + k_round - 1) / k_round * k_round;
 }
+__device__ __forceinline__ int hidden_ld(const KeptRows& t, int, int) { return t.d_ff; }
 __device__ __forceinline__ int hidden_ld(const CompactDown& t, int e, int k_round) {
   return (t.count[e] + k_round - 1) / k_round * k_round;
 }
@@ -994,7 +1045,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   // A workgroup takes every stride-th tile of its XCD's range.  In the first contraction every tile costs the same, the
   // ranges are an eighth of the tiles each, and the grid has a workgroup for each of them: no loop, whose state would
   // have to be kept over the K loop, which leaves no register free for it.
-  constexpr bool kWalk = !std::is_same<TABLE, CompactRows>::value;
+  constexpr bool kWalk = std::is_same<TABLE, CompactDown>::value;
   const int stride = gridDim.x / kXcds;  // kWalk: the grid is one-dimensional
   const int last = __builtin_amdgcn_readfirstlane(xcd_first[xcd + 1]);
   const int first = __builtin_amdgcn_readfirstlane(xcd_first[xcd]);
@@ -1006,7 +1057,8 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
     if (work_off[mid] <= logical) lo = mid; else hi = mid;
   }
   const int e = __builtin_amdgcn_readfirstlane(lo);
-  const ExpertGeom g = expert_geom(tab, e, d_model);
+  ExpertGeom g = expert_geom(tab, e, d_model);
+  g.n_ext = __builtin_amdgcn_readfirstlane(g.n_ext);
   // the expert's rows of the hidden buffer: row of bucket slot s at hid_e + s * hid_ld
   const int64_t hid_ld = hidden_ld(tab, e, k_round);
   const uint64_t hid_off = (uint64_t)sc.hid_off[e];
@@ -1015,9 +1067,10 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   EpiArgs ep = ep_launch;
   const __hip_bfloat16* A = X;
   int64_t lda = ldx;
-  if constexpr (EPI == kEpiHidden) {
+  if constexpr (epi_hidden(EPI)) {
     ep.hidden = static_cast<__hip_bfloat16*>(ep_launch.hidden) + hid_e;
     ep.ld_hidden = hid_ld;
+    if constexpr (EPI == kEpiListed) ep.list = tab.list + (int64_t)e * tab.d_ff;
   } else {
     A = X + hid_e;
     lda = hid_ld;
@@ -1180,8 +1233,8 @@ __global__ __launch_bounds__(256, 6) void grouped_gemm_f32_kernel(
 
   // accumulator element i of a lane: token row 4*quarter + i of the 16-row block, channel col
   const int c = n0 + wave_n * 16 + col;
-  float kept = 1.0f;
-  if constexpr (EPI == kEpiHidden) kept = (c >= d_ff || ep.keep == nullptr || ep.keep[(int64_t)e * d_ff + c]) ? 1.0f : 0.0f;
+  bool kept = true;
+  if constexpr (EPI == kEpiHidden) kept = c >= d_ff || ep.keep == nullptr || ep.keep[(int64_t)e * d_ff + c] != 0;
   float sum = 0.0f, mx = 0.0f;
 #pragma unroll
   for (int b = 0; b < 2; ++b)
@@ -1197,7 +1250,7 @@ __global__ __launch_bounds__(256, 6) void grouped_gemm_f32_kernel(
       } else {
         const float lam = s_a[row] * silu_f32(acc_g[b][i]) * acc_u[b][i];
         if constexpr (EPI == kEpiHidden) {
-          if (row < m_len && c < d_ff) static_cast<float*>(ep.hidden)[out_row * ep.ld_hidden + c] = lam * kept;
+          if (row < m_len && c < d_ff) static_cast<float*>(ep.hidden)[out_row * ep.ld_hidden + c] = kept ? lam : 0.0f;
         } else {
           const float sq = row < m_len ? lam * lam : 0.0f;
           sum += sq;
@@ -1220,6 +1273,54 @@ __global__ __launch_bounds__(256, 6) void grouped_gemm_f32_kernel(
       ep.part_max[(int64_t)slot * d_ff + n0 + tid] = fmaxf(s_red[1][0][tid], s_red[1][1][tid]);
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// The kept micro-experts of a mask, expert by expert: count [n_experts], list [n_experts][d_ff] ascending.  A workgroup per
+// expert; a thread counts a run of flags, takes the prefix and writes its run's entries.
+// ---------------------------------------------------------------------------
+constexpr int kListThreads = 1024;
+__global__ __launch_bounds__(kListThreads) void keep_list_kernel(const uint8_t* __restrict__ keep, int d_ff,
+                                                                 int32_t* __restrict__ count, int32_t* __restrict__ list) {
+  __shared__ int32_t wave_total[kListThreads / kWave];
+  const int e = blockIdx.x, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const uint8_t* flags = keep + (int64_t)e * d_ff;
+  const int begin = (int)((int64_t)d_ff * tid / kListThreads), end = (int)((int64_t)d_ff * (tid + 1) / kListThreads);
+  int mine = 0;
+#pragma unroll 8
+  for (int c = begin; c < end; ++c) mine += flags[c] != 0;
+  int incl = mine;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int up = __shfl_up(incl, d);
+    if (lane >= d) incl += up;
+  }
+  if (lane == kWave - 1) wave_total[wave] = incl;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) incl += wave_total[w];
+  if (tid == kListThreads - 1) count[e] = incl;
+  int32_t* out = list + (int64_t)e * d_ff + (incl - mine);
+#pragma unroll 8
+  for (int c = begin; c < end; ++c)
+    if (flags[c] != 0) *out++ = c;
+}
+
+// Zeros in the hidden rows of the experts that do not keep everything; a workgroup per bucket slot, a row of d_ff (a multiple
+// of 8) elements.
+__global__ __launch_bounds__(256) void zero_hidden_kernel(const int32_t* __restrict__ offsets, int n_experts,
+                                                          const int32_t* __restrict__ count, int d_ff,
+                                                          u32x4* __restrict__ hidden) {
+  const int slot = linear_block();
+  if (slot >= offsets[n_experts]) return;
+  int lo = 0, hi = n_experts;  // offsets[lo] <= slot < offsets[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (offsets[mid] <= slot) lo = mid; else hi = mid;
+  }
+  if (count[lo] == d_ff) return;
+  const int vecs = d_ff / 8;
+  u32x4* row = hidden + (int64_t)slot * vecs;
+  for (int v = threadIdx.x; v < vecs; v += 256) row[v] = u32x4{0, 0, 0, 0};
 }
 
 // Shape of the bf16 kernel: waves (M x N), 32x32 blocks per wave (M x N), K tile, stages of the token ring, stages
@@ -1272,7 +1373,7 @@ hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int
                                int64_t d_ff, int n_experts, const void* W_gate, const void* W_up,
                                int64_t stride_gu, int max_tiles, const BucketTables& t, const GemmEpilogue& e) {
   if (max_tiles <= 0) return hipSuccess;
-  EpiArgs ep{e.part_phi2, e.part_max, e.hidden, e.keep, e.product, e.ld_product, e.col_gap, d_ff, 0, e.stream_product ? 1 : 0};
+  EpiArgs ep{e.part_phi2, e.part_max, e.hidden, e.keep, nullptr, e.product, e.ld_product, e.col_gap, d_ff, 0, e.stream_product ? 1 : 0};
   if (dtype == CAMERA_BF16) {
     switch (e.mode) {
       case GemmEpilogue::kStats:
@@ -1304,7 +1405,9 @@ static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx,
   // tail: some K extent is not a multiple of the K tile, or an operand is too large for 32-bit offsets
   using C = Bf16Cfg;
   int64_t a_ld = ldx, b_rows = 0, b_ld = d_model;
-  if constexpr (std::is_same<TABLE, CompactRows>::value) {
+  if constexpr (std::is_same<TABLE, KeptRows>::value) {
+    b_rows = tab.d_ff;
+  } else if constexpr (std::is_same<TABLE, CompactRows>::value) {
     for (int e = 0; e < tab.n_experts; ++e) b_rows = std::max<int64_t>(b_rows, tab.row_off[e + 1] - tab.row_off[e]);
   } else {
     b_rows = d_model;
@@ -1325,7 +1428,7 @@ static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx,
   // its XCD's range where the cuts by cost give that XCD more (cheaper) tiles than that, or the grid ends at one row.
   int64_t n_blocks = (max_tiles * n_tiles_n_max + kXcds - 1) / kXcds * kXcds;
   if (n_blocks == 0) return hipGetLastError();
-  if (!std::is_same<TABLE, CompactRows>::value) n_blocks = std::min(int64_t(1) << kGridWidthLog2, n_blocks);
+  if (std::is_same<TABLE, CompactDown>::value) n_blocks = std::min(int64_t(1) << kGridWidthLog2, n_blocks);
   if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, launch_grid(n_blocks), dim3(C::kThreads), C::kSmemBytes, stream,
                      static_cast<const __hip_bfloat16*>(X), ldx, (int)d_model, static_cast<const __hip_bfloat16*>(Wg),
@@ -1338,16 +1441,30 @@ hipError_t launch_compact_hidden_gemm(hipStream_t stream, const void* X, int64_t
                                       const void* W_gate, const void* W_up, const CompactRows& tab, int widest,
                                       int max_tiles, const BucketTables& t, int32_t* scratch, void* hidden,
                                       int k_round) {
-  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, 0, 0, 0, k_round, 0};
+  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, 0, k_round, 0};
   return launch_compact<kEpiHidden>(stream, X, ldx, d_model, W_gate, W_up, tab, k_round, d_model % Bf16Cfg::KT != 0,
                                     (widest + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep);
+}
+
+hipError_t launch_kept_hidden_gemm(hipStream_t stream, const void* X, int64_t ldx, int64_t d_model, int64_t d_ff,
+                                   int n_experts, const void* W_gate, const void* W_up, int64_t stride_gu,
+                                   const uint8_t* keep, int max_tiles, int64_t n_pairs, const BucketTables& t, int32_t* kept,
+                                   int32_t* scratch, void* hidden) {
+  int32_t* list = kept + n_experts;
+  hipLaunchKernelGGL(keep_list_kernel, dim3(n_experts), dim3(kListThreads), 0, stream, keep, (int)d_ff, kept, list);
+  hipLaunchKernelGGL(zero_hidden_kernel, launch_grid(n_pairs), dim3(256), 0, stream, t.offsets, n_experts, kept, (int)d_ff,
+                     static_cast<u32x4*>(hidden));
+  const KeptRows tab{n_experts, (int)d_ff, stride_gu, kept, list};
+  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, d_ff, 0, 0};
+  return launch_compact<kEpiListed>(stream, X, ldx, d_model, W_gate, W_up, tab, 8, d_model % Bf16Cfg::KT != 0,
+                                    (d_ff + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep);
 }
 
 hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int64_t d_model, const void* W_down,
                                     const CompactDown& tab, int max_tiles, const BucketTables& t, int32_t* scratch,
                                     float* product, bool stream_product) {
   const int64_t half = d_model / 2;
-  EpiArgs ep{nullptr, nullptr, nullptr, nullptr, product, d_model, (int)half, 0, 0, stream_product ? 1 : 0};
+  EpiArgs ep{nullptr, nullptr, nullptr, nullptr, nullptr, product, d_model, (int)half, 0, 0, stream_product ? 1 : 0};
   return launch_compact<kEpiProduct>(stream, hidden, 0, d_model, W_down, W_down, tab, tab.k_round,
                                      tab.k_round % Bf16Cfg::KT != 0, (half + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t,
                                      scratch, ep);

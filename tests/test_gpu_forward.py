@@ -153,6 +153,31 @@ def test_bucket_order_in_one_launch(cam, compact, top_k, experts, n_shared):
             assert torch.equal(forward(lo, lo + size), whole[lo:lo + size]), (size, lo)
 
 
+@pytest.mark.parametrize("d_model,dense", [(2048, False), (2056, False), (2048, True)])
+def test_kept_micro_experts_by_list(cam, d_model, dense):
+    """From 4e10 products on a masked call computes the kept micro-experts only.  A token's output does not depend on the
+    batch, so the call on all tokens equals the calls on its parts, which compute all of them and zero the pruned ones, bit
+    for bit: experts that keep about half, everything, nothing, the ends, and runs of all alignments."""
+    cfg = small(n_tokens=2500 if not dense else 1250, d_model=d_model, d_ff=4104, n_experts=5, top_k=2, outlier_channels=0)
+    assert cfg.n_tokens * (cfg.n_experts if dense else cfg.top_k) * d_model * cfg.d_ff >= 4e10
+    dev = inputs.make_layer(cfg, 0, device="cuda")
+    X = dev["X"]
+    idx, w = (None, None) if dense else cam.route_topk(X, dev["W_r"], dev["bias"], cfg.top_k)
+    keep = (torch.rand((cfg.n_experts, cfg.d_ff), generator=torch.Generator().manual_seed(3)) < 0.5).to(torch.uint8)
+    keep[1], keep[2], keep[3] = 1, 0, 0
+    keep[3, [0, cfg.d_ff - 1]] = 1
+    keep[4] = (torch.arange(cfg.d_ff) % 13 < 9).to(torch.uint8) * 255
+    dev["W_up"][0, int(torch.nonzero(keep[0] == 0)[0])] = float("inf")  # a pruned micro-expert drops out whatever it holds
+    keep = keep.flatten().cuda()
+
+    def forward(lo, hi):
+        part = (None, None) if dense else (idx[lo:hi], w[lo:hi])
+        return cam.layer_forward(X[lo:hi], *part, dev["W_gate"], dev["W_up"], dev["W_down"], keep_mask=keep)
+    whole, third = forward(0, cfg.n_tokens), cfg.n_tokens // 3
+    assert torch.isfinite(whole).all() and whole.abs().max() > 0
+    assert torch.equal(whole, torch.cat([forward(0, third), forward(third, 2 * third), forward(2 * third, cfg.n_tokens)]))
+
+
 @pytest.mark.parametrize("compact", [False, True])
 def test_product_rows_past_the_caches(cam, compact):
     """From 256 MiB of product rows on they are stored and read past the caches.  A token's output does not depend on the
