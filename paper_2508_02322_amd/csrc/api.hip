@@ -563,7 +563,11 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   plan.take(cv, dense, true, n_experts, n_pairs, max_tiles, n_blocks);
   const size_t es = dtype == CAMERA_BF16 ? 2 : 4;
   const size_t o_hidden = cv.take(es * (size_t)n_pairs * d_ff);
-  const size_t o_product = cv.take(sizeof(float) * (size_t)n_pairs * d_model);
+  const int64_t m_tiles = dense ? max_tiles : camera::expected_m_tiles(n_pairs, n_experts);
+  const int k_parts = dtype != CAMERA_BF16 ? 1
+                                           : camera::product_k_parts(m_tiles * ((d_model / 2 + 127) / 128), d_ff,
+                                                                     (int64_t)sizeof(float) * n_pairs * d_model);
+  const size_t o_product = cv.take(sizeof(float) * (size_t)k_parts * n_pairs * d_model);
   const bool by_list = keep_mask != nullptr && dtype == CAMERA_BF16 && camera::masks_by_list(n_pairs, d_model, d_ff);
   const size_t o_kept = cv.take(by_list ? sizeof(int32_t) * (size_t)(n_micro + n_experts) : 0);
   const size_t o_work = cv.take(by_list ? sizeof(int32_t) * camera::kCompactGemmScratchWords : 0);
@@ -613,6 +617,8 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
     ep.ld_product = d_model;
     ep.col_gap = (int)half;
     ep.stream_product = streams;
+    ep.k_parts = k_parts;
+    ep.part_stride = n_pairs * d_model;
     const char* wd = static_cast<const char*>(W_down);
     CAMERA_HIP(camera::launch_grouped_gemm(stream, dtype, hidden, d_ff, d_ff, half, n_experts, wd,
                                            wd + es * half * d_ff, stride_down, max_tiles, t, ep),
@@ -621,7 +627,7 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   {
     Bracket b(ctx, stream, CAMERA_K_COMBINE);
     CAMERA_HIP(camera::launch_combine(stream, product, t.slot_of, n, top_k, n_experts, d_model,
-                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, Y),
+                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, k_parts, n_pairs * d_model, Y),
                "combine launch");
   }
   return CAMERA_OK;
@@ -713,7 +719,12 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   const size_t o_idx_aug = cv.take(append ? sizeof(int32_t) * n_pairs : 0);
   const size_t o_w_aug = cv.take(append ? sizeof(float) * n_pairs : 0);
   const size_t o_hidden = cv.take(2 * (size_t)n_pairs * ldh);
-  const size_t o_product = cv.take(sizeof(float) * (size_t)(mfma ? 1 : most_chunks) * n_pairs * d_model);
+  int k_parts = 1;
+  if (mfma) {
+    const int64_t m_tiles = dense ? max_tiles : camera::expected_m_tiles(n * top_k, n_experts) + n_shared * ((n + tile_m - 1) / tile_m);
+    k_parts = camera::product_k_parts(m_tiles * ((d_model / 2 + 127) / 128), rows / total, (int64_t)sizeof(float) * n_pairs * d_model);
+  }
+  const size_t o_product = cv.take(sizeof(float) * (size_t)(mfma ? k_parts : most_chunks) * n_pairs * d_model);
   const size_t o_work = cv.take(sizeof(int32_t) * (mfma ? camera::kCompactGemmScratchWords : camera::kCompactWorkWords));
 
   DeviceGuard guard;
@@ -763,12 +774,12 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     {
       Bracket b(ctx, stream, CAMERA_K_DOWN_GEMM);
       CAMERA_HIP(camera::launch_compact_down_gemm(stream, hidden, d_model, W_down_c, tab_down, max_tiles, t, work,
-                                                  product, streams),
+                                                  product, streams, k_parts, n_pairs * d_model),
                  "compact down gemm launch");
     }
     Bracket b(ctx, stream, CAMERA_K_COMBINE);
     CAMERA_HIP(camera::launch_combine(stream, product, t.slot_of, n, terms, n_experts, d_model,
-                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, Y),
+                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, k_parts, n_pairs * d_model, Y),
                "combine launch");
     return CAMERA_OK;
   }

@@ -75,7 +75,18 @@ struct GemmEpilogue {
   int64_t ld_product = 0;
   int col_gap = 0;
   bool stream_product = false;
+  int k_parts = 1;          // parts of K, each with product rows of its own, part_stride floats apart
+  int64_t part_stride = 0;
 };
+// Into how many parts the K extent of the second contraction is cut when there are about `tiles` tiles: as many as make the
+// 256 compute units' rounds of tiles (1.4 us per K tile of 64, 5 us around them) shortest with the product rows that every
+// part writes and the combine reads (6 TB/s while they fit the memory-side cache), if that saves a sixth.  Second
+// contraction, us, whole / in parts: 2048 tokens of the Mixtral shape, 320 tiles of 224 K tiles, 546 / 441 (and 9 -> 23 per
+// combine); 500 tokens of 6 experts and a shared one of 8192, 72 tiles, 132 / 59; 300 tokens of 4 experts, 4096 wide, 64 tiles
+// 63 / 40; 100 tokens, 8 experts of 4096 channels, 1024 wide, 36 / 16.
+int product_k_parts(int64_t tiles, int64_t k_ext, int64_t product_bytes);
+// About as many token tiles as `pairs` spread over n_experts make: one of each, or half a tile of each is padding.
+int64_t expected_m_tiles(int64_t pairs, int64_t n_experts);
 // Whether the product rows of `pairs` slots go past the caches on their way out (second contraction) and back in
 // (combine): from 256 MiB on, which is what the memory-side cache holds, they only displace each other in it.  Second
 // contraction + combine, us, through the caches / past them: 537 MB 291 + 128 / 280 + 107 (8192 tokens of the DeepSeek
@@ -146,9 +157,11 @@ hipError_t launch_full_rank(hipStream_t stream, const float* energy, int64_t n_m
 // ---- forward.hip -----------------------------------------------------------
 // Y[token] (+)= sum of the product rows of the token's slots (routed: slot_of[token*top_k + k], k ascending;
 // slot_of == nullptr: rows e*n + token for e ascending).  product is [pairs][d_model] float32, Y [n][d_model].
-// stream_product: the rows are read once, past the caches (see product_streams).
+// stream_product: the rows are read once, past the caches (see product_streams).  A slot's row is the sum of its k_parts rows,
+// part_stride floats apart, in order.
 hipError_t launch_combine(hipStream_t stream, const float* product, const int32_t* slot_of, int64_t n, int top_k,
-                          int n_experts, int64_t d_model, int accumulate, bool stream_product, float* Y);
+                          int n_experts, int64_t d_model, int accumulate, bool stream_product, int k_parts,
+                          int64_t part_stride, float* Y);
 // per_token [n][4] = ||y - y_hat||^2, ||y||^2, ||y_hat||^2, <y, y_hat>
 hipError_t launch_output_error(hipStream_t stream, const float* Y, const float* Y_hat, int64_t n, int64_t d_model,
                                int64_t ldy, int64_t ldh, float* per_token);
@@ -242,7 +255,7 @@ inline bool masks_by_list(int64_t n_pairs, int64_t d_model, int64_t d_ff) {
 }
 hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int64_t d_model, const void* W_down,
                                     const CompactDown& tab, int max_tiles, const BucketTables& t, int32_t* scratch,
-                                    float* product, bool stream_product);
+                                    float* product, bool stream_product, int k_parts, int64_t part_stride);
 
 // Gather of kept micro-experts (gather.hip).  off: [n_experts + 1] exclusive prefix of the per-expert
 // entry counts (count == nullptr: d_ff each), off_ld: the same of the counts rounded up to a multiple of

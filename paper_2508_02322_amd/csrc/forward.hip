@@ -25,8 +25,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const f32x4* __restrict__ product,
                                                            const int32_t* __restrict__ slot_of, int64_t n, int top_k,
-                                                           int n_experts, int vecs, int accumulate,
-                                                           f32x4* __restrict__ Y) {
+                                                           int n_experts, int vecs, int accumulate, int k_parts,
+                                                           int64_t part_stride, f32x4* __restrict__ Y) {
   const int64_t tok = blockIdx.x;
   const int v = (int)(blockIdx.y * blockDim.x + threadIdx.x);
   if (v >= vecs) return;
@@ -45,6 +45,15 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const f32x4* __restri
     for (int u = 0; u < kTerms; ++u)
       if (row[u] >= 0)  // below 0: past the last term, or an expert id outside the group
         p[u] = STREAM ? __builtin_nontemporal_load(product + row[u] * vecs + v) : product[row[u] * vecs + v];
+    for (int part = 1; part < k_parts; ++part) {
+      f32x4 q[kTerms];
+#pragma unroll
+      for (int u = 0; u < kTerms; ++u)
+        if (row[u] >= 0) q[u] = product[part * part_stride + row[u] * vecs + v];
+#pragma unroll
+      for (int u = 0; u < kTerms; ++u)
+        if (row[u] >= 0) p[u] += q[u];
+    }
 #pragma unroll
     for (int u = 0; u < kTerms; ++u) {
       if (row[u] >= 0) s += p[u];
@@ -88,13 +97,14 @@ __global__ __launch_bounds__(kThreads) void output_error_kernel(const float* __r
 }  // namespace
 
 hipError_t launch_combine(hipStream_t stream, const float* product, const int32_t* slot_of, int64_t n, int top_k,
-                          int n_experts, int64_t d_model, int accumulate, bool stream_product, float* Y) {
+                          int n_experts, int64_t d_model, int accumulate, bool stream_product, int k_parts,
+                          int64_t part_stride, float* Y) {
   if (n <= 0) return hipSuccess;
   const int vecs = (int)(d_model / 4);
   const int threads = vecs < kThreads ? (vecs + kWave - 1) / kWave * kWave : kThreads;
   hipLaunchKernelGGL(stream_product ? combine_kernel<true> : combine_kernel<false>, dim3((unsigned)n, (unsigned)((vecs + threads - 1) / threads)), dim3(threads), 0,
                      stream, reinterpret_cast<const f32x4*>(product), slot_of, n, top_k, n_experts, vecs, accumulate,
-                     reinterpret_cast<f32x4*>(Y));
+                     k_parts, part_stride / 4, reinterpret_cast<f32x4*>(Y));
   return hipGetLastError();
 }
 

@@ -110,6 +110,8 @@ struct EpiArgs {
   int64_t ld_hidden;       // row stride of hidden (d_ff when every expert has the same width)
   int pad_hidden;          // != 0: columns from d_ff up to the next multiple of it are written as zeros (8 or 64)
   int stream_product;      // != 0: product rows go past the caches (see product_streams)
+  int k_parts;             // parts of K (see product_k_parts); part p writes product + p * part_stride
+  int64_t part_stride;
 };
 
 // One wave instruction of the direct global -> LDS path: lane l's 16 bytes at p (+ IMM) go to LDS bytes
@@ -842,6 +844,17 @@ __device__ __forceinline__ void run_tile(const TileWork& w, const __hip_bfloat16
 #undef CAMERA_TILE_FN
 }
 
+// Part `part` of `parts` of a K extent, in whole K tiles but for its end; empty where there are fewer tiles than parts.
+struct KPart {
+  int begin, length;
+};
+template <class C>
+__device__ __forceinline__ KPart k_part(int k_ext, int part, int parts) {
+  const int tiles = (k_ext + C::KT - 1) / C::KT;
+  const int begin = tiles * part / parts * C::KT, end = min(k_ext, tiles * (part + 1) / parts * C::KT);
+  return {begin, max(0, end - begin)};
+}
+
 template <class C, bool TAIL, int EPI>
 __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf16_kernel(
     const __hip_bfloat16* __restrict__ X, int64_t ldx, int d_model, int d_ff,
@@ -863,8 +876,16 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   const int total = tile_offset[n_experts] * n_tiles_n;
   const int per_xcd = (total + kXcds - 1) / kXcds;
   const int block = linear_block();
-  const int seq = block / kXcds;
-  const int logical = (block % kXcds) * per_xcd + seq;
+  int seq = block / kXcds;
+  const int first = (block % kXcds) * per_xcd;
+  int part = 0;
+  if constexpr (EPI == kEpiProduct) {  // the tiles of an XCD with the first part of K, then with the second, ...
+    const int here = max(0, min(per_xcd, total - first));
+    if (seq >= here * ep.k_parts) return;
+    part = seq / here;
+    seq -= part * here;
+  }
+  const int logical = first + seq;
   if (seq >= per_xcd || logical >= total) return;  // block-uniform: nothing here
   const int e = tile_expert[logical / n_tiles_n];  // expert e owns logical ids tile_offset[e] * n_tiles_n ..
   const int m_e = tile_offset[e + 1] - tile_offset[e];
@@ -892,7 +913,14 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   w.n0 = n0;
   w.tok_first = tile_in_expert * BM;
   constexpr int kAux = C::kAliasAux ? 0 : C::kRingBytes;  // the per-tile arrays
-  run_tile<C, TAIL, EPI, kAux>(w, X, ldx, d_model, d_ff, Wg, Wu, stride_gu, d_model, perm, w_perm, zeros, ep);
+  if constexpr (EPI == kEpiProduct) {
+    const KPart k = k_part<C>(d_model, part, ep.k_parts);
+    ep.product += part * ep.part_stride;
+    run_tile<C, TAIL, EPI, kAux>(w, X + k.begin, ldx, k.length, d_ff, Wg + k.begin, Wu + k.begin, stride_gu, d_model, perm, w_perm,
+                                 zeros, ep);
+  } else {
+    run_tile<C, TAIL, EPI, kAux>(w, X, ldx, d_model, d_ff, Wg, Wu, stride_gu, d_model, perm, w_perm, zeros, ep);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1049,7 +1077,14 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   const int stride = gridDim.x / kXcds;  // kWalk: the grid is one-dimensional
   const int last = __builtin_amdgcn_readfirstlane(xcd_first[xcd + 1]);
   const int first = __builtin_amdgcn_readfirstlane(xcd_first[xcd]);
-  for (int logical = first + block / kXcds; logical < last; logical += stride) {
+  const int here = last - first;
+  const int units = kWalk ? here * ep_launch.k_parts : here;  // the tiles with the first part of K, then with the second, ...
+  for (int unit = block / kXcds; unit < units; unit += stride) {
+  int part = 0, logical = first + unit;
+  if constexpr (kWalk) {
+    part = unit / here;
+    logical -= part * here;
+  }
   if constexpr (kWalk) __syncthreads();  // the previous tile's per-tile arrays in LDS are no longer read
   int lo = 0, hi = n_experts;                      // work_off[lo] <= logical < work_off[hi]
   while (hi - lo > 1) {
@@ -1094,8 +1129,11 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   const int m_len = min(BM, offsets[e + 1] - row_first);  // >= 1
   const int n0 = tile_n * BN;
 
+  KPart k{0, g.k_ext};
   if constexpr (EPI == kEpiProduct) {
-    if (g.k_ext == 0) {  // the expert keeps nothing: its product rows are zero
+    k = k_part<C>(g.k_ext, part, ep.k_parts);
+    ep.product += part * ep.part_stride;
+    if (k.length == 0) {  // the expert keeps nothing (in this part): its product rows are zero
       const int width = min(BN, g.n_ext - n0);
       for (int i = threadIdx.x; i < m_len * width; i += C::kThreads) {
         float* row = ep.product + (int64_t)(row_first + i / width) * ep.ld_product + n0 + i % width;
@@ -1113,7 +1151,8 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   w.n0 = n0;
   w.tok_first = tile_in_expert * BM;
   constexpr int kAux = C::kAliasAux ? 0 : C::kRingBytes;  // the per-tile arrays
-  run_tile<C, TAIL, EPI, kAux>(w, A, lda, g.k_ext, g.n_ext, Wg + g.g_off, Wu + g.u_off, 0, g.ldw, perm, w_perm, zeros, ep);
+  run_tile<C, TAIL, EPI, kAux>(w, A + k.begin, lda, k.length, g.n_ext, Wg + g.g_off + k.begin, Wu + g.u_off + k.begin, 0, g.ldw, perm,
+                               w_perm, zeros, ep);
   if constexpr (!kWalk) break;
   }
 }
@@ -1337,6 +1376,23 @@ bool fits_32bit_offsets(int64_t a_rows, int64_t lda, int64_t b_rows, int64_t ldw
 
 }  // namespace
 
+int product_k_parts(int64_t tiles, int64_t k_ext, int64_t product_bytes) {
+  constexpr int kCus = 256, kMost = 8, kFewestTiles = 8;
+  const int64_t k_tiles = (k_ext + Bf16Cfg::KT - 1) / Bf16Cfg::KT;
+  auto us = [&](int parts) {
+    const int64_t rounds = (tiles * parts + kCus - 1) / kCus;
+    return rounds * (1.4 * (double)k_tiles / parts + 5.0) + 2.0 * parts * (double)product_bytes / 6e6;
+  };
+  int best = 1;
+  for (int p = 2; p <= kMost && p * kFewestTiles <= k_tiles && p * product_bytes < (int64_t(256) << 20); ++p)
+    if (us(p) < us(best)) best = p;
+  return us(best) < 0.85 * us(1) ? best : 1;
+}
+int64_t expected_m_tiles(int64_t pairs, int64_t n_experts) {
+  const int64_t used = std::max<int64_t>(1, std::min(pairs, n_experts));
+  return pairs <= used * Bf16Cfg::BM ? used : pairs / Bf16Cfg::BM + used / 2;
+}
+
 int gemm_tile_m(int dtype, int64_t d_ff) {
   (void)d_ff;
   return dtype == CAMERA_BF16 ? Bf16Cfg::BM : F32_BM;
@@ -1360,7 +1416,7 @@ static hipError_t launch_bf16(hipStream_t stream, const void* X, int64_t ldx, in
   static OncePerDevice lds_allowed[2];
   if (hipError_t err = allow_lds(lds_allowed[tail], reinterpret_cast<const void*>(kern), C::kSmemBytes); err != hipSuccess) return err;
   const int64_t n_tiles_n = (d_ff + C::BN - 1) / C::BN;
-  const int64_t n_blocks = (max_tiles * n_tiles_n + kXcds - 1) / kXcds * kXcds;
+  const int64_t n_blocks = (max_tiles * n_tiles_n + kXcds - 1) / kXcds * kXcds * ep.k_parts;
   if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, launch_grid(n_blocks), dim3(C::kThreads), C::kSmemBytes, stream, static_cast<const __hip_bfloat16*>(X), ldx,
                      (int)d_model, (int)d_ff, static_cast<const __hip_bfloat16*>(W_gate),
@@ -1373,7 +1429,8 @@ hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int
                                int64_t d_ff, int n_experts, const void* W_gate, const void* W_up,
                                int64_t stride_gu, int max_tiles, const BucketTables& t, const GemmEpilogue& e) {
   if (max_tiles <= 0) return hipSuccess;
-  EpiArgs ep{e.part_phi2, e.part_max, e.hidden, e.keep, nullptr, e.product, e.ld_product, e.col_gap, d_ff, 0, e.stream_product ? 1 : 0};
+  EpiArgs ep{e.part_phi2, e.part_max, e.hidden, e.keep, nullptr, e.product, e.ld_product, e.col_gap, d_ff, 0, e.stream_product ? 1 : 0,
+             e.k_parts, e.part_stride};
   if (dtype == CAMERA_BF16) {
     switch (e.mode) {
       case GemmEpilogue::kStats:
@@ -1426,7 +1483,7 @@ static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx,
                      t.offsets, t.tile_offset, scratch);
   // an upper bound of the tile count, shared evenly between the XCDs.  In the second contraction a workgroup walks on through
   // its XCD's range where the cuts by cost give that XCD more (cheaper) tiles than that, or the grid ends at one row.
-  int64_t n_blocks = (max_tiles * n_tiles_n_max + kXcds - 1) / kXcds * kXcds;
+  int64_t n_blocks = (max_tiles * n_tiles_n_max + kXcds - 1) / kXcds * kXcds * ep.k_parts;
   if (n_blocks == 0) return hipGetLastError();
   if (std::is_same<TABLE, CompactDown>::value) n_blocks = std::min(int64_t(1) << kGridWidthLog2, n_blocks);
   if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
@@ -1441,7 +1498,7 @@ hipError_t launch_compact_hidden_gemm(hipStream_t stream, const void* X, int64_t
                                       const void* W_gate, const void* W_up, const CompactRows& tab, int widest,
                                       int max_tiles, const BucketTables& t, int32_t* scratch, void* hidden,
                                       int k_round) {
-  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, 0, k_round, 0};
+  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, 0, k_round, 0, 1, 0};
   return launch_compact<kEpiHidden>(stream, X, ldx, d_model, W_gate, W_up, tab, k_round, d_model % Bf16Cfg::KT != 0,
                                     (widest + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep);
 }
@@ -1455,16 +1512,17 @@ hipError_t launch_kept_hidden_gemm(hipStream_t stream, const void* X, int64_t ld
   hipLaunchKernelGGL(zero_hidden_kernel, launch_grid(n_pairs), dim3(256), 0, stream, t.offsets, n_experts, kept, (int)d_ff,
                      static_cast<u32x4*>(hidden));
   const KeptRows tab{n_experts, (int)d_ff, stride_gu, kept, list};
-  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, d_ff, 0, 0};
+  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, d_ff, 0, 0, 1, 0};
   return launch_compact<kEpiListed>(stream, X, ldx, d_model, W_gate, W_up, tab, 8, d_model % Bf16Cfg::KT != 0,
                                     (d_ff + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep);
 }
 
 hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int64_t d_model, const void* W_down,
                                     const CompactDown& tab, int max_tiles, const BucketTables& t, int32_t* scratch,
-                                    float* product, bool stream_product) {
+                                    float* product, bool stream_product, int k_parts, int64_t part_stride) {
   const int64_t half = d_model / 2;
-  EpiArgs ep{nullptr, nullptr, nullptr, nullptr, nullptr, product, d_model, (int)half, 0, 0, stream_product ? 1 : 0};
+  EpiArgs ep{nullptr, nullptr, nullptr, nullptr, nullptr, product, d_model, (int)half, 0, 0, stream_product ? 1 : 0, k_parts,
+             part_stride};
   return launch_compact<kEpiProduct>(stream, hidden, 0, d_model, W_down, W_down, tab, tab.k_round,
                                      tab.k_round % Bf16Cfg::KT != 0, (half + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t,
                                      scratch, ep);

@@ -79,6 +79,15 @@ def test_compacted_layer_output_matches_oracle(cam, case):
         print(f"{case} keep {frac}: rel err {err:.2e}, against the masked layer {err_masked:.2e}, counts {count[:6]}")
 
 
+@pytest.mark.parametrize("case", [
+    dict(n_tokens=300, d_model=64, d_ff=2056, n_experts=2, top_k=1),    # 33 K tiles in four parts, the last with a K tail
+    dict(n_tokens=200, d_model=272, d_ff=1600, n_experts=3, top_k=2),   # 25 in three, two column tiles
+    dict(n_tokens=270, d_model=64, d_ff=8000, n_experts=4, top_k=1),    # an expert whose parts are all empty beside long ones
+])
+def test_second_contraction_in_parts_of_k(cam, case):
+    test_compacted_layer_output_matches_oracle(cam, case)
+
+
 def compact_layer(cam, dev, cfg, keep_r, keep_s, align):
     """Routed and shared experts compacted into one set of buffers: the shared group's rows and blocks behind the routed."""
     d = cfg.d_model

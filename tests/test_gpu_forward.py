@@ -158,7 +158,7 @@ def test_kept_micro_experts_by_list(cam, d_model, dense):
     """From 4e10 products on a masked call computes the kept micro-experts only.  A token's output does not depend on the
     batch, so the call on all tokens equals the calls on its parts, which compute all of them and zero the pruned ones, bit
     for bit: experts that keep about half, everything, nothing, the ends, and runs of all alignments."""
-    cfg = small(n_tokens=2500 if not dense else 1250, d_model=d_model, d_ff=4104, n_experts=5, top_k=2, outlier_channels=0)
+    cfg = small(n_tokens=11000 if not dense else 4500, d_model=d_model, d_ff=952, n_experts=5, top_k=2, outlier_channels=0)
     assert cfg.n_tokens * (cfg.n_experts if dense else cfg.top_k) * d_model * cfg.d_ff >= 4e10
     dev = inputs.make_layer(cfg, 0, device="cuda")
     X = dev["X"]
