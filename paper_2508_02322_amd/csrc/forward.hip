@@ -62,6 +62,9 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const f32x4* __restri
   Y[tok * vecs + v] = s;
 }
 
+// A wave per token.  VEC: four columns per lane and load (rows of whole, aligned vectors), eight loads in flight; a column at
+// a time waited for memory at every step: 2048 tokens of 4096 columns 32 -> 12.9 us, 1500 of 1024 9.9 -> 4.8.
+template <bool VEC>
 __global__ __launch_bounds__(kThreads) void output_error_kernel(const float* __restrict__ Y,
                                                                 const float* __restrict__ Y_hat, int64_t n,
                                                                 int64_t d_model, int64_t ldy, int64_t ldh,
@@ -72,12 +75,34 @@ __global__ __launch_bounds__(kThreads) void output_error_kernel(const float* __r
   const float* y = Y + tok * ldy;
   const float* h = Y_hat + tok * ldh;
   float d2 = 0.f, yy = 0.f, hh = 0.f, yh = 0.f;
-  for (int64_t c = lane; c < d_model; c += kWave) {
-    const float a = y[c], b = h[c], d = a - b;
+  auto add = [&](float a, float b) {
+    const float d = a - b;
     d2 = fmaf(d, d, d2);
     yy = fmaf(a, a, yy);
     hh = fmaf(b, b, hh);
     yh = fmaf(a, b, yh);
+  };
+  if constexpr (VEC) {
+    const f32x4* yv = reinterpret_cast<const f32x4*>(y);
+    const f32x4* hv = reinterpret_cast<const f32x4*>(h);
+    const int64_t vecs = d_model / 4;
+    for (int64_t c0 = 0; c0 < vecs; c0 += 4 * kWave) {
+      f32x4 a[4], b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t c = c0 + u * kWave + lane, in = c < vecs ? c : vecs - 1;
+        a[u] = yv[in];
+        b[u] = hv[in];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (c0 + u * kWave + lane >= vecs) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) add(a[u][i], b[u][i]);
+      }
+    }
+  } else {
+    for (int64_t c = lane; c < d_model; c += kWave) add(y[c], h[c]);
   }
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) {
@@ -112,7 +137,8 @@ hipError_t launch_output_error(hipStream_t stream, const float* Y, const float* 
                                int64_t ldy, int64_t ldh, float* per_token) {
   if (n <= 0) return hipSuccess;
   const int64_t blocks = (n + kTokensPerBlock - 1) / kTokensPerBlock;
-  hipLaunchKernelGGL(output_error_kernel, launch_grid(blocks), dim3(kThreads), 0, stream, Y, Y_hat, n, d_model, ldy,
+  const bool vec = (d_model | ldy | ldh) % 4 == 0 && (reinterpret_cast<uintptr_t>(Y) | reinterpret_cast<uintptr_t>(Y_hat)) % 16 == 0;
+  hipLaunchKernelGGL(vec ? output_error_kernel<true> : output_error_kernel<false>, launch_grid(blocks), dim3(kThreads), 0, stream, Y, Y_hat, n, d_model, ldy,
                      ldh, per_token);
   return hipGetLastError();
 }
