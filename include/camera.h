@@ -311,7 +311,9 @@ int camera_input_channel_energy(camera_ctx* ctx, void* stream,
  * With CAMERA_BF16 Lambda is rounded to bf16 before the second contraction, as the hidden activations of a
  * 16-bit model are (CAMERA_F32 keeps it in float32); both contractions accumulate in float32, and a token's experts are added in the order of its
  * top-k list (no floating-point atomics: the result does not depend on launch order).  The context
- * workspace grows by n*top_k*(2*d_ff + 4*d_model) bytes.  n == 0 does nothing.
+ * workspace grows by n*top_k*(2*d_ff + 4*d_model) bytes; where the second contraction has few tiles, its sums over d_ff
+ * are taken in up to eight parts with 4*d_model bytes each (256 MiB at most in all; how many depends on n, so a token's last
+ * bits may), and a masked call of 4e10 products n*top_k*d_model*d_ff or more needs 4*n_experts*(d_ff + 1).  n == 0 does nothing.
  *
  * camera_output_error: distance of a pruned layer's output from the original one, per token
  *   per_token [n x 4] float32 out: ||y - y_hat||^2, ||y||^2, ||y_hat||^2, <y, y_hat>
