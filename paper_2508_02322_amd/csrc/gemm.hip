@@ -30,7 +30,6 @@ namespace camera {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
@@ -91,7 +90,7 @@ constexpr int kChunkM = 4;     // otherwise this many
 
 // What a tile does with its two accumulator sets (named gate and up after their main use).
 //   kEpiStats   : Lambda = a * silu(gate) * up, column sums of Lambda^2 and column maxima -> part_phi2 / part_max
-//   kEpiHidden  : the same Lambda, times the keep flag of its micro-expert, rounded to bf16 -> hidden[slot row][channel]
+//   kEpiHidden  : the same Lambda, rounded to bf16, zero where the keep flag of its micro-expert is -> hidden[slot row][channel]
 //   kEpiProduct : the plain products -> product[slot row][column] (first B matrix) and [column + col_gap] (second);
 //                 the token rows of this mode are the bucket slots themselves (A = the hidden activations)
 //   kEpiListed  : kEpiHidden over the kept micro-experts only: tile channel i of the expert is micro-expert list[i], whose
@@ -646,14 +645,16 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
   } else if constexpr (EPI == kEpiHidden) {
     const int pad_end = ep.pad_hidden ? (d_ff + ep.pad_hidden - 1) / ep.pad_hidden * ep.pad_hidden : d_ff;
     const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four channels
-    if (col0 < pad_end) {
-      const bool whole = col0 + 3 < d_ff;  // all four inside: one vector store
-      bool kept[4] = {true, true, true, true};
-      if (ep.keep != nullptr) {
+    if (col0 < pad_end) {  // pad_end and the length of a row are multiples of 8: all four lie inside, 8-byte aligned
+      // What the keep flags leave of the four bf16 values; zeros from d_ff on, the K padding of the contraction that reads these
+      // rows.  Bits, not a choice between value and zero (a branch around every exponential) nor a multiplication (a pruned
+      // value that is not finite would stay).  First contraction, us, with the choice / now: 8192 tokens of the DeepSeek shape
+      // 506 / 483, of 4 experts of 14336 256 wide 253 / 211, compacted Qwen2 shape 2208 / 2138.
+      uint32_t kept[2] = {0, 0};
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-          kept[s] = col0 + s < d_ff && ep.keep[(int64_t)st.expert * d_ff + col0 + s] != 0;
-      }
+      for (int s = 0; s < 4; ++s)
+        if (col0 + s < d_ff && (ep.keep == nullptr || ep.keep[(int64_t)st.expert * d_ff + col0 + s] != 0))
+          kept[s / 2] |= 0xffffu << (s % 2 * 16);
 #pragma unroll
       for (int i = 0; i < ACT; ++i)
 #pragma unroll
@@ -664,20 +665,14 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
             if (row >= st.m_len) continue;
             __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(ep.hidden) + (int64_t)(st.row_first + row) * ep.ld_hidden + col0;
             const float a_tok = a_of(i, a, r, row);
-            __hip_bfloat16 lam[4];
+            uint32_t lam[4];
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-              lam[s] = __float2bfloat16(kept[s] ? a_tok * silu_f32(acc_g[i][s / 2][a][s % 2][r]) * acc_u[i][s / 2][a][s % 2][r] : 0.0f);
-            if (whole) {  // rows of the hidden buffer are multiples of 8 elements long: 8-byte aligned
-              uint2 v;
-              v.x = (uint32_t)__builtin_bit_cast(uint16_t, lam[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[1]) << 16);
-              v.y = (uint32_t)__builtin_bit_cast(uint16_t, lam[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[3]) << 16);
-              *reinterpret_cast<uint2*>(dst) = v;
-            } else {  // the last channels of the expert, then the K padding of the contraction that reads these rows
-#pragma unroll
-              for (int s = 0; s < 4; ++s)
-                if (col0 + s < pad_end) dst[s] = col0 + s < d_ff ? lam[s] : __float2bfloat16(0.0f);
-            }
+              lam[s] = __builtin_bit_cast(uint16_t, __float2bfloat16(a_tok * silu_f32(acc_g[i][s / 2][a][s % 2][r]) * acc_u[i][s / 2][a][s % 2][r]));
+            uint2 v;
+            v.x = (lam[0] | lam[1] << 16) & kept[0];
+            v.y = (lam[2] | lam[3] << 16) & kept[1];
+            *reinterpret_cast<uint2*>(dst) = v;
           }
     }
   } else {
@@ -1095,10 +1090,11 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   ExpertGeom g = expert_geom(tab, e, d_model);
   g.n_ext = __builtin_amdgcn_readfirstlane(g.n_ext);
   // the expert's rows of the hidden buffer: row of bucket slot s at hid_e + s * hid_ld
-  const int64_t hid_ld = hidden_ld(tab, e, k_round);
+  const int64_t hid_ld = __builtin_amdgcn_readfirstlane(hidden_ld(tab, e, k_round));
   const uint64_t hid_off = (uint64_t)sc.hid_off[e];
   const int64_t hid_e = (int64_t)((uint64_t)__builtin_amdgcn_readfirstlane((int)(hid_off >> 32)) << 32 |
-                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)hid_off)) - (int64_t)offsets[e] * hid_ld;
+                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)hid_off)) -
+                        __builtin_amdgcn_readfirstlane(offsets[e]) * hid_ld;
   EpiArgs ep = ep_launch;
   const __hip_bfloat16* A = X;
   int64_t lda = ldx;
@@ -1415,6 +1411,7 @@ static hipError_t launch_bf16(hipStream_t stream, const void* X, int64_t ldx, in
   auto kern = tail ? grouped_gemm_bf16_kernel<C, true, EPI> : grouped_gemm_bf16_kernel<C, false, EPI>;
   static OncePerDevice lds_allowed[2];
   if (hipError_t err = allow_lds(lds_allowed[tail], reinterpret_cast<const void*>(kern), C::kSmemBytes); err != hipSuccess) return err;
+  if (EPI == kEpiHidden && d_ff % 8 != 0) return hipErrorInvalidValue;  // its epilogue writes four channels at a time
   const int64_t n_tiles_n = (d_ff + C::BN - 1) / C::BN;
   const int64_t n_blocks = (max_tiles * n_tiles_n + kXcds - 1) / kXcds * kXcds * ep.k_parts;
   if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;

@@ -5,6 +5,7 @@
   the compiler must have no use of its own for it in these kernels.
 * The statistics kernel keeps everything in registers: no scratch memory (a scratch reload would count on the same
   in-order counter as the tile loads and stall the K loop's waits).
+* The hidden rows' epilogue takes the keep flags as bits: no branch around the exponential of a value.
 * The K loop of a full tile holds its accumulators still: no copies between accumulation and vector registers,
   128 MFMAs per K tile, one barrier.
 """
@@ -66,6 +67,19 @@ def test_statistics_kernel_uses_no_scratch(gemm_asm):
             found += 1
             assert scratch == 0, f"{name}: {scratch} bytes of scratch per lane"
     assert found == 2
+
+
+def test_hidden_epilogue_has_no_branch_per_value(gemm_asm):
+    """A lane has four values and one branch (is the row inside the tile?) per output row; with a branch per value there were
+    two and a half branches for every exponential."""
+    found = 0
+    for name, body in _functions(gemm_asm).items():
+        if not re.search(r"Lb[01]ELi1E", name):              # <TAIL, epilogue 1>, with and without per-expert widths
+            continue
+        found += 1
+        values, branches = len(re.findall(r"\bv_exp_f32", body)), len(re.findall(r"\bs_cbranch_execn?z\b", body))
+        assert values >= 512 and branches < values / 2, f"{name}: {branches} branches for {values} values"
+    assert found == 4
 
 
 def test_full_tile_loop_keeps_its_accumulators_in_place(gemm_asm):
