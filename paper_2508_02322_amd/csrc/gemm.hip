@@ -571,7 +571,6 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
     static_assert(TN == 2, "a lane's channels of the four sub-blocks are consecutive");
     const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four channels
     auto write = [&](auto stream) {
-      const bool whole = col0 + 3 < d_ff;  // all four inside: one vector store
 #pragma unroll
       for (int i = 0; i < ACT; ++i)
 #pragma unroll
@@ -587,25 +586,16 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
               u[s] = acc_u[i][s / 2][a][s % 2][r];
             }
             float* dst = ep.product + (int64_t)(st.row_first + row) * ep.ld_product + col0;
-            if (whole) {  // output rows and both column halves are multiples of 4 floats: 16-byte aligned
-              if constexpr (decltype(stream)::value) {
-                __builtin_nontemporal_store(g, reinterpret_cast<f32x4*>(dst));
-                __builtin_nontemporal_store(u, reinterpret_cast<f32x4*>(dst + ep.col_gap));
-              } else {
-                *reinterpret_cast<f32x4*>(dst) = g;
-                *reinterpret_cast<f32x4*>(dst + ep.col_gap) = u;
-              }
+            if constexpr (decltype(stream)::value) {
+              __builtin_nontemporal_store(g, reinterpret_cast<f32x4*>(dst));
+              __builtin_nontemporal_store(u, reinterpret_cast<f32x4*>(dst + ep.col_gap));
             } else {
-#pragma unroll
-              for (int s = 0; s < 4; ++s)
-                if (col0 + s < d_ff) {
-                  dst[s] = g[s];
-                  dst[s + ep.col_gap] = u[s];
-                }
+              *reinterpret_cast<f32x4*>(dst) = g;
+              *reinterpret_cast<f32x4*>(dst + ep.col_gap) = u;
             }
           }
     };
-    if (col0 < d_ff) {
+    if (col0 < d_ff) {  // output rows and both column halves are multiples of 4 floats: all four lie inside, 16-byte aligned
       if (ep.stream_product) write(std::true_type{});
       else write(std::false_type{});
     }
@@ -845,6 +835,7 @@ struct KPart {
 };
 template <class C>
 __device__ __forceinline__ KPart k_part(int k_ext, int part, int parts) {
+  if (parts == 1) return {0, k_ext};
   const int tiles = (k_ext + C::KT - 1) / C::KT;
   const int begin = tiles * part / parts * C::KT, end = min(k_ext, tiles * (part + 1) / parts * C::KT);
   return {begin, max(0, end - begin)};
@@ -877,8 +868,10 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   if constexpr (EPI == kEpiProduct) {  // the tiles of an XCD with the first part of K, then with the second, ...
     const int here = max(0, min(per_xcd, total - first));
     if (seq >= here * ep.k_parts) return;
-    part = seq / here;
-    seq -= part * here;
+    if (ep.k_parts > 1) {
+      part = seq / here;
+      seq -= part * here;
+    }
   }
   const int logical = first + seq;
   if (seq >= per_xcd || logical >= total) return;  // block-uniform: nothing here
@@ -1077,8 +1070,10 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   for (int unit = block / kXcds; unit < units; unit += stride) {
   int part = 0, logical = first + unit;
   if constexpr (kWalk) {
-    part = unit / here;
-    logical -= part * here;
+    if (ep_launch.k_parts > 1) {
+      part = unit / here;
+      logical -= part * here;
+    }
   }
   if constexpr (kWalk) __syncthreads();  // the previous tile's per-tile arrays in LDS are no longer read
   int lo = 0, hi = n_experts;                      // work_off[lo] <= logical < work_off[hi]
@@ -1411,7 +1406,7 @@ static hipError_t launch_bf16(hipStream_t stream, const void* X, int64_t ldx, in
   auto kern = tail ? grouped_gemm_bf16_kernel<C, true, EPI> : grouped_gemm_bf16_kernel<C, false, EPI>;
   static OncePerDevice lds_allowed[2];
   if (hipError_t err = allow_lds(lds_allowed[tail], reinterpret_cast<const void*>(kern), C::kSmemBytes); err != hipSuccess) return err;
-  if (EPI == kEpiHidden && d_ff % 8 != 0) return hipErrorInvalidValue;  // its epilogue writes four channels at a time
+  if (EPI != kEpiStats && d_ff % 4 != 0) return hipErrorInvalidValue;  // the epilogues that write rows write four channels at a time
   const int64_t n_tiles_n = (d_ff + C::BN - 1) / C::BN;
   const int64_t n_blocks = (max_tiles * n_tiles_n + kXcds - 1) / kXcds * kXcds * ep.k_parts;
   if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
@@ -1476,6 +1471,7 @@ static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx,
                    : grouped_gemm_bf16_compact_kernel<C, false, EPI, TABLE>;
   static OncePerDevice lds_allowed[2];
   if (hipError_t err = allow_lds(lds_allowed[tail], reinterpret_cast<const void*>(kern), C::kSmemBytes); err != hipSuccess) return err;
+  if (EPI == kEpiProduct && d_model % 8 != 0) return hipErrorInvalidValue;  // each half in groups of four columns
   hipLaunchKernelGGL((compact_work_kernel<TABLE>), dim3(1), dim3(CAMERA_MAX_EXPERTS), 0, stream, tab, (int)d_model, C::BN, C::KT, k_round,
                      t.offsets, t.tile_offset, scratch);
   // an upper bound of the tile count, shared evenly between the XCDs.  In the second contraction a workgroup walks on through

@@ -82,6 +82,18 @@ def test_hidden_epilogue_has_no_branch_per_value(gemm_asm):
     assert found == 4
 
 
+def test_product_rows_are_written_by_vectors_only(gemm_asm):
+    """Both halves of d_model are multiples of four columns: no columns one by one, whose code lay beside every vector store."""
+    found = 0
+    for name, body in _functions(gemm_asm).items():
+        if "compact" in name or not re.search(r"Lb[01]ELi2E", name):   # <TAIL, epilogue 2>
+            continue
+        found += 1
+        stores = re.findall(r"\b(?:global|flat)_store_\w+", body)
+        assert stores and all(st.endswith("store_dwordx4") for st in stores), set(stores)
+    assert found == 2
+
+
 def test_full_tile_loop_keeps_its_accumulators_in_place(gemm_asm):
     for name, body in _functions(gemm_asm).items():
         if "compact" in name or "Lb0ELi0E" not in name:      # the scoring kernel, K a multiple of the K tile
