@@ -20,9 +20,11 @@ constexpr int kTokensPerBlock = kThreads / kWave;  // one wave per token
 // grid: x = tokens, y = blockDim.x vectors of four columns each.  A workgroup has one token, so its slots are scalar
 // loads, and the rows of eight terms are in flight together: waiting for each row in turn is what a wave per token
 // spent its time on.  8192 tokens, 8 terms, 2048 wide: 143 -> 127 us; 2048 tokens, 2 terms, 4096 wide: 44 -> 19 us.
+// PARTS: a slot's row is the sum of k_parts rows.  An instance of its own: the loop takes 78 registers a lane where one row
+// takes 44: six waves per SIMD, not eight.  (STREAM needs no parts: rows that fill the cache are whole.)
 constexpr int kTerms = 8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-template <bool STREAM>
+template <bool STREAM, bool PARTS>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const f32x4* __restrict__ product,
                                                            const int32_t* __restrict__ slot_of, int64_t n, int top_k,
                                                            int n_experts, int vecs, int accumulate, int k_parts,
@@ -45,14 +47,16 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const f32x4* __restri
     for (int u = 0; u < kTerms; ++u)
       if (row[u] >= 0)  // below 0: past the last term, or an expert id outside the group
         p[u] = STREAM ? __builtin_nontemporal_load(product + row[u] * vecs + v) : product[row[u] * vecs + v];
-    for (int part = 1; part < k_parts; ++part) {
-      f32x4 q[kTerms];
+    if constexpr (PARTS) {
+      for (int part = 1; part < k_parts; ++part) {
+        f32x4 q[kTerms];
 #pragma unroll
-      for (int u = 0; u < kTerms; ++u)
-        if (row[u] >= 0) q[u] = product[part * part_stride + row[u] * vecs + v];
+        for (int u = 0; u < kTerms; ++u)
+          if (row[u] >= 0) q[u] = product[part * part_stride + row[u] * vecs + v];
 #pragma unroll
-      for (int u = 0; u < kTerms; ++u)
-        if (row[u] >= 0) p[u] += q[u];
+        for (int u = 0; u < kTerms; ++u)
+          if (row[u] >= 0) p[u] += q[u];
+      }
     }
 #pragma unroll
     for (int u = 0; u < kTerms; ++u) {
@@ -125,9 +129,11 @@ hipError_t launch_combine(hipStream_t stream, const float* product, const int32_
                           int n_experts, int64_t d_model, int accumulate, bool stream_product, int k_parts,
                           int64_t part_stride, float* Y) {
   if (n <= 0) return hipSuccess;
+  if (stream_product && k_parts > 1) return hipErrorInvalidValue;
   const int vecs = (int)(d_model / 4);
   const int threads = vecs < kThreads ? (vecs + kWave - 1) / kWave * kWave : kThreads;
-  hipLaunchKernelGGL(stream_product ? combine_kernel<true> : combine_kernel<false>, dim3((unsigned)n, (unsigned)((vecs + threads - 1) / threads)), dim3(threads), 0,
+  auto kern = stream_product ? combine_kernel<true, false> : k_parts > 1 ? combine_kernel<false, true> : combine_kernel<false, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)n, (unsigned)((vecs + threads - 1) / threads)), dim3(threads), 0,
                      stream, reinterpret_cast<const f32x4*>(product), slot_of, n, top_k, n_experts, vecs, accumulate,
                      k_parts, part_stride / 4, reinterpret_cast<f32x4*>(Y));
   return hipGetLastError();
