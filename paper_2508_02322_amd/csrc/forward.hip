@@ -67,7 +67,11 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const f32x4* __restri
 }
 
 // A wave per token.  VEC: four columns per lane and load (rows of whole, aligned vectors), eight loads in flight; a column at
-// a time waited for memory at every step: 2048 tokens of 4096 columns 32 -> 12.9 us, 1500 of 1024 9.9 -> 4.8.
+// a time waits for memory at every step: 2048 tokens of 4096 columns 32 -> 12.9 us, 1500 of 1024 9.9 -> 4.8.  From kVecColumns
+// on: a wave of vectors is 256 columns, and loads past the end are made again of the last vector.  Graph replays, us, by
+// columns / by vectors: 1500, 8192 and 50000 tokens of 64 columns 2.5 / 3.1, 4.0 / 4.6, 14.0 / 14.8, of 320 2.97 / 3.11,
+// 4.90 / 4.93, 21.5 / 19.7, of 512 3.30 / 3.13, 5.75 / 5.28, 31.1 / 30.6.
+constexpr int64_t kVecColumns = 512;
 template <bool VEC>
 __global__ __launch_bounds__(kThreads) void output_error_kernel(const float* __restrict__ Y,
                                                                 const float* __restrict__ Y_hat, int64_t n,
@@ -143,7 +147,8 @@ hipError_t launch_output_error(hipStream_t stream, const float* Y, const float* 
                                int64_t ldy, int64_t ldh, float* per_token) {
   if (n <= 0) return hipSuccess;
   const int64_t blocks = (n + kTokensPerBlock - 1) / kTokensPerBlock;
-  const bool vec = (d_model | ldy | ldh) % 4 == 0 && (reinterpret_cast<uintptr_t>(Y) | reinterpret_cast<uintptr_t>(Y_hat)) % 16 == 0;
+  const bool vec = d_model >= kVecColumns && (d_model | ldy | ldh) % 4 == 0 &&
+                   (reinterpret_cast<uintptr_t>(Y) | reinterpret_cast<uintptr_t>(Y_hat)) % 16 == 0;
   hipLaunchKernelGGL(vec ? output_error_kernel<true> : output_error_kernel<false>, launch_grid(blocks), dim3(kThreads), 0, stream, Y, Y_hat, n, d_model, ldy,
                      ldh, per_token);
   return hipGetLastError();

@@ -220,11 +220,11 @@ def test_nothing_kept_gives_zero_and_accumulate_adds_the_shared_experts(cam):
     check_output(Y_shared, O_shared, largest_term(X64, np.ones((cfg.n_tokens, 1)), gate, up, down))
 
 
-@pytest.mark.parametrize("d_model", [1, 3, 4, 63, 252, 256, 260, 1020, 1024, 1028, 4100])
+@pytest.mark.parametrize("d_model", [1, 3, 4, 63, 252, 256, 260, 508, 512, 516, 1020, 1024, 1028, 4100])
 @pytest.mark.parametrize("skip", [0, 1])
 def test_output_error_by_vectors_and_by_columns(cam, d_model, skip):
-    """Rows of whole aligned vectors go four columns at a time, others (odd widths, a start that is not on 16 bytes) one at a
-    time.  Sums of d_model products in float32, at most d_model / 64 of them one after the other: relative error of the
+    """Rows of 512 columns and more of whole aligned vectors go four columns at a time, others (narrow, of odd widths, a start
+    that is not on 16 bytes) one at a time.  Sums of d_model products in float32, at most d_model / 64 of them one after the other: relative error of the
     sums of squares below (d_model / 64 + 8) 2^-24 < 5e-6."""
     n = 37
     g = torch.Generator(device="cuda").manual_seed(d_model)
