@@ -12,7 +12,7 @@
 //             ballots (one per bit of the expert id gives the lanes of equal
 //             expert) and popcounts of the lower lanes, so equal experts keep
 //             their pair order (stable, deterministic).
-// Up to kBucketSmallPairs pairs one workgroup does all of it in one launch.
+// For few pairs one workgroup does all of it in one launch (bucket_small_kernel).
 #include "camera_internal.h"
 
 namespace camera {
@@ -214,8 +214,12 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(const int32_t*
 // all loads of a thread in flight); prefixes over the experts follow, pairs and tiles or work items in one pass.
 // Replaced, us: the three launches, 1024 pairs of 8 experts 9.6 -> 4.8 (and two gaps), 3176 pairs of 128 experts with the work
 // items 19 -> 11; four threads per expert that walked over the pairs, as decoding batches had it, 8 pairs 4.9 -> 4.0, 576
-// pairs of 65 experts 14.5 -> 5.0, 1600 of 128 30.7 -> 7.5.  Beyond 4096 pairs the general sort's workgroups are worth their
-// launches (a lone one takes 3 us for every thousand).
+// pairs of 65 experts 14.5 -> 5.0, 1600 of 128 30.7 -> 7.5.  A lone workgroup takes 3 us
+// for every thousand pairs and the general sort hardly more for many than for few, so they meet: graph replays of a call that does
+// little else, us, three launches / one: 1024 pairs of 8 experts 17.0 / 12.6, 2048 17.2 / 14.3, 3072 17.9 / 17.3, 3584 18.3 / 18.2,
+// 4096 18.0 / 18.8, of 128 experts 2048 16.2 / 13.8, 3072 16.2 / 15.9, 3584 16.4 / 17.2, 4096 16.9 / 18.2: the line lies at 3072.
+// A decoding batch saves a launch more for its work items and another for appended experts, and stays until 4096: 4096 pairs of 64
+// + 2 experts 29.5 / 26.6, of 128 3632 pairs 27.2 / 26.5, 4096 27.3 / 27.8.
 // COMPACT: pair token * (top_k + n_shared) + k is routed choice k, or for k >= top_k the appended expert n_experts + k - top_k
 // with weight 1; work [2][CAMERA_MAX_EXPERTS + 1] gets the work items.  Otherwise: the M-tile tables.
 constexpr int kSmallThreads = 1024;
@@ -357,7 +361,7 @@ __global__ void dense_tables_kernel(int64_t n, int n_experts, int tile_m, int ma
 hipError_t launch_bucket(hipStream_t stream, const int32_t* topk_idx, const float* topk_w, int64_t n, int top_k,
                          int n_experts, int tile_m, int max_tiles, const BucketTables& t) {
   const int64_t n_pairs = n * top_k;
-  if (n_pairs <= kBucketSmallPairs) {
+  if (n_pairs <= kBucketTilesPairs) {
     hipLaunchKernelGGL(bucket_small_kernel<false>, dim3(1), dim3(kSmallThreads), 0, stream, topk_idx, topk_w, (int)n_pairs, top_k,
                        n_experts, 0, CompactWork{}, tile_m, max_tiles, t.counts, t.offsets, t.tile_offset, t.tile_expert, t.perm,
                        t.w_perm, t.slot_of, nullptr);

@@ -43,8 +43,9 @@ hipError_t launch_route_topk(hipStream_t stream, const void* X, int dtype, int64
 constexpr int kBucketChunk = 1024;
 inline int64_t bucket_blocks(int64_t n_pairs) { return (n_pairs + kBucketChunk - 1) / kBucketChunk; }
 
-// Up to this many pairs one workgroup sorts them in one launch.
+// Up to this many pairs one workgroup can sort them in one launch; with the M-tile tables it does up to kBucketTilesPairs.
 constexpr int kBucketSmallPairs = 4096;
+constexpr int kBucketTilesPairs = 3072;
 
 // Stable counting sort of the n*top_k pairs by expert, then the M-tile tables
 // for tiles of `tile_m` rows.

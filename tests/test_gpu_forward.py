@@ -124,9 +124,10 @@ def test_output_columns_at_the_edges_of_a_lane_a_wave_and_a_tile(cam, n_tokens, 
 @pytest.mark.parametrize("top_k,experts,n_shared", [(8, 100, 0), (3, 256, 0), (4, 63, 0), (6, 96, 1), (7, 250, 2)])
 @pytest.mark.parametrize("compact", [False, True])
 def test_bucket_order_in_one_launch(cam, compact, top_k, experts, n_shared):
-    """Up to 4096 pairs one workgroup makes the bucket order, beyond them the general sort does.  A token's output does not
-    depend on the batch: the call on all tokens (more pairs) equals the calls on parts of them with 1 token, a chunk of
-    64 pairs and its neighbours, a whole step of 1024, and the rest, bit for bit.  Some choices are no expert's."""
+    """Up to 3072 pairs (4096 of a decoding batch) one workgroup makes the bucket order, beyond them the general sort does.  With
+    K in one part (d_ff is below 1024) a token's output does not depend on the batch: the call on all tokens (more pairs) equals
+    the calls on parts of them with 1 token, a chunk of 64 pairs and its neighbours, a whole step of 1024, the two lines and
+    their neighbours, bit for bit.  Some choices are no expert's."""
     n_shared = n_shared if compact else 0
     terms = top_k + n_shared
     n_tokens = 4096 // terms + 1
@@ -148,7 +149,7 @@ def test_bucket_order_in_one_launch(cam, compact, top_k, experts, n_shared):
                                          *[torch.cat(p) for p in parts], n_shared=cfg.n_shared, down_row_align=8)
     whole = forward(0, n_tokens)
     assert whole.abs().max() > 0
-    for size in (1, 64 // terms, 64 // terms + 1, 1024 // terms + 1, 4096 // terms):
+    for size in (1, 64 // terms, 64 // terms + 1, 1024 // terms + 1, 3072 // terms, 3072 // terms + 1, 4096 // terms):
         for lo in (0, n_tokens - size):
             assert torch.equal(forward(lo, lo + size), whole[lo:lo + size]), (size, lo)
 
