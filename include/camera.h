@@ -311,9 +311,11 @@ int camera_input_channel_energy(camera_ctx* ctx, void* stream,
  * With CAMERA_BF16 Lambda is rounded to bf16 before the second contraction, as the hidden activations of a
  * 16-bit model are (CAMERA_F32 keeps it in float32); both contractions accumulate in float32, and a token's experts are added in the order of its
  * top-k list (no floating-point atomics: the result does not depend on launch order).  The context
- * workspace grows by n*top_k*(2*d_ff + 4*d_model) bytes; where the second contraction has few tiles, its sums over d_ff
- * are taken in up to eight parts with 4*d_model bytes each (256 MiB at most in all; how many depends on n, so a token's last
- * bits may), and a masked call of 4e10 products n*top_k*d_model*d_ff or more needs 4*n_experts*(d_ff + 1).  n == 0 does nothing.
+ * workspace grows by n*top_k*(2*d_ff + 4*d_model) bytes.  With CAMERA_BF16, where the second contraction has few tiles, its sums
+ * over d_ff are taken in up to eight parts with 4*d_model bytes each; how many depends on n, so a token's last bits may.  Every
+ * call makes the room that the parts of a smaller batch take (256 MiB of such rows at most in all) and, from 4e10 products
+ * n*top_k*d_model*d_ff on, the 4*n_experts*(d_ff + 1) bytes of a masked call: after a call on the largest batch none of the
+ * same layer grows the workspace, with a mask or without.  n == 0 does nothing.
  *
  * camera_output_error: distance of a pruned layer's output from the original one, per token
  *   per_token [n x 4] float32 out: ||y - y_hat||^2, ||y||^2, ||y_hat||^2, <y, y_hat>
@@ -333,7 +335,7 @@ int camera_layer_forward(camera_ctx* ctx, void* stream,
  * lines 10-13 leave: expert e keeps count[e] micro-experts), for the small token batches of decoding
  * (the decoding-speed comparison of a pruned MoE layer, batch of 64 tokens).  Same result as
  * camera_layer_forward with the keep mask that the compaction was made from, but only the kept
- * weights are read, each activated expert's once per 64 of its tokens, and the experts that no token
+ * weights are read, each activated expert's once per 32 of its tokens, and the experts that no token
  * of the batch selected are not read at all: the call is bound by HBM reads, not by arithmetic.
  *
  *   X, n, d_model, ldx, topk_idx, topk_w, top_k, n_experts, flags, Y: as in camera_layer_forward
@@ -342,6 +344,10 @@ int camera_layer_forward(camera_ctx* ctx, void* stream,
  *               tokens; from 64 tokens per expert on average the call runs on the tiled MFMA kernel
  *               of camera_layer_forward with per-expert widths, provided down_row_align is a
  *               multiple of 8 and d_model a multiple of 16 (else it stays on the streaming kernels).
+ *               There the sums over an expert's kept columns may be taken in parts as in
+ *               camera_layer_forward.  Which kernel runs and in how many parts depends on n and on
+ *               count, so a token's last bits may; the workspace of a call on the largest batch
+ *               serves every smaller one of the layer.
  *   n_shared    experts n_experts .. n_experts + n_shared - 1 are shared experts: every token goes
  *               through them with weight 1, in the same launches as the routed ones (a decoding
  *               batch is too small to fill the chip with the shared experts alone).  0 without routing.

@@ -564,13 +564,14 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   const size_t es = dtype == CAMERA_BF16 ? 2 : 4;
   const size_t o_hidden = cv.take(es * (size_t)n_pairs * d_ff);
   const int64_t m_tiles = dense ? max_tiles : camera::expected_m_tiles(n_pairs, n_experts);
-  const int k_parts = dtype != CAMERA_BF16 ? 1
-                                           : camera::product_k_parts(m_tiles * ((d_model / 2 + 127) / 128), d_ff,
-                                                                     (int64_t)sizeof(float) * n_pairs * d_model);
-  const size_t o_product = cv.take(sizeof(float) * (size_t)k_parts * n_pairs * d_model);
-  const bool by_list = keep_mask != nullptr && dtype == CAMERA_BF16 && camera::masks_by_list(n_pairs, d_model, d_ff);
-  const size_t o_kept = cv.take(by_list ? sizeof(int32_t) * (size_t)(n_micro + n_experts) : 0);
-  const size_t o_work = cv.take(by_list ? sizeof(int32_t) * camera::kCompactGemmScratchWords : 0);
+  const int64_t product_bytes = (int64_t)sizeof(float) * n_pairs * d_model;
+  const bool bf16 = dtype == CAMERA_BF16;
+  const int k_parts = bf16 ? camera::product_k_parts(m_tiles * ((d_model / 2 + 127) / 128), d_ff, product_bytes) : 1;
+  // with or without a mask, and for smaller batches too: see product_workspace
+  const size_t o_product = cv.take(bf16 ? camera::product_workspace(product_bytes, d_ff) : product_bytes);
+  const bool listable = bf16 && camera::masks_by_list(n_pairs, d_model, d_ff), by_list = listable && keep_mask != nullptr;
+  const size_t o_kept = cv.take(listable ? sizeof(int32_t) * (size_t)(n_micro + n_experts) : 0);
+  const size_t o_work = cv.take(listable ? sizeof(int32_t) * camera::kCompactGemmScratchWords : 0);
 
   DeviceGuard guard;
   CAMERA_HIP(guard.enter(ctx->device), "hipSetDevice");
@@ -703,7 +704,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   // From about 64 tokens per expert on, the tiles of the grouped MFMA kernel are worth filling: the weights are
   // then read once per 256 tokens of an expert instead of once per 32.  Its 16-byte tile loads need W_down rows
   // that are a multiple of 8 elements long and the two halves of d_model to be multiples of 8.
-  const bool mfma = n_pairs / total > 64 && down_row_align % 8 == 0 && d_model % 16 == 0;
+  const bool mfma = camera::compact_fills_tiles(n_pairs, total) && down_row_align % 8 == 0 && d_model % 16 == 0;
   const bool small = !dense && !mfma && n_pairs <= camera::kBucketSmallPairs;  // one-workgroup bucket order, no M-tile tables
   const int tile_m = camera::gemm_tile_m(dtype, widest);  // M tiles of the MFMA path; otherwise only the bucket order is used
   const int64_t max_tiles64 = dense ? n_experts * ((n + tile_m - 1) / tile_m) : n_pairs / tile_m + total;
@@ -719,13 +720,14 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   const size_t o_idx_aug = cv.take(append ? sizeof(int32_t) * n_pairs : 0);
   const size_t o_w_aug = cv.take(append ? sizeof(float) * n_pairs : 0);
   const size_t o_hidden = cv.take(2 * (size_t)n_pairs * ldh);
+  const int64_t row_bytes = (int64_t)sizeof(float) * d_model;
   int k_parts = 1;
   if (mfma) {
     const int64_t m_tiles = dense ? max_tiles : camera::expected_m_tiles(n * top_k, n_experts) + n_shared * ((n + tile_m - 1) / tile_m);
-    k_parts = camera::product_k_parts(m_tiles * ((d_model / 2 + 127) / 128), rows / total, (int64_t)sizeof(float) * n_pairs * d_model);
+    k_parts = camera::product_k_parts(m_tiles * ((d_model / 2 + 127) / 128), rows / total, n_pairs * row_bytes);
   }
-  const size_t o_product = cv.take(sizeof(float) * (size_t)(mfma ? k_parts : most_chunks) * n_pairs * d_model);
-  const size_t o_work = cv.take(sizeof(int32_t) * (mfma ? camera::kCompactGemmScratchWords : camera::kCompactWorkWords));
+  const size_t o_product = cv.take(camera::compact_product_workspace(n_pairs, total, mfma, row_bytes, rows / total, most_chunks));
+  const size_t o_work = cv.take(sizeof(int32_t) * std::max(camera::kCompactGemmScratchWords, camera::kCompactWorkWords));
 
   DeviceGuard guard;
   CAMERA_HIP(guard.enter(ctx->device), "hipSetDevice");

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/camera.h"
+#include "forward_plan.h"
 #include "host_launch.h"
 
 namespace camera {
@@ -76,23 +77,9 @@ struct GemmEpilogue {
   int64_t ld_product = 0;
   int col_gap = 0;
   bool stream_product = false;
-  int k_parts = 1;          // parts of K, each with product rows of its own, part_stride floats apart
+  int k_parts = 1;          // parts of K (see product_k_parts), each with product rows of its own, part_stride floats apart
   int64_t part_stride = 0;
 };
-// Into how many parts the K extent of the second contraction is cut when there are about `tiles` tiles: as many as make the
-// 256 compute units' rounds of tiles (1.4 us per K tile of 64, 5 us around them) shortest with the product rows that every
-// part writes and the combine reads (6 TB/s while they fit the memory-side cache), if that saves a sixth.  Second
-// contraction, us, whole / in parts: 2048 tokens of the Mixtral shape, 320 tiles of 224 K tiles, 546 / 441 (and 9 -> 23 per
-// combine); 500 tokens of 6 experts and a shared one of 8192, 72 tiles, 132 / 59; 300 tokens of 4 experts, 4096 wide, 64 tiles
-// 63 / 40; 100 tokens, 8 experts of 4096 channels, 1024 wide, 36 / 16.
-int product_k_parts(int64_t tiles, int64_t k_ext, int64_t product_bytes);
-// About as many token tiles as `pairs` spread over n_experts make: one of each, or half a tile of each is padding.
-int64_t expected_m_tiles(int64_t pairs, int64_t n_experts);
-// Whether the product rows of `pairs` slots go past the caches on their way out (second contraction) and back in
-// (combine): from 256 MiB on, which is what the memory-side cache holds, they only displace each other in it.  Second
-// contraction + combine, us, through the caches / past them: 537 MB 291 + 128 / 280 + 107 (8192 tokens of the DeepSeek
-// shape, 40 % pruned), below the line 197 MB 338 + 106 / 335 + 114, 79 MB 74 + 30 / 70 + 35.
-inline bool product_streams(int64_t pairs, int64_t d_model) { return pairs * d_model * 4 >= (int64_t(256) << 20); }
 hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int64_t ldx, int64_t d_model,
                                int64_t d_ff, int n_experts, const void* W_gate, const void* W_up,
                                int64_t stride_gu, int max_tiles, const BucketTables& t, const GemmEpilogue& ep);
@@ -240,20 +227,12 @@ hipError_t launch_compact_hidden_gemm(hipStream_t stream, const void* X, int64_t
                                       const void* W_gate, const void* W_up, const CompactRows& tab, int widest,
                                       int max_tiles, const BucketTables& t, int32_t* scratch, void* hidden,
                                       int k_round);
-// The first contraction of a masked layer over its kept micro-experts only (keep [n_experts * d_ff], 0 = pruned); hidden
+// The first contraction of a masked layer over its kept micro-experts only (see masks_by_list; keep [n_experts * d_ff], 0 = pruned); hidden
 // rows are d_ff long, zero where nothing is kept.  kept: n_experts * (d_ff + 1) int32 words, scratch as above.
 hipError_t launch_kept_hidden_gemm(hipStream_t stream, const void* X, int64_t ldx, int64_t d_model, int64_t d_ff,
                                    int n_experts, const void* W_gate, const void* W_up, int64_t stride_gu,
                                    const uint8_t* keep, int max_tiles, int64_t n_pairs, const BucketTables& t, int32_t* kept,
                                    int32_t* scratch, void* hidden);
-// When that pays: the lists, the zeros and the work table are three launches before it (25-33 us), and a launch with few more
-// tiles than compute units gains little from fewer.  Masked call, first contraction + these, us, against computing every
-// micro-expert and zeroing the pruned ones: 2.4e11 products of 40 % pruned 815 -> 575 + 32, of 20 % 808 -> 757 + 33, of nothing
-// pruned 800 -> 805 + 21; 6.9e10 (40 %) 288 -> 212 + 29; 4.7e10 (60 %) 278 -> 155 + 20; below the line 2.5e10 (40 %) 124 -> 107 + 19,
-// (20 %) 109 -> 112 + 20.
-inline bool masks_by_list(int64_t n_pairs, int64_t d_model, int64_t d_ff) {
-  return (double)n_pairs * d_model * d_ff >= 4e10;
-}
 hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int64_t d_model, const void* W_down,
                                     const CompactDown& tab, int max_tiles, const BucketTables& t, int32_t* scratch,
                                     float* product, bool stream_product, int k_parts, int64_t part_stride);

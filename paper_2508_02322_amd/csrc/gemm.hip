@@ -1356,6 +1356,7 @@ __global__ __launch_bounds__(256) void zero_hidden_kernel(const int32_t* __restr
 // Shape of the bf16 kernel: waves (M x N), 32x32 blocks per wave (M x N), K tile, stages of the token ring, stages
 // of the weight ring.  Four waves of 128 x 64 x {gate, up}: one per SIMD.
 using Bf16Cfg = GemmCfg<2, 2, 4, 2, 64, 2, 3>;
+static_assert(Bf16Cfg::BM == kPlanTileM && Bf16Cfg::BN == kPlanTileN && Bf16Cfg::KT == kPlanTileK, "the plan's tile");
 
 // Whether the scalar-base form of the tile loads can address the operands: 32-bit byte offsets from the start of
 // the token matrix (a_rows rows of lda elements) and of one expert's weight matrix (b_rows rows of ldw elements).
@@ -1366,23 +1367,6 @@ bool fits_32bit_offsets(int64_t a_rows, int64_t lda, int64_t b_rows, int64_t ldw
 }
 
 }  // namespace
-
-int product_k_parts(int64_t tiles, int64_t k_ext, int64_t product_bytes) {
-  constexpr int kCus = 256, kMost = 8, kFewestTiles = 8;
-  const int64_t k_tiles = (k_ext + Bf16Cfg::KT - 1) / Bf16Cfg::KT;
-  auto us = [&](int parts) {
-    const int64_t rounds = (tiles * parts + kCus - 1) / kCus;
-    return rounds * (1.4 * (double)k_tiles / parts + 5.0) + 2.0 * parts * (double)product_bytes / 6e6;
-  };
-  int best = 1;
-  for (int p = 2; p <= kMost && p * kFewestTiles <= k_tiles && p * product_bytes < (int64_t(256) << 20); ++p)
-    if (us(p) < us(best)) best = p;
-  return us(best) < 0.85 * us(1) ? best : 1;
-}
-int64_t expected_m_tiles(int64_t pairs, int64_t n_experts) {
-  const int64_t used = std::max<int64_t>(1, std::min(pairs, n_experts));
-  return pairs <= used * Bf16Cfg::BM ? used : pairs / Bf16Cfg::BM + used / 2;
-}
 
 int gemm_tile_m(int dtype, int64_t d_ff) {
   (void)d_ff;

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2508_02322_amd import inputs
+from paper_2508_02322_amd import binding, inputs
 from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
@@ -101,3 +101,51 @@ def test_compacted_layer_replays_from_a_graph(cam):
         step()
         torch.cuda.synchronize()
         assert torch.equal(got, Y) and float(got.abs().sum()) > 0
+
+
+@pytest.mark.parametrize("compact,largest", [(False, 2000), (False, 5000), (True, 2000)])
+def test_layer_output_of_smaller_batches_captured_after_the_largest(compact, largest):
+    """One call on the largest batch sizes the workspace; smaller batches (1500 tokens take two parts of K and more rows of the
+    product than 2000) and masked ones (5000 tokens by list) are then captured without a call before, and the first graph still
+    names the memory it was captured with."""
+    cam = binding.Camera(device=0)               # a workspace of its own
+    cfg = inputs.scaled(inputs.CONFIGS["mixtral"], n_tokens=largest, d_model=4096, d_ff=2048, n_experts=4, top_k=1, n_layers=1,
+                        outlier_channels=0)
+    dev = inputs.make_layer(cfg, 0, device="cuda")
+    X = dev["X"]
+    idx, w = cam.route_topk(X, dev["W_r"], dev["bias"], cfg.top_k)
+    keep = (torch.rand(cfg.n_experts * cfg.d_ff, generator=torch.Generator().manual_seed(1)) < 0.6).to(torch.uint8).cuda()
+    packed = [dev["W_gate"].flatten(0, 1), dev["W_up"].flatten(0, 1), dev["W_down"].flatten()]
+    sizes = [largest, 1500, 500, 100, 1]
+    Y = {n: torch.empty((n, cfg.d_model), dtype=torch.float32, device="cuda") for n in sizes}
+
+    def forward(n, mask):
+        if compact:
+            return cam.layer_forward_compact(X[:n], idx[:n], w[:n], [cfg.d_ff] * cfg.n_experts, *packed, down_row_align=64, Y=Y[n])
+        return cam.layer_forward(X[:n], idx[:n], w[:n], dev["W_gate"], dev["W_up"], dev["W_down"], keep_mask=mask, Y=Y[n])
+
+    forward(sizes[0], None)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    stream = torch.cuda.Stream()
+    graphs = []
+    for mask in (None,) if compact else (None, keep):
+        for n in sizes:
+            print(f"captured: {n} tokens, mask {mask is not None}, compact {compact}", flush=True)
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.stream(stream):
+                with torch.cuda.graph(graph, stream=stream):
+                    forward(n, mask)
+            torch.cuda.synchronize()
+            graphs.append((graph, n, mask))
+    for trial in range(3):
+        for graph, n, mask in graphs:
+            Y[n].fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            got = Y[n].clone()
+            forward(n, mask)                     # eager work between the replays
+            torch.cuda.synchronize()
+            assert torch.equal(got, Y[n]) and float(got.abs().sum()) > 0, (n, mask is not None)
+    assert torch.cuda.mem_get_info()[0] >= free - (64 << 20)   # graphs and clones aside, nothing grew
+    cam.close()
