@@ -563,10 +563,14 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   plan.take(cv, dense, true, n_experts, n_pairs, max_tiles, n_blocks);
   const size_t es = dtype == CAMERA_BF16 ? 2 : 4;
   const size_t o_hidden = cv.take(es * (size_t)n_pairs * d_ff);
-  const int64_t m_tiles = dense ? max_tiles : camera::expected_m_tiles(n_pairs, n_experts);
   const int64_t product_bytes = (int64_t)sizeof(float) * n_pairs * d_model;
   const bool bf16 = dtype == CAMERA_BF16;
-  const int k_parts = bf16 ? camera::product_k_parts(m_tiles * ((d_model / 2 + 127) / 128), d_ff, product_bytes) : 1;
+  camera::SplitPlan split{1, 0};
+  if (bf16) {
+    const int64_t most_m = dense ? max_tiles : n_pairs / tile_m + std::min<int64_t>(n_pairs, n_experts);
+    split = camera::product_plan(dense ? max_tiles : (n_pairs + tile_m - 1) / tile_m, most_m, d_model, d_ff, product_bytes);
+  }
+  const size_t o_parts = cv.take(sizeof(int32_t));
   // with or without a mask, and for smaller batches too: see product_workspace
   const size_t o_product = cv.take(bf16 ? camera::product_workspace(product_bytes, d_ff) : product_bytes);
   const bool listable = bf16 && camera::masks_by_list(n_pairs, d_model, d_ff), by_list = listable && keep_mask != nullptr;
@@ -580,6 +584,8 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   const camera::BucketTables t = plan.bind(ws, ctx->zeros);
   void* hidden = ws + o_hidden;
   float* product = reinterpret_cast<float*>(ws + o_product);
+  // a dense group's tiles are known here, and where no number of them is better in parts there is nothing to choose
+  int32_t* parts = dense || split.most_parts == 1 ? nullptr : reinterpret_cast<int32_t*>(ws + o_parts);
   const bool streams = camera::product_streams(n_pairs, d_model);
 
   hipStream_t stream = static_cast<hipStream_t>(stream_);
@@ -618,8 +624,10 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
     ep.ld_product = d_model;
     ep.col_gap = (int)half;
     ep.stream_product = streams;
-    ep.k_parts = k_parts;
+    ep.split_plan = split;
+    ep.split = camera::split_cost(d_ff, product_bytes);
     ep.part_stride = n_pairs * d_model;
+    ep.parts = parts;
     const char* wd = static_cast<const char*>(W_down);
     CAMERA_HIP(camera::launch_grouped_gemm(stream, dtype, hidden, d_ff, d_ff, half, n_experts, wd,
                                            wd + es * half * d_ff, stride_down, max_tiles, t, ep),
@@ -628,7 +636,7 @@ int camera_layer_forward(camera_ctx* ctx, void* stream_, const void* X, int dtyp
   {
     Bracket b(ctx, stream, CAMERA_K_COMBINE);
     CAMERA_HIP(camera::launch_combine(stream, product, t.slot_of, n, top_k, n_experts, d_model,
-                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, k_parts, n_pairs * d_model, Y),
+                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, split.most_parts, parts, n_pairs * d_model, Y),
                "combine launch");
   }
   return CAMERA_OK;
@@ -721,11 +729,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
   const size_t o_w_aug = cv.take(append ? sizeof(float) * n_pairs : 0);
   const size_t o_hidden = cv.take(2 * (size_t)n_pairs * ldh);
   const int64_t row_bytes = (int64_t)sizeof(float) * d_model;
-  int k_parts = 1;
-  if (mfma) {
-    const int64_t m_tiles = dense ? max_tiles : camera::expected_m_tiles(n * top_k, n_experts) + n_shared * ((n + tile_m - 1) / tile_m);
-    k_parts = camera::product_k_parts(m_tiles * ((d_model / 2 + 127) / 128), rows / total, n_pairs * row_bytes);
-  }
+  const int k_parts = mfma ? camera::compact_k_parts(n, n_experts, dense ? 0 : top_k, n_shared, d_model, rows / total) : 1;
   const size_t o_product = cv.take(camera::compact_product_workspace(n_pairs, total, mfma, row_bytes, rows / total, most_chunks));
   const size_t o_work = cv.take(sizeof(int32_t) * std::max(camera::kCompactGemmScratchWords, camera::kCompactWorkWords));
 
@@ -781,7 +785,7 @@ int camera_layer_forward_compact(camera_ctx* ctx, void* stream_, const void* X, 
     }
     Bracket b(ctx, stream, CAMERA_K_COMBINE);
     CAMERA_HIP(camera::launch_combine(stream, product, t.slot_of, n, terms, n_experts, d_model,
-                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, k_parts, n_pairs * d_model, Y),
+                                      (flags & CAMERA_ACCUMULATE) ? 1 : 0, streams, k_parts, nullptr, n_pairs * d_model, Y),
                "combine launch");
     return CAMERA_OK;
   }

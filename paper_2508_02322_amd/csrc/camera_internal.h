@@ -77,8 +77,12 @@ struct GemmEpilogue {
   int64_t ld_product = 0;
   int col_gap = 0;
   bool stream_product = false;
-  int k_parts = 1;          // parts of K (see product_k_parts), each with product rows of its own, part_stride floats apart
+  // parts of K, each with product rows of its own, part_stride floats apart: as many as product_k_parts gives for the tiles there
+  // are, at most split_plan.most_parts, and the kernel leaves their number in *parts; with parts NULL split_plan.most_parts
+  SplitPlan split_plan{1, 0};
+  SplitCost split{};
   int64_t part_stride = 0;
+  int32_t* parts = nullptr;
 };
 hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int64_t ldx, int64_t d_model,
                                int64_t d_ff, int n_experts, const void* W_gate, const void* W_up,
@@ -145,11 +149,11 @@ hipError_t launch_full_rank(hipStream_t stream, const float* energy, int64_t n_m
 // ---- forward.hip -----------------------------------------------------------
 // Y[token] (+)= sum of the product rows of the token's slots (routed: slot_of[token*top_k + k], k ascending;
 // slot_of == nullptr: rows e*n + token for e ascending).  product is [pairs][d_model] float32, Y [n][d_model].
-// stream_product: the rows are read once, past the caches (see product_streams).  A slot's row is the sum of its k_parts rows,
-// part_stride floats apart, in order.
+// stream_product: the rows are read once, past the caches (see product_streams).  A slot's row is the sum of its
+// k_parts rows, part_stride floats apart, in order; parts: device word with their number, or NULL: k_parts.
 hipError_t launch_combine(hipStream_t stream, const float* product, const int32_t* slot_of, int64_t n, int top_k,
                           int n_experts, int64_t d_model, int accumulate, bool stream_product, int k_parts,
-                          int64_t part_stride, float* Y);
+                          const int32_t* parts, int64_t part_stride, float* Y);
 // per_token [n][4] = ||y - y_hat||^2, ||y||^2, ||y_hat||^2, <y, y_hat>
 hipError_t launch_output_error(hipStream_t stream, const float* Y, const float* Y_hat, int64_t n, int64_t d_model,
                                int64_t ldy, int64_t ldh, float* per_token);

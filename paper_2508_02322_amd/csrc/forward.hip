@@ -20,50 +20,71 @@ constexpr int kTokensPerBlock = kThreads / kWave;  // one wave per token
 // grid: x = tokens, y = blockDim.x vectors of four columns each.  A workgroup has one token, so its slots are scalar
 // loads, and the rows of eight terms are in flight together: waiting for each row in turn is what a wave per token
 // spent its time on.  8192 tokens, 8 terms, 2048 wide: 143 -> 127 us; 2048 tokens, 2 terms, 4096 wide: 44 -> 19 us.
-// PARTS: a slot's row is the sum of k_parts rows.  An instance of its own: the loop takes 78 registers a lane where one row
-// takes 44: six waves per SIMD, not eight.  (STREAM needs no parts: rows that fill the cache are whole.)
+// PARTS: a slot's row is the sum of its rows of every part, in order; eight rows are in flight whatever terms and parts they are
+// of.  An instance of its own: within the loop over terms the parts took 78 registers a lane where whole rows take 44, six waves
+// per SIMD and not eight.  (STREAM needs no parts: rows that fill the cache are whole.)
 constexpr int kTerms = 8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 template <bool STREAM, bool PARTS>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const f32x4* __restrict__ product,
                                                            const int32_t* __restrict__ slot_of, int64_t n, int top_k,
                                                            int n_experts, int vecs, int accumulate, int k_parts,
-                                                           int64_t part_stride, f32x4* __restrict__ Y) {
+                                                           const int32_t* __restrict__ parts, int64_t part_stride,
+                                                           f32x4* __restrict__ Y) {
   const int64_t tok = blockIdx.x;
   const int v = (int)(blockIdx.y * blockDim.x + threadIdx.x);
-  if (v >= vecs) return;
   const int terms = slot_of ? top_k : n_experts;
-  f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (accumulate) s = Y[tok * vecs + v];
-  for (int k0 = 0; k0 < terms; k0 += kTerms) {
-    int64_t row[kTerms];
-    f32x4 p[kTerms];
+  if constexpr (!PARTS) {
+    if (v >= vecs) return;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    if (accumulate) s = Y[tok * vecs + v];
+    for (int k0 = 0; k0 < terms; k0 += kTerms) {
+      int64_t row[kTerms];
+      f32x4 p[kTerms];
 #pragma unroll
-    for (int u = 0; u < kTerms; ++u) {
-      const int k = k0 + u;
-      row[u] = k >= terms ? -1 : (slot_of ? (int64_t)slot_of[tok * top_k + k] : (int64_t)k * n + tok);
-    }
+      for (int u = 0; u < kTerms; ++u) {
+        const int k = k0 + u;
+        row[u] = k >= terms ? -1 : (slot_of ? (int64_t)slot_of[tok * top_k + k] : (int64_t)k * n + tok);
+      }
 #pragma unroll
-    for (int u = 0; u < kTerms; ++u)
-      if (row[u] >= 0)  // below 0: past the last term, or an expert id outside the group
-        p[u] = STREAM ? __builtin_nontemporal_load(product + row[u] * vecs + v) : product[row[u] * vecs + v];
-    if constexpr (PARTS) {
-      for (int part = 1; part < k_parts; ++part) {
-        f32x4 q[kTerms];
+      for (int u = 0; u < kTerms; ++u)
+        if (row[u] >= 0)  // below 0: past the last term, or an expert id outside the group
+          p[u] = STREAM ? __builtin_nontemporal_load(product + row[u] * vecs + v) : product[row[u] * vecs + v];
 #pragma unroll
-        for (int u = 0; u < kTerms; ++u)
-          if (row[u] >= 0) q[u] = product[part * part_stride + row[u] * vecs + v];
-#pragma unroll
-        for (int u = 0; u < kTerms; ++u)
-          if (row[u] >= 0) p[u] += q[u];
+      for (int u = 0; u < kTerms; ++u) {
+        if (row[u] >= 0) s += p[u];
       }
     }
+    Y[tok * vecs + v] = s;
+  } else {
+    if (v >= vecs) return;
+    if (parts != nullptr) k_parts = *parts;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f}, term = s;
+    if (accumulate) s = Y[tok * vecs + v];
+    const f32x4* rows = product + v;  // of the part of the next row to load
+    int k = 0, part = 0;              // the next row to load
+    int part_add = 0;                 // part of the next row to add
+    while (k < terms) {
+      int64_t row[kTerms];
+      f32x4 p[kTerms];
 #pragma unroll
-    for (int u = 0; u < kTerms; ++u) {
-      if (row[u] >= 0) s += p[u];
+      for (int u = 0; u < kTerms; ++u) {
+        row[u] = k >= terms ? -1 : (slot_of ? (int64_t)slot_of[tok * top_k + k] : (int64_t)k * n + tok);
+        if (row[u] >= 0) p[u] = rows[row[u] * vecs];
+        rows += part_stride;
+        if (++part == k_parts) rows = product + v, part = 0, ++k;
+      }
+#pragma unroll
+      for (int u = 0; u < kTerms; ++u) {
+        if (row[u] >= 0) {
+          term = part_add == 0 ? p[u] : term + p[u];
+          if (part_add == k_parts - 1) s += term;
+        }
+        if (++part_add == k_parts) part_add = 0;
+      }
     }
+    Y[tok * vecs + v] = s;
   }
-  Y[tok * vecs + v] = s;
 }
 
 // A wave per token.  VEC: four columns per lane and load (rows of whole, aligned vectors), eight loads in flight; a column at
@@ -131,7 +152,7 @@ __global__ __launch_bounds__(kThreads) void output_error_kernel(const float* __r
 
 hipError_t launch_combine(hipStream_t stream, const float* product, const int32_t* slot_of, int64_t n, int top_k,
                           int n_experts, int64_t d_model, int accumulate, bool stream_product, int k_parts,
-                          int64_t part_stride, float* Y) {
+                          const int32_t* parts, int64_t part_stride, float* Y) {
   if (n <= 0) return hipSuccess;
   if (stream_product && k_parts > 1) return hipErrorInvalidValue;
   const int vecs = (int)(d_model / 4);
@@ -139,7 +160,7 @@ hipError_t launch_combine(hipStream_t stream, const float* product, const int32_
   auto kern = stream_product ? combine_kernel<true, false> : k_parts > 1 ? combine_kernel<false, true> : combine_kernel<false, false>;
   hipLaunchKernelGGL(kern, dim3((unsigned)n, (unsigned)((vecs + threads - 1) / threads)), dim3(threads), 0,
                      stream, reinterpret_cast<const f32x4*>(product), slot_of, n, top_k, n_experts, vecs, accumulate,
-                     k_parts, part_stride / 4, reinterpret_cast<f32x4*>(Y));
+                     k_parts, parts, part_stride / 4, reinterpret_cast<f32x4*>(Y));
   return hipGetLastError();
 }
 

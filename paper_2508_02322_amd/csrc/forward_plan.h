@@ -1,14 +1,20 @@
-// The forms that the layer outputs take by their sizes, and the workspace for them.  Host code that needs no HIP, so that a
-// plain C++ program can include it.
+// The forms that the layer outputs take by their sizes, and the workspace for them.  It needs no HIP, so that a plain C++
+// program can include it; what a kernel decides by the same rule is for the device too.
 #pragma once
 
 #include <stdint.h>
 
 #include <algorithm>
 
+#ifdef __HIPCC__
+#define CAMERA_PLAN_FN __host__ __device__ inline
+#else
+#define CAMERA_PLAN_FN inline
+#endif
+
 namespace camera {
 
-constexpr int kPlanCus = 256;                    // compute units
+constexpr int kPlanCus = 256, kPlanDies = 8;     // compute units, on that many dies
 constexpr int kPlanTileM = 256, kPlanTileN = 128, kPlanTileK = 64;  // the bf16 contraction's tile (gemm.hip): tokens, channels, K
 constexpr int64_t kPlanCacheBytes = int64_t(256) << 20;  // the memory-side cache
 
@@ -18,32 +24,83 @@ constexpr int64_t kPlanCacheBytes = int64_t(256) << 20;  // the memory-side cach
 // shape, 40 % pruned), below the line 197 MB 338 + 106 / 335 + 114, 79 MB 74 + 30 / 70 + 35.
 inline bool product_streams(int64_t pairs, int64_t d_model) { return pairs * d_model * 4 >= kPlanCacheBytes; }
 
-// About as many token tiles as `pairs` spread over n_experts make: one of each, or half a tile of each is padding.
-inline int64_t expected_m_tiles(int64_t pairs, int64_t n_experts) {
-  const int64_t used = std::max<int64_t>(1, std::min(pairs, n_experts));
-  return pairs <= used * kPlanTileM ? used : pairs / kPlanTileM + used / 2;
-}
+// Column tiles of the second contraction: a tile takes its columns from both halves of d_model.
+inline int64_t product_n_tiles(int64_t d_model) { return (d_model / 2 + kPlanTileN - 1) / kPlanTileN; }
 
 // The most parts that a K extent is cut into: at least eight K tiles each.
+constexpr int kMostParts = 8;
 inline int most_k_parts(int64_t k_ext) {
-  constexpr int kMost = 8, kFewestTiles = 8;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(kMost, (k_ext + kPlanTileK - 1) / kPlanTileK / kFewestTiles));
+  constexpr int kFewestTiles = 8;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kMostParts, (k_ext + kPlanTileK - 1) / kPlanTileK / kFewestTiles));
 }
 
-// Into how many parts the K extent of the second contraction is cut when there are about `tiles` tiles: as many as make the
-// 256 compute units' rounds of tiles (1.4 us per K tile of 64, 5 us around them) shortest with the product rows that every
-// part writes and the combine reads (6 TB/s while they fit the memory-side cache), if that saves a sixth.  Second
-// contraction, us, whole / in parts: 2048 tokens of the Mixtral shape, 320 tiles of 224 K tiles, 546 / 441 (and 9 -> 23 per
-// combine); 500 tokens of 6 experts and a shared one of 8192, 72 tiles, 132 / 59; 300 tokens of 4 experts, 4096 wide, 64 tiles
-// 63 / 40; 100 tokens, 8 experts of 4096 channels, 1024 wide, 36 / 16.
-inline int product_k_parts(int64_t tiles, int64_t k_ext, int64_t product_bytes) {
-  const int64_t k_tiles = (k_ext + kPlanTileK - 1) / kPlanTileK;
+// Time of the second contraction's `tiles` tiles (token tiles times column tiles) in parts of K, with the product rows that every
+// part writes and the combine reads, in ns.  The tiles are dealt evenly to the dies, whose 32 units run them in rounds of 1.4 us
+// per K tile and 8 us around them; a part's rows go at 6 TB/s while they fit the memory-side cache.  Whole numbers: host and device
+// come to the same.
+struct SplitCost {
+  int64_t k_ns, part_ns;  // of all K tiles of a tile; of one part's rows
+};
+inline SplitCost split_cost(int64_t k_ext, int64_t product_bytes) {
+  return {1400 * ((k_ext + kPlanTileK - 1) / kPlanTileK), 2 * product_bytes / 6000};
+}
+CAMERA_PLAN_FN int64_t tiles_per_die(int64_t tiles) { return (tiles + kPlanDies - 1) / kPlanDies; }
+CAMERA_PLAN_FN int64_t split_ns(int64_t tiles, int parts, SplitCost c) {
+  const int64_t rounds = (tiles_per_die(tiles) * parts + kPlanCus / kPlanDies - 1) / (kPlanCus / kPlanDies);
+  return rounds * (c.k_ns / parts + 8000) + parts * c.part_ns;
+}
+// K is cut into the parts that take the shortest time, if that saves a sixth.  How many tiles there are depends on how the routed
+// pairs fall on the experts, so the kernel decides (gemm.hip), by this rule: guessed from the number of pairs, the second
+// contraction + combine of 1900 tokens of the Mixtral shape took four parts and 448 us where its 16 token tiles are one full
+// round and 357, of 1150 tokens of 24 experts of 2048, 768 wide, three parts, 55 us, where two take 42.  Second contraction +
+// combine, us, whole / in the parts taken: 2048 tokens of the Mixtral shape, 20 token tiles by 16 of 224 K tiles, 598 / 496;
+// 300 and 2048 tokens of one expert of 20480, 3584 wide, 309 / 72 and 365 / 236; 500 tokens of 8 experts of 3072, 768 wide,
+// 50 / 27.  Over 334 sizes of 20 shapes the parts taken are 0.8 % above the best and none is slower than whole (by a guess, and
+// with rounds of all 256 units: 3.6 %, up to 1.26 times).
+CAMERA_PLAN_FN bool split_pays(int64_t ns, int64_t whole_ns) { return 100 * ns < 85 * whole_ns; }
+inline int product_k_parts(int64_t tiles, int most, SplitCost c) {
+  int best = 1;
+  for (int p = 2; p <= most; ++p)
+    if (split_ns(tiles, p, c) < split_ns(tiles, best, c)) best = p;
+  return split_pays(split_ns(tiles, best, c), split_ns(tiles, 1, c)) ? best : 1;
+}
+// What a call with between least_m and most_m token tiles may come to: the most parts, and the workgroups (a multiple of the
+// dies) that hold the tiles of every such number in the parts it takes.  A workgroup without a tile still waits for a compute
+// unit's whole LDS (1.5 ns each at the end of the launch), so there are no more than that.
+struct SplitPlan {
+  int most_parts;
+  int64_t blocks;
+};
+inline SplitPlan product_plan(int64_t least_m, int64_t most_m, int64_t d_model, int64_t k_ext, int64_t product_bytes) {
+  const SplitCost c = split_cost(k_ext, product_bytes);
+  const int64_t n_tiles = product_n_tiles(d_model), in_cache = (kPlanCacheBytes - 1) / std::max<int64_t>(1, product_bytes);
+  const int most = (int)std::min<int64_t>(most_k_parts(k_ext), in_cache);
+  SplitPlan plan{1, tiles_per_die(most_m * n_tiles) * kPlanDies};
+  // from six rounds on no number of parts saves a sixth (they save less than one round)
+  for (int64_t m = least_m; m <= most_m && m * n_tiles <= 6 * kPlanCus && most > 1; ++m) {
+    const int p = product_k_parts(m * n_tiles, most, c);
+    plan.most_parts = std::max(plan.most_parts, p);
+    plan.blocks = std::max(plan.blocks, tiles_per_die(m * n_tiles) * p * kPlanDies);
+  }
+  return plan;
+}
+// The parts of a compacted layer's second contraction, of whose n_experts every token takes top_k (0: all of them) and the
+// n_shared behind them.  Its tiles have as many K tiles as their expert keeps and are dealt to the dies by cost, and parts make
+// them more even, so that a guess of their number and of rounds on all units serves better than the rule above: over 98 sizes of 8
+// ragged layers 2.2 % above the best number of parts, none slower than whole.
+inline int compact_k_parts(int64_t n, int64_t n_experts, int64_t top_k, int64_t n_shared, int64_t d_model, int64_t mean_kept) {
+  const int64_t pairs = n * top_k, used = std::max<int64_t>(1, std::min(pairs, n_experts)), dense = (n + kPlanTileM - 1) / kPlanTileM;
+  // one tile of each expert, or half a tile of each is padding
+  const int64_t routed = top_k == 0 ? n_experts * dense : (pairs <= used * kPlanTileM ? used : pairs / kPlanTileM + used / 2);
+  const int64_t tiles = (routed + n_shared * dense) * product_n_tiles(d_model);
+  const int64_t product_bytes = n * ((top_k ? top_k : n_experts) + n_shared) * d_model * 4;
+  const int64_t k_tiles = (mean_kept + kPlanTileK - 1) / kPlanTileK;
   auto us = [&](int parts) {
     const int64_t rounds = (tiles * parts + kPlanCus - 1) / kPlanCus;
     return rounds * (1.4 * (double)k_tiles / parts + 5.0) + 2.0 * parts * (double)product_bytes / 6e6;
   };
   int best = 1;
-  for (int p = 2; p <= most_k_parts(k_ext) && p * product_bytes < kPlanCacheBytes; ++p)
+  for (int p = 2; p <= most_k_parts(mean_kept) && p * product_bytes < kPlanCacheBytes; ++p)
     if (us(p) < us(best)) best = p;
   return us(best) < 0.85 * us(1) ? best : 1;
 }

@@ -109,8 +109,11 @@ struct EpiArgs {
   int64_t ld_hidden;       // row stride of hidden (d_ff when every expert has the same width)
   int pad_hidden;          // != 0: columns from d_ff up to the next multiple of it are written as zeros (8 or 64)
   int stream_product;      // != 0: product rows go past the caches (see product_streams)
-  int k_parts;             // parts of K (see product_k_parts); part p writes product + p * part_stride
+  int k_parts;             // parts of K, or the most of them; part p writes product + p * part_stride
   int64_t part_stride;
+  SplitCost split;         // the kernel chooses the parts by it
+  int32_t* parts;          // and leaves their number here; nullptr: k_parts it is
+  int64_t blocks;          // workgroups, where not every token tile there may be has one for every part (host)
 };
 
 // One wave instruction of the direct global -> LDS path: lane l's 16 bytes at p (+ IMM) go to LDS bytes
@@ -841,6 +844,22 @@ __device__ __forceinline__ KPart k_part(int k_ext, int part, int parts) {
   return {begin, max(0, end - begin)};
 }
 
+// product_k_parts by the lanes of a wave: eight lanes try a number of parts each.
+__device__ __forceinline__ int choose_parts(int tiles, int most, SplitCost c) {
+  static_assert(kMostParts == 8, "eight lanes");
+  int parts = threadIdx.x % 8 + 1;
+  int64_t ns = split_ns(tiles, parts, c);
+  const int64_t whole = __shfl(ns, 0, 8);
+  if (parts > most) ns = INT64_MAX;
+#pragma unroll
+  for (int m = 1; m < 8; m <<= 1) {
+    const int64_t other = __shfl_xor(ns, m);
+    const int other_parts = __shfl_xor(parts, m);
+    if (other < ns || (other == ns && other_parts < parts)) ns = other, parts = other_parts;
+  }
+  return __builtin_amdgcn_readfirstlane(split_pays(ns, whole) ? parts : 1);
+}
+
 template <class C, bool TAIL, int EPI>
 __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf16_kernel(
     const __hip_bfloat16* __restrict__ X, int64_t ldx, int d_model, int d_ff,
@@ -864,11 +883,17 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   const int block = linear_block();
   int seq = block / kXcds;
   const int first = (block % kXcds) * per_xcd;
-  int part = 0;
+  [[maybe_unused]] int part = 0, parts = 1;
   if constexpr (EPI == kEpiProduct) {  // the tiles of an XCD with the first part of K, then with the second, ...
     const int here = max(0, min(per_xcd, total - first));
-    if (seq >= here * ep.k_parts) return;
-    if (ep.k_parts > 1) {
+    parts = ep.k_parts;
+    if (ep.parts != nullptr) {
+      parts = choose_parts(total, ep.k_parts, ep.split);
+      if ((int64_t)per_xcd * parts * kXcds > (int64_t)gridDim.x * gridDim.y) parts = 1;  // (the launch has a workgroup for each)
+      if (block == 0 && threadIdx.x == 0) *ep.parts = parts;
+    }
+    if (seq >= here * parts) return;
+    if (parts > 1) {
       part = seq / here;
       seq -= part * here;
     }
@@ -902,7 +927,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   w.tok_first = tile_in_expert * BM;
   constexpr int kAux = C::kAliasAux ? 0 : C::kRingBytes;  // the per-tile arrays
   if constexpr (EPI == kEpiProduct) {
-    const KPart k = k_part<C>(d_model, part, ep.k_parts);
+    const KPart k = k_part<C>(d_model, part, parts);
     ep.product += part * ep.part_stride;
     run_tile<C, TAIL, EPI, kAux>(w, X + k.begin, ldx, k.length, d_ff, Wg + k.begin, Wu + k.begin, stride_gu, d_model, perm, w_perm,
                                  zeros, ep);
@@ -1356,7 +1381,7 @@ __global__ __launch_bounds__(256) void zero_hidden_kernel(const int32_t* __restr
 // Shape of the bf16 kernel: waves (M x N), 32x32 blocks per wave (M x N), K tile, stages of the token ring, stages
 // of the weight ring.  Four waves of 128 x 64 x {gate, up}: one per SIMD.
 using Bf16Cfg = GemmCfg<2, 2, 4, 2, 64, 2, 3>;
-static_assert(Bf16Cfg::BM == kPlanTileM && Bf16Cfg::BN == kPlanTileN && Bf16Cfg::KT == kPlanTileK, "the plan's tile");
+static_assert(Bf16Cfg::BM == kPlanTileM && Bf16Cfg::BN == kPlanTileN && Bf16Cfg::KT == kPlanTileK && kXcds == kPlanDies, "the plan's tile");
 
 // Whether the scalar-base form of the tile loads can address the operands: 32-bit byte offsets from the start of
 // the token matrix (a_rows rows of lda elements) and of one expert's weight matrix (b_rows rows of ldw elements).
@@ -1392,7 +1417,8 @@ static hipError_t launch_bf16(hipStream_t stream, const void* X, int64_t ldx, in
   if (hipError_t err = allow_lds(lds_allowed[tail], reinterpret_cast<const void*>(kern), C::kSmemBytes); err != hipSuccess) return err;
   if (EPI != kEpiStats && d_ff % 4 != 0) return hipErrorInvalidValue;  // the epilogues that write rows write four channels at a time
   const int64_t n_tiles_n = (d_ff + C::BN - 1) / C::BN;
-  const int64_t n_blocks = (max_tiles * n_tiles_n + kXcds - 1) / kXcds * kXcds * ep.k_parts;
+  int64_t n_blocks = (max_tiles * n_tiles_n + kXcds - 1) / kXcds * kXcds;
+  if (ep.blocks != 0) n_blocks = ep.blocks;
   if (n_blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, launch_grid(n_blocks), dim3(C::kThreads), C::kSmemBytes, stream, static_cast<const __hip_bfloat16*>(X), ldx,
                      (int)d_model, (int)d_ff, static_cast<const __hip_bfloat16*>(W_gate),
@@ -1406,7 +1432,8 @@ hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int
                                int64_t stride_gu, int max_tiles, const BucketTables& t, const GemmEpilogue& e) {
   if (max_tiles <= 0) return hipSuccess;
   EpiArgs ep{e.part_phi2, e.part_max, e.hidden, e.keep, nullptr, e.product, e.ld_product, e.col_gap, d_ff, 0, e.stream_product ? 1 : 0,
-             e.k_parts, e.part_stride};
+             e.split_plan.most_parts, e.part_stride, e.split, e.parts, e.split_plan.blocks};
+  if (ep.k_parts < 1 || ep.k_parts > kMostParts) return hipErrorInvalidValue;
   if (dtype == CAMERA_BF16) {
     switch (e.mode) {
       case GemmEpilogue::kStats:
@@ -1475,7 +1502,7 @@ hipError_t launch_compact_hidden_gemm(hipStream_t stream, const void* X, int64_t
                                       const void* W_gate, const void* W_up, const CompactRows& tab, int widest,
                                       int max_tiles, const BucketTables& t, int32_t* scratch, void* hidden,
                                       int k_round) {
-  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, 0, k_round, 0, 1, 0};
+  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, 0, k_round, 0, 1, 0, {}, nullptr, 0};
   return launch_compact<kEpiHidden>(stream, X, ldx, d_model, W_gate, W_up, tab, k_round, d_model % Bf16Cfg::KT != 0,
                                     (widest + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep);
 }
@@ -1489,7 +1516,7 @@ hipError_t launch_kept_hidden_gemm(hipStream_t stream, const void* X, int64_t ld
   hipLaunchKernelGGL(zero_hidden_kernel, launch_grid(n_pairs), dim3(256), 0, stream, t.offsets, n_experts, kept, (int)d_ff,
                      static_cast<u32x4*>(hidden));
   const KeptRows tab{n_experts, (int)d_ff, stride_gu, kept, list};
-  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, d_ff, 0, 0, 1, 0};
+  EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, d_ff, 0, 0, 1, 0, {}, nullptr, 0};
   return launch_compact<kEpiListed>(stream, X, ldx, d_model, W_gate, W_up, tab, 8, d_model % Bf16Cfg::KT != 0,
                                     (d_ff + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep);
 }
@@ -1499,7 +1526,7 @@ hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int6
                                     float* product, bool stream_product, int k_parts, int64_t part_stride) {
   const int64_t half = d_model / 2;
   EpiArgs ep{nullptr, nullptr, nullptr, nullptr, nullptr, product, d_model, (int)half, 0, 0, stream_product ? 1 : 0, k_parts,
-             part_stride};
+             part_stride, {}, nullptr, 0};
   return launch_compact<kEpiProduct>(stream, hidden, 0, d_model, W_down, W_down, tab, tab.k_round,
                                      tab.k_round % Bf16Cfg::KT != 0, (half + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t,
                                      scratch, ep);

@@ -1,7 +1,7 @@
 """What the layer output's kernels are built around, checked on the generated assembly (no GPU: hipcc cross-compiles gfx950).
 
-The combine waits for memory and little else: it lives from eight waves per SIMD, which 64 vector registers a lane leave.
-The sum over parts of K takes more, so that only calls with parts may carry it.
+The combine waits for memory and little else: it lives from eight waves per SIMD, which 64 vector registers a lane leave, with
+parts of K to add or without.
 """
 import os
 import re
@@ -11,7 +11,7 @@ import subprocess
 import pytest
 
 
-def test_combine_of_whole_rows_leaves_eight_waves_per_simd(tmp_path):
+def test_combine_leaves_eight_waves_per_simd(tmp_path):
     if shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"):
         pytest.skip("hipcc not found")
     from paper_2508_02322_amd import build
@@ -21,5 +21,4 @@ def test_combine_of_whole_rows_leaves_eight_waves_per_simd(tmp_path):
                          capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
     registers = {name: int(n) for name, n in re.findall(r"\.name:\s+(\S*combine_kernel\S*).*?\.vgpr_count:\s+(\d+)", out.read_text(), re.S)}
-    whole = [n for name, n in registers.items() if not re.search(r"Lb1EEEv", name)]   # <.., PARTS = false>
-    assert len(registers) == 3 and len(whole) == 2 and max(whole) <= 64, registers
+    assert len(registers) == 3 and max(registers.values()) <= 64, registers
