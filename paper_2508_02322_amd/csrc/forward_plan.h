@@ -123,14 +123,24 @@ inline int64_t compact_product_workspace(int64_t pairs, int64_t experts, bool ti
   return std::max(product_workspace(pairs * row_bytes, k_ext), chunks * (kStreamingTokens * experts - 1) * row_bytes);
 }
 
-// When a masked call's first contraction goes over the list of the kept micro-experts: the lists, the zeros and the work table
-// are three launches before it (25-33 us), and a launch with few more
-// tiles than compute units gains little from fewer.  Masked call, first contraction + these, us, against computing every
-// micro-expert and zeroing the pruned ones: 2.4e11 products of 40 % pruned 815 -> 575 + 32, of 20 % 808 -> 757 + 33, of nothing
-// pruned 800 -> 805 + 21; 6.9e10 (40 %) 288 -> 212 + 29; 4.7e10 (60 %) 278 -> 155 + 20; below the line 2.5e10 (40 %) 124 -> 107 + 19,
-// (20 %) 109 -> 112 + 20.
+// When a masked call's first contraction is prepared to go over the list of the kept micro-experts: the list, the work table and the
+// zeros are three launches before it (12-16 us where the list is not used, the zeros on top where it is), and a launch with few
+// more tiles than compute units gains little from fewer.  Below the line a list won 4 us of 124 (2.5e10 products, 40 % pruned) or lost.
 inline bool masks_by_list(int64_t n_pairs, int64_t d_model, int64_t d_ff) {
   return (double)n_pairs * d_model * d_ff >= 4e10;
+}
+
+// Whether the list pays, by what it leaves, which the device knows: tiles of the list and of everything, the K tiles of each, and the
+// bytes of the hidden rows that are zeroed for it.  A die's units run its share of the tiles in rounds of 1.4 us per K tile and 8 us
+// around them, 2.3 us more where columns are written one by one; zeros go at 7 TB/s.  First contraction with its preparations, us,
+// everything computed as without a list / by list / as decided: 2048 tokens of the Mixtral shape, 2 % of the mask pruned 824 / 881 /
+// 836, 20 % 820 / 711 / 704, 40 % 821 / 603 / 596; 4096 of the DeepSeek shape 5 % 300 / 354 / 305, 20 % 295 / 308 / 296, 40 % 293 /
+// 247 / 241; 700 of the Qwen2 shape 5 % 438 / 462 / 448, 40 % 440 / 355 / 355; 600 of one expert of 20480 5 % 159 / 177 / 165, 60 %
+// 153 / 97 / 97.
+CAMERA_PLAN_FN bool list_pays(int64_t list_tiles, int64_t all_tiles, int64_t k_tiles, int64_t zero_bytes) {
+  constexpr int kDieCus = kPlanCus / kPlanDies;
+  const int64_t list_rounds = (tiles_per_die(list_tiles) + kDieCus - 1) / kDieCus, all_rounds = (tiles_per_die(all_tiles) + kDieCus - 1) / kDieCus;
+  return list_rounds * (1400 * k_tiles + 10300) + zero_bytes / 7000 < all_rounds * (1400 * k_tiles + 8000);
 }
 
 }  // namespace camera

@@ -94,15 +94,16 @@ constexpr int kChunkM = 4;     // otherwise this many
 //   kEpiProduct : the plain products -> product[slot row][column] (first B matrix) and [column + col_gap] (second);
 //                 the token rows of this mode are the bucket slots themselves (A = the hidden activations)
 //   kEpiListed  : kEpiHidden over the kept micro-experts only: tile channel i of the expert is micro-expert list[i], whose
-//                 weight rows it reads and whose column of the (zeroed) hidden row it writes
+//                 weight rows it reads and whose column of the (zeroed) hidden row it writes.  Where the list does not pay it is
+//                 NULL and tile channel i is micro-expert i
 enum { kEpiStats = 0, kEpiHidden = 1, kEpiProduct = 2, kEpiListed = 3 };
 constexpr bool epi_hidden(int epi) { return epi == kEpiHidden || epi == kEpiListed; }
 struct EpiArgs {
   float* part_phi2;
   float* part_max;
   void* hidden;            // [pairs][ld_hidden], bf16 (MFMA kernel) or float32 (FMA kernel)
-  const uint8_t* keep;     // kEpiHidden: [n_experts * d_ff] or nullptr (all kept)
-  const int32_t* list;     // kEpiListed: the kept micro-experts of the tile's expert
+  const uint8_t* keep;     // kEpiHidden: [n_experts * d_ff] or nullptr (all kept); kEpiListed: the flags of the tile's expert
+  const int32_t* list;     // kEpiListed: the kept micro-experts of the tile's expert, or nullptr
   float* product;          // [pairs][ld_product]
   int64_t ld_product;
   int col_gap;
@@ -603,11 +604,15 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
       else write(std::false_type{});
     }
   } else if constexpr (EPI == kEpiListed) {
-    const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four entries of the list
+    const int col0 = n0 + st.wave_n * TN * 32 + 4 * lane_col;  // this lane's four entries
     if (col0 < d_ff) {
       int at[4];
+      uint32_t kept[2] = {0, 0};  // as for the hidden rows below
 #pragma unroll
-      for (int s = 0; s < 4; ++s) at[s] = col0 + s < d_ff ? ep.list[col0 + s] : -1;
+      for (int s = 0; s < 4; ++s) {
+        at[s] = col0 + s >= d_ff ? -1 : (ep.list != nullptr ? ep.list[col0 + s] : col0 + s);
+        if (at[s] >= 0 && (ep.list != nullptr || ep.keep[at[s]] != 0)) kept[s / 2] |= 0xffffu << (s % 2 * 16);
+      }
       const bool whole = at[3] - at[0] == 3 && at[0] % 4 == 0;  // neighbours, 8-byte aligned: one vector store
 #pragma unroll
       for (int i = 0; i < ACT; ++i)
@@ -619,19 +624,19 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
             if (row >= st.m_len) continue;
             __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(ep.hidden) + (int64_t)(st.row_first + row) * ep.ld_hidden;
             const float a_tok = a_of(i, a, r, row);
-            __hip_bfloat16 lam[4];
+            uint32_t lam[4];
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-              lam[s] = __float2bfloat16(a_tok * silu_f32(acc_g[i][s / 2][a][s % 2][r]) * acc_u[i][s / 2][a][s % 2][r]);
+              lam[s] = __builtin_bit_cast(uint16_t, __float2bfloat16(a_tok * silu_f32(acc_g[i][s / 2][a][s % 2][r]) * acc_u[i][s / 2][a][s % 2][r]));
             if (whole) {
               uint2 v;
-              v.x = (uint32_t)__builtin_bit_cast(uint16_t, lam[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[1]) << 16);
-              v.y = (uint32_t)__builtin_bit_cast(uint16_t, lam[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, lam[3]) << 16);
+              v.x = (lam[0] | lam[1] << 16) & kept[0];
+              v.y = (lam[2] | lam[3] << 16) & kept[1];
               *reinterpret_cast<uint2*>(dst + at[0]) = v;
             } else {
 #pragma unroll
               for (int s = 0; s < 4; ++s)
-                if (at[s] >= 0) dst[at[s]] = lam[s];
+                if (at[s] >= 0) dst[at[s]] = __builtin_bit_cast(__hip_bfloat16, (uint16_t)lam[s]);
             }
           }
     }
@@ -797,7 +802,9 @@ __device__ __forceinline__ void run_tile(const TileWork& w, const __hip_bfloat16
     const int row = b_row0 + j * C::kDmaRows + lane / C::kChunks;
     const int ck = (lane % C::kChunks) ^ swizzle_key<C>(row);
     int c = min(n0 + tile_channel<C, EPI>(row), d_ff - 1);  // channels past d_ff read the last channel again; never written
-    if constexpr (EPI == kEpiListed) c = ep.list[c];
+    if constexpr (EPI == kEpiListed) {
+      if (ep.list != nullptr) c = ep.list[c];
+    }
     const int64_t off = (int64_t)e * stride_gu + (int64_t)c * ldw + ck * 8;
     st.b_k[j] = ck * 8;
     st.g_src[j] = Wg + off - (j % 4) * 512;
@@ -962,15 +969,18 @@ __device__ __forceinline__ ExpertGeom expert_geom(const CompactDown& t, int e, i
 }
 
 // A masked layer's first contraction over its kept micro-experts: their number and list on the device (keep_list_kernel),
-// the matrices as they are.
+// the matrices as they are.  by_list, which compact_work_kernel decides: false, every micro-expert is computed and the flags are
+// applied to the values.
 struct KeptRows {
   int n_experts, d_ff;
   int64_t stride_gu;
   const int32_t* count;  // [n_experts]
   const int32_t* list;   // [n_experts][d_ff], ascending
+  const uint8_t* keep;   // [n_experts][d_ff]
+  bool by_list;
 };
 __device__ __forceinline__ ExpertGeom expert_geom(const KeptRows& t, int e, int d_model) {
-  return {t.count[e], d_model, d_model, e * t.stride_gu, e * t.stride_gu};
+  return {t.by_list ? t.count[e] : t.d_ff, d_model, d_model, e * t.stride_gu, e * t.stride_gu};
 }
 
 // Scratch of a compacted-layer launch, written by compact_work_kernel:
@@ -978,20 +988,23 @@ __device__ __forceinline__ ExpertGeom expert_geom(const KeptRows& t, int e, int 
 //   xcd_first [kXcds + 1]      XCD x runs the logical ids xcd_first[x] .. xcd_first[x + 1].  The cuts are placed by
 //                              cost (tiles times K tiles of their expert), not by tile count: in the second
 //                              contraction a shared expert's tiles can be many times longer than a routed expert's.
+//   by_list   [1]              of a masked layer: whether the kept micro-experts are computed by their list
 //   hid_off   [n_experts]      (int64) first element of expert e's rows in the hidden buffer, which holds the rows of
 //                              expert e back to back, hidden_ld(e) elements each: rows as long as the widest expert's
 //                              would spread a routed expert's 3 KB rows over 24 KB strides
 struct CompactScratch {
   int32_t* work_off;
   int32_t* xcd_first;
+  int32_t* by_list;
   int64_t* hid_off;
 };
 __host__ __device__ inline CompactScratch compact_scratch(int32_t* base, int n_experts) {
   CompactScratch s;
   s.work_off = base;
   s.xcd_first = base + n_experts + 1;
+  s.by_list = base + n_experts + 1 + kXcds + 1;
   // 8-byte aligned: the int32 part is padded to an even count
-  s.hid_off = reinterpret_cast<int64_t*>(base + ((n_experts + 1 + kXcds + 1 + 1) & ~1));
+  s.hid_off = reinterpret_cast<int64_t*>(base + ((n_experts + 1 + kXcds + 1 + 1 + 1) & ~1));
   return s;
 }
 // Length of expert e's hidden rows: its kept count rounded up to k_round (the K extent of the second contraction).
@@ -1016,6 +1029,29 @@ __global__ __launch_bounds__(CAMERA_MAX_EXPERTS) void compact_work_kernel(TABLE 
   __shared__ int64_t s_hid[2][CAMERA_MAX_EXPERTS];
   const CompactScratch sc = compact_scratch(scratch, tab.n_experts);
   const int e = threadIdx.x, n = tab.n_experts;
+  if constexpr (std::is_same<TABLE, KeptRows>::value) {
+    __shared__ int32_t s_sum[3][CAMERA_MAX_EXPERTS / kWave];
+    int32_t sum[3] = {0, 0, 0};  // tiles of the list and of everything, hidden rows that the list leaves zeros in
+    if (e < n) {
+      const int m = tile_offset[e + 1] - tile_offset[e], kept = tab.count[e];
+      sum[0] = m * ((kept + bn - 1) / bn);
+      sum[1] = m * ((tab.d_ff + bn - 1) / bn);
+      sum[2] = kept == tab.d_ff ? 0 : offsets[e + 1] - offsets[e];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) sum[i] += __shfl_xor(sum[i], d);
+      if (e % kWave == 0) s_sum[i][e / kWave] = sum[i];
+    }
+    __syncthreads();
+    for (int i = 0; i < 3; ++i) {
+      sum[i] = 0;
+      for (int w = 0; w < CAMERA_MAX_EXPERTS / kWave; ++w) sum[i] += s_sum[i][w];
+    }
+    tab.by_list = list_pays(sum[0], sum[1], (d_model + kt - 1) / kt, (int64_t)sum[2] * tab.d_ff * 2);
+    if (e == 0) *sc.by_list = tab.by_list;
+  }
   int32_t tiles = 0;
   int64_t cost = 0, hid = 0;
   if (e < n) {
@@ -1079,6 +1115,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   constexpr int BM = C::BM, BN = C::BN;
   const int n_experts = tab.n_experts;
   const CompactScratch sc = compact_scratch(scratch, n_experts);
+  if constexpr (std::is_same<TABLE, KeptRows>::value) tab.by_list = *sc.by_list != 0;
   const int32_t* work_off = sc.work_off;
   const int32_t* xcd_first = sc.xcd_first;
   const int block = linear_block();
@@ -1121,7 +1158,10 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerSimd) void grouped_gemm_bf
   if constexpr (epi_hidden(EPI)) {
     ep.hidden = static_cast<__hip_bfloat16*>(ep_launch.hidden) + hid_e;
     ep.ld_hidden = hid_ld;
-    if constexpr (EPI == kEpiListed) ep.list = tab.list + (int64_t)e * tab.d_ff;
+    if constexpr (EPI == kEpiListed) {
+      ep.list = tab.by_list ? tab.list + (int64_t)e * tab.d_ff : nullptr;
+      ep.keep = tab.keep + (int64_t)e * tab.d_ff;
+    }
   } else {
     A = X + hid_e;
     lda = hid_ld;
@@ -1332,50 +1372,74 @@ __global__ __launch_bounds__(256, 6) void grouped_gemm_f32_kernel(
 
 // ---------------------------------------------------------------------------
 // The kept micro-experts of a mask, expert by expert: count [n_experts], list [n_experts][d_ff] ascending.  A workgroup per
-// expert; a thread counts a run of flags, takes the prefix and writes its run's entries.
+// expert; a thread has eight flags at a time (one load where the flags are 8-byte aligned; d_ff is a multiple of 8), counts them,
+// takes the prefix over the workgroup and writes its entries.
 // ---------------------------------------------------------------------------
 constexpr int kListThreads = 1024;
-__global__ __launch_bounds__(kListThreads) void keep_list_kernel(const uint8_t* __restrict__ keep, int d_ff,
+__global__ __launch_bounds__(kListThreads) void keep_list_kernel(const uint8_t* __restrict__ keep, int d_ff, int aligned,
                                                                  int32_t* __restrict__ count, int32_t* __restrict__ list) {
-  __shared__ int32_t wave_total[kListThreads / kWave];
+  __shared__ int32_t wave_total[2][kListThreads / kWave];
   const int e = blockIdx.x, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const uint8_t* flags = keep + (int64_t)e * d_ff;
-  const int begin = (int)((int64_t)d_ff * tid / kListThreads), end = (int)((int64_t)d_ff * (tid + 1) / kListThreads);
-  int mine = 0;
-#pragma unroll 8
-  for (int c = begin; c < end; ++c) mine += flags[c] != 0;
-  int incl = mine;
+  int32_t* out = list + (int64_t)e * d_ff;
+  int before = 0;  // kept in the rounds before this one
+  for (int c0 = 0, round = 0; c0 < d_ff; c0 += kListThreads * 8, ++round) {
+    const int c = c0 + tid * 8;
+    uint64_t f = 0;
+    if (c < d_ff) {
+      if (aligned) {
+        f = *reinterpret_cast<const uint64_t*>(flags + c);
+      } else {
 #pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int up = __shfl_up(incl, d);
-    if (lane >= d) incl += up;
+        for (int i = 0; i < 8; ++i) f |= (uint64_t)flags[c + i] << (8 * i);
+      }
+    }
+    // one bit per flag that is not zero
+    f |= f >> 4;
+    f |= f >> 2;
+    f |= f >> 1;
+    f &= 0x0101010101010101ull;
+    const int mine = __popcll(f);
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int up = __shfl_up(incl, d);
+      if (lane >= d) incl += up;
+    }
+    if (lane == kWave - 1) wave_total[round % 2][wave] = incl;
+    __syncthreads();  // (two sets of totals: a round writes its own while a slower wave still reads the one before)
+    int place = before + incl - mine;
+#pragma unroll
+    for (int w = 0; w < kListThreads / kWave; ++w) {
+      const int t = wave_total[round % 2][w];
+      before += t;
+      place += w < wave ? t : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (f >> (8 * i) & 1) out[place++] = c + i;
   }
-  if (lane == kWave - 1) wave_total[wave] = incl;
-  __syncthreads();
-  for (int w = 0; w < wave; ++w) incl += wave_total[w];
-  if (tid == kListThreads - 1) count[e] = incl;
-  int32_t* out = list + (int64_t)e * d_ff + (incl - mine);
-#pragma unroll 8
-  for (int c = begin; c < end; ++c)
-    if (flags[c] != 0) *out++ = c;
+  if (tid == 0) count[e] = before;
 }
 
-// Zeros in the hidden rows of the experts that do not keep everything; a workgroup per bucket slot, a row of d_ff (a multiple
-// of 8) elements.
+// Zeros in the hidden rows of the experts that do not keep everything, where the list is used; a workgroup has every gridDim-th
+// bucket slot, a row of d_ff (a multiple of 8) elements each.
+constexpr int kZeroBlocks = 2048;  // eight for each compute unit; one for each of 24576 rows took 6 us to find nothing to do
 __global__ __launch_bounds__(256) void zero_hidden_kernel(const int32_t* __restrict__ offsets, int n_experts,
-                                                          const int32_t* __restrict__ count, int d_ff,
-                                                          u32x4* __restrict__ hidden) {
-  const int slot = linear_block();
-  if (slot >= offsets[n_experts]) return;
-  int lo = 0, hi = n_experts;  // offsets[lo] <= slot < offsets[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (offsets[mid] <= slot) lo = mid; else hi = mid;
+                                                          const int32_t* __restrict__ count, const int32_t* __restrict__ by_list,
+                                                          int d_ff, u32x4* __restrict__ hidden) {
+  if (*by_list == 0) return;
+  const int slots = offsets[n_experts], vecs = d_ff / 8;
+  for (int slot = blockIdx.x; slot < slots; slot += gridDim.x) {
+    int lo = 0, hi = n_experts;  // offsets[lo] <= slot < offsets[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (offsets[mid] <= slot) lo = mid; else hi = mid;
+    }
+    if (count[lo] == d_ff) continue;
+    u32x4* row = hidden + (int64_t)slot * vecs;
+    for (int v = threadIdx.x; v < vecs; v += 256) row[v] = u32x4{0, 0, 0, 0};
   }
-  if (count[lo] == d_ff) return;
-  const int vecs = d_ff / 8;
-  u32x4* row = hidden + (int64_t)slot * vecs;
-  for (int v = threadIdx.x; v < vecs; v += 256) row[v] = u32x4{0, 0, 0, 0};
 }
 
 // Shape of the bf16 kernel: waves (M x N), 32x32 blocks per wave (M x N), K tile, stages of the token ring, stages
@@ -1461,7 +1525,8 @@ hipError_t launch_grouped_gemm(hipStream_t stream, int dtype, const void* X, int
 template <int EPI, class TABLE>
 static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx, int64_t d_model, const void* Wg,
                                  const void* Wu, const TABLE& tab, int k_round, bool tail, int64_t n_tiles_n_max,
-                                 int max_tiles, const BucketTables& t, int32_t* scratch, const EpiArgs& ep) {
+                                 int max_tiles, const BucketTables& t, int32_t* scratch, const EpiArgs& ep,
+                                 int64_t n_pairs = 0) {
   // tail: some K extent is not a multiple of the K tile, or an operand is too large for 32-bit offsets
   using C = Bf16Cfg;
   int64_t a_ld = ldx, b_rows = 0, b_ld = d_model;
@@ -1485,6 +1550,9 @@ static hipError_t launch_compact(hipStream_t stream, const void* X, int64_t ldx,
   if (EPI == kEpiProduct && d_model % 8 != 0) return hipErrorInvalidValue;  // each half in groups of four columns
   hipLaunchKernelGGL((compact_work_kernel<TABLE>), dim3(1), dim3(CAMERA_MAX_EXPERTS), 0, stream, tab, (int)d_model, C::BN, C::KT, k_round,
                      t.offsets, t.tile_offset, scratch);
+  if constexpr (std::is_same<TABLE, KeptRows>::value)
+    hipLaunchKernelGGL(zero_hidden_kernel, dim3((unsigned)std::min<int64_t>(n_pairs, kZeroBlocks)), dim3(256), 0, stream, t.offsets, tab.n_experts, tab.count,
+                       compact_scratch(scratch, tab.n_experts).by_list, tab.d_ff, static_cast<u32x4*>(ep.hidden));
   // an upper bound of the tile count, shared evenly between the XCDs.  In the second contraction a workgroup walks on through
   // its XCD's range where the cuts by cost give that XCD more (cheaper) tiles than that, or the grid ends at one row.
   int64_t n_blocks = (max_tiles * n_tiles_n_max + kXcds - 1) / kXcds * kXcds * ep.k_parts;
@@ -1512,13 +1580,12 @@ hipError_t launch_kept_hidden_gemm(hipStream_t stream, const void* X, int64_t ld
                                    const uint8_t* keep, int max_tiles, int64_t n_pairs, const BucketTables& t, int32_t* kept,
                                    int32_t* scratch, void* hidden) {
   int32_t* list = kept + n_experts;
-  hipLaunchKernelGGL(keep_list_kernel, dim3(n_experts), dim3(kListThreads), 0, stream, keep, (int)d_ff, kept, list);
-  hipLaunchKernelGGL(zero_hidden_kernel, launch_grid(n_pairs), dim3(256), 0, stream, t.offsets, n_experts, kept, (int)d_ff,
-                     static_cast<u32x4*>(hidden));
-  const KeptRows tab{n_experts, (int)d_ff, stride_gu, kept, list};
+  hipLaunchKernelGGL(keep_list_kernel, dim3(n_experts), dim3(kListThreads), 0, stream, keep, (int)d_ff,
+                     reinterpret_cast<uintptr_t>(keep) % 8 == 0 ? 1 : 0, kept, list);
+  const KeptRows tab{n_experts, (int)d_ff, stride_gu, kept, list, keep, false};
   EpiArgs ep{nullptr, nullptr, hidden, nullptr, nullptr, nullptr, 0, 0, d_ff, 0, 0, 1, 0, {}, nullptr, 0};
   return launch_compact<kEpiListed>(stream, X, ldx, d_model, W_gate, W_up, tab, 8, d_model % Bf16Cfg::KT != 0,
-                                    (d_ff + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep);
+                                    (d_ff + Bf16Cfg::BN - 1) / Bf16Cfg::BN, max_tiles, t, scratch, ep, n_pairs);
 }
 
 hipError_t launch_compact_down_gemm(hipStream_t stream, const void* hidden, int64_t d_model, const void* W_down,

@@ -21,5 +21,8 @@ int64_t compact_product_workspace(int64_t pairs, int64_t experts, int tiled, int
 }
 int compact_fills_tiles(int64_t pairs, int64_t experts) { return camera::compact_fills_tiles(pairs, experts); }
 int product_streams(int64_t pairs, int64_t d_model) { return camera::product_streams(pairs, d_model); }
+int list_pays(int64_t list_tiles, int64_t all_tiles, int64_t k_tiles, int64_t zero_bytes) {
+  return camera::list_pays(list_tiles, all_tiles, k_tiles, zero_bytes);
+}
 int masks_by_list(int64_t pairs, int64_t d_model, int64_t d_ff) { return camera::masks_by_list(pairs, d_model, d_ff); }
 }

@@ -18,7 +18,8 @@ class Plan:
         for name, args in (("product_k_parts", [i64] * 6 + [ptr(ctypes.c_int), ptr(i64)]), ("compact_k_parts", [i64] * 6),
                            ("product_workspace", [i64, i64]),
                            ("compact_product_workspace", [i64, i64, ctypes.c_int, i64, i64, ctypes.c_int]),
-                           ("compact_fills_tiles", [i64, i64]), ("product_streams", [i64, i64]), ("masks_by_list", [i64, i64, i64])):
+                           ("compact_fills_tiles", [i64, i64]), ("product_streams", [i64, i64]), ("masks_by_list", [i64, i64, i64]),
+                           ("list_pays", [i64] * 4)):
             fn = getattr(so, name)
             fn.argtypes = args
             fn.restype = i64 if name.endswith("workspace") else ctypes.c_int
@@ -104,3 +105,20 @@ def test_k_stays_whole_where_its_tiles_fill_the_rounds(plan):
         assert parts in best, (m_tiles, pairs, d_model, d_ff, parts)
     # no number of tiles that these pairs can make is better in parts: nothing is prepared for them
     assert plan.parts(9000, 8, 4096, 14336, 40)[1:] == (1, (9000 // 256 + 8) * 16)
+
+
+def test_list_of_kept_micro_experts_where_it_leaves_enough_out(plan):
+    """Token tiles, d_model, d_ff, pairs and the share pruned (in every expert alike) of masked calls: by list where that was
+    faster when measured, everything computed where it was not (masks that keep nearly everything, few rounds of tiles)."""
+    for m_tiles, d_model, d_ff, pairs, pruned, by_list in (
+            (20, 4096, 14336, 4096, 0.0, False), (20, 4096, 14336, 4096, 0.02, False), (20, 4096, 14336, 4096, 0.2, True),
+            (20, 4096, 14336, 4096, 0.4, True), (128, 2048, 1408, 24576, 0.05, False),
+            (128, 2048, 1408, 24576, 0.3, True), (64, 3584, 2560, 5600, 0.1, False), (64, 3584, 2560, 5600, 0.25, True),
+            (3, 3584, 20480, 600, 0.3, False), (3, 3584, 20480, 600, 0.6, True), (8, 4096, 14336, 800, 0.1, False),
+            (8, 4096, 14336, 800, 0.15, True), (280, 3584, 2560, 65536, 0.05, False), (280, 3584, 2560, 65536, 0.2, True)):
+        assert plan.masks_by_list(pairs, d_model, d_ff)
+        tiles = lambda width: m_tiles * -(-width // 128)
+        kept = d_ff - int(pruned * d_ff)
+        zero_bytes = 2 * pairs * d_ff if pruned else 0
+        got = plan.list_pays(tiles(kept), tiles(d_ff), -(-d_model // 64), zero_bytes)
+        assert bool(got) == by_list, (m_tiles, d_model, d_ff, pairs, pruned)

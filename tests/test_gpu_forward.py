@@ -16,6 +16,7 @@ import torch
 from oracle import camera_oracle as orc
 from paper_2508_02322_amd import inputs
 from tests import helpers as H
+from tests.test_forward_plan import plan  # noqa: F401  (the fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -176,6 +177,37 @@ def test_kept_micro_experts_by_list(cam, d_model, dense):
         return cam.layer_forward(X[lo:hi], *part, dev["W_gate"], dev["W_up"], dev["W_down"], keep_mask=keep)
     whole, third = forward(0, cfg.n_tokens), cfg.n_tokens // 3
     assert torch.isfinite(whole).all() and whole.abs().max() > 0
+    assert torch.equal(whole, torch.cat([forward(0, third), forward(third, 2 * third), forward(2 * third, cfg.n_tokens)]))
+
+
+@pytest.mark.parametrize("pruned,unaligned", [(0.0, 0), (0.02, 0), (0.05, 1), (0.8, 4), (0.9, 3), (1.0, 0)])
+def test_masks_of_every_weight_by_list_or_whole(cam, plan, pruned, unaligned):
+    """Light masks are computed whole and the flags applied, others by their list; flags from any address.  Both equal the calls on
+    thirds of the tokens, which are below the list's line, bit for bit.  One expert keeps everything and one all but one."""
+    cfg = small(n_tokens=11000, d_model=2048, d_ff=952, n_experts=5, top_k=2, outlier_channels=0)
+    dev = inputs.make_layer(cfg, 0, device="cuda")
+    X = dev["X"]
+    idx, w = cam.route_topk(X, dev["W_r"], dev["bias"], cfg.top_k)
+    flags = torch.zeros(cfg.n_experts * cfg.d_ff + unaligned, dtype=torch.uint8)
+    keep = flags[unaligned:].view(cfg.n_experts, cfg.d_ff)
+    keep.copy_(torch.rand(keep.shape, generator=torch.Generator().manual_seed(4)) >= pruned)
+    if 0 < pruned < 1:
+        keep[1], keep[3] = 7, 1
+        keep[3, 500] = 0
+    mask = flags.cuda()[unaligned:]
+    assert mask.data_ptr() % 8 == unaligned
+    rows = torch.bincount(idx.flatten().long(), minlength=cfg.n_experts).tolist()
+    kept = (keep != 0).sum(1).tolist()
+    tiles = [sum(-(-r // 256) * -(-width // 128) for r, width in zip(rows, widths)) for widths in (kept, [cfg.d_ff] * cfg.n_experts)]
+    zeroed = sum(2 * r * cfg.d_ff for r, k in zip(rows, kept) if k < cfg.d_ff)
+    assert plan.masks_by_list(sum(rows), cfg.d_model, cfg.d_ff)
+    assert bool(plan.list_pays(*tiles, cfg.d_model // 64, zeroed)) == (pruned >= 0.8)
+
+    def forward(lo, hi):
+        return cam.layer_forward(X[lo:hi], idx[lo:hi], w[lo:hi], dev["W_gate"], dev["W_up"], dev["W_down"], keep_mask=mask)
+    whole, third = forward(0, cfg.n_tokens), cfg.n_tokens // 3 + 1
+    assert not plan.masks_by_list(third * cfg.top_k, cfg.d_model, cfg.d_ff)
+    assert torch.isfinite(whole).all() and (whole.abs().max() > 0 or pruned == 1.0)
     assert torch.equal(whole, torch.cat([forward(0, third), forward(third, 2 * third), forward(2 * third, cfg.n_tokens)]))
 
 
