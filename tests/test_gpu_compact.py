@@ -13,6 +13,7 @@ import torch
 from oracle import camera_oracle as orc
 from paper_2508_02322_amd import binding, inputs
 from tests import helpers as H
+from tests.test_forward_plan import plan  # noqa: F401  (the fixture)
 from tests.test_gpu_forward import check_output, dense_A, expert_lists, largest_term, small
 
 pytestmark = pytest.mark.gpu
@@ -84,7 +85,9 @@ def test_compacted_layer_output_matches_oracle(cam, case):
     dict(n_tokens=200, d_model=272, d_ff=1600, n_experts=3, top_k=2),   # 25 in three, two column tiles
     dict(n_tokens=270, d_model=64, d_ff=8000, n_experts=4, top_k=1),    # an expert whose parts are all empty beside long ones
 ])
-def test_second_contraction_in_parts_of_k(cam, case):
+def test_second_contraction_in_parts_of_k(cam, plan, case):
+    for kept in (1.0, 0.63):
+        assert plan.compact_k_parts(case["n_tokens"], case["n_experts"], case["top_k"], 0, case["d_model"], int(kept * case["d_ff"])) > 1
     test_compacted_layer_output_matches_oracle(cam, case)
 
 

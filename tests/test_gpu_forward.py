@@ -126,7 +126,7 @@ def test_output_columns_at_the_edges_of_a_lane_a_wave_and_a_tile(cam, n_tokens, 
 @pytest.mark.parametrize("compact", [False, True])
 def test_bucket_order_in_one_launch(cam, compact, top_k, experts, n_shared):
     """Up to 3072 pairs (4096 of a decoding batch) one workgroup makes the bucket order, beyond them the general sort does.  With
-    K in one part (d_ff is below 1024) a token's output does not depend on the batch: the call on all tokens (more pairs) equals
+    K in one part (d_ff has fewer than 16 tiles of 64) a token's output does not depend on the batch: the call on all tokens (more pairs) equals
     the calls on parts of them with 1 token, a chunk of 64 pairs and its neighbours, a whole step of 1024, the two lines and
     their neighbours, bit for bit.  Some choices are no expert's."""
     n_shared = n_shared if compact else 0
@@ -157,8 +157,8 @@ def test_bucket_order_in_one_launch(cam, compact, top_k, experts, n_shared):
 
 @pytest.mark.parametrize("d_model,dense", [(2048, False), (2056, False), (2048, True)])
 def test_kept_micro_experts_by_list(cam, d_model, dense):
-    """From 4e10 products on a masked call computes the kept micro-experts only.  A token's output does not depend on the
-    batch, so the call on all tokens equals the calls on its parts, which compute all of them and zero the pruned ones, bit
+    """From 4e10 products on a masked call computes the kept micro-experts only, where that leaves enough out.  With K in one part
+    (d_ff has fewer than 16 tiles of 64) a token's output does not depend on the batch, so the call on all tokens equals the calls on its parts, which compute all of them and zero the pruned ones, bit
     for bit: experts that keep about half, everything, nothing, the ends, and runs of all alignments."""
     cfg = small(n_tokens=11000 if not dense else 4500, d_model=d_model, d_ff=952, n_experts=5, top_k=2, outlier_channels=0)
     assert cfg.n_tokens * (cfg.n_experts if dense else cfg.top_k) * d_model * cfg.d_ff >= 4e10
@@ -178,6 +178,49 @@ def test_kept_micro_experts_by_list(cam, d_model, dense):
     whole, third = forward(0, cfg.n_tokens), cfg.n_tokens // 3
     assert torch.isfinite(whole).all() and whole.abs().max() > 0
     assert torch.equal(whole, torch.cat([forward(0, third), forward(third, 2 * third), forward(2 * third, cfg.n_tokens)]))
+
+
+def test_masked_layer_by_list_with_k_in_parts(cam, plan):
+    """A masked call whose first contraction goes by list and whose second is cut into parts of K, against the oracle on tokens
+    from every tile (the first and last ones of the batch, and some between)."""
+    cfg = small(n_tokens=2500, d_model=1024, d_ff=8192, n_experts=4, top_k=2, outlier_channels=0)
+    layer = inputs.make_layer(cfg, 0, device="cuda")
+    X, n_pairs = layer["X"], cfg.n_tokens * cfg.top_k
+    idx, w = cam.route_topk(X, layer["W_r"], layer["bias"], cfg.top_k)
+    keep = (torch.rand(cfg.n_experts * cfg.d_ff, generator=torch.Generator().manual_seed(5)) < 0.6).to(torch.uint8)
+    keep[:cfg.d_ff][::2] = 0                                                 # experts of different widths
+    rows = torch.bincount(idx.flatten().long(), minlength=cfg.n_experts).tolist()
+    kept = keep.view(cfg.n_experts, cfg.d_ff).sum(1).tolist()
+    m = [-(-r // 256) for r in rows]
+    tiles = [sum(t * -(-width // 128) for t, width in zip(m, widths)) for widths in (kept, [cfg.d_ff] * cfg.n_experts)]
+    assert plan.masks_by_list(n_pairs, cfg.d_model, cfg.d_ff) and plan.list_pays(*tiles, cfg.d_model // 64, 2 * n_pairs * cfg.d_ff)
+    assert plan.parts(n_pairs, cfg.n_experts, cfg.d_model, cfg.d_ff, sum(m))[0] > 1
+    Y = cam.layer_forward(X, idx, w, layer["W_gate"], layer["W_up"], layer["W_down"], keep_mask=keep.cuda())
+    torch.cuda.synchronize()
+    tokens = torch.cat([torch.arange(8), torch.arange(100, 2400, 230), torch.arange(2492, 2500)])
+    A = dense_A(idx.cpu().numpy().astype(np.int64)[tokens], w.cpu().numpy().astype(np.float64)[tokens], cfg.n_experts)
+    gate, up, down = expert_lists(layer, "W")
+    X64 = H.f64(X[tokens.cuda()])
+    O = orc.layer_forward(X64, A, gate, up, down, keep=keep.numpy(), round_hidden=orc.round_to_bf16)
+    check_output(Y[tokens.cuda()], O, largest_term(X64, A, gate, up, down, keep.numpy()))
+
+
+@pytest.mark.parametrize("n_tokens,experts,d_model,d_ff", [(300, 2, 64, 2056), (257, 1, 264, 1544), (70, 5, 128, 1024), (1, 1, 8, 4096)])
+def test_dense_group_with_k_in_parts_added_to_the_output(cam, plan, n_tokens, experts, d_model, d_ff):
+    """The combine's sum over parts without routing, onto what Y holds; the last part has a K tail where d_ff is no multiple of 64."""
+    cfg = small(n_tokens=n_tokens, d_model=d_model, d_ff=d_ff, n_experts=experts, top_k=1, outlier_channels=0)
+    assert plan.parts(n_tokens * experts, experts, d_model, d_ff, experts * -(-n_tokens // 256), dense=True)[0] > 1
+    layer = inputs.make_layer(cfg, 0, device="cpu")
+    dev = H.to_dev(layer)
+    before = torch.randn((n_tokens, d_model), generator=torch.Generator().manual_seed(6))
+    Y = cam.layer_forward(dev["X"], None, None, dev["W_gate"], dev["W_up"], dev["W_down"], Y=before.cuda(), accumulate=True)
+    Y_alone = cam.layer_forward(dev["X"], None, None, dev["W_gate"], dev["W_up"], dev["W_down"])
+    torch.cuda.synchronize()
+    gate, up, down = expert_lists(layer, "W")
+    X64, A = H.f64(layer["X"]), np.ones((n_tokens, experts))
+    O, term = orc.layer_forward(X64, A, gate, up, down, round_hidden=orc.round_to_bf16), largest_term(X64, A, gate, up, down)
+    check_output(Y_alone, O, term)
+    check_output(Y, O + H.f64(before), term)
 
 
 @pytest.mark.parametrize("pruned,unaligned", [(0.0, 0), (0.02, 0), (0.05, 1), (0.8, 4), (0.9, 3), (1.0, 0)])
@@ -213,8 +256,8 @@ def test_masks_of_every_weight_by_list_or_whole(cam, plan, pruned, unaligned):
 
 @pytest.mark.parametrize("compact", [False, True])
 def test_product_rows_past_the_caches(cam, compact):
-    """From 256 MiB of product rows on they are stored and read past the caches.  A token's output does not depend on the
-    batch, so the call on all tokens equals the calls on their halves (below the line) bit for bit."""
+    """From 256 MiB of product rows on they are stored and read past the caches.  With K in one part (d_ff is one tile of 64) a
+    token's output does not depend on the batch, so the call on all tokens equals the calls on their halves (below the line) bit for bit."""
     cfg = small(n_tokens=9001, d_model=1032 if not compact else 1040, d_ff=64, n_experts=9, top_k=8, outlier_channels=0)
     assert cfg.n_tokens * cfg.top_k * cfg.d_model * 4 >= 256 << 20 > (cfg.n_tokens // 2 + 1) * cfg.top_k * cfg.d_model * 4
     dev = inputs.make_layer(cfg, 0, device="cuda")
