@@ -312,7 +312,7 @@ int camera_input_channel_energy(camera_ctx* ctx, void* stream,
  * 16-bit model are (CAMERA_F32 keeps it in float32); both contractions accumulate in float32, and a token's experts are added in the order of its
  * top-k list (no floating-point atomics: the result does not depend on launch order).  The context
  * workspace grows by n*top_k*(2*d_ff + 4*d_model) bytes.  With CAMERA_BF16, where the second contraction has few tiles, its sums
- * over d_ff are taken in up to eight parts with 4*d_model bytes each; how many depends on n, so a token's last bits may.  Every
+ * over d_ff are taken in up to eight parts with 4*d_model bytes each; how many depends on n and on the routing, so a token's last bits may.  Every
  * call makes the room that the parts of a smaller batch take (256 MiB of such rows at most in all) and, from 4e10 products
  * n*top_k*d_model*d_ff on, the 4*n_experts*(d_ff + 1) bytes of a masked call: after a call on the largest batch none of the
  * same layer grows the workspace, with a mask or without.  n == 0 does nothing.

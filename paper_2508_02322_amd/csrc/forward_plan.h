@@ -56,7 +56,8 @@ CAMERA_PLAN_FN int64_t split_ns(int64_t tiles, int parts, SplitCost c) {
 // combine, us, whole / in the parts taken: 2048 tokens of the Mixtral shape, 20 token tiles by 16 of 224 K tiles, 598 / 496;
 // 300 and 2048 tokens of one expert of 20480, 3584 wide, 309 / 72 and 365 / 236; 500 tokens of 8 experts of 3072, 768 wide,
 // 50 / 27.  Over 334 sizes of 20 shapes the parts taken are 0.8 % above the best and none is slower than whole (by a guess, and
-// with rounds of all 256 units: 3.6 %, up to 1.26 times).
+// with rounds of all 256 units: 3.6 %, up to 1.26 times); a call that is left whole but might have been cut pays up to 4 % of these
+// two kernels for the workgroups prepared for it.
 CAMERA_PLAN_FN bool split_pays(int64_t ns, int64_t whole_ns) { return 100 * ns < 85 * whole_ns; }
 inline int product_k_parts(int64_t tiles, int most, SplitCost c) {
   int best = 1;

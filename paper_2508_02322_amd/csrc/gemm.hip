@@ -722,7 +722,7 @@ __device__ __forceinline__ void tile_body16(const TileState<C>& st, int n0, int 
 // rows 16 apart.  The epilogues that write per token row deal the channels of a wave (32 TN) to its 16-row sub-blocks one at a
 // time, so that a lane owns 2 TN = 4 consecutive channels, one per sub-block: the 16 lanes that a store instruction serves at
 // a time then write one token row side by side, 256 bytes of float32 or 128 of bf16.  With a lane per token row, transposed,
-// they wrote 16 (8) bytes of 16 rows each, and memory took 1.31 bytes for every byte of the product.  Second contraction,
+// they wrote 16 (8) bytes of 16 rows each, and memory took 1.34 bytes for every byte of the product.  Second contraction,
 // 8192 tokens of the DeepSeek shape, 40 % pruned, 537 MB of product rows, K of 14 tiles: 361 -> 288 us (208 without any
 // store); first contraction of the Mixtral shape, 2048 tokens: 825 -> 815 us.
 template <class C, int EPI>
